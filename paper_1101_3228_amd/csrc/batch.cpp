@@ -120,6 +120,8 @@ struct qtree_batch {
   std::vector<qtree::BdpTask> bdp_tasks;  // all backward steps, step by step
   std::vector<int> step_off;              // tasks of step j: [step_off[j], step_off[j + 1])
   int max_last = 0;                       // largest n_pay x N_n of a job
+  int max_nq = 0;                         // most payoffs of a job
+  int min_n1 = 0x7FFFFFFF;                // smallest N_k, k >= 1, of a contract
   std::vector<Group> groups;
   std::vector<double> unit_cost;
   qtree::BatchContract* d_contracts = nullptr;
@@ -246,8 +248,9 @@ hipError_t enqueue_forward(const qtree_batch* b, const BatchConfig& c, hipStream
 hipError_t enqueue_all(const qtree_batch* b, hipStream_t s) {
   hipError_t e = enqueue_forward(b, b->cfg, s);
   if (e != hipSuccess) return e;
-  return qtree::launch_bdp_steps(b->d_jobs, (int)b->jobs.size(), b->max_last, b->d_bdp_tasks,
-                                 b->step_off.data(), (int)b->step_off.size() - 1, s);
+  return qtree::launch_bdp_steps(b->d_jobs, (int)b->jobs.size(), b->max_last, b->max_nq,
+                                 b->min_n1, b->d_bdp_tasks, b->step_off.data(),
+                                 (int)b->step_off.size() - 1, s);
 }
 
 // The candidate configurations of a batch: samples per lane 8 / 4, serial or
@@ -382,6 +385,7 @@ qtree_status qtree_batch_plan(const qtree_contract* contracts, int32_t n, qtree_
     mix((uint64_t)p->n);
     mix(C.M);
     for (int k = 0; k <= p->n; ++k) mix((uint64_t)p->N[k]);
+    for (int k = 1; k <= p->n; ++k) b->min_n1 = std::min(b->min_n1, (int)p->N[k]);
     b->dmax = std::max(b->dmax, (int)p->d);
     if (p->d == 1) {
       maxP = std::max(maxP, p->maxP);
@@ -425,6 +429,7 @@ qtree_status qtree_batch_plan(const qtree_contract* contracts, int32_t n, qtree_
       b->jobs.push_back(j);
       job_contract.push_back(i);
       b->max_last = std::max(b->max_last, j.nq * p->N[p->n]);
+      b->max_nq = std::max(b->max_nq, (int)j.nq);
     }
     v0_off += C.n_pay;
   }

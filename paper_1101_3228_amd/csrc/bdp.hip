@@ -2,10 +2,10 @@
 //   V_n = phi_n,  V_k(i) = max(phi_k(i), sum_j c_ij V_{k+1}(j) / p_i),
 // with pi^k_ij = c_ij / p_i estimated by the forward counts.  The
 // conditional expectation on the tree is the row reduction
-// sum_j pi_ij f(x_j) of Sec. 2.  One 64-lane wave reduces one row of the
-// count block for up to kPay obstacle vectors at once, so the int32 counts
-// are read from HBM once per group of payoffs.  Also the obstacle phi_k on
-// the grid points.
+// sum_j pi_ij f(x_j) of Sec. 2: a product of the count block with the value
+// vectors of up to kPay payoffs, on the FP64 matrix cores.  Also the
+// obstacle phi_k on the grid points.
+#include "bdp_tile.hpp"
 #include "qtree_batch.hpp"
 #include "qtree_internal.hpp"
 
@@ -13,120 +13,251 @@ namespace qtree {
 
 namespace {
 constexpr int kBlock = 256;
-constexpr int kWaves = kBlock / 64;
-constexpr int kPay = 16;
-constexpr int kRowUnroll = 8;
-constexpr int kFewPay = 2;  // payoffs per pass whose V entries are loaded with the counts
-constexpr int kFewUnroll = 16;  // ... and the row loads in flight per lane then
+constexpr int kPay = 16;     // payoffs per pass: the columns of a matrix-core tile
+constexpr int kRows = 16;    // rows per workgroup: the rows of a tile
+constexpr int kFewPay = 2;   // payoffs a pass of the few-payoff path takes
+constexpr int kFewRows = 4;  // ... and rows per workgroup
+constexpr int kFewWaves = 4;
 
-// One wave's share of a count row (len entries from row) against nq <= kPay
-// value vectors V + (q0 + q) P + col0: the row total p and the sums
-// s_q = sum_j c_j V_q(j) of this lane's columns.  kRowUnroll row loads are
-// in flight per lane (a long dense row is otherwise one HBM round trip per
-// 64 columns); a column whose count is zero adds nothing, and its V entries
-// are not read.
-template <bool FEW>
-__device__ __forceinline__ void row_sums(const int32_t* __restrict__ row, int len,
-                                         const double* __restrict__ V, int64_t P, int q0,
-                                         int nq, int64_t col0, int lane, int64_t& p,
-                                         double (&s)[kPay]) {
-  p = 0;
+// The rows of a tile: this lane's row (lane % 16), a pointer indexed by
+// column, and the columns [lo, hi) it holds; [from, to) covers every row and
+// every row holds [all_lo, all_hi) (the same for the workgroup).
+struct TileRows {
+  const int32_t* row;
+  int lo, hi, from, to, all_lo, all_hi;
+};
+
+// One tile of kRows rows by one workgroup of W waves: wave w takes the
+// chunks of 16 columns w, w + W, ..., AHEAD of them in flight, and the waves'
+// products and row totals meet in LDS.  Thread t < 256 returns S of row
+// t / 16 and payoff t % 16, and the row's total.  x: the values of this
+// lane's payoff (lane % 16) by column, n1 of them (a lane without a payoff
+// repeats another's: its sums are dropped).  DENSE: the rows hold all n1 >= 4
+// columns.
+//
+// What bounds a layer is the latency of one launch: counts and values are
+// one round trip, and nothing is reduced across lanes.  N = 500, 12
+// payoffs: 5.2 us a layer, against 14.0 when a wave walked one row and
+// reduced its 16 sums over the lanes with about 200 shuffles; N = 256: 4.2
+// against 12.1; N = 2000: 14.7 against 39.8.
+template <int W, int AHEAD, bool DENSE>
+__device__ __forceinline__ bool tile_sums(const TileRows& R, const double* __restrict__ x, int n1,
+                                          double& sum, int64_t& total) {
+  __shared__ double part[W][kRows][kPay];
+  __shared__ int64_t part_p[W][kRows];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int g = lane >> 4;
+  f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+  int64_t p = 0;
+  for (int j0 = R.from + 16 * wave; j0 < R.to; j0 += 16 * W * AHEAD) {
+    int32_t c[AHEAD][4];
+    double v[AHEAD][4];
+    const int last = j0 + 16 * W * (AHEAD - 1) + 16;
+    load_chunks<AHEAD, DENSE>(R.row, x, j0 + 4 * g, 16 * W, R.lo, R.hi, n1,
+                              j0 >= R.all_lo && last <= R.all_hi && last <= n1, c, v);
 #pragma unroll
-  for (int q = 0; q < kPay; ++q) s[q] = 0.0;
-  if (FEW && nq <= kFewPay) {
-    // few payoffs: the V entries are loaded with the counts, not after them
-    // (a load that waits on its count is a second round trip per group);
-    // a zero count still adds nothing (a select, not a multiply by zero)
-    for (int j0 = lane; j0 < len; j0 += 64 * kFewUnroll) {
-      int32_t c[kFewUnroll];
-      double v[kFewUnroll][kFewPay];
-#pragma unroll
-      for (int u = 0; u < kFewUnroll; ++u) {
-        const int j = j0 + 64 * u;
-        c[u] = j < len ? row[j] : 0;
-#pragma unroll
-        for (int q = 0; q < kFewPay; ++q)
-          v[u][q] = (j < len && q < nq) ? V[(int64_t)(q0 + q) * P + col0 + j] : 0.0;
-      }
-#pragma unroll
-      for (int u = 0; u < kFewUnroll; ++u) {
-        p += c[u];
-        const double cd = (double)c[u];
-#pragma unroll
-        for (int q = 0; q < kFewPay; ++q) s[q] = c[u] != 0 ? fma(cd, v[u][q], s[q]) : s[q];
-      }
-    }
-    return;
-  }
-  for (int j0 = lane; j0 < len; j0 += 64 * kRowUnroll) {
-    int32_t c[kRowUnroll];
-#pragma unroll
-    for (int u = 0; u < kRowUnroll; ++u) {
-      const int j = j0 + 64 * u;
-      c[u] = j < len ? row[j] : 0;
-    }
-#pragma unroll
-    for (int u = 0; u < kRowUnroll; ++u) {
-      p += c[u];
-      if (c[u] != 0) {
-        const double cd = (double)c[u];
-        const int64_t col = col0 + j0 + 64 * u;
-#pragma unroll
-        for (int q = 0; q < kPay; ++q)
-          if (q < nq) s[q] = fma(cd, V[(int64_t)(q0 + q) * P + col], s[q]);
-      }
+    for (int a = 0; a < AHEAD; ++a) {
+      p += (int64_t)c[a][0] + c[a][1] + c[a][2] + c[a][3];
+      chunk_product(c[a], v[a], lane, acc);
     }
   }
+  p += __shfl_xor(p, 16, 64);
+  p += __shfl_xor(p, 32, 64);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) part[wave][g + 4 * r][lane & 15] = acc[r];
+  if (lane < kRows) part_p[wave][lane] = p;
+  __syncthreads();
+  const int t = (int)threadIdx.x;
+  if (t >= kRows * kPay) return false;
+  sum = 0.0;
+  total = 0;
+#pragma unroll
+  for (int w = 0; w < W; ++w) {
+    sum += part[w][t >> 4][t & 15];
+    total += part_p[w][t >> 4];
+  }
+  return true;
+}
+
+// Sum over the 64 lanes of v[0 .. M): lane exchanges halve the values while
+// they halve the lanes, so that lane l ends with the sum of value
+// sum_slot<M>(l) (repeated over the lanes of a slot).
+template <int M>
+__device__ __forceinline__ double lane_sums(const double (&v)[M], int lane, int off) {
+  if constexpr (M == 1) {
+    double s = v[0];
+    for (; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    return s;
+  } else {
+    constexpr int H = M / 2;
+    double w[H];
+    const bool up = (lane & off) != 0;
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+      const double keep = up ? v[H + i] : v[i], give = up ? v[i] : v[H + i];
+      w[i] = keep + __shfl_xor(give, off, 64);
+    }
+    return lane_sums<H>(w, lane, off >> 1);
+  }
+}
+
+// kFewRows rows by one workgroup for Q <= kFewPay payoffs on vector FMAs: a
+// wave takes blocks of 256 columns (four consecutive ones per lane, the
+// values loaded once for all rows), the lanes' sums and the waves' meet by
+// exchange and LDS.  Thread t < kFewRows Q returns S of row t / Q and payoff
+// t % Q, and the row's total (exact in FP64: below 2^53).  A tile on the
+// matrix cores would spend 14 of its 16 columns on nothing and leave half of
+// the chip without a row tile (N = 2000, 2 payoffs: 11.4 us a layer).  Here
+// 6.5 us, against 12.7 with one wave per row; N = 990: 4.1 against 6.9; N =
+// 500, 1 payoff: 3.1 against 6.4; N = 100: 3.6 against 6.5, launch included.
+template <int Q>
+__device__ __forceinline__ bool few_sums(const int32_t* __restrict__ rows, int nrows,
+                                         const double* __restrict__ x, int64_t P, int n1,
+                                         double& sum, double& total) {
+  constexpr int kVals = kFewRows * (Q == 1 ? 2 : 4);  // per row: Q sums, the total (and a pad)
+  __shared__ double part[kFewWaves][kVals];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  double s[kVals];
+#pragma unroll
+  for (int i = 0; i < kVals; ++i) s[i] = 0.0;
+  constexpr int kPer = kVals / kFewRows;
+  for (int j0 = 256 * wave; j0 < n1; j0 += 256 * kFewWaves) {
+    const int j = j0 + 4 * lane;
+    int32_t c[kFewRows][4];
+    double v[Q][4];
+    const Cols4 t(j, n1);
+#pragma unroll
+    for (int r = 0; r < kFewRows; ++r) {
+      const int i = r < nrows ? r : nrows - 1;  // rows past the end repeat the last one
+      const Int4U y = *reinterpret_cast<const Int4U*>(rows + (int64_t)i * n1 + t.at);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) c[r][u] = y.v[u];
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const Dbl4U y = *reinterpret_cast<const Dbl4U*>(x + q * P + t.at);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[q][u] = y.v[u];
+    }
+    if (j0 + 256 > n1) {
+#pragma unroll
+      for (int r = 0; r < kFewRows; ++r) drop_front(c[r], t.drop);
+#pragma unroll
+      for (int q = 0; q < Q; ++q) drop_front(v[q], t.drop);
+    }
+    bool finite = true;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) finite = finite && finite4(v[q]);
+    if (__all(finite)) {
+#pragma unroll
+      for (int r = 0; r < kFewRows; ++r)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const double cd = (double)c[r][u];
+          s[r * kPer + Q] += cd;
+#pragma unroll
+          for (int q = 0; q < Q; ++q) s[r * kPer + q] = fma(cd, v[q][u], s[r * kPer + q]);
+        }
+    } else {  // a zero count adds nothing, whatever its value is
+#pragma unroll
+      for (int r = 0; r < kFewRows; ++r)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const double cd = (double)c[r][u];
+          s[r * kPer + Q] += cd;
+#pragma unroll
+          for (int q = 0; q < Q; ++q)
+            if (c[r][u] != 0) s[r * kPer + q] = fma(cd, v[q][u], s[r * kPer + q]);
+        }
+    }
+  }
+  const double mine = lane_sums<kVals>(s, lane, 32);
+  // the halving gives value i to the lanes whose top bits spell i
+  constexpr int kLanes = 64 / kVals;
+  if (lane % kLanes == 0) part[wave][lane / kLanes] = mine;
+  __syncthreads();
+  const int t = (int)threadIdx.x;
+  if (t >= kFewRows * Q) return false;
+  sum = total = 0.0;
+#pragma unroll
+  for (int w = 0; w < kFewWaves; ++w) {
+    sum += part[w][(t / Q) * kPer + t % Q];
+    total += part[w][(t / Q) * kPer + Q];
+  }
+  return true;
 }
 }  // namespace
 
-// One layer for every payoff: blockIdx.y selects the group of kPay payoffs
-// (the count row is re-read per group, from L2 for all but the first).
-// FEW: the instance for at most kFewPay payoffs.  The general instance does
-// not carry the few-payoff path's registers (98 VGPRs against 119): its
-// workgroups, launched beside a sampling pass on another stream, then find
-// room on the CUs sooner (the 1-D workload's pipelined step: 1.86 against
-// 2.14-2.19 ms with one instance for both).
-template <bool FEW>
-__global__ __launch_bounds__(kBlock) void bdp_layer_kernel(BdpArgs a, int N_k, int N_k1,
+// One layer for every payoff: workgroup (x, y) takes rows 16 x .. + 15 and
+// payoffs 16 y .. + 15 (the count rows are re-read per group of payoffs, from
+// L2 for all but the first).
+template <int W, int AHEAD, bool DENSE>
+__global__ __launch_bounds__(64 * W) void bdp_layer_kernel(BdpArgs a, int N_k, int N_k1,
                                                            int64_t pt_k, int64_t pt_k1,
                                                            int64_t cnt_k) {
   const int lane = threadIdx.x & 63;
-  const int i = blockIdx.x * kWaves + (threadIdx.x >> 6);
-  if (i >= N_k) return;
   const int q0 = blockIdx.y * kPay;
   const int nq = (a.n_pay - q0) < kPay ? (a.n_pay - q0) : kPay;
-  // the row's counts: dense, or the band of columns j0 .. j0 + len - 1
-  const int32_t* row;
-  int len;
-  int64_t col0 = pt_k1;
-  if (a.band_off) {
+  const int i0 = blockIdx.x * kRows;
+  // rows past the end repeat the last one (their results are dropped)
+  const int i = i0 + (lane & 15) < N_k ? i0 + (lane & 15) : N_k - 1;
+  TileRows R;
+  if (!DENSE && a.band_off) {
+    // the band of columns band_lo .. of every row; the tile covers them all
     const int64_t r = pt_k + i;
     const int64_t o = a.band_off[r];
-    row = a.counts + o;
-    len = (int)(a.band_off[r + 1] - o);
-    col0 += a.band_lo[r];
+    R.lo = a.band_lo[r];
+    R.hi = R.lo + (int)(a.band_off[r + 1] - o);
+    R.row = a.counts + o - R.lo;
+    R.from = R.all_lo = R.lo;
+    R.to = R.all_hi = R.hi;
+#pragma unroll
+    for (int m = 8; m > 0; m >>= 1) {
+      R.from = min(R.from, __shfl_xor(R.from, m, 64));
+      R.to = max(R.to, __shfl_xor(R.to, m, 64));
+      R.all_lo = max(R.all_lo, __shfl_xor(R.all_lo, m, 64));
+      R.all_hi = min(R.all_hi, __shfl_xor(R.all_hi, m, 64));
+    }
+    R.from = __builtin_amdgcn_readfirstlane(R.from);
+    R.to = __builtin_amdgcn_readfirstlane(R.to);
+    R.all_lo = __builtin_amdgcn_readfirstlane(R.all_lo);
+    R.all_hi = __builtin_amdgcn_readfirstlane(R.all_hi);
   } else {
-    row = a.counts + cnt_k + (int64_t)i * N_k1;
-    len = N_k1;
+    R.row = a.counts + cnt_k + (int64_t)i * N_k1;
+    R.lo = R.from = R.all_lo = 0;
+    R.hi = R.to = R.all_hi = N_k1;
   }
+  const int q = lane & 15;
+  double s;
   int64_t p;
-  double s[kPay];
-  row_sums<FEW>(row, len, a.V, a.P, q0, nq, col0, lane, p, s);
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    p += __shfl_xor(p, off, 64);
-#pragma unroll
-    for (int q = 0; q < kPay; ++q) s[q] += __shfl_xor(s[q], off, 64);
+  if (!tile_sums<W, AHEAD, DENSE>(R, a.V + (int64_t)(q0 + (q < nq ? q : 0)) * a.P + pt_k1, N_k1,
+                                  s, p))
+    return;
+  const int row = i0 + (int)(threadIdx.x >> 4), col = (int)(threadIdx.x & 15);
+  if (row < N_k && col < nq) {
+    const double cont = p > 0 ? s / (double)p : 0.0;
+    const int64_t at = (int64_t)(q0 + col) * a.P + pt_k + row;
+    const double f = a.phi[at];
+    a.V[at] = f > cont ? f : cont;
   }
-  if (lane < nq) {
-    // lane q finalises payoff q0 + q
-    double sq = s[0];
-#pragma unroll
-    for (int q = 1; q < kPay; ++q)
-      if (lane == q) sq = s[q];
-    const double cont = p > 0 ? sq / (double)p : 0.0;
-    const int64_t at = (int64_t)(q0 + lane) * a.P + pt_k + i;
+}
+
+// The same for Q <= kFewPay payoffs and rows of at least four columns, dense.
+template <int Q>
+__global__ __launch_bounds__(64 * kFewWaves) void bdp_few_kernel(BdpArgs a, int N_k, int N_k1,
+                                                                 int64_t pt_k, int64_t pt_k1,
+                                                                 int64_t cnt_k) {
+  const int i0 = blockIdx.x * kFewRows;
+  double s, p;
+  if (!few_sums<Q>(a.counts + cnt_k + (int64_t)i0 * N_k1, min(kFewRows, N_k - i0), a.V + pt_k1,
+                   a.P, N_k1, s, p))
+    return;
+  const int row = i0 + (int)threadIdx.x / Q;
+  if (row < N_k) {
+    const double cont = p > 0.0 ? s / p : 0.0;
+    const int64_t at = (int64_t)((int)threadIdx.x % Q) * a.P + pt_k + row;
     const double f = a.phi[at];
     a.V[at] = f > cont ? f : cont;
   }
@@ -144,14 +275,25 @@ __global__ void copy_last_layer_kernel(BdpArgs a, int64_t pt_n, int N_n) {
 hipError_t launch_bdp_layer(const BdpArgs& a, int k, int N_k, int N_k1, int64_t pt_k,
                             int64_t pt_k1, int64_t cnt_k, hipStream_t s) {
   (void)k;
-  const unsigned blocks = (unsigned)((N_k + kWaves - 1) / kWaves);
-  const unsigned groups = (unsigned)((a.n_pay + kPay - 1) / kPay);
-  if (a.n_pay <= kFewPay)
-    hipLaunchKernelGGL(bdp_layer_kernel<true>, dim3(blocks, groups), dim3(kBlock), 0, s, a, N_k,
-                       N_k1, pt_k, pt_k1, cnt_k);
-  else
-    hipLaunchKernelGGL(bdp_layer_kernel<false>, dim3(blocks, groups), dim3(kBlock), 0, s, a, N_k,
-                       N_k1, pt_k, pt_k1, cnt_k);
+  const bool dense = !a.band_off && N_k1 >= 4;
+  if (dense && a.n_pay <= kFewPay) {
+    const dim3 grid((unsigned)((N_k + kFewRows - 1) / kFewRows)), block(64 * kFewWaves);
+    if (a.n_pay == 1)
+      hipLaunchKernelGGL(bdp_few_kernel<1>, grid, block, 0, s, a, N_k, N_k1, pt_k, pt_k1, cnt_k);
+    else
+      hipLaunchKernelGGL(bdp_few_kernel<2>, grid, block, 0, s, a, N_k, N_k1, pt_k, pt_k1, cnt_k);
+    return hipGetLastError();
+  }
+  const dim3 grid((unsigned)((N_k + kRows - 1) / kRows), (unsigned)((a.n_pay + kPay - 1) / kPay));
+#define QTREE_BDP(W, DENSE)                                                                    \
+  hipLaunchKernelGGL((bdp_layer_kernel<W, 4, DENSE>), grid, dim3(64 * W), 0, s, a, N_k, N_k1, \
+                     pt_k, pt_k1, cnt_k)
+  // waves enough for a row to be in flight at once, up to 1024 columns
+  if (!dense) QTREE_BDP(8, false);
+  else if (N_k1 <= 256) QTREE_BDP(4, true);
+  else if (N_k1 <= 512) QTREE_BDP(8, true);
+  else QTREE_BDP(16, true);
+#undef QTREE_BDP
   return hipGetLastError();
 }
 
@@ -164,11 +306,14 @@ hipError_t launch_copy_last_layer(const BdpArgs& a, int64_t pt_n, int N_n, hipSt
 
 // Batched BDP.  The recursion is sequential in k, so it runs as backward
 // steps: step j takes layer n - 1 - j of every contract with n > j, its rows
-// cut into tasks of up to kBdpTaskRows rows, one wave per row (as
-// bdp_layer_kernel) for the job's up to kPay payoffs; a launch boundary
-// separates the steps.  Every contract's work is spread over the whole chip
-// at every step.
-constexpr int kBdpBlock = 64 * kBdpTaskRows;
+// cut into tasks of kBdpTaskRows rows; a launch boundary separates the steps.
+// Every contract's work is spread over the whole chip at every step.  A task
+// is one tile for the job's up to kPay payoffs; a batch whose jobs all have
+// at most kFewPay payoffs and no layer below four points cuts a task into
+// workgroups of kFewRows rows instead.
+constexpr int kStepWaves = 8;
+static_assert(kBdpTaskRows == kRows, "a task is one tile");
+static_assert(kBdpTaskRows % kFewRows == 0, "a task is whole few-payoff workgroups");
 
 __global__ void bdp_batch_copy_kernel(const BdpJob* jobs) {
   const BdpJob& J = jobs[blockIdx.y];
@@ -182,50 +327,81 @@ __global__ void bdp_batch_copy_kernel(const BdpJob* jobs) {
   }
 }
 
-__global__ __launch_bounds__(kBdpBlock) void bdp_step_kernel(const BdpJob* jobs,
-                                                             const BdpTask* tasks) {
+template <bool DENSE>
+__global__ __launch_bounds__(64 * kStepWaves) void bdp_step_kernel(const BdpJob* jobs,
+                                                                   const BdpTask* tasks) {
   const BdpTask T = tasks[blockIdx.x];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (wave >= T.nrows) return;
+  const int lane = threadIdx.x & 63;
   const BdpJob& J = jobs[T.job];
   const LayerDev* layers = as_global(J.layers);
   const LayerDev& L = layers[T.k];
   const LayerDev& L1 = layers[T.k + 1];
   double* V = as_global(J.V);
-  const int i = T.row0 + wave;
-  const int32_t* row = as_global(J.counts) + L.cnt_off + (int64_t)i * L.N1;
+  const int r = lane & 15;  // rows past the end repeat the last one
+  TileRows R;
+  R.row = as_global(J.counts) + L.cnt_off + (int64_t)(T.row0 + (r < T.nrows ? r : T.nrows - 1)) * L.N1;
+  R.lo = R.from = R.all_lo = 0;
+  R.hi = R.to = R.all_hi = L.N1;
+  const double* x = V + (int64_t)(J.q0 + (r < J.nq ? r : 0)) * J.P + L1.pt_off;
+  double s;
   int64_t p;
-  double s[kPay];
-  row_sums<true>(row, L.N1, V, J.P, J.q0, J.nq, L1.pt_off, lane, p, s);
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    p += __shfl_xor(p, off, 64);
-#pragma unroll
-    for (int q = 0; q < kPay; ++q) s[q] += __shfl_xor(s[q], off, 64);
-  }
-  if (lane < J.nq) {
-    double sq = s[0];
-#pragma unroll
-    for (int q = 1; q < kPay; ++q)
-      if (lane == q) sq = s[q];
-    const double cont = p > 0 ? sq / (double)p : 0.0;
-    const int64_t at = (int64_t)(J.q0 + lane) * J.P + L.pt_off + i;
+  if (!tile_sums<kStepWaves, 4, DENSE>(R, x, L.N1, s, p)) return;
+  const int row = (int)(threadIdx.x >> 4), col = (int)(threadIdx.x & 15);
+  if (row < T.nrows && col < J.nq) {
+    const double cont = p > 0 ? s / (double)p : 0.0;
+    const int64_t at = (int64_t)(J.q0 + col) * J.P + L.pt_off + T.row0 + row;
     const double f = as_global(J.phi)[at];
     V[at] = f > cont ? f : cont;
   }
 }
 
-hipError_t launch_bdp_steps(const BdpJob* jobs, int n_jobs, int max_last, const BdpTask* tasks,
-                            const int* step_off, int n_steps, hipStream_t s) {
+__global__ __launch_bounds__(64 * kFewWaves) void bdp_step_few_kernel(const BdpJob* jobs,
+                                                                      const BdpTask* tasks) {
+  constexpr int kParts = kBdpTaskRows / kFewRows;
+  const BdpTask T = tasks[blockIdx.x / kParts];
+  const int r0 = (int)(blockIdx.x % kParts) * kFewRows;
+  if (r0 >= T.nrows) return;
+  const BdpJob& J = jobs[T.job];
+  const LayerDev* layers = as_global(J.layers);
+  const LayerDev& L = layers[T.k];
+  const LayerDev& L1 = layers[T.k + 1];
+  double* V = as_global(J.V);
+  const int i0 = T.row0 + r0;
+  // a one-payoff job repeats its payoff as the second one
+  double s, p;
+  if (!few_sums<kFewPay>(as_global(J.counts) + L.cnt_off + (int64_t)i0 * L.N1,
+                         min(kFewRows, T.nrows - r0), V + (int64_t)J.q0 * J.P + L1.pt_off,
+                         J.nq > 1 ? J.P : 0, L.N1, s, p))
+    return;
+  const int row = (int)threadIdx.x / kFewPay, q = (int)threadIdx.x % kFewPay;
+  if (r0 + row < T.nrows && q < J.nq) {
+    const double cont = p > 0.0 ? s / p : 0.0;
+    const int64_t at = (int64_t)(J.q0 + q) * J.P + L.pt_off + i0 + row;
+    const double f = as_global(J.phi)[at];
+    V[at] = f > cont ? f : cont;
+  }
+}
+
+hipError_t launch_bdp_steps(const BdpJob* jobs, int n_jobs, int max_last, int max_nq, int min_n1,
+                            const BdpTask* tasks, const int* step_off, int n_steps,
+                            hipStream_t s) {
   if (n_jobs <= 0) return hipSuccess;
   const unsigned cx = (unsigned)((max_last + kBlock - 1) / kBlock);
   hipLaunchKernelGGL(bdp_batch_copy_kernel, dim3(cx < 1 ? 1 : cx, (unsigned)n_jobs), dim3(kBlock),
                      0, s, jobs);
+  const bool few = max_nq <= kFewPay && min_n1 >= 4;
   for (int j = 0; j < n_steps; ++j) {
     const int cnt = step_off[j + 1] - step_off[j];
-    if (cnt > 0)
-      hipLaunchKernelGGL(bdp_step_kernel, dim3((unsigned)cnt), dim3(kBdpBlock), 0, s, jobs,
-                         tasks + step_off[j]);
+    if (cnt <= 0) continue;
+    if (few)
+      hipLaunchKernelGGL(bdp_step_few_kernel, dim3((unsigned)(cnt * (kBdpTaskRows / kFewRows))),
+                         dim3(64 * kFewWaves), 0, s, jobs, tasks + step_off[j]);
+    else if (min_n1 >= 4)
+      hipLaunchKernelGGL(bdp_step_kernel<true>, dim3((unsigned)cnt), dim3(64 * kStepWaves), 0, s,
+                         jobs, tasks + step_off[j]);
+    else
+      hipLaunchKernelGGL(bdp_step_kernel<false>, dim3((unsigned)cnt), dim3(64 * kStepWaves), 0, s,
+                         jobs, tasks + step_off[j]);
   }
   return hipGetLastError();
 }
