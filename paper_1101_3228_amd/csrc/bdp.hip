@@ -20,11 +20,10 @@ constexpr int kFewRows = 4;  // ... and rows per workgroup
 constexpr int kFewWaves = 4;
 
 // The rows of a tile: this lane's row (lane % 16), a pointer indexed by
-// column, and the columns [lo, hi) it holds; [from, to) covers every row and
-// every row holds [all_lo, all_hi) (the same for the workgroup).
+// column, and the columns [lo, hi) it holds; [from, to) covers every row.
 struct TileRows {
   const int32_t* row;
-  int lo, hi, from, to, all_lo, all_hi;
+  int lo, hi, from, to;
 };
 
 // One tile of kRows rows by one workgroup of W waves: wave w takes the
@@ -53,9 +52,21 @@ __device__ __forceinline__ bool tile_sums(const TileRows& R, const double* __res
   for (int j0 = R.from + 16 * wave; j0 < R.to; j0 += 16 * W * AHEAD) {
     int32_t c[AHEAD][4];
     double v[AHEAD][4];
-    const int last = j0 + 16 * W * (AHEAD - 1) + 16;
-    load_chunks<AHEAD, DENSE>(R.row, x, j0 + 4 * g, 16 * W, R.lo, R.hi, n1,
-                              j0 >= R.all_lo && last <= R.all_hi && last <= n1, c, v);
+    const int j = j0 + 4 * g;
+    if (DENSE) {
+      load_cols(R.row, n1, j, 16 * W, c);
+      load_cols(x, n1, j, 16 * W, v);
+      if (j0 + 16 * W * (AHEAD - 1) + 16 > n1) {
+        drop_tails(n1, j, 16 * W, c);
+        drop_tails(n1, j, 16 * W, v);
+      }
+    } else {
+#pragma unroll
+      for (int a = 0; a < AHEAD; ++a)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[a][u] = x[min(j + 16 * W * a + u, n1 - 1)];
+      load_band(R.row, R.lo, R.hi, j, 16 * W, c);
+    }
 #pragma unroll
     for (int a = 0; a < AHEAD; ++a) {
       p += (int64_t)c[a][0] + c[a][1] + c[a][2] + c[a][3];
@@ -211,23 +222,19 @@ __global__ __launch_bounds__(64 * W) void bdp_layer_kernel(BdpArgs a, int N_k, i
     R.lo = a.band_lo[r];
     R.hi = R.lo + (int)(a.band_off[r + 1] - o);
     R.row = a.counts + o - R.lo;
-    R.from = R.all_lo = R.lo;
-    R.to = R.all_hi = R.hi;
+    R.from = R.lo;
+    R.to = R.hi;
 #pragma unroll
     for (int m = 8; m > 0; m >>= 1) {
       R.from = min(R.from, __shfl_xor(R.from, m, 64));
       R.to = max(R.to, __shfl_xor(R.to, m, 64));
-      R.all_lo = max(R.all_lo, __shfl_xor(R.all_lo, m, 64));
-      R.all_hi = min(R.all_hi, __shfl_xor(R.all_hi, m, 64));
     }
     R.from = __builtin_amdgcn_readfirstlane(R.from);
     R.to = __builtin_amdgcn_readfirstlane(R.to);
-    R.all_lo = __builtin_amdgcn_readfirstlane(R.all_lo);
-    R.all_hi = __builtin_amdgcn_readfirstlane(R.all_hi);
   } else {
     R.row = a.counts + cnt_k + (int64_t)i * N_k1;
-    R.lo = R.from = R.all_lo = 0;
-    R.hi = R.to = R.all_hi = N_k1;
+    R.lo = R.from = 0;
+    R.hi = R.to = N_k1;
   }
   const int q = lane & 15;
   double s;
@@ -340,8 +347,8 @@ __global__ __launch_bounds__(64 * kStepWaves) void bdp_step_kernel(const BdpJob*
   const int r = lane & 15;  // rows past the end repeat the last one
   TileRows R;
   R.row = as_global(J.counts) + L.cnt_off + (int64_t)(T.row0 + (r < T.nrows ? r : T.nrows - 1)) * L.N1;
-  R.lo = R.from = R.all_lo = 0;
-  R.hi = R.to = R.all_hi = L.N1;
+  R.lo = R.from = 0;
+  R.hi = R.to = L.N1;
   const double* x = V + (int64_t)(J.q0 + (r < J.nq ? r : 0)) * J.P + L1.pt_off;
   double s;
   int64_t p;

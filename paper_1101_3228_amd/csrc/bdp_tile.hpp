@@ -44,63 +44,50 @@ struct Cols4 {
   __device__ Cols4(int j, int n) : at(min(j, n - 4)), drop(j - at) {}
 };
 
-// Counts and values of A chunks, this lane's columns j + stride a .. + 3 of
-// each: c from the row that holds columns [lo, hi) at row[lo .. hi), x from
-// the n1 values v; zero outside.  whole (the same for the wave): all of them
-// are held.  DENSE: lo = 0, hi = n1 >= 4; else every address is clamped into
-// its array.
-template <int A, bool DENSE>
-__device__ __forceinline__ void load_chunks(const int32_t* __restrict__ row,
-                                            const double* __restrict__ v, int j, int stride,
-                                            int lo, int hi, int n1, bool whole,
-                                            int32_t (&c)[A][4], double (&x)[A][4]) {
-  if (whole) {
+// A chunks, this lane's columns j + stride a .. + 3 of each (as Cols4): the
+// loads, and the drops where a chunk of the wave crosses the end.
+template <int A>
+__device__ __forceinline__ void load_cols(const int32_t* __restrict__ row, int n, int j, int stride,
+                                          int32_t (&c)[A][4]) {
 #pragma unroll
-    for (int a = 0; a < A; ++a) {
-      const Int4U q = *reinterpret_cast<const Int4U*>(row + j + stride * a);
-      const Dbl4U y = *reinterpret_cast<const Dbl4U*>(v + j + stride * a);
+  for (int a = 0; a < A; ++a) {
+    const Int4U q = *reinterpret_cast<const Int4U*>(row + Cols4(j + stride * a, n).at);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        c[a][u] = q.v[u];
-        x[a][u] = y.v[u];
-      }
-    }
-  } else if (DENSE) {
-#pragma unroll
-    for (int a = 0; a < A; ++a) {
-      const Cols4 t(j + stride * a, n1);
-      const Int4U q = *reinterpret_cast<const Int4U*>(row + t.at);
-      const Dbl4U y = *reinterpret_cast<const Dbl4U*>(v + t.at);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        c[a][u] = q.v[u];
-        x[a][u] = y.v[u];
-      }
-    }
-#pragma unroll
-    for (int a = 0; a < A; ++a) {
-      const Cols4 t(j + stride * a, n1);
-      drop_front(c[a], t.drop);
-      drop_front(x[a], t.drop);
-    }
-  } else {
-#pragma unroll
-    for (int a = 0; a < A; ++a)
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int t = j + stride * a + u;
-        c[a][u] = row[min(max(t, lo), hi - 1)];
-        x[a][u] = v[min(t, n1 - 1)];
-      }
-#pragma unroll
-    for (int a = 0; a < A; ++a)
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int t = j + stride * a + u;
-        c[a][u] = (t >= lo && t < hi) ? c[a][u] : 0;
-        x[a][u] = t < n1 ? x[a][u] : 0.0;
-      }
+    for (int u = 0; u < 4; ++u) c[a][u] = q.v[u];
   }
+}
+template <int A>
+__device__ __forceinline__ void load_cols(const double* __restrict__ v, int n, int j, int stride,
+                                          double (&x)[A][4]) {
+#pragma unroll
+  for (int a = 0; a < A; ++a) {
+    const Dbl4U y = *reinterpret_cast<const Dbl4U*>(v + Cols4(j + stride * a, n).at);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) x[a][u] = y.v[u];
+  }
+}
+template <int A, class T>
+__device__ __forceinline__ void drop_tails(int n, int j, int stride, T (&x)[A][4]) {
+#pragma unroll
+  for (int a = 0; a < A; ++a) drop_front(x[a], Cols4(j + stride * a, n).drop);
+}
+
+// Counts of A chunks from a row that holds columns [lo, hi), hi > lo, at
+// row[lo .. hi) (a band, or a row too short for Cols4), zero outside.
+template <int A>
+__device__ __forceinline__ void load_band(const int32_t* __restrict__ row, int lo, int hi, int j,
+                                          int stride, int32_t (&c)[A][4]) {
+#pragma unroll
+  for (int a = 0; a < A; ++a)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) c[a][u] = row[min(max(j + stride * a + u, lo), hi - 1)];
+#pragma unroll
+  for (int a = 0; a < A; ++a)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int t = j + stride * a + u;
+      c[a][u] = (t >= lo && t < hi) ? c[a][u] : 0;
+    }
 }
 
 __device__ __forceinline__ bool finite4(const double (&x)[4]) {

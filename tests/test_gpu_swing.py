@@ -92,3 +92,42 @@ def test_swing_rejects_bad_constraints():
         with pytest.raises(qt.QtreeError) as e:
             plan.swing(counts, v, *Q)
         assert e.value.status == 1
+
+
+@pytest.mark.parametrize("sides", [(1, 3), (3, 5), (4, 4), (4, 9), (16, 33)], ids=str)
+@pytest.mark.parametrize("Q", [(0, 13), (3, 14), (31, 31), (2, 40), (90, 155)], ids=str)
+def test_swing_tile_edges(sides, Q):
+    """Points below a load of four columns, below, at and past a tile of 16
+    rows, past two rounds of 256 columns (528); levels below, at and past the 15
+    or 31 a workgroup writes (one tile of levels, and two with (16, 33)
+    points and more than 135 levels).  Tolerance: sums of the same products in another
+    order, 2 n m 2^-53 of the largest term (n <= 160, m <= 528): 2e-11."""
+    _case(f"swing tiles {sides} {Q}")
+    spec, grid, N, plan, counts = _ou_tree(max(40, Q[1] + 5), sides, 3000, seed=3)
+    v = plan.payoff_forward(20.0, 19.0, 0.02, 1.0, [0.7, 1.4])
+    P0, P = plan.swing(counts, v, *Q)
+    rP0, rP = O.swing(counts.cpu().numpy(), N, v.cpu().numpy(), *Q, want_all=True)
+    Pg, Pr = P.cpu().numpy().T, rP
+    fin = np.isfinite(Pr)
+    assert np.array_equal(np.where(fin, 0.0, Pg), np.where(fin, 0.0, Pr))
+    assert np.abs(Pg[fin] - Pr[fin]).max() <= 2e-11 * np.abs(Pr[fin]).max()
+    assert P0 == pytest.approx(rP0, rel=2e-11, abs=1e-12)
+
+
+def test_swing_infinite_obstacle_reaches_only_its_rows():
+    """An infinite obstacle of one point (the caller's) makes the states that
+    can reach it infinite and leaves the others finite (a zero count times
+    infinity would be NaN)."""
+    _case("swing infinite obstacle")
+    spec, grid, N, plan, counts = _ou_tree(6, (5, 5), 400, seed=4)
+    v = plan.payoff_forward(20.0, 20.0, 0.0, 1.0, [0.7, 1.4])
+    pt, off, c = plan.point_offsets(), plan.count_offsets(), counts.cpu().numpy()
+    v[int(pt[5]) + 3] = np.inf
+    _, P = plan.swing(counts, v, 0, 6)
+    P = P.cpu().numpy()
+    reach = np.arange(25) == 3                          # layer 5: the point itself
+    for k in range(4, 0, -1):
+        inf = np.isinf(P[pt[k + 1]:pt[k + 2], 0])
+        assert np.array_equal(inf, reach), k + 1
+        assert not np.isnan(P[pt[k + 1]:pt[k + 2]]).any()
+        reach = (c[off[k]:off[k + 1]].reshape(25, 25)[:, reach] != 0).any(1)
