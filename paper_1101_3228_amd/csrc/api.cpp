@@ -106,7 +106,13 @@ int64_t total_buckets(int n, const int32_t* N) {
   return b;
 }
 
-WsLayout ws_layout(int d, int n, const int32_t* N, int64_t batch_chunks) {
+int64_t path_cells(int n, const int32_t* N) {
+  if (max_tiles_of(n, N) > kPathTiles) return 0;
+  const int64_t c = std::min<int64_t>(kPathCells, kPathBytes / (2 * (int64_t)n) / 1024 * 1024);
+  return c < 4096 ? 0 : c;
+}
+
+WsLayout ws_layout(int d, int n, const int32_t* N, int64_t batch_chunks, int64_t cells) {
   WsLayout l{};
   size_t off = 0;
   l.layers = off;
@@ -133,6 +139,8 @@ WsLayout ws_layout(int d, int n, const int32_t* N, int64_t batch_chunks) {
   const int64_t buckets = d == 2 ? total_buckets(n, N) : 0;
   l.bk_rows = off;
   off = align_up(off + sizeof(uint16_t) * kBucketRow * (size_t)buckets, 256);
+  l.path = off;
+  off = align_up(off + sizeof(uint16_t) * (size_t)n * (size_t)cells, 256);
   // scratch of the two-pass counting (only when every count block has at
   // most kMaxTiles tiles)
   const int mt = max_tiles_of(n, N);
@@ -281,7 +289,8 @@ qtree_status qtree_workspace_size(int32_t d, int32_t n, const int32_t* N, uint64
   if (s != QTREE_OK) return s;
   if (batch_samples == 0) batch_samples = qtree::kDefaultBatch;
   if (batch_samples > (1ull << 31)) return fail(QTREE_EINVAL, "batch_samples must be <= 2^31");
-  *bytes = qtree::ws_layout(d, n, N, qtree::chunks_for(d, batch_samples)).total;
+  *bytes = qtree::ws_layout(d, n, N, qtree::chunks_for(d, batch_samples),
+                            qtree::path_cells(n, N)).total;
   return QTREE_OK;
 }
 
@@ -466,23 +475,31 @@ qtree_status qtree_plan_create(const qtree_model* model, const float* grid, cons
   }
   // the scratch takes whatever the workspace holds beyond the layer tables
   p.max_tiles = qtree::max_tiles_of(n, N);
-  const qtree::WsLayout base = qtree::ws_layout(d, n, N, 0);
+  qtree::WsLayout base = qtree::ws_layout(d, n, N, 0, 0);
   if (workspace_bytes < base.total)
     return fail(QTREE_ENOMEM, "workspace needs at least " + std::to_string(base.total) + " bytes");
+  // the pathwise scratch, where the workspace holds it beside a chunk per layer
+  const bool two = qtree::two_pass_fits(d, n, N);
+  const int64_t cells = qtree::path_cells(n, N);
+  if (cells > 0 && qtree::ws_layout(d, n, N, two ? 1 : 0, cells).total <= workspace_bytes) {
+    p.path_cells = cells;
+    base = qtree::ws_layout(d, n, N, 0, cells);
+  }
   p.batch_chunks = 0;
-  if (qtree::two_pass_fits(d, n, N)) {
+  if (two) {
     const size_t per = (size_t)n * (sizeof(uint16_t) * qtree::kChunk +
                                     sizeof(uint32_t) * (size_t)(p.max_tiles + 1));
     int64_t c = (int64_t)((workspace_bytes - base.total) / per);
-    while (c > 0 && qtree::ws_layout(d, n, N, c).total > workspace_bytes) --c;
+    while (c > 0 && qtree::ws_layout(d, n, N, c, p.path_cells).total > workspace_bytes) --c;
     p.batch_chunks = c;
   }
   p.two_pass_ok = p.batch_chunks > 0;
-  p.two_pass_shape = qtree::two_pass_fits(d, n, N);
-  p.lay = qtree::ws_layout(d, n, N, p.batch_chunks);
+  p.two_pass_shape = two;
+  p.lay = qtree::ws_layout(d, n, N, p.batch_chunks, p.path_cells);
 
-  // host image of the workspace
-  std::vector<char> img(p.lay.total, 0);
+  // host image of the workspace's tables (the bucket rows are built on the
+  // device, the scratch behind them is written before it is read)
+  std::vector<char> img(p.lay.bk_rows, 0);
   auto* layers = reinterpret_cast<qtree::LayerDev*>(img.data() + p.lay.layers);
   // histogram parts: a layer with fewer super tiles than the largest layer
   // is split over the chunks into up to that ratio (at most 16), so that no
@@ -597,7 +614,7 @@ qtree_status qtree_plan_create(const qtree_model* model, const float* grid, cons
     }
     if (d == 2) bucket_boxes(p, model, grid, layers);
   }
-  hipError_t e = hipMemcpy(workspace, img.data(), p.lay.total, hipMemcpyHostToDevice);
+  hipError_t e = hipMemcpy(workspace, img.data(), img.size(), hipMemcpyHostToDevice);
   if (e != hipSuccess) return hip_fail(e, "hipMemcpy(workspace)");
   p.ws = static_cast<char*>(workspace);
   if (p.buckets > 0) {
@@ -891,6 +908,45 @@ qtree_status qtree_plan_tune(qtree_plan* plan, int32_t key, int64_t value) {
   return fail(QTREE_EINVAL, "unknown tuning key");
 }
 
+// Pathwise counts through the plan's cell scratch, in passes of at most
+// path_cells paths.  Calls on other streams or threads keep working: the
+// scratch is handed over by an event, and a stream under capture, whose
+// replays no event could order, does not use it (*used = false: nothing was
+// launched).
+static hipError_t path_passes(const qtree_plan* p, qtree::FwdArgs a, bool zero, hipStream_t s,
+                              bool* used) {
+  *used = false;
+  if (p->path_cells == 0) return hipSuccess;
+  if (s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamIsCapturing(s, &st);
+    if (e != hipSuccess) return e;
+    if (st != hipStreamCaptureStatusNone) return hipSuccess;
+  }
+  qtree_plan::PathUse& u = *p->path_use;
+  std::lock_guard<std::mutex> hold(u.lock);
+  hipError_t e = hipSuccess;
+  if (!u.done) {
+    e = hipEventCreateWithFlags(&u.done, hipEventDisableTiming);
+  } else if (u.last != s) {
+    e = hipStreamWaitEvent(s, u.done, 0);
+  }
+  if (e != hipSuccess) return e;
+  *used = true;
+  a.total_tiles = p->total_tiles;
+  uint16_t* cells = reinterpret_cast<uint16_t*>(p->ws + p->lay.path);
+  const uint64_t m0 = a.m0, M = a.M;
+  for (uint64_t lo = 0; lo < M && e == hipSuccess; lo += (uint64_t)p->path_cells) {
+    a.m0 = m0 + lo;
+    a.M = std::min<uint64_t>((uint64_t)p->path_cells, M - lo);
+    e = qtree::launch_path_counts(a, cells, p->path_cells, zero && lo == 0, s);
+  }
+  // recorded also after a failed launch: what was queued before it may run
+  const hipError_t r = hipEventRecord(u.done, s);
+  u.last = s;
+  return e != hipSuccess ? e : r;
+}
+
 static qtree_status transitions_impl(const qtree_plan* plan, uint64_t m0, uint64_t M,
                                      uint64_t seed, uint32_t contract_id, qtree_mode mode,
                                      int32_t* counts, void* stream, bool zero,
@@ -920,12 +976,18 @@ static qtree_status transitions_impl(const qtree_plan* plan, uint64_t m0, uint64
     return fail(QTREE_EUNSUPPORTED, "two-pass counting needs scratch this call does not have");
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e = hipSuccess;
+  qtree::FwdArgs a = fwd_args(plan, m0, M, seed, contract_id, counts);
+  if (mode == QTREE_PATHWISE && M > 0 && !scratch) {
+    bool used = false;
+    e = path_passes(plan, a, zero, s, &used);
+    if (e != hipSuccess) return hip_fail(e, "pathwise launch");
+    if (used) return QTREE_OK;
+  }
   if (zero && !two) {
     e = qtree::launch_zero_i32(counts, plan->entries, s);
     if (e != hipSuccess) return hip_fail(e, "zero fill");
   }
   if (M == 0) return QTREE_OK;
-  qtree::FwdArgs a = fwd_args(plan, m0, M, seed, contract_id, counts);
   if (mode == QTREE_PATHWISE) {
     e = qtree::launch_fwd_path(a, s);
   } else if (two) {

@@ -10,8 +10,6 @@
 //                   paper's choice over kd-trees, Sec. 3 "Nearest Neighbor
 //                   search"), S samples per lane so each LDS broadcast read
 //                   feeds S distance evaluations.
-//  - fwd_path     : pathwise estimate (Sec. 3, Algorithms I/II), one lane per
-//                   path walking all layers.
 // Counts are incremented with device-scope atomic adds (Sec. 3, "Updating
 // p^k_ij"); integer addition makes the result independent of the order.
 #include "qtree_internal.hpp"
@@ -136,90 +134,6 @@ __global__ __launch_bounds__(kBlock) void fwd_layer_nd(FwdArgs a) {
   }
 }
 
-// Pathwise (Algorithm I/II): one lane per path.  d = 1 keeps the midpoints of
-// every layer in LDS when they fit (ws_mids_in_lds), d >= 2 stages the grid
-// of the next layer in LDS at every step (the whole block walks the layers
-// together).
-template <int D>
-__global__ __launch_bounds__(kBlock) void fwd_path(FwdArgs a, int mids_in_lds) {
-  extern __shared__ float lds[];
-  const uint64_t m = a.m0 + (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-  const bool live = m < a.m0 + a.M;
-  const uint32_t mc = (uint32_t)(live ? m : a.m0);
-  float x[D];
-#pragma unroll
-  for (int c = 0; c < D; ++c) x[c] = a.layers[0].x0[c];
-  int i = 0;
-  if (D == 1) {
-    const float* mids = a.mids;
-    if (mids_in_lds) {
-      for (int64_t t = threadIdx.x; t < a.mids_total; t += kBlock) lds[t] = a.mids[t];
-      __syncthreads();
-      mids = lds;
-    }
-    float zb[4];
-    for (int k = 0; k < a.n; ++k) {
-      const LayerDev& L = a.layers[k];
-      if ((k & 3) == 0) {
-        const U4 r = philox4x32_10(U4{mc, (uint32_t)(k >> 2), a.contract, 1u}, a.key0, a.key1);
-        box_muller(r.x, r.y, zb[0], zb[1]);
-        box_muller(r.z, r.w, zb[2], zb[3]);
-      }
-      const float e = zb[k & 3];
-      const float y = fmaf(L.T[0], e, fmaf(L.A[0], x[0], L.b[0]));
-      const LayerDev& L1 = a.layers[k + 1];
-      const int j = cell_1d(mids + L1.aux_off, L1.logP, y);
-      if (live) count_add(a.counts + L.cnt_off + (int64_t)i * L.N1 + j);
-      i = j;
-      x[0] = y;
-    }
-  } else {
-    float4* g = reinterpret_cast<float4*>(lds);
-    float eb[4];
-    for (int k = 0; k < a.n; ++k) {
-      const LayerDev& L = a.layers[k];
-      const LayerDev& L1 = a.layers[k + 1];
-      __syncthreads();
-      for (int t = threadIdx.x; t < L1.N; t += kBlock) g[t] = a.pts[L1.pt_off + t];
-      __syncthreads();
-      float e[D];
-      if (D == 2) {
-        if ((k & 1) == 0) {
-          const U4 r = philox4x32_10(U4{mc, (uint32_t)(k >> 1), a.contract, 1u}, a.key0, a.key1);
-          box_muller(r.x, r.y, eb[0], eb[1]);
-          box_muller(r.z, r.w, eb[2], eb[3]);
-        }
-        e[0] = eb[(k & 1) * 2];
-        e[1] = eb[(k & 1) * 2 + 1];
-      } else {
-        const U4 r = philox4x32_10(U4{mc, (uint32_t)k, a.contract, 1u}, a.key0, a.key1);
-        float unused;
-        box_muller(r.x, r.y, e[0], e[1]);
-        box_muller(r.z, r.w, e[D - 1], unused);
-      }
-      float y[D];
-#pragma unroll
-      for (int r = 0; r < D; ++r) {
-        float v = L.b[r];
-#pragma unroll
-        for (int c = 0; c < D; ++c) v = fmaf(L.A[r * D + c], x[c], v);
-#pragma unroll
-        for (int c = 0; c < D; ++c) v = fmaf(L.T[r * D + c], e[c], v);
-        y[r] = v;
-      }
-      float yq[1][D];
-#pragma unroll
-      for (int c = 0; c < D; ++c) yq[0][c] = y[c];
-      int j;
-      argmin_scan<D, 1>(g, L1.N, yq, &j);
-      if (live) count_add(a.counts + L.cnt_off + (int64_t)i * L.N1 + j);
-      i = j;
-#pragma unroll
-      for (int c = 0; c < D; ++c) x[c] = y[c];
-    }
-  }
-}
-
 hipError_t launch_zero_i32(int32_t* p, int64_t count, hipStream_t s) {
   if (count <= 0) return hipSuccess;
   int64_t blocks = ((count >> 2) + kBlock - 1) / kBlock;
@@ -260,23 +174,6 @@ hipError_t launch_fwd_layer_nd(const FwdArgs& a, hipStream_t s) {
     e = allow_lds(fwd_layer_nd<3, 4>, lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((fwd_layer_nd<3, 4>), unit_grid(a), dim3(kBlock), lds, s, a);
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_fwd_path(const FwdArgs& a, hipStream_t s) {
-  const uint64_t blocks = (a.M + kBlock - 1) / kBlock;
-  if (a.d == 1) {
-    // midpoints of every layer in LDS when they fit in 64 KiB
-    const int in_lds = a.mids_total * 4 <= 65536;
-    const size_t lds = in_lds ? sizeof(float) * (size_t)a.mids_total : 0;
-    hipLaunchKernelGGL((fwd_path<1>), dim3((unsigned)blocks), dim3(kBlock), lds, s, a, in_lds);
-  } else {
-    const size_t lds = sizeof(float4) * (size_t)a.maxN;
-    if (a.d == 2)
-      hipLaunchKernelGGL((fwd_path<2>), dim3((unsigned)blocks), dim3(kBlock), lds, s, a, 0);
-    else
-      hipLaunchKernelGGL((fwd_path<3>), dim3((unsigned)blocks), dim3(kBlock), lds, s, a, 0);
   }
   return hipGetLastError();
 }

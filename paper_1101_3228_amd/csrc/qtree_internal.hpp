@@ -106,13 +106,26 @@ struct WsLayout {
   size_t band;     // d == 1: int64[R + 1] band offsets, then int32[R] first band columns
                    // of the R = sum_{k<n} N_k count rows (banded stratified counts)
   size_t bk_rows;  // d == 2: uint16[buckets][kBucketRow] bucket rows (count, candidates)
+  size_t path;     // uint16[n][path cells] cells of the pathwise mode
   size_t keys;     // uint16[n][batch chunks][kChunk] pass-A keys
   size_t segs;     // uint32[n][batch chunks][max tiles + 1] segment starts
   size_t total;
 };
 
-// Layout for a scratch that holds `batch_chunks` chunks per layer (0: none).
-WsLayout ws_layout(int d, int n, const int32_t* N, int64_t batch_chunks);
+// Pathwise scratch: a cell of 2 bytes per path and layer, for up to 2^17
+// paths a pass (a path's walk is a serial chain: 2^17 fill the chip) in at
+// most 96 MiB (n = 365 still takes 2^17); no scratch where that is under 4096
+// paths, or where a count block has more than kPathTiles super tiles (about
+// 1450 points a layer), each of which reads every cell pair: the direct
+// atomics then cost about as much.
+constexpr int64_t kPathCells = 1 << 17;
+constexpr int64_t kPathBytes = 96ll << 20;
+constexpr int kPathTiles = 128;
+int64_t path_cells(int n, const int32_t* N);
+
+// Layout for a scratch that holds `batch_chunks` chunks per layer (0: none)
+// and `cells` path cells per layer (path_cells or 0).
+WsLayout ws_layout(int d, int n, const int32_t* N, int64_t batch_chunks, int64_t cells);
 bool two_pass_fits(int d, int n, const int32_t* N);
 
 struct FwdArgs {
@@ -180,7 +193,12 @@ hipError_t launch_swing(const SwingArgs& a, const int32_t* N_host, hipStream_t s
 hipError_t launch_zero_i32(int32_t* p, int64_t count, hipStream_t s);
 hipError_t launch_fwd_layer_1d(const FwdArgs& a, hipStream_t s);
 hipError_t launch_fwd_layer_nd(const FwdArgs& a, hipStream_t s);
+// Pathwise counts of paths a.m0 .. + a.M - 1: with a device-scope atomic per
+// step, or through a.M <= stride cells per layer (stride a multiple of 8) in
+// `cells`, stored (first) or added.  a.total_tiles: super tiles of all layers.
 hipError_t launch_fwd_path(const FwdArgs& a, hipStream_t s);
+hipError_t launch_path_counts(const FwdArgs& a, uint16_t* cells, int64_t stride, bool first,
+                              hipStream_t s);
 hipError_t launch_fwd_keys(const FwdArgs& a, hipStream_t s);
 hipError_t launch_count_tiles(const FwdArgs& a, hipStream_t s);
 // Zero the count blocks of the split layers in [layer0, layer0 + nl).

@@ -2,6 +2,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -36,6 +38,7 @@ struct qtree_plan {
   int32_t gt_Kmax = -1;           // d = 1: largest guide K over the layers (-1: no tables)
   int32_t gt_Bmax = 1;            // d = 1: largest guide table
   int64_t batch_chunks = 0;      // scratch chunks per layer per pass
+  int64_t path_cells = 0;        // pathwise scratch: cells per layer (0: none)
   bool two_pass_ok = false;       // the workspace holds two-pass scratch
   bool two_pass_shape = false;    // the count blocks and LDS allow two-pass counting
   hipEvent_t trace_keys = nullptr;
@@ -44,6 +47,18 @@ struct qtree_plan {
   mutable hipStream_t aux = nullptr;
   mutable hipEvent_t fork[kMaxGroups] = {};
   mutable hipEvent_t join = nullptr;
+
+  // The pathwise scratch serves one call at a time: a call on another stream
+  // than the last one's waits on the device for that call's event.
+  struct PathUse {
+    std::mutex lock;
+    hipEvent_t done = nullptr;   // recorded after each use
+    hipStream_t last = nullptr;  // stream of the last use (once `done` exists)
+    ~PathUse() {
+      if (done) (void)hipEventDestroy(done);
+    }
+  };
+  std::shared_ptr<PathUse> path_use = std::make_shared<PathUse>();
 
   ~qtree_plan() {
     if (aux) (void)hipStreamSynchronize(aux);

@@ -1,0 +1,134 @@
+"""GPU checks of the pathwise counts where their kernels change form, bit for
+bit against the oracle: layers in groups of four (d = 1) and a remainder, one
+super tile and several, the bucket tables and the full scan (d = 2), d = 3,
+layers too large for the staged search, more paths than one pass of the cell
+scratch holds, added counts, a workspace without the scratch, other streams,
+and a captured call."""
+import numpy as np
+import pytest
+
+import oracle as O
+import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+import paper_1101_3228_amd as qt  # noqa: E402
+
+SEED = 0x5EED0007
+
+
+def _case(name):
+    print(f"[gpu-case] {name}", flush=True)
+
+
+def _model(spec):
+    return O.Model(spec["d"], spec["n"], spec["A"], spec["b"], spec["T"], spec["mu"], spec["L"],
+                   spec["x0"])
+
+
+def _ref(spec, grid, N, M, **kw):
+    return O.transitions(_model(spec), grid, N, M, seed=SEED, mode=1, nthreads=8, **kw)
+
+
+@pytest.mark.parametrize("sizes", [[1, 5], [1, 2, 1, 300], [1, 100, 99, 257, 128, 64],
+                                   [1, 10, 4100, 12, 700, 3, 1, 2, 9]], ids=str)
+@pytest.mark.parametrize("M", [1, 257, 20_001])
+def test_paths_1d(sizes, M):
+    _case(f"paths 1-D {sizes} {M}")
+    spec = synth.bm_model(1, len(sizes) - 1)
+    grid, N = synth.layer_grids(spec, sizes)
+    plan = qt.Plan(spec, grid, N, batch_samples=1)
+    got = plan.transitions(M, SEED, mode=qt.PATHWISE, m0=3).cpu().numpy()
+    assert np.array_equal(got, _ref(spec, grid, N, M, m0=3))
+
+
+@pytest.mark.parametrize("d,side", [(2, (1, 1)), (2, (5, 6)), (2, (33, 34)), (2, (16, 16)),
+                                    (3, (4, 5, 6))], ids=str)
+@pytest.mark.parametrize("buckets", [1, 0])
+def test_paths_nd(d, side, buckets):
+    _case(f"paths {d}-D {side} {buckets}")
+    spec = synth.bm_model(d, 5, rho=0.3)
+    grid, N = synth.layer_grids(spec, [1, side, side, tuple([2] * d), side, side])
+    plan = qt.Plan(spec, grid, N, batch_samples=1).tune(buckets=buckets)
+    got = plan.transitions(10_001, SEED, mode=qt.PATHWISE).cpu().numpy()
+    assert np.array_equal(got, _ref(spec, grid, N, 10_001))
+
+
+def _tree():
+    spec = synth.bm_model(1, 6)
+    grid, N = synth.layer_grids(spec, [1, 20, 150, 130, 7, 40, 33])
+    return spec, grid, N
+
+
+def test_more_paths_than_a_pass_and_added_counts():
+    _case("paths in several passes")
+    spec, grid, N = _tree()
+    plan = qt.Plan(spec, grid, N, batch_samples=1)
+    M = 2 * (1 << 17) + 4097
+    ref = _ref(spec, grid, N, M)
+    counts = plan.transitions(M, SEED, mode=qt.PATHWISE)
+    assert np.array_equal(counts.cpu().numpy(), ref)
+    plan.transitions_add(counts, 1000, SEED, mode=qt.PATHWISE, m0=M)
+    assert np.array_equal(counts.cpu().numpy(), _ref(spec, grid, N, M + 1000))
+
+
+def test_workspace_without_the_cell_scratch():
+    """A workspace of the tables alone is still accepted and counts directly."""
+    _case("paths without scratch")
+    import ctypes
+    spec, grid, N = _tree()
+    plan = qt.Plan(spec, grid, N, batch_samples=1)
+    ref = plan.transitions(30_000, SEED, mode=qt.PATHWISE).cpu().numpy()
+    model = qt._Model(plan.d, plan.n, *(plan._keep[k].ctypes.data
+                                        for k in ("A", "b", "T", "mu", "L", "x0")))
+    size = plan.workspace.numel() - 6 * 2 * (1 << 17)   # less than the cells need
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    h = ctypes.c_void_p()
+    qt._check(qt.lib().qtree_plan_create(ctypes.byref(model), qt._np_ptr(plan.grid),
+                                         qt._np_ptr(plan.N), ws.data_ptr(), size,
+                                         ctypes.byref(h)))
+    out = plan.new_counts()
+    qt._check(qt.lib().qtree_transitions(h, 0, 30_000, SEED, 0, qt.PATHWISE, out.data_ptr(),
+                                         qt._stream_handle()))
+    torch.cuda.synchronize()
+    assert np.array_equal(out[:plan.entries].cpu().numpy(), ref)
+    qt.lib().qtree_plan_destroy(h)
+
+
+def test_paths_on_two_streams_share_the_plan():
+    _case("paths on two streams")
+    spec, grid, N = _tree()
+    plan = qt.Plan(spec, grid, N, batch_samples=1)
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    outs = [plan.new_counts() for _ in range(6)]
+    torch.cuda.synchronize()
+    for i, out in enumerate(outs):
+        plan.transitions(50_000, SEED, contract=i, mode=qt.PATHWISE, counts=out,
+                         stream=streams[i % 2])
+    torch.cuda.synchronize()
+    for i, out in enumerate(outs):
+        ref = O.transitions(_model(spec), grid, N, 50_000, seed=SEED, contract=i, mode=1,
+                            nthreads=8)
+        assert np.array_equal(out[:plan.entries].cpu().numpy(), ref), i
+
+
+def test_captured_paths_replay():
+    _case("paths captured")
+    spec, grid, N = _tree()
+    plan = qt.Plan(spec, grid, N, batch_samples=1)
+    ref = _ref(spec, grid, N, 20_000)
+    other = plan.transitions(20_000, SEED + 1, mode=qt.PATHWISE).cpu().numpy()
+    out = plan.new_counts()
+    s = torch.cuda.Stream()
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, stream=s):
+        plan.transitions(20_000, SEED, mode=qt.PATHWISE, counts=out, stream=s)
+    for _ in range(3):
+        out.zero_()
+        eager = plan.transitions(20_000, SEED + 1, mode=qt.PATHWISE)
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(out[:plan.entries].cpu().numpy(), ref)
+        assert np.array_equal(eager.cpu().numpy(), other)
