@@ -83,9 +83,12 @@ const char *qtree_version(void);
  * N: host [n+1]) when its counting scratch is to hold `batch_samples`
  * LAYERWISE samples per layer per pass (0: 2^22).  Larger M runs in several
  * passes; a plan uses all the scratch its workspace has room for.  For d = 2
- * it includes the bucket tables of the cell search, 64 bytes per bucket and
- * about 64 buckets per grid point (8 MB for a layer of 2000 points).  Pure
- * host arithmetic. */
+ * it includes the bucket tables of the cell search, 24 bytes per bucket and
+ * about 36 buckets per grid point (1.7 MB for a layer of 2000 points), and for
+ * layers of up to about 1450 points the cell scratch of PATHWISE calls, 2
+ * bytes per layer and path for up to 2^17 paths a pass, at most 96 MiB (a
+ * plan given a smaller workspace counts those calls with atomics).  Pure host
+ * arithmetic. */
 qtree_status qtree_workspace_size(int32_t d, int32_t n, const int32_t *N, uint64_t batch_samples,
                                   size_t *bytes);
 

@@ -139,6 +139,8 @@ WsLayout ws_layout(int d, int n, const int32_t* N, int64_t batch_chunks, int64_t
   const int64_t buckets = d == 2 ? total_buckets(n, N) : 0;
   l.bk_rows = off;
   off = align_up(off + sizeof(uint16_t) * kBucketRow * (size_t)buckets, 256);
+  l.bk_long = off;
+  off = align_up(off + sizeof(uint16_t) * kLongRow * (size_t)long_rows(buckets), 256);
   l.path = off;
   off = align_up(off + sizeof(uint16_t) * (size_t)n * (size_t)cells, 256);
   // scratch of the two-pass counting (only when every count block has at
@@ -622,7 +624,8 @@ qtree_status qtree_plan_create(const qtree_model* model, const float* grid, cons
     e = qtree::launch_bucket_build(
         reinterpret_cast<const qtree::LayerDev*>(p.ws + p.lay.layers), n + 1, (int)p.buckets,
         reinterpret_cast<const float4*>(p.ws + p.lay.points),
-        reinterpret_cast<uint16_t*>(p.ws + p.lay.bk_rows), nullptr);
+        reinterpret_cast<uint16_t*>(p.ws + p.lay.bk_rows),
+        reinterpret_cast<uint16_t*>(p.ws + p.lay.bk_long), nullptr);
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     if (e != hipSuccess) return hip_fail(e, "bucket tables");
   }
@@ -667,7 +670,8 @@ static qtree::FwdArgs fwd_args(const qtree_plan* p, uint64_t m0, uint64_t M, uin
   a.total_tiles = p->unit_off[p->n];
   a.nd_samples = p->tune_nd_samples;
   a.bucketed = (p->buckets > 0 && p->tune_buckets) ? 1 : 0;
-  a.bk_rows = reinterpret_cast<const uint4*>(p->ws + p->lay.bk_rows);
+  a.bk.rows = reinterpret_cast<const uint4*>(p->ws + p->lay.bk_rows);
+  a.bk.longs = reinterpret_cast<const uint4*>(p->ws + p->lay.bk_long);
   return a;
 }
 
@@ -833,9 +837,10 @@ qtree_status qtree_plan_bucket_counts(const qtree_plan* plan, int32_t k, uint16_
   hipError_t e = hipMemcpy(&L, plan->ws + plan->lay.layers + sizeof(qtree::LayerDev) * (size_t)k,
                            sizeof(L), hipMemcpyDeviceToHost);
   const size_t nb = (size_t)B[0] * (size_t)B[1];
-  std::vector<uint16_t> rows;
+  std::vector<uint16_t> rows, longs;
   try {
     rows.resize(nb * qtree::kBucketRow);
+    longs.resize((size_t)qtree::long_rows(plan->buckets) * qtree::kLongRow);
   } catch (const std::bad_alloc&) {
     return fail(QTREE_ENOMEM, "host copy of the bucket rows");
   }
@@ -843,8 +848,15 @@ qtree_status qtree_plan_bucket_counts(const qtree_plan* plan, int32_t k, uint16_
     e = hipMemcpy(rows.data(),
                   plan->ws + plan->lay.bk_rows + sizeof(uint16_t) * qtree::kBucketRow * (size_t)L.bk_off,
                   sizeof(uint16_t) * rows.size(), hipMemcpyDeviceToHost);
+  if (e == hipSuccess)
+    e = hipMemcpy(longs.data(), plan->ws + plan->lay.bk_long, sizeof(uint16_t) * longs.size(),
+                  hipMemcpyDeviceToHost);
   if (e != hipSuccess) return hip_fail(e, "bucket rows copy");
-  for (size_t t = 0; t < nb; ++t) counts[t] = rows[t * qtree::kBucketRow];  // entry 0: the count
+  for (size_t t = 0; t < nb; ++t) {  // entry 0: the count
+    const uint16_t* row = rows.data() + t * qtree::kBucketRow;
+    const size_t at = (size_t)row[6] | (size_t)row[7] << 16;
+    counts[t] = row[0] == qtree::kBucketLong ? longs[at * qtree::kLongRow] : row[0];
+  }
   return QTREE_OK;
 }
 

@@ -69,7 +69,7 @@ struct KeysJob {
   uint64_t lo, hi;
   uint16_t* keys;  // kChunk slots of this chunk
   uint32_t* seg;   // T + 1 segment starts of this chunk
-  const uint4* bk_rows;  // d = 2 bucket rows (bucketed search only)
+  BucketTab bk;          // d = 2 bucket rows (bucketed search only)
   int nd_sub;            // d >= 2: sub-counters per tile in the sort (kNdSub or 1)
 };
 
@@ -464,15 +464,18 @@ __device__ __forceinline__ void keys_chunk_nd(const KeysJob& j, float4* lds4) {
     if constexpr (BK && D == 2) {
       // each sample's own bucket list (the same cells as the full scan); the
       // rows of all 2 S searches are fetched before the first is walked
-      int sx[S], sy[S];
       uint4 wx[S], wy[S];
-      bucket_rows<S>(L0, j.bk_rows, xs, sx, wx);
-      bucket_rows<S>(L1, j.bk_rows, ys, sy, wy);
-      float bx[S], by[S];
-      bucket_first<S>(xy0, N0, xs, sx, wx, bx, ii);
-      bucket_first<S>(xy1, N1, ys, sy, wy, by, jj);
-      bucket_rest<S>(xy0, N0, j.bk_rows, xs, sx, wx, bx, ii);
-      bucket_rest<S>(xy1, N1, j.bk_rows, ys, sy, wy, by, jj);
+      bucket_rows<S>(L0, N0, j.bk, xs, wx);
+      bucket_rows<S>(L1, N1, j.bk, ys, wy);
+      bucket_first<S>(xy0, xs, wx, ii);
+      bucket_first<S>(xy1, ys, wy, jj);
+      bucket_rest<S>(xy0, N0, j.bk, xs, wx, ii);
+      bucket_rest<S>(xy1, N1, j.bk, ys, wy, jj);
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        ii[s] = cell_index(ii[s]);
+        jj[s] = cell_index(jj[s]);
+      }
     } else {
       argmin_scan_tiled<D, S, kNdTile>(gk, P0, xs, ii);
       argmin_scan_tiled<D, S, kNdTile>(gk1, P1, ys, jj);
@@ -481,7 +484,8 @@ __device__ __forceinline__ void keys_chunk_nd(const KeysJob& j, float4* lds4) {
     // uniform select (a dynamic index would put the array in scratch)
 #pragma unroll
     for (int s = 0; s < S; ++s) {
-      const uint32_t kk = (uint32_t)ii[s] * (uint32_t)N1 + (uint32_t)jj[s];
+      // 24-bit factors (at most 4096 points)
+      const uint32_t kk = __umul24((uint32_t)ii[s], (uint32_t)N1) + (uint32_t)jj[s];
       const uint32_t v = live[s] ? kk : 0xFFFFFFFFu;
 #pragma unroll
       for (int q = 0; q < kKeys / S; ++q) key[q * S + s] = q == r ? v : key[q * S + s];
@@ -634,7 +638,7 @@ __device__ __forceinline__ KeysJob plan_job(const FwdArgs& a, int k, int c) {
   j.hi = a.m0 + a.M;
   j.keys = a.keys + ((size_t)k * a.chunks + c) * kChunk;
   j.seg = a.segs + ((size_t)k * a.chunks + c) * a.seg_stride;
-  j.bk_rows = a.bk_rows;
+  j.bk = a.bk;
   j.nd_sub = nd_subs(a.max_tiles);
   return j;
 }
@@ -762,7 +766,8 @@ __device__ __forceinline__ void batch_loop(const BatchArgs& a, Body body) {
       j.keys = as_global(a.keys) + ((size_t)C.chunk_base + (size_t)U.k * C.chunks + c) * kChunk;
       j.seg = as_global(a.segs) + (size_t)C.seg_base +
               ((size_t)U.k * C.chunks + c) * (size_t)C.seg_stride;
-      j.bk_rows = as_global(C.bk_rows);
+      j.bk.rows = as_global(C.bk.rows);
+      j.bk.longs = as_global(C.bk.longs);
       j.nd_sub = a.sub;
       body(C, j);
     }

@@ -81,10 +81,9 @@ __global__ __launch_bounds__(kBlock) void cells_kernel(FwdArgs a, int k, const f
     for (int c = 0; c < D; ++c) q[s][c] = x[ii * D + c];
   }
   if constexpr (BK && D == 2) {
-    int slot[kCellsS];
     uint4 w[kCellsS];
-    bucket_rows<kCellsS>(L, a.bk_rows, q, slot, w);
-    bucket_argmin<kCellsS>(xy, N, a.bk_rows, q, slot, w, idx);
+    bucket_rows<kCellsS>(L, N, a.bk, q, w);
+    bucket_argmin<kCellsS>(xy, N, a.bk, q, w, idx);
   } else {
     argmin_scan_tiled<D, kCellsS, kScanTile>(recs, Npad, q, idx);
   }

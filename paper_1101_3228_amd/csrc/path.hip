@@ -151,7 +151,6 @@ void walk_2d_wide(FwdArgs a, Visits v) {
   ConstLayer* layers = (ConstLayer*)a.layers;
   const float2* pts = reinterpret_cast<const float2*>(a.pts);  // x, y of point q at 2 q
   const float2 nan2 = make_float2(__builtin_nanf(""), __builtin_nanf(""));
-  constexpr int kRowVecs = kBucketRow / 8;
   float x0 = layers[0].x0[0], x1 = layers[0].x0[1];
   float2* mine = points + 2 * seg * buf;
   for (int kb = 0; kb < a.n; kb += kWideSteps) {
@@ -194,33 +193,19 @@ void walk_2d_wide(FwdArgs a, Visits v) {
       }
     }
     if (steps == 0) continue;
-    int slot[2][1], N[2];
-    uint4 w[2][1], w2[2];
+    int N[2];
+    uint4 w[2][1];
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
       ConstLayer& L1 = layers[min(ks + s + 1, a.n)];
       N[s] = L1.N;
-      // the bucket, as bucket_rows finds it
-      const float f0 = (xs[s][0][0] - L1.bk_lo[0]) * L1.bk_scale[0];
-      const float f1 = (xs[s][0][1] - L1.bk_lo[1]) * L1.bk_scale[1];
-      const bool in = f0 >= 0.0f && f1 >= 0.0f && f0 < (float)L1.bk_B[0] && f1 < (float)L1.bk_B[1];
-      const int row = in ? L1.bk_off + (int)f0 * L1.bk_B[1] + (int)f1 : 0;
-      slot[s][0] = in ? row : -1;
-      w[s][0] = a.bk_rows[(int64_t)row * kRowVecs];
-      w2[s] = a.bk_rows[(int64_t)row * kRowVecs + 1];
+      bucket_rows<1>(L1, N[s], a.bk, xs[s], w[s]);
     }
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
       if (s >= steps) break;
-      const float2* g = mine + s * buf;
-      float best[1];
       int j[1];
-      bucket_first<1>(g, N[s], xs[s], slot[s], w[s], best, j);
-      const int c = slot[s][0] >= 0 ? (int)(w[s][0].x & 0xFFFFu) : (int)kBucketFull;
-      // of 64 lanes, one has eight or more candidates in most steps: the
-      // row's second 16 bytes came with the first
-      if (c >= 8 && c < 16) bucket_group(g, w2[s], 0, xs[s][0][0], xs[s][0][1], best[0], j[0]);
-      if (c >= 16) bucket_argmin<1>(g, N[s], a.bk_rows, xs[s], slot[s], w[s], j);
+      bucket_argmin<1>(mine + s * buf, N[s], a.bk, xs[s], w[s], j);
       if (live) v.cells[(int64_t)(ks + s) * v.stride + (int64_t)t] = (uint16_t)j[0];
     }
   }
@@ -251,11 +236,11 @@ __global__ __launch_bounds__(kBlock) void walk_2d(FwdArgs a, Visits v) {
       box_muller(r.z, r.w, eb[2], eb[3]);
     }
     step_2d(layers[k], (k & 1) ? eb[2] : eb[0], (k & 1) ? eb[3] : eb[1], x[0][0], x[0][1]);
-    int slot[1], j[1];
+    int j[1];
     uint4 w[1];
-    bucket_rows<1>(a.layers[k + 1], a.bk_rows, x, slot, w);
+    bucket_rows<1>(layers[k + 1], N1, a.bk, x, w);
     __syncthreads();
-    bucket_argmin<1>(xy, N1, a.bk_rows, x, slot, w, j);
+    bucket_argmin<1>(xy, N1, a.bk, x, w, j);
     visit<false>(a, v, k, t, live, i, j[0]);
     i = j[0];
   }

@@ -72,27 +72,40 @@ struct alignas(16) LayerDev {
   // from bk_lo in bk_B[0] x bk_B[1] buckets; x is in bucket
   // (floor((x_0 - bk_lo[0]) bk_scale[0]), floor((x_1 - bk_lo[1]) bk_scale[1]))
   // in FP32, and bucket (i, j) owns row bk_off + i bk_B[1] + j of the row
-  // array: entry 0 its candidate count c (kBucketFull: more than kBucketCap,
-  // the full scan decides), entries 1..c every point that can be the FP32
-  // argmin anywhere in it, in increasing index, padded to a whole 8-entry
-  // group with N (the search's pad record, whose key is NaN)
+  // array (kBucketRow entries): entry 0 its candidate count c, entries 1..c
+  // every point that can be the FP32 argmin anywhere in it, in increasing
+  // index, the others the pad N (the search's pad record, whose key is NaN);
+  // points and pad as byte offsets of 8-byte pairs.  A bucket of more
+  // candidates has c = kBucketLong, pads, and in entries 6 and 7 the index
+  // (low half first) of a row of the plan's pool of longer ones (kLongRow
+  // entries, the same layout); where they do not fit there either, c =
+  // kBucketFull, and the full scan decides.
   float bk_lo[2], bk_scale[2];
   int32_t bk_B[2];
   int32_t bk_off;
 };
-constexpr int kBucketRow = 32;            // uint16 entries of a bucket row (64 bytes)
-constexpr int kBucketCap = kBucketRow - 1; // candidates a row holds
+constexpr int kBucketRow = 8;             // uint16 entries of a bucket row (16 bytes)
+constexpr int kBucketCap = kBucketRow - 1; // candidates it holds
+constexpr int kLongRow = 32;              // uint16 entries of a pool row (64 bytes)
+constexpr int kLongCap = kLongRow - 1;    // candidates it holds
 constexpr uint16_t kBucketFull = 0xFFFF;  // row count: candidates did not fit
-// Buckets per side of a d = 2 layer of N points: about 64 buckets per point,
-// at most 512 per side, 4 KB of rows per point (the 2-D workload, N = 2000:
-// a step of 3.82 ms at 64 per point, 3.89 at 96, 3.97 at 128, 4.15 at 32;
-// its first form's sampling pass 5.16 ms at 32, 5.68 at 24, 6.28 at 16,
-// 8.42 at 8).  Denser buckets list fewer candidates, so fewer waves walk a
-// second group; beyond 64 the rows no longer stay in the caches.
+constexpr uint16_t kBucketLong = 0xFFFE;  // row count: in a pool row
+// Rows of the pool: one for every kBucketsPerLong buckets and row 0, whose
+// first word counts the rows taken.  (On product grids about one bucket in
+// thousands needs one.)
+constexpr int64_t kBucketsPerLong = 8;
+inline int64_t long_rows(int64_t buckets) { return buckets > 0 ? 1 + buckets / kBucketsPerLong : 0; }
+// Buckets per side of a d = 2 layer of N points: about 36 buckets per point,
+// at most 512 per side.  Denser buckets list fewer candidates, but four are
+// looked at anyway, and the rows of two layers (2.3 MB at N = 2000) have to
+// stay in an XCD's 4 MB L2.  Buckets per point 24 / 36 / 64 / 128 / 256: the
+// 2-D max-call (n = 30, N = 2000, 1e7 pairs) 3.24 / 3.14 / 3.43 / 3.40 / 3.41
+// ms a call, n = 365, N = 500, 1e5 pairs 0.42 / 0.40 / 0.42 / 0.47 / 0.51 ms,
+// a ragged book of N up to 1000 2.54 / 2.49 / 2.43 / 2.49 / 2.48 ms.
 inline int bucket_side(int N) {
   if (N <= 1) return 1;
   int b = 1;
-  while ((double)b * b < 64.0 * N) ++b;
+  while ((double)b * b < 36.0 * N) ++b;
   return b < 512 ? b : 512;
 }
 
@@ -106,6 +119,7 @@ struct WsLayout {
   size_t band;     // d == 1: int64[R + 1] band offsets, then int32[R] first band columns
                    // of the R = sum_{k<n} N_k count rows (banded stratified counts)
   size_t bk_rows;  // d == 2: uint16[buckets][kBucketRow] bucket rows (count, candidates)
+  size_t bk_long;  // d == 2: uint16[long_rows][kLongRow] pool of longer rows
   size_t path;     // uint16[n][path cells] cells of the pathwise mode
   size_t keys;     // uint16[n][batch chunks][kChunk] pass-A keys
   size_t segs;     // uint32[n][batch chunks][max tiles + 1] segment starts
@@ -127,6 +141,12 @@ int64_t path_cells(int n, const int32_t* N);
 // and `cells` path cells per layer (path_cells or 0).
 WsLayout ws_layout(int d, int n, const int32_t* N, int64_t batch_chunks, int64_t cells);
 bool two_pass_fits(int d, int n, const int32_t* N);
+
+// The rows of the d = 2 bucketed cell search of a plan.
+struct BucketTab {
+  const uint4* rows;   // a row per bucket
+  const uint4* longs;  // pool rows, kLongRow / 8 words of 16 bytes each
+};
 
 struct FwdArgs {
   const LayerDev* layers;
@@ -161,7 +181,7 @@ struct FwdArgs {
   int32_t tile0;          // first histogram unit of this launch
   // d = 2 bucketed cell search (bucketed = 0: the full scan)
   int32_t bucketed;
-  const uint4* bk_rows;
+  BucketTab bk;
 };
 
 // Forward obstacle on the sum of the factors (see qtree_payoff_forward).
@@ -359,7 +379,8 @@ size_t lloyd_lds_bytes(int d, int N, int Npad, int P);
 // Bucket rows of the d = 2 bucketed cell search of every layer (records
 // and LayerDev already in the workspace).
 hipError_t launch_bucket_build(const LayerDev* layers, int n_layers_total, int total_buckets,
-                               const float4* pts, uint16_t* rows, hipStream_t s);
+                               const float4* pts, uint16_t* rows, uint16_t* longs,
+                               hipStream_t s);
 hipError_t launch_lloyd_prepare(const LloydArgs& a, hipStream_t s);
 hipError_t launch_lloyd_step(const LloydArgs& a, int blocks, hipStream_t s);
 // Moment-matching grids: exact integer moment sums of a device sample set,

@@ -202,21 +202,22 @@ __device__ __forceinline__ void argmin_scan_tiled(const float4* __restrict__ g, 
 }
 
 // d = 2 cells by the layer's bucket tables, in two steps so that the row
-// loads of many points are in flight together.  A bucket's row (kBucketRow
-// uint16, 16-byte aligned) holds its candidate count c in entry 0 and, in
-// entries 1..c, every point that can be the FP32 argmin of h - <x, g>
-// anywhere in the bucket, in increasing index, then the pad index N to the
-// end of its last 8-entry group.  The first minimum over the list is the
-// full scan's cell (the lowest index of the minimal key).  Outside the box,
-// in a bucket whose candidates did not fit (c = kBucketFull), or in a layer
-// without tables, the full scan over the N points decides.
+// loads of many points are in flight together.  A bucket's row (16 bytes)
+// holds its candidate count c in entry 0 and, from entry 1 on, every point
+// that can be the FP32 argmin of h - <x, g> anywhere in the bucket, in
+// increasing index, then pads; more than kBucketCap of them are in a row of
+// the pool.  The first minimum over the list is the full scan's cell (the
+// lowest index of the minimal key).  Outside the box, in a bucket whose
+// candidates did not fit (c = kBucketFull), or in a layer without tables, the
+// full scan over the N points decides.
 //
 // The points are (x, y) pairs in LDS, 8 bytes each, with a pad pair (NaN,
 // NaN) at index N: its key is NaN, which never wins a comparison, and the
-// lanes that read it share one LDS access.  Consecutive points fall in
-// different bank pairs, where 16-byte records would share a quarter of the
-// banks (and 12-byte (x, y, h) triples take two reads).  The half norm is
-// recomputed as h = (x x + y y) / 2 with one product, one fma and one
+// lanes that read it share one LDS access.  Entries are byte offsets of the
+// pairs, and so is the cell (cell_index gives its index).  Consecutive points
+// fall in different bank pairs, where 16-byte records would share a quarter
+// of the banks (and 12-byte (x, y, h) triples take two reads).  The half norm
+// is recomputed as h = (x x + y y) / 2 with one product, one fma and one
 // halving, the order in which the records' own half norms are formed, so
 // the key is bit for bit the scan's.
 __device__ __forceinline__ float half_norm_key(float2 r, float x0, float x1) {
@@ -224,97 +225,130 @@ __device__ __forceinline__ float half_norm_key(float2 r, float x0, float x1) {
   return fmaf(-x1, r.y, fmaf(-x0, r.x, h));
 }
 
-// bucket_rows: the row index of each of S points (-1: full scan) and the
-// first 16 bytes of its row (count and candidates 1..7).  Every point loads
-// a row (row 0 when it has none, so that the load is not under a branch and
-// all S stay in flight); bucket_argmin ignores what a -1 point loaded.
-template <int S>
-__device__ __forceinline__ void bucket_rows(const LayerDev& L, const uint4* __restrict__ rows,
-                                            const float (*xs)[2], int* slot, uint4* w) {
+__device__ __forceinline__ int cell_index(int offset) { return offset >> 3; }
+
+// The bucket of a point (FP32) in a layer's tables, -1 outside the box, for
+// NaN and for a layer without tables (bk_B = 0).
+template <class LAYER>
+__device__ __forceinline__ int bucket_of(LAYER& L, float x0, float x1) {
+  const float f0 = (x0 - L.bk_lo[0]) * L.bk_scale[0];
+  const float f1 = (x1 - L.bk_lo[1]) * L.bk_scale[1];
+  const bool in = f0 >= 0.0f && f1 >= 0.0f && f0 < (float)L.bk_B[0] && f1 < (float)L.bk_B[1];
+  return in ? L.bk_off + (int)f0 * L.bk_B[1] + (int)f1 : -1;
+}
+
+// bucket_rows: the row of each of S points in a layer of N points; pads and
+// the count kBucketFull where it has none (every point loads a row, row 0
+// then, so that the load is not under a branch and all S stay in flight).
+template <int S, class LAYER>
+__device__ __forceinline__ void bucket_rows(LAYER& L, int N, const BucketTab& t,
+                                            const float (*xs)[2], uint4* w) {
+  const uint32_t pads = 8u * (uint32_t)N * 0x10001u;
+  int r[S];
 #pragma unroll
   for (int s = 0; s < S; ++s) {
-    const float f0 = (xs[s][0] - L.bk_lo[0]) * L.bk_scale[0];
-    const float f1 = (xs[s][1] - L.bk_lo[1]) * L.bk_scale[1];
-    // false for a layer without tables (bk_B = 0) and for NaN
-    const bool in =
-        f0 >= 0.0f && f1 >= 0.0f && f0 < (float)L.bk_B[0] && f1 < (float)L.bk_B[1];
-    const int r = in ? L.bk_off + (int)f0 * L.bk_B[1] + (int)f1 : 0;
-    slot[s] = in ? r : -1;
-    w[s] = rows[(int64_t)r * (kBucketRow / 8)];
+    r[s] = bucket_of(L, xs[s][0], xs[s][1]);
+    w[s] = t.rows[(uint32_t)max(r[s], 0)];
+  }
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    w[s].x = r[s] < 0 ? pads | 0xFFFFu : w[s].x;
+    w[s].y = r[s] < 0 ? pads : w[s].y;
+    w[s].z = r[s] < 0 ? pads : w[s].z;
   }
 }
 
-// One 8-entry group of a row: entries e0..7 (candidates or pads).
-__device__ __forceinline__ void bucket_group(const float2* __restrict__ g, uint4 w, int e0,
-                                             float x0, float x1, float& best, int& idx) {
+// Entry e of 8.
+__device__ __forceinline__ int bucket_entry(const uint4& w, int e) {
   const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
+  return (int)((e & 1) ? ww[e >> 1] >> 16 : ww[e >> 1] & 0xFFFFu);
+}
+__device__ __forceinline__ float bucket_key(const float2* __restrict__ g, int at, float x0,
+                                            float x1) {
+  return half_norm_key(*reinterpret_cast<const float2*>(reinterpret_cast<const char*>(g) + at), x0,
+                       x1);
+}
+
+// Entries e0 .. 7 (candidates or pads).
+__device__ __forceinline__ void bucket_group(const float2* __restrict__ g, const uint4& w, int e0,
+                                             float x0, float x1, float& best, int& at) {
 #pragma unroll
   for (int e = e0; e < 8; ++e) {
-    const int p = (int)((ww[e >> 1] >> ((e & 1) * 16)) & 0xFFFFu);
-    const float key = half_norm_key(g[p], x0, x1);
+    const int p = bucket_entry(w, e);
+    const float key = bucket_key(g, p, x0, x1);
     const bool lt = key < best;
     best = lt ? key : best;
-    idx = lt ? p : idx;
+    at = lt ? p : at;
   }
 }
 
-// bucket_first: the minimum over the first group of each of S points'
-// rows, in straight-line code so that the LDS reads of all S points can be
-// in flight together.  A point without a row (outside the box) walks pads
-// only; a full row's first entries are valid points of the layer, and
-// bucket_rest replaces what they give.
+// bucket_first: the minimum over the first kFirst candidates of each of S
+// points' rows, in straight-line code so that the LDS reads of all S points
+// can be in flight together.  The first entry is always a candidate of a
+// listed row.  (Cells meet at most four at a time on the usual grids, and of
+// a wave's 64 points one lies near such a corner in most rounds: with three,
+// the branch for the fourth was taken almost always.)
+constexpr int kFirst = 4;
 template <int S>
-__device__ __forceinline__ void bucket_first(const float2* __restrict__ g, int N,
-                                             const float (*xs)[2], const int* slot,
-                                             const uint4* w, float* best, int* idx) {
-  const uint32_t pads = (uint32_t)N | ((uint32_t)N << 16);
+__device__ __forceinline__ void bucket_first(const float2* __restrict__ g, const float (*xs)[2],
+                                             const uint4* w, int* at) {
 #pragma unroll
   for (int s = 0; s < S; ++s) {
-    const uint4 v = slot[s] >= 0 ? w[s] : make_uint4(pads, pads, pads, pads);
-    best[s] = __builtin_huge_valf();
-    idx[s] = 0;
-    bucket_group(g, v, 1, xs[s][0], xs[s][1], best[s], idx[s]);
+    at[s] = bucket_entry(w[s], 1);
+    float best = bucket_key(g, at[s], xs[s][0], xs[s][1]);
+#pragma unroll
+    for (int e = 2; e <= kFirst; ++e) {
+      const int p = bucket_entry(w[s], e);
+      const float key = bucket_key(g, p, xs[s][0], xs[s][1]);
+      const bool lt = key < best;
+      best = lt ? key : best;
+      at[s] = lt ? p : at[s];
+    }
   }
 }
 
-// bucket_rest: the further groups of rows longer than 7 candidates, and the
-// full scan for points outside the box or in a full bucket; idx then holds
-// the cells.
+// bucket_rest: the rows of more candidates from their start, and the full
+// scan; at then holds the cells.
 template <int S>
 __device__ __forceinline__ void bucket_rest(const float2* __restrict__ g, int N,
-                                            const uint4* __restrict__ rows,
-                                            const float (*xs)[2], const int* slot,
-                                            const uint4* w, float* best, int* idx) {
+                                            const BucketTab& t, const float (*xs)[2],
+                                            const uint4* w, int* at) {
 #pragma unroll
   for (int s = 0; s < S; ++s) {
-    const int c = slot[s] >= 0 ? (int)(w[s].x & 0xFFFFu) : (int)kBucketFull;
-    if (c == (int)kBucketFull) {
-      float b = __builtin_huge_valf();
-      int bi = 0;
-      for (int p = 0; p < N; ++p) {
-        const float key = half_norm_key(g[p], xs[s][0], xs[s][1]);
-        const bool lt = key < b;
-        b = lt ? key : b;
-        bi = lt ? p : bi;
-      }
-      idx[s] = bi;
+    const uint32_t c = w[s].x & 0xFFFFu;
+    if (c <= (uint32_t)kFirst) continue;
+    float best = __builtin_huge_valf();
+    int found = 0;
+    if (c <= (uint32_t)kBucketCap) {
+      bucket_group(g, w[s], 1, xs[s][0], xs[s][1], best, found);
+    } else if (c == kBucketLong) {
+      const uint4* row = t.longs + (size_t)w[s].w * (kLongRow / 8);
+      const int cl = (int)(row[0].x & 0xFFFFu);
+      bucket_group(g, row[0], 1, xs[s][0], xs[s][1], best, found);
+      for (int q = 8; q <= cl; q += 8)
+        bucket_group(g, row[q >> 3], 0, xs[s][0], xs[s][1], best, found);
     } else {
-      for (int q = 8; q <= c; q += 8)
-        bucket_group(g, rows[(int64_t)slot[s] * (kBucketRow / 8) + (q >> 3)], 0, xs[s][0],
-                     xs[s][1], best[s], idx[s]);
+#pragma unroll 4
+      for (int p = 0; p < 8 * N; p += 8) {
+        const float key = bucket_key(g, p, xs[s][0], xs[s][1]);
+        const bool lt = key < best;
+        best = lt ? key : best;
+        found = lt ? p : found;
+      }
     }
+    at[s] = found;
   }
 }
 
 // bucket_argmin: the cells of the S points whose rows bucket_rows fetched.
 template <int S>
 __device__ __forceinline__ void bucket_argmin(const float2* __restrict__ g, int N,
-                                              const uint4* __restrict__ rows,
-                                              const float (*xs)[2], const int* slot,
+                                              const BucketTab& t, const float (*xs)[2],
                                               const uint4* w, int* idx) {
-  float best[S];
-  bucket_first<S>(g, N, xs, slot, w, best, idx);
-  bucket_rest<S>(g, N, rows, xs, slot, w, best, idx);
+  bucket_first<S>(g, xs, w, idx);
+  bucket_rest<S>(g, N, t, xs, w, idx);
+#pragma unroll
+  for (int s = 0; s < S; ++s) idx[s] = cell_index(idx[s]);
 }
 
 // Standard normals z (for X_k) and eps (for the innovation) of LAYERWISE

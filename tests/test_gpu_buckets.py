@@ -122,3 +122,43 @@ def test_bucketed_counts_equal_full_scan_and_oracle():
         assert np.array_equal(off_, ref), s
         assert np.array_equal(on, ref), s
     plan.tune(nd_samples=4, buckets=1)
+
+
+@pytest.mark.parametrize("case", ["ring", "piles", "line", "huge"])
+def test_lists_of_many_candidates(case):
+    """Rows past the four candidates of the straight-line search, past the
+    seven of a row (pool rows), past the 31 of a pool row (the full scan): a
+    ring of points whose cells all meet in its centre, piles of 1 to 40 equal
+    points, points on a line, and a layer at the point limit (byte offsets up
+    to 8 x 4096)."""
+    _case(f"bucket lists {case}")
+    rng = np.random.default_rng(5)
+    if case == "ring":
+        t = np.linspace(0.0, 2.0 * np.pi, 24, endpoint=False)
+        g = np.concatenate([np.stack([np.cos(t), np.sin(t)], 1) * r for r in (1.0, 1.0 + 1e-7)])
+    elif case == "piles":
+        c = rng.standard_normal((12, 2))
+        g = np.repeat(c, [1, 2, 3, 4, 5, 6, 7, 8, 9, 31, 32, 40], axis=0)
+        g = g[rng.permutation(len(g))]
+    elif case == "line":
+        g = np.stack([np.linspace(-3, 3, 200), np.zeros(200)], 1)
+    else:
+        g = rng.standard_normal((4096, 2))
+    spec = synth.bm_model(2, 2, T=1.0)
+    g = g.astype(np.float32)
+    grid = np.concatenate([np.zeros((1, 2), np.float32), g, g])
+    N = np.array([1, len(g), len(g)], np.int32)
+    plan = qt.Plan(spec, grid, N)
+    c = plan.bucket_counts(1)
+    if case == "ring":
+        assert ((c > 7) & (c != 0xFFFF)).any()
+    if case == "piles":
+        assert (c == 0xFFFF).any() and ((c > 7) & (c < 32)).any() and ((c > 4) & (c < 8)).any()
+    x = np.concatenate([rng.standard_normal((30_000, 2)), 1e-3 * rng.standard_normal((30_000, 2)),
+                        g]).astype(np.float32)
+    got = qt.cells(plan, 1, torch.from_numpy(x).cuda()).cpu().numpy()
+    assert np.array_equal(got, O.cells_bulk(g, 2, x))
+    ref = O.transitions(_omodel(spec), grid, N, 30_001, seed=9, nthreads=8)
+    assert np.array_equal(plan.transitions(30_001, 9).cpu().numpy(), ref)
+    ref = O.transitions(_omodel(spec), grid, N, 30_001, seed=9, mode=1, nthreads=8)
+    assert np.array_equal(plan.transitions(30_001, 9, mode=qt.PATHWISE).cpu().numpy(), ref)
