@@ -104,18 +104,41 @@ __global__ __launch_bounds__(kBlock) void walk_1d(FwdArgs a, Visits v) {
   }
 }
 
-// The layers' records through the constant address space: uniform loads
-// become scalar loads (the kernels' stores could alias a generic pointer's
-// target).
-typedef const LayerDev __attribute__((address_space(4))) ConstLayer;
-
 // X_{k+1} = b + A x + T e, in the order of layer_pair.
-__device__ __forceinline__ void step_2d(ConstLayer& L, float e0, float e1, float& x0, float& x1) {
-  const float z0 = fmaf(L.A[1], x1, fmaf(L.A[0], x0, L.b[0]));
-  const float z1 = fmaf(L.A[3], x1, fmaf(L.A[2], x0, L.b[1]));
-  x0 = fmaf(L.T[1], e1, fmaf(L.T[0], e0, z0));
-  x1 = fmaf(L.T[3], e1, fmaf(L.T[2], e0, z1));
+__device__ __forceinline__ void step_2d(const float* A, const float* T, const float* b, float e0,
+                                        float e1, float& x0, float& x1) {
+  const float z0 = fmaf(A[1], x1, fmaf(A[0], x0, b[0]));
+  const float z1 = fmaf(A[3], x1, fmaf(A[2], x0, b[1]));
+  x0 = fmaf(T[1], e1, fmaf(T[0], e0, z0));
+  x1 = fmaf(T[3], e1, fmaf(T[2], e0, z1));
 }
+
+// What step k needs of the records of layers k and k + 1, in LDS.
+struct alignas(16) StepRec {
+  float A[4], T[4], b[2];
+  float bk_lo[2], bk_scale[2];
+  int32_t bk_B[2];
+  int32_t bk_off, N, pt_off, pad;
+};
+constexpr int kRecWords = sizeof(StepRec) / 4;
+// Word w of the record of step k.
+__device__ __forceinline__ uint32_t step_word(const FwdArgs& a, int k, int w) {
+  constexpr int kLay = sizeof(LayerDev) / 4;
+#define QTREE_W(f) ((int)(offsetof(LayerDev, f) / 4))
+  int at;
+  if (w < 4) at = QTREE_W(A) + w;
+  else if (w < 8) at = QTREE_W(T) + w - 4;
+  else if (w < 10) at = QTREE_W(b) + w - 8;
+  else if (w < 16) at = kLay + QTREE_W(bk_lo) + w - 10;  // lo, scale and B are adjacent
+  else if (w == 16) at = kLay + QTREE_W(bk_off);
+  else if (w == 17) at = kLay + QTREE_W(N);
+  else at = kLay + QTREE_W(pt_off);
+#undef QTREE_W
+  return reinterpret_cast<const uint32_t*>(a.layers + k)[at];
+}
+static_assert(offsetof(LayerDev, bk_scale) == offsetof(LayerDev, bk_lo) + 8 &&
+                  offsetof(LayerDev, bk_B) == offsetof(LayerDev, bk_lo) + 16,
+              "copied as one run");
 
 // d = 2 with bucket tables, cells to scratch.  A path's normals and its cell
 // searches are independent of each other; only the state X_k is a chain, of
@@ -127,56 +150,72 @@ __device__ __forceinline__ void step_2d(ConstLayer& L, float e0, float e1, float
 //
 // One wave per 64 paths and all of their work (1e5 paths: 1.5 waves per SIMD)
 // took 1.4 us a step at 240 points, 312 instructions at 11 clocks each: a
-// serial chain on an idle chip.
+// serial chain on an idle chip.  64 VGPRs let 1024 of these workgroups be
+// resident (1e5 paths are 782; at 80 VGPRs 14 of them ran after the others,
+// 611 us for 365 steps against 408), and the layers' records come through LDS
+// a turn ahead (333 us; as scalar loads, every step of the chain waited for
+// its own).
 constexpr int kWidePaths = 128, kSegments = 4, kWideSteps = 2 * kSegments;
 constexpr int kWideBlock = kWidePaths * kSegments;
+static_assert(kWideSteps * kRecWords <= kWideBlock, "one word of the records per thread");
 
 size_t wide_lds(int maxN) {
-  return sizeof(float) * 2 * kWideSteps * kWidePaths +
+  return 2 * sizeof(StepRec) * kWideSteps + sizeof(float) * 2 * kWideSteps * kWidePaths +
          sizeof(float2) * kWideSteps * (size_t)((maxN + 2) & ~1);
 }
 
-__global__ __launch_bounds__(kWideBlock) __attribute__((amdgpu_waves_per_eu(6)))
+__global__ __launch_bounds__(kWideBlock) __attribute__((amdgpu_waves_per_eu(8)))
 void walk_2d_wide(FwdArgs a, Visits v) {
-  extern __shared__ float lds[];
-  float* eps = lds;  // [2 kWideSteps][kWidePaths]
+  extern __shared__ float4 lds4[];
+  StepRec* recs = reinterpret_cast<StepRec*>(lds4);  // [2][kWideSteps]
+  float* eps = reinterpret_cast<float*>(recs + 2 * kWideSteps);  // [2 kWideSteps][kWidePaths]
+  float2* points = reinterpret_cast<float2*>(eps + 2 * kWideSteps * kWidePaths);
   const int buf = (a.maxN + 2) & ~1;
-  float2* points = reinterpret_cast<float2*>(lds + 2 * kWideSteps * kWidePaths);
   const int seg = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWidePaths);
   const int p = (int)threadIdx.x % kWidePaths;
   const uint64_t t = (uint64_t)blockIdx.x * kWidePaths + (uint64_t)p;
   const bool live = t < a.M;
   const uint32_t mc = (uint32_t)(a.m0 + (live ? t : 0));
-  const uint32_t k0 = vgpr_copy(a.key0), k1 = vgpr_copy(a.key1);
-  ConstLayer* layers = (ConstLayer*)a.layers;
   const float2* pts = reinterpret_cast<const float2*>(a.pts);  // x, y of point q at 2 q
   const float2 nan2 = make_float2(__builtin_nanf(""), __builtin_nanf(""));
-  float x0 = layers[0].x0[0], x1 = layers[0].x0[1];
+  float x0 = a.layers[0].x0[0], x1 = a.layers[0].x0[1];
   float2* mine = points + 2 * seg * buf;
-  for (int kb = 0; kb < a.n; kb += kWideSteps) {
+  // this thread's word of the records of kWideSteps steps (clamped to the last)
+  const int rw = (int)threadIdx.x % kRecWords, rs = (int)threadIdx.x / kRecWords;
+  auto fetch = [&](int kb) {
+    return rs < kWideSteps ? step_word(a, min(kb + rs, a.n - 1), rw) : 0u;
+  };
+  auto keep = [&](int half, uint32_t word) {
+    if (rs < kWideSteps)
+      reinterpret_cast<uint32_t*>(recs + half * kWideSteps)[rs * kRecWords + rw] = word;
+  };
+  keep(0, fetch(0));
+  __syncthreads();
+  int half = 0;
+  for (int kb = 0; kb < a.n; kb += kWideSteps, half ^= 1) {
+    const StepRec* R = recs + half * kWideSteps;
+    const uint32_t ahead = fetch(kb + kWideSteps);
     const int ks = kb + 2 * seg;  // this segment's steps ks, ks + 1
     const int steps = min(max(a.n - ks, 0), 2);
     float e[4] = {0.f, 0.f, 0.f, 0.f};
     if (steps > 0) {
-      const U4 r = philox4x32_10(U4{mc, (uint32_t)(ks >> 1), a.contract, 1u}, k0, k1);
+      const U4 r = philox4x32_10_vk(U4{mc, (uint32_t)(ks >> 1), a.contract, 1u}, a.key0, a.key1);
       box_muller(r.x, r.y, e[0], e[1]);
       box_muller(r.z, r.w, e[2], e[3]);
     }
     __syncthreads();  // the searches of the steps before
+    keep(half ^ 1, ahead);
 #pragma unroll
     for (int u = 0; u < 4; ++u) eps[(4 * seg + u) * kWidePaths + p] = e[u];
     for (int s = 0; s < steps; ++s) {
-      const int N1 = layers[ks + s + 1].N, pt = layers[ks + s + 1].pt_off;
+      const int N1 = __builtin_amdgcn_readfirstlane(R[2 * seg + s].N);
+      const int pt = __builtin_amdgcn_readfirstlane(R[2 * seg + s].pt_off);
       float2* to = mine + s * buf;
-      for (int q0 = p; q0 <= N1; q0 += 4 * kWidePaths) {
-        float2 r[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) r[u] = pts[2 * (pt + min(q0 + u * kWidePaths, N1 - 1))];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int q = q0 + u * kWidePaths;
-          if (q <= N1) to[q] = q < N1 ? r[u] : nan2;
-        }
+      for (int q0 = p; q0 <= N1; q0 += 2 * kWidePaths) {
+        const int q1 = q0 + kWidePaths;
+        const float2 r0 = pts[2 * (pt + min(q0, N1 - 1))], r1 = pts[2 * (pt + min(q1, N1 - 1))];
+        to[q0] = q0 < N1 ? r0 : nan2;
+        if (q1 <= N1) to[q1] = q1 < N1 ? r1 : nan2;
       }
     }
     __syncthreads();
@@ -185,27 +224,22 @@ void walk_2d_wide(FwdArgs a, Visits v) {
 #pragma unroll
     for (int s = 0; s < kWideSteps; ++s) {
       if (kb + s < a.n)
-        step_2d(layers[kb + s], eps[(2 * s) * kWidePaths + p], eps[(2 * s + 1) * kWidePaths + p],
-                x0, x1);
+        step_2d(R[s].A, R[s].T, R[s].b, eps[(2 * s) * kWidePaths + p],
+                eps[(2 * s + 1) * kWidePaths + p], x0, x1);
       if (s >> 1 == seg) {
         xs[s & 1][0][0] = x0;
         xs[s & 1][0][1] = x1;
       }
     }
     if (steps == 0) continue;
-    int N[2];
     uint4 w[2][1];
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      ConstLayer& L1 = layers[min(ks + s + 1, a.n)];
-      N[s] = L1.N;
-      bucket_rows<1>(L1, N[s], a.bk, xs[s], w[s]);
-    }
+    for (int s = 0; s < 2; ++s) bucket_rows<1>(R[2 * seg + s], R[2 * seg + s].N, a.bk, xs[s], w[s]);
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
       if (s >= steps) break;
       int j[1];
-      bucket_argmin<1>(mine + s * buf, N[s], a.bk, xs[s], w[s], j);
+      bucket_argmin<1>(mine + s * buf, R[2 * seg + s].N, a.bk, xs[s], w[s], j);
       if (live) v.cells[(int64_t)(ks + s) * v.stride + (int64_t)t] = (uint16_t)j[0];
     }
   }
@@ -221,7 +255,7 @@ __global__ __launch_bounds__(kBlock) void walk_2d(FwdArgs a, Visits v) {
   const uint32_t k0 = vgpr_copy(a.key0), k1 = vgpr_copy(a.key1);
   const float2* pts = reinterpret_cast<const float2*>(a.pts);  // x, y of point q at 2 q
   const float2 nan2 = make_float2(__builtin_nanf(""), __builtin_nanf(""));
-  ConstLayer* layers = (ConstLayer*)a.layers;
+  const LayerDev* layers = a.layers;
   float x[1][2] = {{layers[0].x0[0], layers[0].x0[1]}};
   float eb[4];
   int i = 0;
@@ -235,7 +269,8 @@ __global__ __launch_bounds__(kBlock) void walk_2d(FwdArgs a, Visits v) {
       box_muller(r.x, r.y, eb[0], eb[1]);
       box_muller(r.z, r.w, eb[2], eb[3]);
     }
-    step_2d(layers[k], (k & 1) ? eb[2] : eb[0], (k & 1) ? eb[3] : eb[1], x[0][0], x[0][1]);
+    const LayerDev& L = a.layers[k];
+    step_2d(L.A, L.T, L.b, (k & 1) ? eb[2] : eb[0], (k & 1) ? eb[3] : eb[1], x[0][0], x[0][1]);
     int j[1];
     uint4 w[1];
     bucket_rows<1>(layers[k + 1], N1, a.bk, x, w);
