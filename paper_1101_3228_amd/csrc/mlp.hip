@@ -1,9 +1,9 @@
-// Pricing-surrogate kernels for gfx950: fused forward (inference and
-// training), fused back-propagation of the activation gradients, the weight
-// gradients of the two 256x256 layers as an MFMA reduction over the batch,
-// the remaining sums, and Adam with the refresh of the BF16 weight copies.
+// Pricing-surrogate kernels for gfx950: inference, forward and back-propagation
+// of a training tile in one kernel, the weight gradients of the two 256x256
+// layers as an MFMA reduction over the batch, the remaining sums, and Adam
+// with the refresh of the BF16 weight copies.
 //
-// MFMA mapping.  A wave owns 32 samples.  A 256x256 layer is computed as
+// MFMA mapping.  A tile is 32 samples.  A 256x256 layer is computed as
 // Z^T = W H^T with the weights as the A operand (rows = output units) and
 // the activations as the B operand (columns = samples), 8 output blocks x
 // 16 K-steps of v_mfma_f32_32x32x16_bf16.  Lane l holds accumulator r of
@@ -63,28 +63,29 @@ __host__ __device__ __forceinline__ int frag_index(int i, int k) {
   return (((i >> 5) * 16 + t) * 64 + lane) * 8 + e;
 }
 
-// The 16 accumulators of output block jb (already activated) as the B
-// operands of K-steps 2 jb and 2 jb + 1, in TERMS BF16 parts.
+// The 16 accumulators of an output block (already activated) as the B
+// operands of its two K-steps, in TERMS BF16 parts.
+template <int TERMS>
+__device__ __forceinline__ void operand_pair(const float (&v)[16], bf16x8 (&one)[TERMS][2]) {
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const __bf16 p = (__bf16)v[8 * k + e];
+      one[0][k][e] = p;
+      if (TERMS == 2) one[TERMS - 1][k][e] = (__bf16)(v[8 * k + e] - (float)p);
+    }
+}
+
 template <int TERMS>
 __device__ __forceinline__ void to_operand(const float (&v)[16], bf16x8 (&op)[TERMS][16],
                                            int jb) {
-  bf16x8 a0, a1, b0, b1;
+  bf16x8 one[TERMS][2];
+  operand_pair<TERMS>(v, one);
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const __bf16 p = (__bf16)v[e];
-    const __bf16 q = (__bf16)v[8 + e];
-    a0[e] = p;
-    a1[e] = q;
-    if (TERMS == 2) {
-      b0[e] = (__bf16)(v[e] - (float)p);
-      b1[e] = (__bf16)(v[8 + e] - (float)q);
-    }
-  }
-  op[0][2 * jb] = a0;
-  op[0][2 * jb + 1] = a1;
-  if (TERMS == 2) {
-    op[TERMS - 1][2 * jb] = b0;
-    op[TERMS - 1][2 * jb + 1] = b1;
+  for (int q = 0; q < TERMS; ++q) {
+    op[q][2 * jb] = one[q][0];
+    op[q][2 * jb + 1] = one[q][1];
   }
 }
 
@@ -92,19 +93,14 @@ __device__ __forceinline__ int unit_of(int jb, int r, int h) {
   return 32 * jb + 8 * (r >> 2) + 4 * h + (r & 3);
 }
 
-// acc[ib] = bias + sum over the 16 K-steps of fragment(ib, t) x op[.][t]
-// (bias: per-unit LDS array, or NULL for zero).
+// acc[ib] = sum over the 16 K-steps of fragment(ib, t) x op[.][t].
 template <int TERMS>
 __device__ __forceinline__ void mfma_layer(const uint16_t* __restrict__ frags,
                                            const bf16x8 (&op)[TERMS][16], int lane,
-                                           const float* bias, f32x16 (&acc)[8]) {
+                                           f32x16 (&acc)[8]) {
   const bf16x8* wf = reinterpret_cast<const bf16x8*>(frags);
-  const int h = lane >> 5;
 #pragma unroll
-  for (int ib = 0; ib < 8; ++ib) {
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[ib][r] = bias ? bias[unit_of(ib, r, h)] : 0.0f;
-  }
+  for (int ib = 0; ib < 8; ++ib) acc[ib] = f32x16{};
 #pragma unroll
   for (int t = 0; t < 16; ++t) {
 #pragma unroll
@@ -117,9 +113,8 @@ __device__ __forceinline__ void mfma_layer(const uint16_t* __restrict__ frags,
   }
 }
 
-// Offset of accumulator r of block jb of a lane inside its wave's tile of a
-// per-unit training array (the wave's base is wave * 8192).
-__device__ __forceinline__ int tile_off(int jb, int r) { return (jb * 16 + r) * 64; }
+// Elements of a tile (32 samples) of a per-unit training array: accumulator r
+// of block jb of a lane is at (16 jb + r) 64 + lane.
 constexpr int kWaveTile = 8 * 16 * 64;
 
 // Tile-layout offset of (unit, sample s) (for kernels that walk units).
@@ -138,6 +133,48 @@ __device__ __forceinline__ float bs_put(float s, float sig, float r, float T) {
   return expf(-r * T) * 0.5f * erfcf(d2 * 0.70710678f) - s * 0.5f * erfcf(d1 * 0.70710678f);
 }
 
+// Inputs of row `row` (dead rows: the box's lower corner, u = 0): u the
+// normalised ones, raw the first four; whether all lie in the box.
+__device__ __forceinline__ bool normalise(const Weights& W, const float* __restrict__ x,
+                                          int64_t row, bool live, float (&u)[kIn],
+                                          float (&raw)[4]) {
+  bool inside = true;
+#pragma unroll
+  for (int c = 0; c < kIn; ++c) {
+    const float xv = live ? x[row * kIn + c] : W.lo[c];
+    if (c < 4) raw[c] = xv;
+    inside = inside && xv >= W.lo[c] && xv <= W.hi[c];
+    u[c] = live ? fmaf(xv - W.lo[c], W.scale[c], W.shift[c]) : 0.0f;
+  }
+  return inside;
+}
+
+// Layer 1's B operand: the inputs as two BF16 terms in the 16 K-slots.
+__device__ __forceinline__ bf16x8 input_operand(const float (&u)[kIn], int h) {
+  float q[16];
+#pragma unroll
+  for (int c = 0; c < kIn; ++c) {
+    const __bf16 a = (__bf16)u[c];
+    q[c] = (float)a;
+    q[kIn + c] = (float)(__bf16)(u[c] - (float)a);
+  }
+#pragma unroll
+  for (int c = 2 * kIn; c < 16; ++c) q[c] = 0.0f;
+  bf16x8 ub;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) ub[e] = (__bf16)(h ? q[8 + e] : q[e]);
+  return ub;
+}
+
+// The network's output from this lane half's head sum.
+__device__ __forceinline__ float output(const Weights& W, float part, bool base,
+                                        const float (&raw)[4]) {
+  part += __shfl_xor(part, 32);
+  float y = W.out_scale * (part + W.master[kOffB4]);
+  if (W.baseline && base) y += bs_put(raw[0], raw[1], raw[2], raw[3]);
+  return y;
+}
+
 struct FwdIO {
   const float* x;
   int64_t B;
@@ -145,11 +182,9 @@ struct FwdIO {
   uint8_t* in_range;
 };
 
-// Forward pass of 32 samples per wave.  TRAIN: rows come from the training
-// set through idx, pre-activations and layer inputs are kept for the
-// backward pass, and the loss gradient dL/dy replaces y.
-template <int TERMS, bool TRAIN>
-__global__ __launch_bounds__(kBlock) void mlp_forward(Weights W, FwdIO io, Train T) {
+// Forward pass of 32 samples per wave (large batches).
+template <int TERMS>
+__global__ __launch_bounds__(kBlock) void mlp_forward(Weights W, FwdIO io) {
   __shared__ float sb[3][kHid];
   __shared__ float sw4[kHid];
   for (int i = threadIdx.x; i < kHid; i += kBlock) {
@@ -163,43 +198,15 @@ __global__ __launch_bounds__(kBlock) void mlp_forward(Weights W, FwdIO io, Train
   const int lane = threadIdx.x & 63, h = lane >> 5;
   const int64_t wave = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
   const int64_t s = wave * kWaveRows + (lane & 31);
-  const int64_t B = TRAIN ? T.B : io.B;
-  const bool live = s < B;
-  const int64_t tb = wave * kWaveTile + lane;  // this lane's place in a training tile
-
-  int64_t row = s;
-  if (TRAIN && live && T.idx) row = T.idx[s];
-  const float* xs = TRAIN ? T.x : io.x;
+  const bool live = s < io.B;
   float u[kIn], raw[4];
-  bool inside = true;
-#pragma unroll
-  for (int c = 0; c < kIn; ++c) {
-    const float xv = live ? xs[row * kIn + c] : W.lo[c];
-    if (c < 4) raw[c] = xv;
-    inside = inside && xv >= W.lo[c] && xv <= W.hi[c];
-    u[c] = live ? fmaf(xv - W.lo[c], W.scale[c], W.shift[c]) : 0.0f;
-  }
-  if (TRAIN && h == 0) {
-#pragma unroll
-    for (int c = 0; c < kIn; ++c) T.u[s * 8 + c] = u[c];
-  }
+  const bool inside = normalise(W, io.x, s, live, u, raw);
 
   bf16x8 op[TERMS][16];
   f32x16 acc[8];
   {
     // layer 1 (MFMA): z1 = b1 + W1 (u_hi + u_lo), one K-step per block
-    float q[16];
-#pragma unroll
-    for (int c = 0; c < kIn; ++c) {
-      const __bf16 a = (__bf16)u[c];
-      q[c] = (float)a;
-      q[kIn + c] = (float)(__bf16)(u[c] - (float)a);
-    }
-#pragma unroll
-    for (int c = 2 * kIn; c < 16; ++c) q[c] = 0.0f;
-    bf16x8 ub;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) ub[e] = (__bf16)(h ? q[8 + e] : q[e]);
+    const bf16x8 ub = input_operand(u, h);
     const bf16x8* w1f = reinterpret_cast<const bf16x8*>(W.w1);
 #pragma unroll
     for (int ib = 0; ib < 8; ++ib) {
@@ -212,155 +219,340 @@ __global__ __launch_bounds__(kBlock) void mlp_forward(Weights W, FwdIO io, Train
   for (int jb = 0; jb < 8; ++jb) {
     float v[16];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const float z = acc[jb][r];
-      v[r] = silu(z);
-      if (TRAIN) {
-        T.z1[tb + tile_off(jb, r)] = z;
-        T.h1[tb + tile_off(jb, r)] = bf16_bits(v[r]);
-      }
-    }
+    for (int r = 0; r < 16; ++r) v[r] = silu(acc[jb][r]);
     to_operand<TERMS>(v, op, jb);
   }
   // layer 2 (MFMA)
-  mfma_layer<TERMS>(W.w2f, op, lane, nullptr, acc);
+  mfma_layer<TERMS>(W.w2f, op, lane, acc);
 #pragma unroll
   for (int jb = 0; jb < 8; ++jb) {
     float v[16];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const float z = acc[jb][r] + sb[1][unit_of(jb, r, h)];
-      v[r] = silu(z);
-      if (TRAIN) {
-        T.z2[tb + tile_off(jb, r)] = z;
-        T.h2[tb + tile_off(jb, r)] = bf16_bits(v[r]);
-      }
-    }
+    for (int r = 0; r < 16; ++r) v[r] = silu(acc[jb][r] + sb[1][unit_of(jb, r, h)]);
     to_operand<TERMS>(v, op, jb);
   }
   // layer 3 (MFMA) and the head
-  mfma_layer<TERMS>(W.w3f, op, lane, nullptr, acc);
+  mfma_layer<TERMS>(W.w3f, op, lane, acc);
   float part = 0.0f;
 #pragma unroll
   for (int jb = 0; jb < 8; ++jb) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int unit = unit_of(jb, r, h);
-      const float z = acc[jb][r] + sb[2][unit];
-      if (TRAIN) T.z3[tb + tile_off(jb, r)] = z;
-      part = fmaf(sw4[unit], silu(z), part);
+      part = fmaf(sw4[unit], silu(acc[jb][r] + sb[2][unit]), part);
     }
   }
-  part += __shfl_xor(part, 32);
-  float y = W.out_scale * (part + W.master[kOffB4]);
-  if (W.baseline && live && inside) y += bs_put(raw[0], raw[1], raw[2], raw[3]);
+  const float y = output(W, part, live && inside, raw);
+  if (h == 0 && live) {
+    io.y[s] = y;
+    if (io.in_range) io.in_range[s] = inside ? 1 : 0;
+  }
+}
 
-  if (!TRAIN) {
-    if (h == 0 && live) {
-      io.y[s] = y;
-      if (io.in_range) io.in_range[s] = inside ? 1 : 0;
-    }
-    return;
+// ------------------------------------------------ one tile per workgroup
+//
+// Eight waves share the 32 samples of a tile: wave ib computes output block
+// ib of every layer (32 units), and the activations pass through LDS as the
+// next layer's B operands.  The sums are those of mlp_forward in the same
+// order, so the results are the same bits.  A batch of 4096 is 128 tiles: with
+// a wave per tile and all eight blocks in it, 32 CUs worked through a chain
+// of 256 products and 768 activations per lane (forward 89 us, backward 159
+// us), and a single query took 40 us.
+
+constexpr int kTileBlock = 512;
+// Inference takes this path up to two workgroups of 64 KiB LDS per CU.
+constexpr int64_t kForwardTiles = 512;
+constexpr int kOps = 16 * 64;  // B operands of a layer (one term)
+
+// The 16 activations of this wave's block as B operands of K-steps 2 ib, 2 ib
+// + 1, in TERMS BF16 parts: ops[term][t][lane].
+template <int TERMS>
+__device__ __forceinline__ void share_operand(const float (&v)[16], bf16x8* ops, int ib, int lane) {
+  bf16x8 one[TERMS][2];
+  operand_pair<TERMS>(v, one);
+#pragma unroll
+  for (int q = 0; q < TERMS; ++q)
+#pragma unroll
+    for (int e = 0; e < 2; ++e) ops[q * kOps + (2 * ib + e) * 64 + lane] = one[q][e];
+}
+
+// This wave's 16 weight fragments of a layer, and their product with ops.
+__device__ __forceinline__ void load_frags(const uint16_t* __restrict__ frags, int ib, int lane,
+                                           bf16x8 (&f)[16]) {
+  const bf16x8* wf = reinterpret_cast<const bf16x8*>(frags);
+#pragma unroll
+  for (int t = 0; t < 16; ++t) f[t] = wf[(ib * 16 + t) * 64 + lane];
+}
+template <int TERMS>
+__device__ __forceinline__ f32x16 tile_layer(const bf16x8 (&f)[16], const bf16x8* ops, int lane) {
+  f32x16 acc = f32x16{};
+#pragma unroll
+  for (int t = 0; t < 16; ++t)
+#pragma unroll
+    for (int q = 0; q < TERMS; ++q)
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[t], ops[q * kOps + t * 64 + lane], acc, 0, 0,
+                                                    0);
+  return acc;
+}
+
+// Four values of this lane's units 32 ib + 8 g + 4 h .. + 3 for g = 0..3.
+__device__ __forceinline__ void load_units(const float* __restrict__ p, int ib, int h,
+                                           float (&v)[16]) {
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const float4 q = *reinterpret_cast<const float4*>(p + unit_of(ib, 4 * g, h));
+    v[4 * g] = q.x;
+    v[4 * g + 1] = q.y;
+    v[4 * g + 2] = q.z;
+    v[4 * g + 3] = q.w;
   }
-  float lc = 0.0f;
-  if (h == 0) {
-    float g = 0.0f;
-    if (live) {
+}
+
+// Forward of the tile: z1, z2, z3 of this wave's block, and in wave 0 the
+// head's sum over the units (`part`, of this lane's half).  lds: 64 KiB, its
+// first half free on return to all waves after their next barrier.
+struct TileForward {
+  float z1[16], z2[16], z3[16];
+  float part;
+};
+template <int TERMS, bool TRAIN>
+__device__ __forceinline__ void tile_forward(const Weights& W, const Train& T, const float (&u)[kIn],
+                                             int64_t tile, bf16x8* lds, int ib, int lane,
+                                             TileForward& o) {
+  const int h = lane >> 5;
+  bf16x8* const opsA = lds;
+  bf16x8* const opsB = lds + 2 * kOps;
+  const int64_t at = tile * kWaveTile + (int64_t)ib * 1024 + lane;
+  bf16x8 f2[16], f3[16];
+  load_frags(W.w2f, ib, lane, f2);
+  float b[16], v[16];
+  load_units(W.master + kOffB1, ib, h, b);
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = b[r];
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+      reinterpret_cast<const bf16x8*>(W.w1)[ib * 64 + lane], input_operand(u, h), acc, 0, 0, 0);
+  load_frags(W.w3f, ib, lane, f3);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    o.z1[r] = acc[r];
+    v[r] = silu(acc[r]);
+    if (TRAIN) T.h1[at + 64 * r] = bf16_bits(v[r]);
+  }
+  share_operand<TERMS>(v, opsA, ib, lane);
+  load_units(W.master + kOffB2, ib, h, b);
+  __syncthreads();
+  acc = tile_layer<TERMS>(f2, opsA, lane);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    o.z2[r] = acc[r] + b[r];
+    v[r] = silu(o.z2[r]);
+    if (TRAIN) T.h2[at + 64 * r] = bf16_bits(v[r]);
+  }
+  share_operand<TERMS>(v, opsB, ib, lane);
+  load_units(W.master + kOffB3, ib, h, b);
+  __syncthreads();
+  acc = tile_layer<TERMS>(f3, opsB, lane);
+  // the head's terms through LDS: wave 0 sums them in the order of the units
+  float* head = reinterpret_cast<float*>(opsA);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    o.z3[r] = acc[r] + b[r];
+    head[(16 * ib + r) * 64 + lane] = silu(o.z3[r]);
+  }
+  __syncthreads();
+  o.part = 0.0f;
+  if (ib == 0) {
+#pragma unroll
+    for (int jb = 0; jb < 8; ++jb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        o.part = fmaf(bf16_float(W.w4[unit_of(jb, r, h)]), head[(16 * jb + r) * 64 + lane], o.part);
+  }
+}
+
+template <int TERMS>
+__global__ __launch_bounds__(kTileBlock) void mlp_forward_tile(Weights W, FwdIO io) {
+  extern __shared__ bf16x8 lds[];
+  const int lane = threadIdx.x & 63, h = lane >> 5;
+  const int ib = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t s = (int64_t)blockIdx.x * kWaveRows + (lane & 31);
+  const bool live = s < io.B;
+  float u[kIn], raw[4];
+  const bool inside = normalise(W, io.x, s, live, u, raw);
+  TileForward o;
+  tile_forward<TERMS, false>(W, Train{}, u, blockIdx.x, lds, ib, lane, o);
+  if (ib != 0) return;
+  const float y = output(W, o.part, live && inside, raw);
+  if (h == 0 && live) {
+    io.y[s] = y;
+    if (io.in_range) io.in_range[s] = inside ? 1 : 0;
+  }
+}
+
+// Sums over the tile's 32 samples of v[r] (and of v[r] u[c]) for every unit
+// of this wave's block, through its own 4 KiB of LDS: unit lane % 32 sums
+// samples 16 (lane / 32) .. + 15, then the halves meet.
+template <int C>
+__device__ __forceinline__ void unit_sums(const float (&v)[16], float* tr,
+                                          const float* __restrict__ us, int lane, float (&sum)[C]) {
+  const int h = lane >> 5, s = lane & 31;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int unit = 8 * (r >> 2) + 4 * h + (r & 3);
+    tr[32 * unit + (s ^ unit)] = v[r];
+  }
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int c = 0; c < C; ++c) sum[c] = 0.0f;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int q = 16 * h + i;
+    const float x = tr[32 * s + (q ^ s)];
+    sum[0] += x;
+#pragma unroll
+    for (int c = 1; c < C; ++c) sum[c] = fmaf(x, us[8 * q + c - 1], sum[c]);
+  }
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int c = 0; c < C; ++c) sum[c] += __shfl_xor(sum[c], 32);
+}
+
+// Forward and backward of one tile: the pre-activations stay in registers;
+// what leaves the workgroup are the BF16 operands of the weight-gradient
+// products (h1, h2, dz2, dz3) and the tile's sums of every other gradient.
+template <int TERMS>
+__global__ __launch_bounds__(kTileBlock) void mlp_grad_tile(Weights W, Train T) {
+  extern __shared__ bf16x8 lds[];  // two layers' operands, then the waves' transposes
+  __shared__ float us[kWaveRows][8], dys[kWaveRows];
+  const int lane = threadIdx.x & 63, h = lane >> 5;
+  const int ib = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  float* tr = reinterpret_cast<float*>(lds + 4 * kOps) + 1024 * ib;
+  const int64_t tile = blockIdx.x;
+  const int64_t s = tile * kWaveRows + (lane & 31);
+  const bool live = s < T.B;
+  const int64_t row = (live && T.idx) ? (int64_t)T.idx[s] : s;
+  float u[kIn], raw[4];
+  const bool inside = normalise(W, T.x, row, live, u, raw);
+  if (ib == 0 && h == 0) {
+#pragma unroll
+    for (int c = 0; c < kIn; ++c) us[lane][c] = u[c];
+  }
+  TileForward o;
+  tile_forward<TERMS, true>(W, T, u, tile, lds, ib, lane, o);
+  bf16x8 f[16];
+  load_frags(W.w3t, ib, lane, f);
+  if (ib == 0) {
+    const float y = output(W, o.part, live && inside, raw);
+    float lc = 0.0f, g = 0.0f;
+    if (h == 0 && live) {
       const float wv = T.w ? T.w[row] : 1.0f;
       const float res = y - T.t[row];
       g = 2.0f * wv * res * T.inv_b;
       lc = wv * res * res * T.inv_b;
     }
-    T.dy[s] = g;
-  }
+    if (h == 0) dys[lane] = g;
 #pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) lc += __shfl_xor(lc, m);
-  if (lane == 0) T.lossp[wave] = lc;
-}
-
-// Back-propagation of dL/dy to dz3, dz2, dz1 for 32 samples per wave, the
-// transposed weights as the A operand (same register layout as forward).
-__global__ __launch_bounds__(kBlock) void mlp_backward(Weights W, Train T) {
-  __shared__ float sw4[kHid];
-  for (int i = threadIdx.x; i < kHid; i += kBlock) sw4[i] = bf16_float(W.w4[i]);
+    for (int m = 32; m >= 1; m >>= 1) {
+      lc += __shfl_xor(lc, m);
+      g += __shfl_xor(g, m);
+    }
+    if (lane == 0) {
+      T.tsum[2 * tile] = g;
+      T.tsum[2 * tile + 1] = lc;
+    }
+  }
+  float w4[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) w4[r] = bf16_float(W.w4[unit_of(ib, r, h)]);
   __syncthreads();
-  const int lane = threadIdx.x & 63, h = lane >> 5;
-  const int64_t wave = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
-  const int64_t s = wave * kWaveRows + (lane & 31);
-  const int64_t tb = wave * kWaveTile + lane;
-  const float gy = W.out_scale * T.dy[s];
-
-  bf16x8 op[1][16];
-  f32x16 acc[8];
+  const float dy = dys[lane & 31];
+  const float gy = W.out_scale * dy;
+  const int64_t at = tile * kWaveTile + (int64_t)ib * 1024 + lane;
+  float* out = T.usum + (tile * kHid + 32 * ib) * kUnitSums;
+  bf16x8* const opsA = lds;
+  bf16x8* const opsB = lds + 2 * kOps;
+  float v[16], one[1], in[kIn + 1];
 #pragma unroll
-  for (int jb = 0; jb < 8; ++jb) {
-    float v[16];
+  for (int r = 0; r < 16; ++r) v[r] = dy * silu(o.z3[r]);
+  unit_sums<1>(v, tr, nullptr, lane, one);
+  const float dw4 = one[0];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int unit = unit_of(jb, r, h);
-      const float dz = sw4[unit] * gy * dsilu(T.z3[tb + tile_off(jb, r)]);
-      T.dz3[tb + tile_off(jb, r)] = dz;
-      v[r] = dz;
-    }
-    to_operand<1>(v, op, jb);
+  for (int r = 0; r < 16; ++r) {
+    v[r] = w4[r] * gy * dsilu(o.z3[r]);
+    T.dz3[at + 64 * r] = bf16_bits(v[r]);
   }
-  mfma_layer<1>(W.w3t, op, lane, nullptr, acc);  // dh2 = W3^T dz3
+  share_operand<1>(v, opsB, ib, lane);
+  unit_sums<1>(v, tr, nullptr, lane, one);
+  const float db3 = one[0];
+  __syncthreads();
+  f32x16 acc = tile_layer<1>(f, opsB, lane);  // dh2 = W3^T dz3
+  load_frags(W.w2t, ib, lane, f);
 #pragma unroll
-  for (int jb = 0; jb < 8; ++jb) {
-    float v[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const float dz = acc[jb][r] * dsilu(T.z2[tb + tile_off(jb, r)]);
-      T.dz2[tb + tile_off(jb, r)] = dz;
-      v[r] = dz;
-    }
-    to_operand<1>(v, op, jb);
+  for (int r = 0; r < 16; ++r) {
+    v[r] = acc[r] * dsilu(o.z2[r]);
+    T.dz2[at + 64 * r] = bf16_bits(v[r]);
   }
-  mfma_layer<1>(W.w2t, op, lane, nullptr, acc);  // dh1 = W2^T dz2
+  share_operand<1>(v, opsA, ib, lane);
+  unit_sums<1>(v, tr, nullptr, lane, one);
+  const float db2 = one[0];
+  __syncthreads();
+  acc = tile_layer<1>(f, opsA, lane);  // dh1 = W2^T dz2
 #pragma unroll
-  for (int jb = 0; jb < 8; ++jb) {
+  for (int r = 0; r < 16; ++r) v[r] = acc[r] * dsilu(o.z1[r]);
+  unit_sums<kIn + 1>(v, tr, us[0], lane, in);
+  if (h == 0) {
+    float* q = out + lane * kUnitSums;
 #pragma unroll
-    for (int r = 0; r < 16; ++r)
-      T.dz1[tb + tile_off(jb, r)] = acc[jb][r] * dsilu(T.z1[tb + tile_off(jb, r)]);
+    for (int c = 0; c < kIn; ++c) q[c] = in[c + 1];
+    q[6] = in[0];
+    q[7] = db2;
+    q[8] = db3;
+    q[9] = dw4;
   }
 }
 
-// Partial weight gradients dW[i][k] = sum_s dz[i][s] h[k][s] of layers 2
-// and 3 over one chunk of kChunk samples: one 32x32 tile per wave, the
-// samples as the K dimension.
+// Partial weight gradients dW[i][k] = sum_s dz[i][s] h[k][s] of layers 2 and
+// 3 over one chunk of kChunk samples, the samples as the K dimension: a
+// workgroup takes 128 x 128 of the matrix, each of its four waves 64 x 64 (an
+// operand row is loaded once for two products, where a wave per 32 x 32 tile
+// loaded it for one: 100 MB through the L2s at 4096 samples, 15 us).
 __global__ __launch_bounds__(kBlock) void mlp_wgrad(Train T) {
   const int nchunks = (int)(T.Bp / kChunk);
-  const int job = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
-  const int q = job % nchunks;
-  const int tile = (job / nchunks) & 63;
-  const int L = job / (nchunks * 64);
-  if (L >= 2) return;
-  const int ib = tile >> 3, kb = tile & 7;
+  const int q = (int)blockIdx.x % nchunks;
+  const int quad = ((int)blockIdx.x / nchunks) & 3;
+  const int L = (int)blockIdx.x / (nchunks * 4);
+  const int wave = threadIdx.x >> 6;
+  const int ib = 4 * (quad >> 1) + 2 * (wave >> 1), kb = 4 * (quad & 1) + 2 * (wave & 1);
   const int lane = threadIdx.x & 63, h = lane >> 5, row = lane & 31;
-  const float* dz = L ? T.dz3 : T.dz2;
+  const uint16_t* dz = L ? T.dz3 : T.dz2;
   const uint16_t* hh = L ? T.h2 : T.h1;
-  f32x16 acc = f32x16{};
-  for (int s0 = q * kChunk; s0 < (q + 1) * kChunk; s0 += 16) {
+  f32x16 acc[2][2] = {{f32x16{}, f32x16{}}, {f32x16{}, f32x16{}}};
+#pragma unroll 8
+  for (int s0 = 0; s0 < kChunk; s0 += 16) {
     // 8 consecutive samples of one unit are contiguous in the tile layout
-    const int64_t sa = s0 + 8 * h;
-    const float4 p0 = *reinterpret_cast<const float4*>(dz + tile_index(32 * ib + row, sa));
-    const float4 p1 = *reinterpret_cast<const float4*>(dz + tile_index(32 * ib + row, sa) + 4);
-    bf16x8 a;
-    a[0] = (__bf16)p0.x;
-    a[1] = (__bf16)p0.y;
-    a[2] = (__bf16)p0.z;
-    a[3] = (__bf16)p0.w;
-    a[4] = (__bf16)p1.x;
-    a[5] = (__bf16)p1.y;
-    a[6] = (__bf16)p1.z;
-    a[7] = (__bf16)p1.w;
-    const bf16x8 b = *reinterpret_cast<const bf16x8*>(hh + tile_index(32 * kb + row, sa));
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
+    const int64_t sa = (int64_t)q * kChunk + s0 + 8 * h;
+    bf16x8 a[2], b[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      a[e] = *reinterpret_cast<const bf16x8*>(dz + tile_index(32 * (ib + e) + row, sa));
+      b[e] = *reinterpret_cast<const bf16x8*>(hh + tile_index(32 * (kb + e) + row, sa));
+    }
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+      for (int g = 0; g < 2; ++g)
+        acc[e][g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[e], b[g], acc[e][g], 0, 0, 0);
   }
   float* out = T.part + ((size_t)(L * nchunks + q) << 16);
 #pragma unroll
-  for (int r = 0; r < 16; ++r)
-    out[(32 * ib + 8 * (r >> 2) + 4 * h + (r & 3)) * kHid + 32 * kb + row] = acc[r];
+  for (int e = 0; e < 2; ++e)
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        out[(32 * (ib + e) + 8 * (r >> 2) + 4 * h + (r & 3)) * kHid + 32 * (kb + g) + row] =
+            acc[e][g][r];
 }
 
 __device__ __forceinline__ float block_sum(float v, float* red) {
@@ -375,54 +567,48 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
   return t;
 }
 
-// Gradient sums in a fixed order: blocks [0, 512) add the partials of dW2
-// and dW3; block 512 + u sums unit u's dW1 row, db1, db2, db3 and dw4 over
-// the batch; the last block db4 and the loss.
+// Gradient sums in a fixed order: blocks [0, 512) add the partials of dW2 and
+// dW3; the next kSumBlocks the tiles' sums of dW1, db1, db2, db3 and dw4, 16
+// of them each, 16 threads to a sum; the last block db4 and the loss.
+constexpr int kSumBlocks = kHid * kUnitSums / 16;
 __global__ __launch_bounds__(kBlock) void mlp_reduce(Weights W, Train T, float* grad,
                                                      float* loss) {
-  __shared__ float red[kBlock / 64];
+  __shared__ float red[kBlock];
   const int nchunks = (int)(T.Bp / kChunk);
+  const int64_t tiles = T.Bp / kWaveRows;
   const int b = blockIdx.x;
   if (b < 512) {
     const int e = b * kBlock + threadIdx.x;
     const int L = e >> 16, at = e & 0xFFFF;
     float sum = 0.0f;
+#pragma unroll 8
     for (int q = 0; q < nchunks; ++q) sum += T.part[((size_t)(L * nchunks + q) << 16) + at];
     grad[(L ? kOffW3 : kOffW2) + at] = sum;
     return;
   }
-  const int64_t Bp = T.Bp;
-  if (b < 512 + kHid) {
-    const int unit = b - 512;
-    float a[10];
+  if (b < 512 + kSumBlocks) {
+    const int e = (b - 512) * 16 + (int)(threadIdx.x & 15), part = (int)(threadIdx.x >> 4);
+    float sum = 0.0f;
+#pragma unroll 8
+    for (int64_t t = part; t < tiles; t += 16) sum += T.usum[t * (kHid * kUnitSums) + e];
+    red[threadIdx.x] = sum;
+    __syncthreads();
+    if (part != 0) return;
 #pragma unroll
-    for (int i = 0; i < 10; ++i) a[i] = 0.0f;
-    for (int64_t s = threadIdx.x; s < Bp; s += kBlock) {
-      const int64_t at = tile_index(unit, s);
-      const float d1 = T.dz1[at];
-#pragma unroll
-      for (int c = 0; c < kIn; ++c) a[c] = fmaf(d1, T.u[s * 8 + c], a[c]);
-      a[6] += d1;
-      a[7] += T.dz2[at];
-      a[8] += T.dz3[at];
-      a[9] = fmaf(T.dy[s], silu(T.z3[at]), a[9]);
-    }
-    float tot[10];
-#pragma unroll
-    for (int i = 0; i < 10; ++i) tot[i] = block_sum(a[i], red);
-    if (threadIdx.x == 0) {
-#pragma unroll
-      for (int c = 0; c < kIn; ++c) grad[kOffW1 + unit * kIn + c] = tot[c];
-      grad[kOffB1 + unit] = tot[6];
-      grad[kOffB2 + unit] = tot[7];
-      grad[kOffB3 + unit] = tot[8];
-      grad[kOffW4 + unit] = W.out_scale * tot[9];
-    }
+    for (int p = 1; p < 16; ++p) sum += red[16 * p + threadIdx.x];
+    const int unit = e / kUnitSums, c = e - unit * kUnitSums;
+    if (c < kIn) grad[kOffW1 + unit * kIn + c] = sum;
+    else if (c == 6) grad[kOffB1 + unit] = sum;
+    else if (c == 7) grad[kOffB2 + unit] = sum;
+    else if (c == 8) grad[kOffB3 + unit] = sum;
+    else grad[kOffW4 + unit] = W.out_scale * sum;
     return;
   }
   float gy = 0.0f, l = 0.0f;
-  for (int64_t s = threadIdx.x; s < Bp; s += kBlock) gy += T.dy[s];
-  for (int64_t w = threadIdx.x; w < Bp / kWaveRows; w += kBlock) l += T.lossp[w];
+  for (int64_t t = threadIdx.x; t < tiles; t += kBlock) {
+    gy += T.tsum[2 * t];
+    l += T.tsum[2 * t + 1];
+  }
   gy = block_sum(gy, red);
   l = block_sum(l, red);
   if (threadIdx.x == 0) {
@@ -468,34 +654,52 @@ __global__ __launch_bounds__(kBlock) void mlp_adam(AdamArgs a) {
 
 // ------------------------------------------------------------- launchers
 
+// Dynamic LDS beyond the 64 KiB default (gfx950 has 160 KiB per CU).
+template <typename F>
+static hipError_t allow_lds(F* kernel, size_t bytes) {
+  if (bytes <= 65536) return hipSuccess;
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
+
 hipError_t launch_forward(const Weights& W, int terms, const float* x, int64_t B, float* y,
                           uint8_t* in_range, hipStream_t s) {
   FwdIO io{x, B, y, in_range};
-  Train T{};
+  const int64_t tiles = (B + kWaveRows - 1) / kWaveRows;
+  if (tiles <= kForwardTiles) {
+    const size_t lds = sizeof(bf16x8) * 4 * kOps;
+    if (terms == 2)
+      hipLaunchKernelGGL(mlp_forward_tile<2>, dim3((unsigned)tiles), dim3(kTileBlock), lds, s, W,
+                         io);
+    else
+      hipLaunchKernelGGL(mlp_forward_tile<1>, dim3((unsigned)tiles), dim3(kTileBlock), lds, s, W,
+                         io);
+    return hipGetLastError();
+  }
   const dim3 grid((unsigned)((B + kBlockRows - 1) / kBlockRows));
   if (terms == 2)
-    hipLaunchKernelGGL((mlp_forward<2, false>), grid, dim3(kBlock), 0, s, W, io, T);
+    hipLaunchKernelGGL(mlp_forward<2>, grid, dim3(kBlock), 0, s, W, io);
   else
-    hipLaunchKernelGGL((mlp_forward<1, false>), grid, dim3(kBlock), 0, s, W, io, T);
+    hipLaunchKernelGGL(mlp_forward<1>, grid, dim3(kBlock), 0, s, W, io);
   return hipGetLastError();
 }
 
 hipError_t launch_train_grad(const Weights& W, int terms, const Train& T, float* grad,
                              float* loss, hipStream_t s) {
-  FwdIO io{};
-  const dim3 rows((unsigned)(T.Bp / kBlockRows));
-  if (terms == 2)
-    hipLaunchKernelGGL((mlp_forward<2, true>), rows, dim3(kBlock), 0, s, W, io, T);
-  else
-    hipLaunchKernelGGL((mlp_forward<1, true>), rows, dim3(kBlock), 0, s, W, io, T);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(mlp_backward, rows, dim3(kBlock), 0, s, W, T);
+  const dim3 tiles((unsigned)(T.Bp / kWaveRows));
+  const size_t lds = sizeof(bf16x8) * 4 * kOps + sizeof(float) * 1024 * (kTileBlock / 64);
+  hipError_t e;
+  if (terms == 2) {
+    if ((e = allow_lds(mlp_grad_tile<2>, lds)) != hipSuccess) return e;
+    hipLaunchKernelGGL(mlp_grad_tile<2>, tiles, dim3(kTileBlock), lds, s, W, T);
+  } else {
+    if ((e = allow_lds(mlp_grad_tile<1>, lds)) != hipSuccess) return e;
+    hipLaunchKernelGGL(mlp_grad_tile<1>, tiles, dim3(kTileBlock), lds, s, W, T);
+  }
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  const int jobs = 2 * 64 * (int)(T.Bp / kChunk);
-  hipLaunchKernelGGL(mlp_wgrad, dim3((unsigned)(jobs / (kBlock / 64))), dim3(kBlock), 0, s, T);
+  hipLaunchKernelGGL(mlp_wgrad, dim3((unsigned)(2 * 4 * (T.Bp / kChunk))), dim3(kBlock), 0, s, T);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(mlp_reduce, dim3(512 + kHid + 1), dim3(kBlock), 0, s, W, T, grad, loss);
+  hipLaunchKernelGGL(mlp_reduce, dim3(512 + kSumBlocks + 1), dim3(kBlock), 0, s, W, T, grad, loss);
   return hipGetLastError();
 }
 

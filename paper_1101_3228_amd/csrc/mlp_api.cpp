@@ -22,7 +22,7 @@ constexpr int64_t kMaxBatch = int64_t(1) << 24;
 // Byte offsets of every buffer in the workspace.
 struct MlpLayout {
   size_t master, mom, vel, grad, w1, w4, w2f, w3f, w2t, w3t;
-  size_t z1, z2, z3, h1, h2, dz1, dz2, dz3, u, dy, lossp, part;
+  size_t h1, h2, dz2, dz3, usum, tsum, part;
   size_t total;
   int64_t bp;
 };
@@ -50,17 +50,13 @@ MlpLayout mlp_layout(int64_t max_batch) {
   L.bp = bp;
   if (bp > 0) {
     const size_t per = (size_t)M::kHid * (size_t)bp;
-    L.z1 = take(4 * per);
-    L.z2 = take(4 * per);
-    L.z3 = take(4 * per);
+    const size_t tiles = (size_t)(bp / M::kWaveRows);
     L.h1 = take(2 * per);
     L.h2 = take(2 * per);
-    L.dz1 = take(4 * per);
-    L.dz2 = take(4 * per);
-    L.dz3 = take(4 * per);
-    L.u = take(4 * 8 * (size_t)bp);
-    L.dy = take(4 * (size_t)bp);
-    L.lossp = take(4 * (size_t)(bp / M::kWaveRows));
+    L.dz2 = take(2 * per);
+    L.dz3 = take(2 * per);
+    L.usum = take(4 * tiles * M::kHid * M::kUnitSums);
+    L.tsum = take(4 * tiles * 2);
     L.part = take(4 * 2 * (size_t)(bp / M::kChunk) * M::kHid * M::kHid);
   }
   L.total = off;
@@ -140,17 +136,12 @@ M::Train train_args(const qtree_mlp* m, const float* x, const float* t, const fl
   T.B = B;
   T.Bp = (B + M::kChunk - 1) / M::kChunk * M::kChunk;
   T.inv_b = (float)(1.0 / (double)B);
-  T.z1 = m->at<float>(m->lay.z1);
-  T.z2 = m->at<float>(m->lay.z2);
-  T.z3 = m->at<float>(m->lay.z3);
   T.h1 = m->at<uint16_t>(m->lay.h1);
   T.h2 = m->at<uint16_t>(m->lay.h2);
-  T.dz1 = m->at<float>(m->lay.dz1);
-  T.dz2 = m->at<float>(m->lay.dz2);
-  T.dz3 = m->at<float>(m->lay.dz3);
-  T.u = m->at<float>(m->lay.u);
-  T.dy = m->at<float>(m->lay.dy);
-  T.lossp = m->at<float>(m->lay.lossp);
+  T.dz2 = m->at<uint16_t>(m->lay.dz2);
+  T.dz3 = m->at<uint16_t>(m->lay.dz3);
+  T.usum = m->at<float>(m->lay.usum);
+  T.tsum = m->at<float>(m->lay.tsum);
   T.part = m->at<float>(m->lay.part);
   return T;
 }

@@ -38,9 +38,12 @@ struct Weights {
   int baseline;  // 1: add the Black-Scholes European put per unit strike
 };
 
+constexpr int kUnitSums = 10;         // per unit: dW1 row (6), db1, db2, db3, dw4
+
 // Training batch and its buffers.  Rows are padded to Bp (a multiple of
-// kChunk).  Per-unit arrays (z, h, dz) are stored in the accumulator tile
-// layout of the kernels: element (unit, sample s) at
+// kChunk), in tiles of 32.  The per-unit arrays (h, dz; the BF16 operands of
+// the weight gradients) are stored in the accumulator layout of the kernels:
+// element (unit, sample s) at
 //   ((s / 32) * 8 + unit / 32) * 1024 + r * 64 + 32 h + s % 32
 // with u = unit % 32, h = (u / 4) % 2, r = 4 (u / 8) + u % 4, so that a wave
 // addresses its 32 samples with constant offsets and the 32 samples of one
@@ -52,17 +55,12 @@ struct Train {
   const int32_t* idx;  // [B] rows of this batch, or NULL (0..B-1)
   int64_t B, Bp;
   float inv_b;
-  float* z1;
-  float* z2;
-  float* z3;
   uint16_t* h1;        // BF16 inputs of layers 2 and 3 (hi term)
   uint16_t* h2;
-  float* dz1;
-  float* dz2;
-  float* dz3;
-  float* u;            // [Bp][8] normalised inputs
-  float* dy;           // [Bp]
-  float* lossp;        // [Bp / 32]
+  uint16_t* dz2;       // BF16 dL/dz of layers 2 and 3
+  uint16_t* dz3;
+  float* usum;         // [Bp / 32][256][kUnitSums] sums over a tile, per unit
+  float* tsum;         // [Bp / 32][2] dL/dy and loss summed over a tile
   float* part;         // [2][Bp / kChunk][256][256] weight-gradient partials
 };
 

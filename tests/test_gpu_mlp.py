@@ -246,3 +246,36 @@ def test_c5_surrogate_accuracy_at_full_size():
           f"p99 {np.quantile(err, 0.99):.2e} max {err.max():.2e} "
           f"within 1e-3 {np.mean(err <= 1e-3):.3f}", flush=True)
     assert err.mean() <= 1e-3
+
+
+@pytest.mark.parametrize("terms", [1, 2])
+@pytest.mark.parametrize("B", [1, 33, 16384, 16385])
+def test_both_forward_paths_agree_bit_for_bit(terms, B):
+    """A tile per workgroup (up to 16384 queries) and a tile per wave sum in
+    the same order: the first queries of a larger batch equal the batch of
+    them alone."""
+    _case(f"mlp forward paths terms={terms} B={B}")
+    x = torch.from_numpy(synth.box_queries(20_000, 9, frac_out=0.05)).cuda()
+    net = S.MLP(_params(5), LO, HI, out_scale=0.1, act_terms=terms, baseline=1)
+    y, m = net.forward(x)
+    yb, mb = net.forward(x[:B].contiguous())
+    assert torch.equal(yb, y[:B]) and torch.equal(mb, m[:B])
+
+
+@pytest.mark.parametrize("B", [1, 31, 32, 257, 1025])
+def test_gradient_at_tile_edges(B):
+    """Rows past the batch in the last tile and the last chunk add nothing;
+    unweighted and unindexed.  Tolerance as the gradient test above; a single
+    row's per-tensor error is one BF16 rounding of each factor."""
+    _case(f"mlp grad edges B={B}")
+    p = _params(6)
+    x = synth.box_queries(B, 23)
+    t = np.random.default_rng(B).uniform(0.0, 0.3, B).astype(np.float32)
+    net = S.MLP(p, LO, HI, out_scale=0.1, act_terms=2, max_batch=1025)
+    g, loss = net.grad(torch.from_numpy(x).cuda(), torch.from_numpy(t).cuda())
+    g = g.cpu().numpy().astype(np.float64)
+    L, gr, _ = M.loss_and_grad(p, x, t, np.ones(B, np.float32), LO, HI, 0.1, terms=2)
+    assert float(loss.item()) == pytest.approx(L, rel=1e-3)
+    for name, a, b in TENSORS:
+        nb = np.linalg.norm(gr[a:b])
+        assert np.linalg.norm(g[a:b] - gr[a:b]) <= 1e-2 * nb, name
