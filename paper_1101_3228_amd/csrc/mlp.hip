@@ -77,40 +77,8 @@ __device__ __forceinline__ void operand_pair(const float (&v)[16], bf16x8 (&one)
     }
 }
 
-template <int TERMS>
-__device__ __forceinline__ void to_operand(const float (&v)[16], bf16x8 (&op)[TERMS][16],
-                                           int jb) {
-  bf16x8 one[TERMS][2];
-  operand_pair<TERMS>(v, one);
-#pragma unroll
-  for (int q = 0; q < TERMS; ++q) {
-    op[q][2 * jb] = one[q][0];
-    op[q][2 * jb + 1] = one[q][1];
-  }
-}
-
 __device__ __forceinline__ int unit_of(int jb, int r, int h) {
   return 32 * jb + 8 * (r >> 2) + 4 * h + (r & 3);
-}
-
-// acc[ib] = sum over the 16 K-steps of fragment(ib, t) x op[.][t].
-template <int TERMS>
-__device__ __forceinline__ void mfma_layer(const uint16_t* __restrict__ frags,
-                                           const bf16x8 (&op)[TERMS][16], int lane,
-                                           f32x16 (&acc)[8]) {
-  const bf16x8* wf = reinterpret_cast<const bf16x8*>(frags);
-#pragma unroll
-  for (int ib = 0; ib < 8; ++ib) acc[ib] = f32x16{};
-#pragma unroll
-  for (int t = 0; t < 16; ++t) {
-#pragma unroll
-    for (int ib = 0; ib < 8; ++ib) {
-      const bf16x8 a = wf[(ib * 16 + t) * 64 + lane];
-      acc[ib] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, op[0][t], acc[ib], 0, 0, 0);
-      if (TERMS == 2)
-        acc[ib] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, op[TERMS - 1][t], acc[ib], 0, 0, 0);
-    }
-  }
 }
 
 // Elements of a tile (32 samples) of a per-unit training array: accumulator r
@@ -166,10 +134,9 @@ __device__ __forceinline__ bf16x8 input_operand(const float (&u)[kIn], int h) {
   return ub;
 }
 
-// The network's output from this lane half's head sum.
+// The network's output from the head's sum.
 __device__ __forceinline__ float output(const Weights& W, float part, bool base,
                                         const float (&raw)[4]) {
-  part += __shfl_xor(part, 32);
   float y = W.out_scale * (part + W.master[kOffB4]);
   if (W.baseline && base) y += bs_put(raw[0], raw[1], raw[2], raw[3]);
   return y;
@@ -182,87 +149,16 @@ struct FwdIO {
   uint8_t* in_range;
 };
 
-// Forward pass of 32 samples per wave (large batches).
-template <int TERMS>
-__global__ __launch_bounds__(kBlock) void mlp_forward(Weights W, FwdIO io) {
-  __shared__ float sb[3][kHid];
-  __shared__ float sw4[kHid];
-  for (int i = threadIdx.x; i < kHid; i += kBlock) {
-    sb[0][i] = W.master[kOffB1 + i];
-    sb[1][i] = W.master[kOffB2 + i];
-    sb[2][i] = W.master[kOffB3 + i];
-    sw4[i] = bf16_float(W.w4[i]);
-  }
-  __syncthreads();
-
-  const int lane = threadIdx.x & 63, h = lane >> 5;
-  const int64_t wave = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
-  const int64_t s = wave * kWaveRows + (lane & 31);
-  const bool live = s < io.B;
-  float u[kIn], raw[4];
-  const bool inside = normalise(W, io.x, s, live, u, raw);
-
-  bf16x8 op[TERMS][16];
-  f32x16 acc[8];
-  {
-    // layer 1 (MFMA): z1 = b1 + W1 (u_hi + u_lo), one K-step per block
-    const bf16x8 ub = input_operand(u, h);
-    const bf16x8* w1f = reinterpret_cast<const bf16x8*>(W.w1);
-#pragma unroll
-    for (int ib = 0; ib < 8; ++ib) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[ib][r] = sb[0][unit_of(ib, r, h)];
-      acc[ib] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1f[ib * 64 + lane], ub, acc[ib], 0, 0, 0);
-    }
-  }
-#pragma unroll
-  for (int jb = 0; jb < 8; ++jb) {
-    float v[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) v[r] = silu(acc[jb][r]);
-    to_operand<TERMS>(v, op, jb);
-  }
-  // layer 2 (MFMA)
-  mfma_layer<TERMS>(W.w2f, op, lane, acc);
-#pragma unroll
-  for (int jb = 0; jb < 8; ++jb) {
-    float v[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) v[r] = silu(acc[jb][r] + sb[1][unit_of(jb, r, h)]);
-    to_operand<TERMS>(v, op, jb);
-  }
-  // layer 3 (MFMA) and the head
-  mfma_layer<TERMS>(W.w3f, op, lane, acc);
-  float part = 0.0f;
-#pragma unroll
-  for (int jb = 0; jb < 8; ++jb) {
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int unit = unit_of(jb, r, h);
-      part = fmaf(sw4[unit], silu(acc[jb][r] + sb[2][unit]), part);
-    }
-  }
-  const float y = output(W, part, live && inside, raw);
-  if (h == 0 && live) {
-    io.y[s] = y;
-    if (io.in_range) io.in_range[s] = inside ? 1 : 0;
-  }
-}
-
-// ------------------------------------------------ one tile per workgroup
-//
 // Eight waves share the 32 samples of a tile: wave ib computes output block
 // ib of every layer (32 units), and the activations pass through LDS as the
-// next layer's B operands.  The sums are those of mlp_forward in the same
-// order, so the results are the same bits.  A batch of 4096 is 128 tiles: with
-// a wave per tile and all eight blocks in it, 32 CUs worked through a chain
-// of 256 products and 768 activations per lane (forward 89 us, backward 159
-// us), and a single query took 40 us.
+// next layer's B operands.  A wave that owned a tile and all eight blocks read
+// every weight from L2 for 32 samples (8.5 TB at 1e6 queries, 0.59 ms), and
+// put a batch of 4096 on 32 CUs, each in a chain of 256 products and 768
+// activations per lane (forward 89 us, backward 159 us; a single query 38 us).
 
 constexpr int kTileBlock = 512;
-// Inference takes this path up to two workgroups of 64 KiB LDS per CU.
-constexpr int64_t kForwardTiles = 512;
 constexpr int kOps = 16 * 64;  // B operands of a layer (one term)
+constexpr int64_t kCus = 256;  // workgroups that hold the weights: one per CU
 
 // The 16 activations of this wave's block as B operands of K-steps 2 ib, 2 ib
 // + 1, in TERMS BF16 parts: ops[term][t][lane].
@@ -308,16 +204,104 @@ __device__ __forceinline__ void load_units(const float* __restrict__ p, int ib, 
   }
 }
 
-// Forward of the tile: z1, z2, z3 of this wave's block, and in wave 0 the
-// head's sum over the units (`part`, of this lane's half).  lds: 64 KiB, its
-// first half free on return to all waves after their next barrier.
+// This wave's part of the head, sum of w4 h3 over its 32 units, for the
+// samples lane % 32 (in both lane halves).
+__device__ __forceinline__ float head_part(const float (&w4)[16], const float (&h3)[16]) {
+  float part = 0.0f;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) part = fmaf(w4[r], h3[r], part);
+  return part + __shfl_xor(part, 32);
+}
+
+// Inference.  A workgroup keeps the weight fragments of layers 2 and 3 in
+// registers (128 of them) and goes through its share of the batch, S tiles at a
+// time: S = 2 has the matrix cores work on one tile while the other's
+// activations are computed (the exponentials and reciprocals of SiLU, which
+// bound the kernel), two barriers a turn.  The outputs of a turn are finished
+// by one wave, another each time, after the next turn's first barrier.
+template <int TERMS, int S>
+__global__ __launch_bounds__(kTileBlock) void mlp_forward(Weights W, FwdIO io, int64_t groups) {
+  extern __shared__ bf16x8 lds[];  // [2][S][TERMS][kOps]
+  __shared__ float head[S][kTileBlock / 64][kWaveRows];
+  constexpr int kBuf = TERMS * kOps;
+  const int lane = threadIdx.x & 63, h = lane >> 5;
+  const int ib = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  bf16x8* const opsA = lds;
+  bf16x8* const opsB = lds + S * kBuf;
+  const bf16x8 f1 = reinterpret_cast<const bf16x8*>(W.w1)[ib * 64 + lane];
+  bf16x8 f2[16], f3[16];
+  load_frags(W.w2f, ib, lane, f2);
+  load_frags(W.w3f, ib, lane, f3);
+  float b1[16], b2[16], b3[16], w4[16];
+  load_units(W.master + kOffB1, ib, h, b1);
+  load_units(W.master + kOffB2, ib, h, b2);
+  load_units(W.master + kOffB3, ib, h, b3);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) w4[r] = bf16_float(W.w4[unit_of(ib, r, h)]);
+  // samples 32 S g .. of group g: lanes 0 .. 32 S - 1 of the wave whose turn it is
+  auto finish = [&](int64_t g) {
+    if (lane >= kWaveRows * S) return;
+    const int64_t s = g * (kWaveRows * S) + lane;
+    if (s >= io.B) return;
+    float u[kIn], raw[4];
+    const bool inside = normalise(W, io.x, s, true, u, raw);
+    float part = 0.0f;
+#pragma unroll
+    for (int w = 0; w < kTileBlock / 64; ++w) part += head[lane >> 5][w][lane & 31];
+    io.y[s] = output(W, part, inside, raw);
+    if (io.in_range) io.in_range[s] = inside ? 1 : 0;
+  };
+  int turn = 0;
+  int64_t g = blockIdx.x;
+  for (; g < groups; g += gridDim.x, ++turn) {
+#pragma unroll
+    for (int q = 0; q < S; ++q) {
+      const int64_t s = (g * S + q) * kWaveRows + (lane & 31);
+      float u[kIn], raw[4], v[16];
+      normalise(W, io.x, s, s < io.B, u, raw);
+      f32x16 acc;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[r] = b1[r];
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f1, input_operand(u, h), acc, 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) v[r] = silu(acc[r]);
+      share_operand<TERMS>(v, opsA + q * kBuf, ib, lane);
+    }
+    __syncthreads();
+    if (turn > 0 && ib == (turn & 7)) finish(g - gridDim.x);
+#pragma unroll
+    for (int q = 0; q < S; ++q) {
+      const f32x16 acc = tile_layer<TERMS>(f2, opsA + q * kBuf, lane);
+      float v[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) v[r] = silu(acc[r] + b2[r]);
+      share_operand<TERMS>(v, opsB + q * kBuf, ib, lane);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < S; ++q) {
+      const f32x16 acc = tile_layer<TERMS>(f3, opsB + q * kBuf, lane);
+      float v[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) v[r] = silu(acc[r] + b3[r]);
+      const float part = head_part(w4, v);
+      if (h == 0) head[q][ib][lane] = part;
+    }
+  }
+  __syncthreads();
+  if (turn > 0 && ib == (turn & 7)) finish(g - gridDim.x);
+}
+
+// Forward of a training tile: z1, z2, z3 of this wave's block, h1 and h2 to
+// memory, and the tile's head sum (after a barrier).  lds: 64 KiB.
 struct TileForward {
   float z1[16], z2[16], z3[16];
-  float part;
+  float head;
 };
-template <int TERMS, bool TRAIN>
+template <int TERMS>
 __device__ __forceinline__ void tile_forward(const Weights& W, const Train& T, const float (&u)[kIn],
-                                             int64_t tile, bf16x8* lds, int ib, int lane,
+                                             const float (&w4)[16], int64_t tile, bf16x8* lds,
+                                             float (*head)[kWaveRows], int ib, int lane,
                                              TileForward& o) {
   const int h = lane >> 5;
   bf16x8* const opsA = lds;
@@ -337,7 +321,7 @@ __device__ __forceinline__ void tile_forward(const Weights& W, const Train& T, c
   for (int r = 0; r < 16; ++r) {
     o.z1[r] = acc[r];
     v[r] = silu(acc[r]);
-    if (TRAIN) T.h1[at + 64 * r] = bf16_bits(v[r]);
+    T.h1[at + 64 * r] = bf16_bits(v[r]);
   }
   share_operand<TERMS>(v, opsA, ib, lane);
   load_units(W.master + kOffB2, ib, h, b);
@@ -347,47 +331,23 @@ __device__ __forceinline__ void tile_forward(const Weights& W, const Train& T, c
   for (int r = 0; r < 16; ++r) {
     o.z2[r] = acc[r] + b[r];
     v[r] = silu(o.z2[r]);
-    if (TRAIN) T.h2[at + 64 * r] = bf16_bits(v[r]);
+    T.h2[at + 64 * r] = bf16_bits(v[r]);
   }
   share_operand<TERMS>(v, opsB, ib, lane);
   load_units(W.master + kOffB3, ib, h, b);
   __syncthreads();
   acc = tile_layer<TERMS>(f3, opsB, lane);
-  // the head's terms through LDS: wave 0 sums them in the order of the units
-  float* head = reinterpret_cast<float*>(opsA);
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     o.z3[r] = acc[r] + b[r];
-    head[(16 * ib + r) * 64 + lane] = silu(o.z3[r]);
+    v[r] = silu(o.z3[r]);
   }
+  const float part = head_part(w4, v);
+  if (h == 0) head[ib][lane] = part;
   __syncthreads();
-  o.part = 0.0f;
-  if (ib == 0) {
+  o.head = 0.0f;
 #pragma unroll
-    for (int jb = 0; jb < 8; ++jb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        o.part = fmaf(bf16_float(W.w4[unit_of(jb, r, h)]), head[(16 * jb + r) * 64 + lane], o.part);
-  }
-}
-
-template <int TERMS>
-__global__ __launch_bounds__(kTileBlock) void mlp_forward_tile(Weights W, FwdIO io) {
-  extern __shared__ bf16x8 lds[];
-  const int lane = threadIdx.x & 63, h = lane >> 5;
-  const int ib = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int64_t s = (int64_t)blockIdx.x * kWaveRows + (lane & 31);
-  const bool live = s < io.B;
-  float u[kIn], raw[4];
-  const bool inside = normalise(W, io.x, s, live, u, raw);
-  TileForward o;
-  tile_forward<TERMS, false>(W, Train{}, u, blockIdx.x, lds, ib, lane, o);
-  if (ib != 0) return;
-  const float y = output(W, o.part, live && inside, raw);
-  if (h == 0 && live) {
-    io.y[s] = y;
-    if (io.in_range) io.in_range[s] = inside ? 1 : 0;
-  }
+  for (int w = 0; w < kTileBlock / 64; ++w) o.head += head[w][lane & 31];
 }
 
 // Sums over the tile's 32 samples of v[r] (and of v[r] u[c]) for every unit
@@ -424,7 +384,7 @@ __device__ __forceinline__ void unit_sums(const float (&v)[16], float* tr,
 template <int TERMS>
 __global__ __launch_bounds__(kTileBlock) void mlp_grad_tile(Weights W, Train T) {
   extern __shared__ bf16x8 lds[];  // two layers' operands, then the waves' transposes
-  __shared__ float us[kWaveRows][8], dys[kWaveRows];
+  __shared__ float us[kWaveRows][8], dys[kWaveRows], head[kTileBlock / 64][kWaveRows];
   const int lane = threadIdx.x & 63, h = lane >> 5;
   const int ib = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   float* tr = reinterpret_cast<float*>(lds + 4 * kOps) + 1024 * ib;
@@ -438,12 +398,15 @@ __global__ __launch_bounds__(kTileBlock) void mlp_grad_tile(Weights W, Train T) 
 #pragma unroll
     for (int c = 0; c < kIn; ++c) us[lane][c] = u[c];
   }
+  float w4[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) w4[r] = bf16_float(W.w4[unit_of(ib, r, h)]);
   TileForward o;
-  tile_forward<TERMS, true>(W, T, u, tile, lds, ib, lane, o);
+  tile_forward<TERMS>(W, T, u, w4, tile, lds, head, ib, lane, o);
   bf16x8 f[16];
   load_frags(W.w3t, ib, lane, f);
   if (ib == 0) {
-    const float y = output(W, o.part, live && inside, raw);
+    const float y = output(W, o.head, live && inside, raw);
     float lc = 0.0f, g = 0.0f;
     if (h == 0 && live) {
       const float wv = T.w ? T.w[row] : 1.0f;
@@ -462,9 +425,6 @@ __global__ __launch_bounds__(kTileBlock) void mlp_grad_tile(Weights W, Train T) 
       T.tsum[2 * tile + 1] = lc;
     }
   }
-  float w4[16];
-#pragma unroll
-  for (int r = 0; r < 16; ++r) w4[r] = bf16_float(W.w4[unit_of(ib, r, h)]);
   __syncthreads();
   const float dy = dys[lane & 31];
   const float gy = W.out_scale * dy;
@@ -664,24 +624,21 @@ static hipError_t allow_lds(F* kernel, size_t bytes) {
 
 hipError_t launch_forward(const Weights& W, int terms, const float* x, int64_t B, float* y,
                           uint8_t* in_range, hipStream_t s) {
-  FwdIO io{x, B, y, in_range};
+  const FwdIO io{x, B, y, in_range};
   const int64_t tiles = (B + kWaveRows - 1) / kWaveRows;
-  if (tiles <= kForwardTiles) {
-    const size_t lds = sizeof(bf16x8) * 4 * kOps;
-    if (terms == 2)
-      hipLaunchKernelGGL(mlp_forward_tile<2>, dim3((unsigned)tiles), dim3(kTileBlock), lds, s, W,
-                         io);
-    else
-      hipLaunchKernelGGL(mlp_forward_tile<1>, dim3((unsigned)tiles), dim3(kTileBlock), lds, s, W,
-                         io);
+  // one tile per workgroup while that leaves a CU for each
+  const int S = tiles <= kCus ? 1 : 2;
+  const int64_t groups = (tiles + S - 1) / S;
+  const dim3 grid((unsigned)(groups < kCus ? groups : kCus));
+  const size_t lds = sizeof(bf16x8) * 2 * (size_t)S * (size_t)terms * kOps;
+  auto go = [&](auto* kernel) {
+    const hipError_t e = allow_lds(kernel, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, grid, dim3(kTileBlock), lds, s, W, io, groups);
     return hipGetLastError();
-  }
-  const dim3 grid((unsigned)((B + kBlockRows - 1) / kBlockRows));
-  if (terms == 2)
-    hipLaunchKernelGGL(mlp_forward<2>, grid, dim3(kBlock), 0, s, W, io);
-  else
-    hipLaunchKernelGGL(mlp_forward<1>, grid, dim3(kBlock), 0, s, W, io);
-  return hipGetLastError();
+  };
+  if (terms == 2) return S == 2 ? go(mlp_forward<2, 2>) : go(mlp_forward<2, 1>);
+  return S == 2 ? go(mlp_forward<1, 2>) : go(mlp_forward<1, 1>);
 }
 
 hipError_t launch_train_grad(const Weights& W, int terms, const Train& T, float* grad,
