@@ -213,14 +213,69 @@ __device__ __forceinline__ float head_part(const float (&w4)[16], const float (&
   return part + __shfl_xor(part, 32);
 }
 
-// Inference.  A workgroup keeps the weight fragments of layers 2 and 3 in
-// registers (128 of them) and goes through its share of the batch, S tiles at a
-// time: S = 2 has the matrix cores work on one tile while the other's
-// activations are computed (the exponentials and reciprocals of SiLU, which
-// bound the kernel), two barriers a turn.  The outputs of a turn are finished
+// Inference, one tile per workgroup (batches of up to a tile per CU).
+template <int TERMS>
+__global__ __launch_bounds__(kTileBlock) void mlp_forward(Weights W, FwdIO io) {
+  extern __shared__ bf16x8 lds[];  // [2][TERMS][kOps]
+  __shared__ float head[kTileBlock / 64][kWaveRows];
+  const int lane = threadIdx.x & 63, h = lane >> 5;
+  const int ib = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  bf16x8* const opsA = lds;
+  bf16x8* const opsB = lds + TERMS * kOps;
+  const int64_t s = (int64_t)blockIdx.x * kWaveRows + (lane & 31);
+  const bool live = s < io.B;
+  float u[kIn], raw[4], b[16], w4[16], v[16];
+  bf16x8 f2[16], f3[16];
+  const bool inside = normalise(W, io.x, s, live, u, raw);
+  load_frags(W.w2f, ib, lane, f2);
+  load_units(W.master + kOffB1, ib, h, b);
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = b[r];
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+      reinterpret_cast<const bf16x8*>(W.w1)[ib * 64 + lane], input_operand(u, h), acc, 0, 0, 0);
+  load_frags(W.w3f, ib, lane, f3);
+  load_units(W.master + kOffB2, ib, h, b);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) v[r] = silu(acc[r]);
+  share_operand<TERMS>(v, opsA, ib, lane);
+  __syncthreads();
+  acc = tile_layer<TERMS>(f2, opsA, lane);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) v[r] = silu(acc[r] + b[r]);
+  share_operand<TERMS>(v, opsB, ib, lane);
+  load_units(W.master + kOffB3, ib, h, b);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) w4[r] = bf16_float(W.w4[unit_of(ib, r, h)]);
+  __syncthreads();
+  acc = tile_layer<TERMS>(f3, opsB, lane);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) v[r] = silu(acc[r] + b[r]);
+  const float part = head_part(w4, v);
+  if (h == 0) head[ib][lane] = part;
+  __syncthreads();
+  if (ib != 0 || h != 0 || !live) return;
+  float sum = 0.0f;
+#pragma unroll
+  for (int w = 0; w < kTileBlock / 64; ++w) sum += head[w][lane];
+  io.y[s] = output(W, sum, inside, raw);
+  if (io.in_range) io.in_range[s] = inside ? 1 : 0;
+}
+
+// Inference, large batches.  A workgroup keeps the weight fragments of layers
+// 2 and 3 in registers (128 of them) and goes through its share of the batch
+// two tiles at a time, two barriers a turn.  The outputs of a turn are finished
 // by one wave, another each time, after the next turn's first barrier.
-template <int TERMS, int S>
-__global__ __launch_bounds__(kTileBlock) void mlp_forward(Weights W, FwdIO io, int64_t groups) {
+//
+// 1e6 queries: 345 us with one activation term, 13.6 k clocks a turn of 64
+// samples; the exponentials and reciprocals of SiLU (6.1 k), the matrix cores
+// (4.2 k) and the LDS reads of the operands (4.1 k) follow one another.  One
+// tile's products interleaved with the other's SiLU by the scheduler's
+// groups, at a barrier per product: 360 us.
+constexpr int S = 2;
+template <int TERMS>
+__global__ __launch_bounds__(kTileBlock) void mlp_forward_pairs(Weights W, FwdIO io,
+                                                                int64_t groups) {
   extern __shared__ bf16x8 lds[];  // [2][S][TERMS][kOps]
   __shared__ float head[S][kTileBlock / 64][kWaveRows];
   constexpr int kBuf = TERMS * kOps;
@@ -626,19 +681,23 @@ hipError_t launch_forward(const Weights& W, int terms, const float* x, int64_t B
                           uint8_t* in_range, hipStream_t s) {
   const FwdIO io{x, B, y, in_range};
   const int64_t tiles = (B + kWaveRows - 1) / kWaveRows;
-  // one tile per workgroup while that leaves a CU for each
-  const int S = tiles <= kCus ? 1 : 2;
-  const int64_t groups = (tiles + S - 1) / S;
-  const dim3 grid((unsigned)(groups < kCus ? groups : kCus));
-  const size_t lds = sizeof(bf16x8) * 2 * (size_t)S * (size_t)terms * kOps;
+  const size_t lds = sizeof(bf16x8) * 2 * (size_t)terms * kOps;
+  if (tiles <= kCus) {
+    if (terms == 2)
+      hipLaunchKernelGGL(mlp_forward<2>, dim3((unsigned)tiles), dim3(kTileBlock), lds, s, W, io);
+    else
+      hipLaunchKernelGGL(mlp_forward<1>, dim3((unsigned)tiles), dim3(kTileBlock), lds, s, W, io);
+    return hipGetLastError();
+  }
+  const int64_t pairs = (tiles + 1) / 2;
+  const dim3 grid((unsigned)(pairs < kCus ? pairs : kCus));
   auto go = [&](auto* kernel) {
-    const hipError_t e = allow_lds(kernel, lds);
+    const hipError_t e = allow_lds(kernel, 2 * lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kernel, grid, dim3(kTileBlock), lds, s, W, io, groups);
+    hipLaunchKernelGGL(kernel, grid, dim3(kTileBlock), 2 * lds, s, W, io, pairs);
     return hipGetLastError();
   };
-  if (terms == 2) return S == 2 ? go(mlp_forward<2, 2>) : go(mlp_forward<2, 1>);
-  return S == 2 ? go(mlp_forward<1, 2>) : go(mlp_forward<1, 1>);
+  return terms == 2 ? go(mlp_forward_pairs<2>) : go(mlp_forward_pairs<1>);
 }
 
 hipError_t launch_train_grad(const Weights& W, int terms, const Train& T, float* grad,
