@@ -1467,7 +1467,7 @@ qtree_status qtree_bdp_many(const qtree_plan* plan, const void* pi, size_t pi_by
   const PiLayout l = pi_layout(plan);
   if (pi_bytes < l.total)
     return fail(QTREE_ENOMEM, "pi needs " + std::to_string(l.total) + " bytes");
-  if (qtree::bdp_many_maxr(plan->maxN) < 0)
+  if (!qtree::bdp_many_fits(plan->maxN))
     return fail(QTREE_EUNSUPPORTED, "qtree_bdp_many takes layers of at most 256 points");
   const char* base = static_cast<const char*>(pi);
   qtree::ManyArgs a{};
@@ -1484,6 +1484,7 @@ qtree_status qtree_bdp_many(const qtree_plan* plan, const void* pi, size_t pi_by
   a.d = plan->d;
   a.max_n = plan->maxN;
   a.np_max = (plan->maxN + 3) & ~3;
+  a.cols = qtree::bdp_many_cols((n_q + 63) / 64);
   hipError_t e = qtree::launch_bdp_many(a, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? QTREE_OK : hip_fail(e, "bdp_many launch");
 }
@@ -1519,13 +1520,14 @@ qtree_status qtree_bdp_many_trees(int32_t n_trees, const qtree_plan* const* plan
     return fail(QTREE_EINVAL, "specs and V0 must be non-NULL");
   if (reinterpret_cast<uintptr_t>(specs) % 8 || reinterpret_cast<uintptr_t>(V0) % 8)
     return fail(QTREE_EINVAL, "specs and V0 must be 8-byte aligned");
-  if (qtree::bdp_many_maxr(max_n) < 0)
+  if (!qtree::bdp_many_fits(max_n))
     return fail(QTREE_EUNSUPPORTED, "qtree_bdp_many takes layers of at most 256 points");
   if (blocks >= (1ll << 31)) return fail(QTREE_EOVERFLOW, "too many contracts");
   if (!workspace || workspace_bytes < sizeof(qtree::ManyTree) * (size_t)n_trees)
     return fail(QTREE_ENOMEM, "workspace must hold " + std::to_string(n_trees) + " tree records");
   if (reinterpret_cast<uintptr_t>(workspace) % 16) return fail(QTREE_EINVAL, "workspace must be 16-byte aligned");
   if (blocks == 0) return QTREE_OK;
+  const int64_t cols = qtree::bdp_many_cols(blocks);
   // trees with the most layers (the longest workgroups) first
   std::stable_sort(order.begin(), order.end(),
                    [&](int x, int y) { return plans[x]->n > plans[y]->n; });
@@ -1547,7 +1549,7 @@ qtree_status qtree_bdp_many_trees(int32_t n_trees, const qtree_plan* const* plan
     T.nq = q_begin[t + 1] - q_begin[t];
     T.blk0 = blk;
     T.n = p->n;
-    blk += (int32_t)((T.nq + 63) / 64);
+    blk += (int32_t)((T.nq + cols - 1) / cols);
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e = hipMemcpyAsync(workspace, tab.data(), sizeof(qtree::ManyTree) * tab.size(),
@@ -1561,7 +1563,8 @@ qtree_status qtree_bdp_many_trees(int32_t n_trees, const qtree_plan* const* plan
   a.np_max = (max_n + 3) & ~3;
   a.trees = static_cast<const qtree::ManyTree*>(workspace);
   a.n_trees = n_trees;
-  a.blocks = (int32_t)blocks;
+  a.blocks = blk;
+  a.cols = (int32_t)cols;
   e = qtree::launch_bdp_many(a, s);
   return e == hipSuccess ? QTREE_OK : hip_fail(e, "bdp_many launch");
 }

@@ -470,12 +470,11 @@ hipError_t launch_payoff(const PayoffArgs& a, hipStream_t s) {
 // (FP64, rows padded with zeros to a multiple of 4 columns) and records the
 // range of the nonzero columns of every row; bdp_many_kernel then runs the
 // whole backward recursion of 64 contracts per workgroup with their V_{k+1}
-// resident in LDS ([j][64]: lane = contract, so every LDS read is one
-// conflict-free 512-byte row), the obstacle phi_k computed where it is
-// used, and pi read with scalar loads (a wave's rows are uniform).  One
-// launch may cover many trees (a table of trees, one per number of layers
-// for instance): workgroup b then prices 64 contracts of the tree whose
-// range of workgroups holds b, the trees with the most layers first.
+// resident in LDS ([point][contract]), the products on the FP64 matrix cores
+// and the obstacle phi_k computed where it is used.  One launch may cover
+// many trees (a table of trees, one per number of layers for instance):
+// workgroup b then prices 64 contracts of the tree whose range of workgroups
+// holds b, the trees with the most layers first.
 
 __global__ __launch_bounds__(256) void pi_kernel(PiArgs a) {
   const int lane = threadIdx.x & 63;
@@ -615,22 +614,32 @@ typedef const int64_t __attribute__((address_space(1)))* GlobalI64;
 typedef const uint64_t __attribute__((address_space(1)))* GlobalU64;
 
 
-// Workgroup b prices contracts 64 b .. 64 b + 63 (lane = contract); wave w
-// of W owns the rows i = w + W t of every layer, R of them at a time, and
-// keeps their new values in registers until every wave has finished reading
-// V_{k+1}.  MAXR >= ceil(N_max / W).  The weights of a row group reach the
-// FMAs as scalar operands: the loads of the next column group are issued
-// once the current group's V_{k+1} values are in (scalar and LDS loads share
-// one counter), so they travel while the current group's FMAs run.
-template <int D, int W, int MAXR, int R>
-__global__ __launch_bounds__(64 * W) void bdp_many_kernel(ManyArgs a) {
-  extern __shared__ double Vs[];  // [Np_max][64]
-  const int lane = threadIdx.x & 63;
+// Workgroup b prices 16 CTS contracts.  Wave w of 8 has contracts 16 (w % CTS)
+// .. + 15 (one per lane % 16, for the whole recursion) and the tiles of 16
+// rows w / CTS, w / CTS + 8 / CTS, ... of every layer: at most TILES of them,
+// whose new values stay in registers until every wave has read V_{k+1}.
+// A tile's product covers the columns of its rows' bands, 16 at a time, with
+// the K order of bdp_tile.hpp (lane group g takes columns 4 g .. + 3 of the
+// 16, 32 bytes of its row).
+//
+// The products (64 clocks of a matrix core for 1024 multiply-adds, the rate
+// of the vector units) run beside the obstacles' exponentials of other waves.
+// With lane = contract, vector multiply-adds and the weights as scalar
+// operands, every 16 of them waited for four scalar loads, and the four rows
+// of a step were 8 apart, their bands' union half as wide again.
+constexpr int kManyWaves = 8;
+
+template <int D, int CTS, int TILES>
+__global__ __launch_bounds__(64 * kManyWaves) void bdp_many_kernel(ManyArgs a) {
+  constexpr int kCols = 16 * CTS, kRowTiles = kManyWaves / CTS;
+  extern __shared__ double Vs[];  // [np_max][kCols]
+  const int lane = threadIdx.x & 63, g = lane >> 4, m = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int ct = wave % CTS, rt0 = wave / CTS;
   // the workgroup's tree: the one tree, or the last table entry with
   // blk0 <= blockIdx.x
   ManyTree T;
-  int64_t qb = (int64_t)blockIdx.x * 64, qe = a.nq;
+  int64_t qb = (int64_t)blockIdx.x * kCols, qe = a.nq;
   if (a.trees) {
     // the table is read through a global pointer, so the record's values are
     // known to be uniform (a generic load could be a per-lane one)
@@ -646,7 +655,7 @@ __global__ __launch_bounds__(64 * W) void bdp_many_kernel(ManyArgs a) {
 #pragma unroll
     for (int w = 0; w < kWords; ++w) raw[w] = tab[lo * kWords + w];
     __builtin_memcpy(&T, raw, sizeof(ManyTree));
-    qb = T.q0 + ((int64_t)blockIdx.x - T.blk0) * 64;
+    qb = T.q0 + ((int64_t)blockIdx.x - T.blk0) * kCols;
     qe = T.q0 + T.nq;
   } else {
     T.layers = a.layers;
@@ -657,10 +666,11 @@ __global__ __launch_bounds__(64 * W) void bdp_many_kernel(ManyArgs a) {
     T.band = a.band;
     T.n = a.n;
   }
-  const int64_t q = qb + lane;
+  const int col = 16 * ct + m;
+  const int64_t q = qb + col;
   const Contract C = a.specs[q < qe ? q : qe - 1];
   // zero the padding rows once (they meet only zero weights, but must be finite)
-  for (int j = wave; j < a.np_max; j += W) Vs[j * 64 + lane] = 0.0;
+  for (int j = threadIdx.x; j < kCols * a.np_max; j += 64 * kManyWaves) Vs[j] = 0.0;
   __syncthreads();
   // per-layer fields through global pointers (uniform values)
   const GlobalI32 lay = (GlobalI32)T.layers;
@@ -671,10 +681,10 @@ __global__ __launch_bounds__(64 * W) void bdp_many_kernel(ManyArgs a) {
     const int Nn = lay[T.n * kLayWords + kN];
     const int64_t pt = lay[T.n * kLayWords + kPt];
     const LayerObstacle ob = layer_obstacle<D>(C, T.n, T.n);
-    for (int i = wave; i < Nn; i += W) {
+    for (int i = 4 * rt0 + g; i < Nn; i += 4 * kRowTiles) {
       float xs[3];
       grid_point<D>(T, pt, i, xs);
-      Vs[i * 64 + lane] = obstacle<D>(C, ob, xs);
+      Vs[i * kCols + col] = obstacle<D>(C, ob, xs);
     }
   }
   __syncthreads();
@@ -684,116 +694,87 @@ __global__ __launch_bounds__(64 * W) void bdp_many_kernel(ManyArgs a) {
     const GlobalF64 P = (GlobalF64)T.pi + ((GlobalI64)T.pi_off)[k];
     const GlobalI32 B = (GlobalI32)(T.band + pt);  // (lo, hi) pairs
     const LayerObstacle ob = layer_obstacle<D>(C, T.n, k);
-    double res[MAXR];
+    f64x4 res[TILES];
 #pragma unroll
-    for (int t0 = 0; t0 < MAXR; t0 += R) {
-      const int ib = wave + W * t0;
-      if (ib >= Nk) break;
-      int jlo = 1 << 30, jhi = 0;
+    for (int t = 0; t < TILES; ++t) {
+      const int i0 = 16 * (rt0 + kRowTiles * t);
+      if (i0 >= Nk) break;
+      // the tile's band: whole groups of 4 columns, empty rows (lo = hi) apart
+      const int i = min(i0 + m, Nk - 1);  // rows past the end repeat the last one
+      int lo = B[2 * i], hi = B[2 * i + 1];
+      lo = hi > lo ? lo : 1 << 30;
 #pragma unroll
-      for (int t = 0; t < R; ++t) {
-        const int i = ib + W * t;
-        if (i < Nk) {
-          const int bx = B[2 * i], by = B[2 * i + 1];
-          if (by > bx) {
-            jlo = bx < jlo ? bx : jlo;
-            jhi = by > jhi ? by : jhi;
-          }
-        }
+      for (int s = 8; s > 0; s >>= 1) {
+        lo = min(lo, __shfl_xor(lo, s, 64));
+        hi = max(hi, __shfl_xor(hi, s, 64));
       }
-      double acc[R];
+      lo = __builtin_amdgcn_readfirstlane(lo);
+      hi = __builtin_amdgcn_readfirstlane(hi);
+      const GlobalF64 row = P + (int64_t)i * N1p;
+      f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+      for (int j0 = lo; j0 < hi; j0 += 16) {
+        // a group past the row's end reads its last columns, times nothing
+        const int j = j0 + 4 * g, jc = min(j, N1p - 4);
+        double w[4];
 #pragma unroll
-      for (int t = 0; t < R; ++t) acc[t] = 0.0;
-      GlobalF64 prow[R];
+        for (int u = 0; u < 4; ++u) w[u] = row[jc + u];
 #pragma unroll
-      for (int t = 0; t < R; ++t) {
-        const int i = ib + W * t < Nk ? ib + W * t : ib;  // rows past the end repeat row ib
-        prow[t] = P + (int64_t)i * N1p;
-      }
-      if (jlo < jhi) {
-        double w[R][4];
-#pragma unroll
-        for (int t = 0; t < R; ++t)
-#pragma unroll
-          for (int u = 0; u < 4; ++u) w[t][u] = prow[t][jlo + u];
-        for (int j = jlo; j < jhi; j += 4) {
-          double v[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) v[u] = Vs[(j + u) * 64 + lane];
-          // this group's V and weights are in; only then the next group's
-          // weights are requested (the last group re-reads its own)
-          __builtin_amdgcn_sched_barrier(0);
-          __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-          __builtin_amdgcn_sched_barrier(0);
-          const int jn = j + 4 < jhi ? j + 4 : j;
-          double wn[R][4];
-#pragma unroll
-          for (int t = 0; t < R; ++t)
-#pragma unroll
-            for (int u = 0; u < 4; ++u) wn[t][u] = prow[t][jn + u];
-#pragma unroll
-          for (int t = 0; t < R; ++t)
-#pragma unroll
-            for (int u = 0; u < 4; ++u) acc[t] = fma(w[t][u], v[u], acc[t]);
-#pragma unroll
-          for (int t = 0; t < R; ++t)
-#pragma unroll
-            for (int u = 0; u < 4; ++u) w[t][u] = wn[t][u];
-        }
+        for (int u = 0; u < 4; ++u)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(j < N1p ? w[u] : 0.0,
+                                                     Vs[(jc + u) * kCols + col], acc, 0, 0, 0);
       }
 #pragma unroll
-      for (int t = 0; t < R; ++t) {
-        const int i = ib + W * t;
-        if (i < Nk) {
-          float xs[3];
-          grid_point<D>(T, pt, i, xs);
-          const double f = obstacle<D>(C, ob, xs);
-          res[t0 + t] = f > acc[t] ? f : acc[t];
-        }
+      for (int r = 0; r < 4; ++r) {
+        const int ir = min(i0 + g + 4 * r, Nk - 1);
+        float xs[3];
+        grid_point<D>(T, pt, ir, xs);
+        const double f = obstacle<D>(C, ob, xs);
+        res[t][r] = f > acc[r] ? f : acc[r];
       }
     }
     __syncthreads();
 #pragma unroll
-    for (int t = 0; t < MAXR; ++t) {
-      const int i = wave + W * t;
-      if (i < Nk) Vs[i * 64 + lane] = res[t];
+    for (int t = 0; t < TILES; ++t) {
+      const int i0 = 16 * (rt0 + kRowTiles * t);
+      if (i0 >= Nk) break;
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (i0 + g + 4 * r < Nk) Vs[(i0 + g + 4 * r) * kCols + col] = res[t][r];
     }
     __syncthreads();
   }
-  if (wave == 0 && q < qe) a.V0[q] = Vs[lane];
+  if (threadIdx.x < kCols && qb + threadIdx.x < qe) a.V0[qb + threadIdx.x] = Vs[threadIdx.x];
 }
 
-constexpr int kManyWaves = 8;  // waves per workgroup sharing the LDS of 64 contracts
+bool bdp_many_fits(int max_n) { return max_n <= 256; }
 
-int bdp_many_maxr(int max_n) {
-  const int rows = (max_n + kManyWaves - 1) / kManyWaves;
-  return rows <= 8 ? 8 : rows <= 16 ? 16 : rows <= 32 ? 32 : -1;
-}
 
-size_t bdp_many_lds(int max_np) { return sizeof(double) * 64 * (size_t)max_np; }
+
+// A layer of a workgroup is a chain (products, obstacles, two barriers): 16
+// contracts and a tile of rows per wave make it short and the workgroups many,
+// 64 and four tiles load each weight once for four products.  Trees of 10 to
+// 100 layers of 100 points, 16 / 64 contracts a workgroup: 1000 contracts 324 /
+// 904 us, 15000 470 / 894, 30000 767 / 970, 100000 2338 / 2162 (the lane =
+// contract kernel: 6470 us).
+int bdp_many_cols(int64_t blocks64) { return blocks64 < 1024 ? 16 : 64; }
 
 template <int D>
 static hipError_t launch_bdp_many_d(const ManyArgs& a, hipStream_t s) {
-  const dim3 grid(a.trees ? (unsigned)a.blocks : (unsigned)((a.nq + 63) / 64));
-  const size_t lds = bdp_many_lds(a.np_max);
-  hipError_t e = hipSuccess;
-  switch (bdp_many_maxr(a.max_n)) {
-#define QTREE_MANY(MR)                                                                        \
-  case MR:                                                                                    \
-    if (lds > 65536)                                                                          \
-      e = hipFuncSetAttribute(                                                                \
-          reinterpret_cast<const void*>(bdp_many_kernel<D, kManyWaves, MR, 4>),               \
-          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                              \
-    if (e != hipSuccess) return e;                                                            \
-    hipLaunchKernelGGL((bdp_many_kernel<D, kManyWaves, MR, 4>), grid, dim3(64 * kManyWaves),  \
-                       lds, s, a);                                                            \
-    break;
-    QTREE_MANY(8) QTREE_MANY(16) QTREE_MANY(32)
-#undef QTREE_MANY
-    default:
-      return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
+  const dim3 grid(a.trees ? (unsigned)a.blocks : (unsigned)((a.nq + a.cols - 1) / a.cols));
+  const size_t lds = sizeof(double) * (size_t)a.cols * (size_t)a.np_max;
+  auto go = [&](auto* kernel) {
+    hipError_t e = hipSuccess;
+    if (lds > 65536)
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, grid, dim3(64 * kManyWaves), lds, s, a);
+    return hipGetLastError();
+  };
+  if (!bdp_many_fits(a.max_n)) return hipErrorInvalidValue;
+  const bool small = a.max_n <= 128;
+  if (a.cols == 16) return small ? go(bdp_many_kernel<D, 1, 1>) : go(bdp_many_kernel<D, 1, 2>);
+  return small ? go(bdp_many_kernel<D, 4, 4>) : go(bdp_many_kernel<D, 4, 8>);
 }
 
 hipError_t launch_bdp_many(const ManyArgs& a, hipStream_t s) {

@@ -273,9 +273,9 @@ struct PiArgs {
 };
 hipError_t launch_pi(const PiArgs& a, hipStream_t s);
 
-// Backward recursion of many contracts on one tree (64 per workgroup).
+// Backward recursion of many contracts on one tree (`cols` per workgroup).
 // One tree of a many-tree launch: its tables and weights, and the contracts
-// q0 .. q0 + nq - 1 it prices (workgroups blk0 .. blk0 + ceil(nq / 64) - 1).
+// q0 .. q0 + nq - 1 it prices (workgroups blk0 .. blk0 + ceil(nq / cols) - 1).
 struct alignas(16) ManyTree {
   const LayerDev* layers;
   const float* pts1;
@@ -302,9 +302,11 @@ struct ManyArgs {
   // largest over the trees)
   const ManyTree* trees;
   int32_t n_trees, blocks;
+  int32_t cols;  // contracts per workgroup (bdp_many_cols)
 };
-int bdp_many_maxr(int max_n);  // -1: beyond the supported 256 points per layer
-size_t bdp_many_lds(int max_np);
+bool bdp_many_fits(int max_n);  // layers of up to 256 points
+// Contracts per workgroup when 64 of them would make `blocks64` workgroups.
+int bdp_many_cols(int64_t blocks64);
 hipError_t launch_bdp_many(const ManyArgs& a, hipStream_t s);
 
 // Stratified time-layer counts (d = 1): Ms samples per cell of layer k.

@@ -139,3 +139,24 @@ def test_bdp_many_trees_equals_one_tree_at_a_time():
     specs = torch.from_numpy(np.concatenate(recs).view(np.uint8).reshape(-1)).cuda()
     got = qt.bdp_many_trees(trees, specs, q_begin).cpu().numpy()
     assert np.array_equal(got[:q_begin[-1]].view(np.uint64), np.concatenate(want).view(np.uint64))
+
+
+@pytest.mark.parametrize("d,sizes", [(1, [1, 15, 16, 17, 33]), (1, [1, 3, 128, 129, 256]),
+                                     (2, [1, (3, 5), (8, 16), (5, 7)])], ids=str)
+def test_workgroups_of_16_and_64_contracts_agree(d, sizes):
+    """Both workgroup forms (16 contracts, and 64 from 1024 workgroups of 64
+    on) sum a tile of rows in the same order: the first contracts of a large
+    launch equal a launch of them alone bit for bit, and the oracle within
+    1e-9 (rows below, at and past a tile, more tiles than waves)."""
+    _case(f"bdp_many forms {d} {sizes}")
+    spec = synth.bm_model(d, len(sizes) - 1, T=1.0)
+    grid, N = synth.layer_grids(spec, sizes)
+    plan = qt.Plan(spec, grid, N)
+    counts = plan.transitions(30_000, 3)
+    _check(plan, spec, grid, N, counts, 37, 8)
+    pi = plan.pi(counts)
+    kinds, S0, K, r, T, sigma, mix = _contracts(np.random.default_rng(2), 1024 * 64 + 5, d)
+    sp = qt.payoff_specs(d, kinds, S0, K, r, T, sigma, mix)
+    many = plan.bdp_many(pi, sp).cpu().numpy()
+    few = plan.bdp_many(pi, sp[-1005:]).cpu().numpy()
+    assert np.array_equal(many[-1005:].view(np.uint64), few.view(np.uint64))
