@@ -588,10 +588,21 @@ qtree_status qtree_batch_plan(const qtree_contract* contracts, int32_t n, qtree_
       const qtree::BdpJob& J = b->jobs[jb];
       if (J.n <= step) continue;
       const int k = J.n - 1 - step;
-      const int rows = contracts[job_contract[jb]].plan->N[k];
-      for (int r0 = 0; r0 < rows; r0 += qtree::kBdpTaskRows)
-        b->bdp_tasks.push_back(qtree::BdpTask{(int32_t)jb, k, r0,
-                                              std::min(qtree::kBdpTaskRows, rows - r0)});
+      const qtree_plan* p = contracts[job_contract[jb]].plan;
+      const int rows = p->N[k];
+      for (int r0 = 0; r0 < rows; r0 += qtree::kBdpTaskRows) {
+        const int64_t at = (int64_t)J.q0 * J.P + p->pt_off[k] + r0;
+        qtree::BdpTask t{};
+        t.counts = J.counts + p->cnt_off[k] + (int64_t)r0 * p->N[k + 1];
+        t.next = J.V + (int64_t)J.q0 * J.P + p->pt_off[k + 1];
+        t.phi = J.phi + at;
+        t.V = J.V + at;
+        t.P = J.P;
+        t.n1 = p->N[k + 1];
+        t.nrows = std::min(qtree::kBdpTaskRows, rows - r0);
+        t.nq = J.nq;
+        b->bdp_tasks.push_back(t);
+      }
     }
     b->step_off.push_back((int)b->bdp_tasks.size());
   }

@@ -335,57 +335,47 @@ __global__ void bdp_batch_copy_kernel(const BdpJob* jobs) {
 }
 
 template <bool DENSE>
-__global__ __launch_bounds__(64 * kStepWaves) void bdp_step_kernel(const BdpJob* jobs,
-                                                                   const BdpTask* tasks) {
-  const BdpTask T = tasks[blockIdx.x];
+__global__ __launch_bounds__(64 * kStepWaves) void bdp_step_kernel(const BdpTask* tasks) {
+  const BdpTask& T = tasks[blockIdx.x];
   const int lane = threadIdx.x & 63;
-  const BdpJob& J = jobs[T.job];
-  const LayerDev* layers = as_global(J.layers);
-  const LayerDev& L = layers[T.k];
-  const LayerDev& L1 = layers[T.k + 1];
-  double* V = as_global(J.V);
+  const int n1 = T.n1, nrows = T.nrows, nq = T.nq;
+  const int64_t P = T.P;
   const int r = lane & 15;  // rows past the end repeat the last one
   TileRows R;
-  R.row = as_global(J.counts) + L.cnt_off + (int64_t)(T.row0 + (r < T.nrows ? r : T.nrows - 1)) * L.N1;
+  R.row = as_global(T.counts) + (int64_t)(r < nrows ? r : nrows - 1) * n1;
   R.lo = R.from = 0;
-  R.hi = R.to = L.N1;
-  const double* x = V + (int64_t)(J.q0 + (r < J.nq ? r : 0)) * J.P + L1.pt_off;
+  R.hi = R.to = n1;
+  const double* x = as_global(T.next) + (int64_t)(r < nq ? r : 0) * P;
   double s;
   int64_t p;
-  if (!tile_sums<kStepWaves, 4, DENSE>(R, x, L.N1, s, p)) return;
+  if (!tile_sums<kStepWaves, 4, DENSE>(R, x, n1, s, p)) return;
   const int row = (int)(threadIdx.x >> 4), col = (int)(threadIdx.x & 15);
-  if (row < T.nrows && col < J.nq) {
+  if (row < nrows && col < nq) {
     const double cont = p > 0 ? s / (double)p : 0.0;
-    const int64_t at = (int64_t)(J.q0 + col) * J.P + L.pt_off + T.row0 + row;
-    const double f = as_global(J.phi)[at];
-    V[at] = f > cont ? f : cont;
+    const int64_t at = (int64_t)col * P + row;
+    const double f = as_global(T.phi)[at];
+    as_global(T.V)[at] = f > cont ? f : cont;
   }
 }
 
-__global__ __launch_bounds__(64 * kFewWaves) void bdp_step_few_kernel(const BdpJob* jobs,
-                                                                      const BdpTask* tasks) {
+__global__ __launch_bounds__(64 * kFewWaves) void bdp_step_few_kernel(const BdpTask* tasks) {
   constexpr int kParts = kBdpTaskRows / kFewRows;
-  const BdpTask T = tasks[blockIdx.x / kParts];
+  const BdpTask& T = tasks[blockIdx.x / kParts];
   const int r0 = (int)(blockIdx.x % kParts) * kFewRows;
-  if (r0 >= T.nrows) return;
-  const BdpJob& J = jobs[T.job];
-  const LayerDev* layers = as_global(J.layers);
-  const LayerDev& L = layers[T.k];
-  const LayerDev& L1 = layers[T.k + 1];
-  double* V = as_global(J.V);
-  const int i0 = T.row0 + r0;
+  const int n1 = T.n1, nrows = T.nrows, nq = T.nq;
+  const int64_t P = T.P;
+  if (r0 >= nrows) return;
   // a one-payoff job repeats its payoff as the second one
   double s, p;
-  if (!few_sums<kFewPay>(as_global(J.counts) + L.cnt_off + (int64_t)i0 * L.N1,
-                         min(kFewRows, T.nrows - r0), V + (int64_t)J.q0 * J.P + L1.pt_off,
-                         J.nq > 1 ? J.P : 0, L.N1, s, p))
+  if (!few_sums<kFewPay>(as_global(T.counts) + (int64_t)r0 * n1, min(kFewRows, nrows - r0),
+                         as_global(T.next), nq > 1 ? P : 0, n1, s, p))
     return;
-  const int row = (int)threadIdx.x / kFewPay, q = (int)threadIdx.x % kFewPay;
-  if (r0 + row < T.nrows && q < J.nq) {
+  const int row = r0 + (int)threadIdx.x / kFewPay, q = (int)threadIdx.x % kFewPay;
+  if (row < nrows && q < nq) {
     const double cont = p > 0.0 ? s / p : 0.0;
-    const int64_t at = (int64_t)(J.q0 + q) * J.P + L.pt_off + i0 + row;
-    const double f = as_global(J.phi)[at];
-    V[at] = f > cont ? f : cont;
+    const int64_t at = (int64_t)q * P + row;
+    const double f = as_global(T.phi)[at];
+    as_global(T.V)[at] = f > cont ? f : cont;
   }
 }
 
@@ -402,13 +392,14 @@ hipError_t launch_bdp_steps(const BdpJob* jobs, int n_jobs, int max_last, int ma
     if (cnt <= 0) continue;
     if (few)
       hipLaunchKernelGGL(bdp_step_few_kernel, dim3((unsigned)(cnt * (kBdpTaskRows / kFewRows))),
-                         dim3(64 * kFewWaves), 0, s, jobs, tasks + step_off[j]);
+                         dim3(64 * kFewWaves), 0, s,
+                         tasks + step_off[j]);
     else if (min_n1 >= 4)
       hipLaunchKernelGGL(bdp_step_kernel<true>, dim3((unsigned)cnt), dim3(64 * kStepWaves), 0, s,
-                         jobs, tasks + step_off[j]);
+                         tasks + step_off[j]);
     else
       hipLaunchKernelGGL(bdp_step_kernel<false>, dim3((unsigned)cnt), dim3(64 * kStepWaves), 0, s,
-                         jobs, tasks + step_off[j]);
+                         tasks + step_off[j]);
   }
   return hipGetLastError();
 }

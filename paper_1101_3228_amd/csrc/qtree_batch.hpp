@@ -79,9 +79,16 @@ struct BdpJob {
   int32_t n, q0, nq, pad_;
 };
 
-// Rows [row0, row0 + nrows) of layer k of job `job` (nrows <= kBdpTaskRows).
-struct BdpTask {
-  int32_t job, k, row0, nrows;
+// nrows <= kBdpTaskRows rows of a layer of a job, with everything a step needs
+// of them in one record (a chain of task, job and layer records is a round
+// trip to memory each, in every one of the steps).
+struct alignas(16) BdpTask {
+  const int32_t* counts;  // first row, n1 entries each
+  const double* next;     // V_{k+1} of the job's first payoff; the others P apart
+  const double* phi;      // phi_k and V_k of the first row and payoff
+  double* V;
+  int64_t P;
+  int32_t n1, nrows, nq, pad_;
 };
 constexpr int kBdpTaskRows = 16;
 
