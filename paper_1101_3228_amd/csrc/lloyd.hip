@@ -6,23 +6,24 @@
 // samples of its Voronoi cell (the stationarity condition of eq. Qerr).
 //
 // One step on the device:
+//   tables (d = 2 on Philox samples): the bucket lists of the tree's 2-D cell
+//     search for the current grid over the box of the samples.
 //   accumulate: a persistent grid of workgroups; each stages the current grid
-//     (d >= 2: records (g, |g|^2 / 2); d = 1: midpoints padded with +inf) in
-//     LDS, draws samples (Philox counter (m, step, 0, 2), Box-Muller, X = L z
-//     as fused multiply-add chains from 0), assigns them with the tree's own
-//     cell search, and adds to LDS accumulators: the count, each coordinate
-//     as the integer rint(x 2^24) and the squared distance to the cell's
-//     point as rint(|x - g|^2 2^16) (FP64).  The workgroup stores its totals,
-//     zeros included, as row b of a partial table with plain stores.
-//   reduce: each workgroup sums 8 columns of the table over its rows (the
-//     step's cell sums, counts and distortion).  Integer sums make the result
-//     independent of the order of the samples and of the workgroups (the
-//     table replaces device atomics from every workgroup onto the same ~N d
-//     words, which serialized at the L2).
-//   update: one thread per cell: new point = (sum 2^-24) / count in FP64,
-//     rounded once to FP32 (an empty cell keeps its point), or the point
-//     moved a fraction gamma of the way there; the distortion of the step.
-//     The records or midpoints are then rebuilt from the new grid.
+//     (d >= 2: records (g, |g|^2 / 2), or pairs where there are tables; d = 1:
+//     midpoints padded with +inf) in LDS, draws samples (Philox counter
+//     (m, step, 0, 2), Box-Muller, X = L z as fused multiply-add chains from
+//     0), assigns them with the tree's own cell search, and adds to LDS
+//     accumulators: the count, each coordinate as the integer rint(x 2^24) and
+//     the squared distance to the cell's point as rint(|x - g|^2 2^16) (FP64).
+//     The workgroup stores its totals, zeros included, as row b of a partial
+//     table with plain stores.
+//   update: each workgroup sums the columns of 4 cells over the table's rows
+//     (integer sums make the result independent of the order of the samples
+//     and of the workgroups; the table replaces device atomics from every
+//     workgroup onto the same ~N d words, which serialized at the L2), and
+//     moves them: new point = (sum 2^-24) / count in FP64, rounded once to
+//     FP32 (an empty cell keeps its point), or the point moved a fraction
+//     gamma of the way there; one more workgroup forms the distortion.
 //
 // The samples may instead be windows of a caller's sample set (Lloyd's
 // method on an empirical measure, for marginals of any law): step t takes
@@ -33,6 +34,7 @@
 // an optimal grid): exact integer sums of x and x x' over the admissible
 // samples of a set, then, in one workgroup, the mean, covariance and lower
 // Cholesky factor in FP64 and the grid mean + chol base.
+#include "bucket_list.hpp"
 #include "qtree_internal.hpp"
 #include "qtree_rng.hpp"
 #include "qtree_search.hpp"
@@ -83,34 +85,211 @@ __device__ __forceinline__ void lloyd_sample(const LloydArgs& a, uint64_t m, flo
   }
 }
 
-}  // namespace
-
-// Records or midpoints of the current grid (the start grid, then the grid
-// of every step).
-__global__ void lloyd_prepare_kernel(LloydArgs a, int first) {
-  const int i = (int)(blockIdx.x * kBlock + threadIdx.x);
-  if (first && i == 0 && a.rej_total) *a.rej_total = 0ull;
-  if (a.d == 1) {
-    if (i >= a.P) return;
-    float m = __builtin_huge_valf();
-    if (i + 1 < a.N) {
-      m = 0.5f * (a.grid[i] + a.grid[i + 1]);
-      if (m == 0.0f) m = 0.0f;
-    }
-    a.mids[i] = m;
-  } else {
-    if (i >= a.Npad) return;
-    float4 rec = make_float4(0.f, 0.f, 0.f, __builtin_huge_valf());
-    if (i < a.N) {
-      const float* g = a.grid + (size_t)i * a.d;
-      float h = g[0] * g[0];
-      for (int c = 1; c < a.d; ++c) h = fmaf(g[c], g[c], h);
-      rec = make_float4(g[0], a.d > 1 ? g[1] : 0.f, a.d > 2 ? g[2] : 0.f, 0.5f * h);
-    }
-    a.recs[i] = rec;
-  }
+__device__ __forceinline__ float4 record_of(const float* g, int d) {
+  float h = g[0] * g[0];
+  for (int c = 1; c < d; ++c) h = fmaf(g[c], g[c], h);
+  return make_float4(g[0], g[1], d > 2 ? g[2] : 0.f, 0.5f * h);
 }
 
+// Adds a sample of cell i (point g) to the workgroup's sums; returns its
+// squared distance in units of 2^-16.
+template <int D>
+__device__ __forceinline__ unsigned long long add_sample(unsigned long long* sum,
+                                                         unsigned int* cnt, int i, const float* x,
+                                                         const float* g) {
+  double d2 = 0.0;
+#pragma unroll
+  for (int c = 0; c < D; ++c) {
+    const double dx = (double)x[c] - (double)g[c];
+    d2 = d2 + dx * dx;
+    atomicAdd(&sum[(size_t)i * D + c], (unsigned long long)fixed_of((double)x[c], 0x1p24));
+  }
+  atomicAdd(&cnt[i], 1u);
+  return (unsigned long long)fixed_of(d2, 0x1p16);
+}
+
+// The workgroup's row of the partial table: its sums and counts, and the
+// totals of its BLOCK threads' distances, admissible and inadmissible samples.
+template <int BLOCK>
+__device__ __forceinline__ void store_partials(const LloydArgs& a, const unsigned long long* sum,
+                                               const unsigned int* cnt, unsigned long long dist,
+                                               unsigned long long used, unsigned long long rej) {
+  __shared__ unsigned long long part[3][BLOCK / 64];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    dist += __shfl_xor(dist, off, 64);
+    used += __shfl_xor(used, off, 64);
+    rej += __shfl_xor(rej, off, 64);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    part[0][threadIdx.x >> 6] = dist;
+    part[1][threadIdx.x >> 6] = used;
+    part[2][threadIdx.x >> 6] = rej;
+  }
+  __syncthreads();
+  unsigned long long* row = a.part + (size_t)blockIdx.x * a.E;
+  const int nd = a.N * a.d;
+  if (threadIdx.x < 3) {
+    unsigned long long t = 0ull;
+    for (int w = 0; w < BLOCK / 64; ++w) t += part[threadIdx.x][w];
+    row[nd + a.N + threadIdx.x] = t;
+  }
+  for (int i = threadIdx.x; i < nd; i += BLOCK) row[i] = sum[i];
+  for (int i = threadIdx.x; i < a.N; i += BLOCK) row[nd + i] = cnt[i];
+}
+
+}  // namespace
+
+// Records of the start grid (d >= 2), and an empty pool of longer rows.
+__global__ void lloyd_records_kernel(LloydArgs a) {
+  const int i = (int)(blockIdx.x * kBlock + threadIdx.x);
+  if (i < 2 && a.bk_longs) reinterpret_cast<uint32_t*>(a.bk_longs)[i] = 0u;
+  if (i >= a.Npad) return;
+  a.recs[i] = i < a.N ? record_of(a.grid + (size_t)i * a.d, a.d)
+                      : make_float4(0.f, 0.f, 0.f, __builtin_huge_valf());
+}
+
+// Bucket tables of the current grid (candidate rule: buckets.hip).  They are
+// made anew in every step, so the N-point loops of one thread per bucket
+// (about 20 us at N = 500) are split: a workgroup takes a tile of 4 x 4
+// buckets and first lists the points that can win anywhere in the tile (a
+// bucket's limit is at most its tile's), in increasing index; 16 lanes per
+// bucket then share those.  (Tiles of 8 x 8 and 4 lanes: 24 us a step instead
+// of 10, the corner tests of the crowded buckets being the longest chain;
+// tiles of 2 x 2 read all points too often, 38 instead of 25 us for the
+// whole step.)  A bucket whose candidates fit nowhere is counted
+// in the pool's second word, and the step then scans: tables pay only where
+// they answer nearly every sample.
+constexpr int kTileSide = kLloydTile;
+constexpr int kPerBucket = kBlock / (kTileSide * kTileSide);
+constexpr int kTileCand = 64;  // candidates of a bucket before the corner test
+__global__ __launch_bounds__(kBlock) void lloyd_tables_kernel(LloydArgs a) {
+  extern __shared__ float4 list[];  // [N] the tile's points: x, y, index
+  __shared__ uint16_t cand[kTileSide * kTileSide][kTileCand];
+  __shared__ double red[4][kBlock / 64];
+  __shared__ int wave_n[kBlock / 64];
+  const int t = (int)threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int tiles = a.bk_B[1] / kTileSide;
+  const int i0 = (int)(blockIdx.x / tiles) * kTileSide, j0 = (int)(blockIdx.x % tiles) * kTileSide;
+  const double w0 = 1.0 / (double)a.bk_scale[0], w1 = 1.0 / (double)a.bk_scale[1];
+  auto box_of = [&](int i, int j, int n) {
+    BucketBox b;
+    b.a0 = (double)a.bk_lo[0] + (double)i * w0 - w0 / 64.0;
+    b.b0 = (double)a.bk_lo[0] + (double)(i + n) * w0 + w0 / 64.0;
+    b.a1 = (double)a.bk_lo[1] + (double)j * w1 - w1 / 64.0;
+    b.b1 = (double)a.bk_lo[1] + (double)(j + n) * w1 + w1 / 64.0;
+    return b;
+  };
+  BucketBox tile = box_of(i0, j0, kTileSide);
+  double U = __builtin_huge_val(), hmax = 0.0, G0 = 0.0, G1 = 0.0;
+  for (int p = t; p < a.N; p += kBlock) {
+    const float4 q = a.recs[p];
+    U = fmin(U, tile.far2(q.x, q.y));
+    hmax = fmax(hmax, (double)q.w);
+    G0 = fmax(G0, fabs((double)q.x));
+    G1 = fmax(G1, fabs((double)q.y));
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    U = fmin(U, __shfl_xor(U, off, 64));
+    hmax = fmax(hmax, __shfl_xor(hmax, off, 64));
+    G0 = fmax(G0, __shfl_xor(G0, off, 64));
+    G1 = fmax(G1, __shfl_xor(G1, off, 64));
+  }
+  if (lane == 0) {
+    red[0][wave] = U;
+    red[1][wave] = hmax;
+    red[2][wave] = G0;
+    red[3][wave] = G1;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kBlock / 64; ++w) {
+    U = fmin(U, red[0][w]);
+    hmax = fmax(hmax, red[1][w]);
+    G0 = fmax(G0, red[2][w]);
+    G1 = fmax(G1, red[3][w]);
+  }
+  tile.set_error(hmax, G0, G1);
+  const double tile_thr = tile.limit(U);
+  int n = 0;
+  for (int p0 = 0; p0 < a.N; p0 += kBlock) {
+    const int p = p0 + t;
+    float4 q = a.recs[p < a.N ? p : 0];
+    const bool in = p < a.N && tile.near2(q.x, q.y) <= tile_thr;
+    const uint64_t mask = __ballot(in);
+    if (lane == 0) wave_n[wave] = __popcll(mask);
+    __syncthreads();
+    int at = n + __popcll(mask & ((1ull << lane) - 1));
+#pragma unroll
+    for (int w = 0; w < kBlock / 64; ++w) {
+      if (w < wave) at += wave_n[w];
+      n += wave_n[w];
+    }
+    if (in) {
+      q.z = __int_as_float(p);
+      list[at] = q;
+    }
+    __syncthreads();
+  }
+  const int b = t / kPerBucket, sub = t % kPerBucket;
+  const int bi = i0 + b / kTileSide, bj = j0 + b % kTileSide;
+  BucketBox box = box_of(bi, bj, 1);
+  box.set_error(hmax, G0, G1);
+  U = __builtin_huge_val();
+  float nx = list[0].x, ny = list[0].y;  // n >= 1: the point that sets the tile's U
+  for (int p = sub; p < n; p += kPerBucket) {
+    const float4 q = list[p];
+    const double d = box.far2(q.x, q.y);
+    nx = d < U ? q.x : nx;
+    ny = d < U ? q.y : ny;
+    U = fmin(U, d);
+  }
+#pragma unroll
+  for (int off = 1; off < kPerBucket; off <<= 1) {
+    const double o = __shfl_xor(U, off, 64);
+    const float ox = __shfl_xor(nx, off, 64), oy = __shfl_xor(ny, off, 64);
+    nx = o < U ? ox : nx;
+    ny = o < U ? oy : ny;
+    U = fmin(U, o);
+  }
+  // (on equal U the lanes may hold different points; each is a valid witness)
+  const double thr = box.limit(U);
+  constexpr uint64_t kGroup = ~0ull >> (64 - kPerBucket);
+  const int shift = lane & ~(kPerBucket - 1);
+  int c = 0;
+  for (int p0 = 0; p0 < n; p0 += kPerBucket) {
+    const float4 q = list[min(p0 + sub, n - 1)];
+    const bool in = p0 + sub < n && box.near2(q.x, q.y) <= thr && !box.beaten(q.x, q.y, nx, ny);
+    const uint64_t group = __ballot(in) >> shift & kGroup;
+    const int at = c + __popcll(group & ((1ull << sub) - 1));
+    if (in && at < kTileCand) cand[b][at] = (uint16_t)(p0 + sub);
+    c += __popcll(group);
+  }
+  __syncthreads();
+  const int listed = c < kTileCand ? c : kTileCand;
+  uint64_t keep = 0;
+  for (int p = sub; p < listed; p += kPerBucket) {
+    const float4 gp = list[cand[b][p]];
+    bool out = false;
+    for (int q = 0; q < listed && !out; ++q) {
+      const float4 gq = list[cand[b][q]];
+      out = q != p && box.beaten(gp.x, gp.y, gq.x, gq.y);
+    }
+    keep |= out ? 0ull : 1ull << p;
+  }
+#pragma unroll
+  for (int off = 1; off < kPerBucket; off <<= 1) keep |= __shfl_xor(keep, off, 64);
+  if (sub != 0) return;
+  const bool ok = write_bucket_row(
+      a.bk_rows + (size_t)(bi * a.bk_B[1] + bj) * kBucketRow, a.bk_longs, a.bk_pool, a.N,
+      c <= kTileCand, __popcll(keep), [&](int) {
+        const int p = __ffsll((unsigned long long)keep) - 1;  // called in order
+        keep &= keep - 1;
+        return __float_as_int(list[cand[b][p]].z);
+      });
+  if (!ok) atomicAdd(reinterpret_cast<uint32_t*>(a.bk_longs) + 1, 1u);
+}
 
 // LDS: d = 1: midpoints [P], points [N]; d >= 2: records [Npad]; then the
 // counts [N] and the sums [N][d] (8-byte aligned).
@@ -125,10 +304,16 @@ __global__ __launch_bounds__(kBlock) void lloyd_accum_kernel(LloydArgs a) {
   unsigned long long* sum =
       reinterpret_cast<unsigned long long*>(ldsf + ((grid_words + 1) & ~(size_t)1));
   unsigned int* cnt = reinterpret_cast<unsigned int*>(sum + (size_t)a.N * D);
-  __shared__ unsigned long long part[3][kBlock / 64];
 
   if (D == 1) {
-    for (int i = threadIdx.x; i < a.P; i += kBlock) mids[i] = a.mids[i];
+    for (int i = threadIdx.x; i < a.P; i += kBlock) {
+      float m = __builtin_huge_valf();
+      if (i + 1 < a.N) {
+        m = 0.5f * (a.grid[i] + a.grid[i + 1]);
+        if (m == 0.0f) m = 0.0f;
+      }
+      mids[i] = m;
+    }
     for (int i = threadIdx.x; i < a.N; i += kBlock) pts1[i] = a.grid[i];
   } else {
     for (int i = threadIdx.x; i < a.Npad; i += kBlock) recs[i] = a.recs[i];
@@ -175,108 +360,145 @@ __global__ __launch_bounds__(kBlock) void lloyd_accum_kernel(LloydArgs a) {
         if (D > 1) g[1] = r.y;
         if (D > 2) g[2] = r.z;
       }
-      double d2 = 0.0;
-#pragma unroll
-      for (int c = 0; c < D; ++c) {
-        const double dx = (double)xs[s][c] - (double)g[c];
-        d2 = d2 + dx * dx;
-        atomicAdd(&sum[(size_t)i * D + c],
-                  (unsigned long long)fixed_of((double)xs[s][c], 0x1p24));
-      }
-      atomicAdd(&cnt[i], 1u);
-      dist += (unsigned long long)fixed_of(d2, 0x1p16);
+      dist += add_sample<D>(sum, cnt, i, xs[s], g);
     }
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    dist += __shfl_xor(dist, off, 64);
-    used += __shfl_xor(used, off, 64);
-    rej += __shfl_xor(rej, off, 64);
+  store_partials<kBlock>(a, sum, cnt, dist, used, rej);
+}
+
+// The same with the step's bucket tables.  LDS: the points as pairs and the
+// pad pair (or the records, where the tables do not answer), sums, counts.
+// A sample's search is then its row (16 bytes from the L2, 64 KB of them at
+// N = 500) and four pairs instead of N records, and what is left is latency:
+// 16 waves a workgroup, 2 samples of a lane in flight (4: 3 us more a step).
+// 10^6 samples, N = 500: 60 -> 12.4 us.
+__global__ __launch_bounds__(kLloydWideThreads) void lloyd_accum_wide_kernel(LloydArgs a) {
+  constexpr int S = kLloydWideSamples, kThreads = kLloydWideThreads;
+  extern __shared__ float4 lds4[];
+  float2* pairs = reinterpret_cast<float2*>(lds4);
+  unsigned long long* sum = reinterpret_cast<unsigned long long*>(lds4 + a.Npad);
+  unsigned int* cnt = reinterpret_cast<unsigned int*>(sum + (size_t)a.N * 2);
+  const BucketTab tab{reinterpret_cast<const uint4*>(a.bk_rows),
+                      reinterpret_cast<const uint4*>(a.bk_longs)};
+  const bool scan = reinterpret_cast<const uint32_t*>(a.bk_longs)[1] != 0u;
+  if (scan) {
+    for (int i = threadIdx.x; i < a.Npad; i += kThreads) lds4[i] = a.recs[i];
+  } else {
+    const float nan = __builtin_nanf("");
+    for (int i = threadIdx.x; i <= a.N; i += kThreads)
+      pairs[i] = i < a.N ? make_float2(a.grid[2 * i], a.grid[2 * i + 1]) : make_float2(nan, nan);
   }
-  if ((threadIdx.x & 63) == 0) {
-    part[0][threadIdx.x >> 6] = dist;
-    part[1][threadIdx.x >> 6] = used;
-    part[2][threadIdx.x >> 6] = rej;
-  }
+  for (int i = threadIdx.x; i < a.N * 2; i += kThreads) sum[i] = 0ull;
+  for (int i = threadIdx.x; i < a.N; i += kThreads) cnt[i] = 0u;
   __syncthreads();
-  unsigned long long* row = a.part + (size_t)blockIdx.x * a.E;
-  const int nd = a.N * D;
-  if (threadIdx.x < 3) {
+  const uint64_t per_round = (uint64_t)gridDim.x * kThreads * S;
+  unsigned long long dist = 0ull, used = 0ull;
+  for (uint64_t base = (uint64_t)blockIdx.x * kThreads * S; base < a.M; base += per_round) {
+    float xs[S][2];
+    bool live[S];
+    int idx[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const uint64_t m = base + (uint64_t)s * kThreads + threadIdx.x;
+      live[s] = m < a.M;
+      lloyd_sample<2>(a, live[s] ? m : 0, xs[s]);
+      used += live[s] ? 1ull : 0ull;
+    }
+    if (scan) {
+      argmin_scan_tiled<2, S, 4>(lds4, a.Npad, xs, idx);
+    } else {
+      uint4 w[S];
+      bucket_rows<S>(a, a.N, tab, xs, w);
+      bucket_argmin<S>(pairs, a.N, tab, xs, w, idx);
+    }
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      if (!live[s]) continue;
+      float g[2];
+      if (scan) {
+        const float4 r = lds4[idx[s]];
+        g[0] = r.x;
+        g[1] = r.y;
+      } else {
+        const float2 r = pairs[idx[s]];
+        g[0] = r.x;
+        g[1] = r.y;
+      }
+      dist += add_sample<2>(sum, cnt, idx[s], xs[s], g);
+    }
+  }
+  store_partials<kThreads>(a, sum, cnt, dist, used, 0ull);
+}
+
+// Workgroup b sums the columns of cells [4 b, 4 b + 4) over the `rows` rows of
+// the partial table (thread t: column t mod 16, rows t / 16 + 16 i, so that
+// the loads of a row are one or two segments and a thread's loads are all in
+// flight) and gives these cells their new points: the mean, or the old point
+// moved the fraction gamma towards it, or the old point of an empty cell.  The
+// last workgroup sums the three totals.  Sum, update and the next grid's
+// records were three launches of 9, 4.5 and 4.7 us a step (N = 500);
+// this one takes 4.3, and the whole step went from 68 to 25 us.
+constexpr int kCells = 4;
+template <int D>
+__global__ __launch_bounds__(kBlock) void lloyd_update_kernel(LloydArgs a, int rows) {
+  constexpr int kCols = 16;
+  static_assert(kCells * (D + 1) <= kCols, "a row's columns fit the threads");
+  __shared__ unsigned long long red[kBlock / 64][kCols];
+  const int col = (int)threadIdx.x % kCols, grp = (int)threadIdx.x / kCols;
+  const int nd = a.N * D, c0 = (int)blockIdx.x * kCells;
+  const bool totals = blockIdx.x == gridDim.x - 1;
+  int column = -1;
+  if (totals) column = col < 3 ? nd + a.N + col : -1;
+  else if (col < kCells * D) column = c0 * D + col < nd ? c0 * D + col : -1;
+  else if (col < kCells * (D + 1) && c0 + col - kCells * D < a.N)
+    column = nd + c0 + col - kCells * D;
+  unsigned long long acc = 0ull;
+  if (column >= 0) {
+#pragma unroll 8
+    for (int r = grp; r < rows; r += kBlock / kCols) acc += a.part[(size_t)r * a.E + column];
+  }
+  acc += __shfl_xor(acc, 16, 64);
+  acc += __shfl_xor(acc, 32, 64);
+  if ((threadIdx.x & 63) < kCols) red[threadIdx.x >> 6][col] = acc;
+  __syncthreads();
+  auto total = [&](int c) {
     unsigned long long t = 0ull;
-    for (int w = 0; w < kBlock / 64; ++w) t += part[threadIdx.x][w];
-    row[nd + a.N + threadIdx.x] = t;
-  }
-  for (int i = threadIdx.x; i < nd; i += kBlock) row[i] = sum[i];
-  for (int i = threadIdx.x; i < a.N; i += kBlock) row[nd + i] = cnt[i];
-}
-
-// Column sums of the partial table over its `rows` rows: workgroup b takes
-// columns [8 b, 8 b + 8); lane l adds rows l, l + 256, ...; the 256 lane
-// sums of each column are then added in LDS.
-constexpr int kReduceCols = 8;
-__global__ __launch_bounds__(kBlock) void lloyd_reduce_kernel(LloydArgs a, int rows) {
-  __shared__ unsigned long long red[kReduceCols][kBlock];
-  const int c0 = (int)blockIdx.x * kReduceCols;
-  unsigned long long acc[kReduceCols] = {};
-  for (int r = threadIdx.x; r < rows; r += kBlock) {
-    const unsigned long long* src = a.part + (size_t)r * a.E + c0;
 #pragma unroll
-    for (int q = 0; q < kReduceCols; ++q)
-      if (c0 + q < a.E) acc[q] += src[q];
-  }
-#pragma unroll
-  for (int q = 0; q < kReduceCols; ++q) red[q][threadIdx.x] = acc[q];
-  __syncthreads();
-  for (int w = kBlock / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w)
-#pragma unroll
-      for (int q = 0; q < kReduceCols; ++q) red[q][threadIdx.x] += red[q][threadIdx.x + w];
-    __syncthreads();
-  }
-  if ((int)threadIdx.x < kReduceCols) {
-    const int c = c0 + (int)threadIdx.x;
-    const int nd = a.N * a.d;
-    const unsigned long long v = red[threadIdx.x][0];
-    if (c < nd) a.sum[c] = v;
-    else if (c < nd + a.N) a.cnt[c - nd] = (unsigned int)v;
-    else if (c == nd + a.N) *a.dist = v;
-    else if (c == nd + a.N + 1) *a.used = v;
-    else if (c == nd + a.N + 2) *a.rej = v;
-  }
-}
-
-// New point of cell i from the accumulators (the old point when empty):
-// the cell mean, or the old point moved the fraction gamma towards it.
-__device__ __forceinline__ float lloyd_new(const LloydArgs& a, int i, int c) {
-  const float g = a.grid[(size_t)i * a.d + c];
-  const unsigned int n = a.cnt[i];
-  if (n == 0u) return g;
-  const double mean = ((double)(long long)a.sum[(size_t)i * a.d + c] * 0x1p-24) / (double)n;
-  return a.gamma == 1.0 ? (float)mean : (float)((double)g + a.gamma * (mean - (double)g));
-}
-
-// One thread per cell: its new point (each thread reads and writes only its
-// own point), and the step's distortion and sample counts; the records or
-// midpoints are rebuilt by lloyd_prepare_kernel afterwards.
-__global__ void lloyd_update_kernel(LloydArgs a) {
-  const int i = (int)(blockIdx.x * kBlock + threadIdx.x);
-  if (i == 0) {
-    if (a.xs) {
-      const unsigned long long used = *a.used;
+    for (int w = 0; w < kBlock / 64; ++w) t += red[w][c];
+    return t;
+  };
+  if (totals) {
+    if (threadIdx.x == 0) {
+      const unsigned long long dist = total(0), used = total(1);
       if (a.distortion)
         a.distortion[a.it] =
-            used > 0ull ? ((double)(long long)*a.dist * 0x1p-16) / (double)(long long)used : 0.0;
-      const unsigned long long total = *a.rej_total + *a.rej;
-      *a.rej_total = total;
-      if (a.rejected) *a.rejected = (long long)total;
-    } else if (a.distortion) {
-      a.distortion[a.it] = ((double)(long long)*a.dist * 0x1p-16) / (double)a.M;
+            used > 0ull ? ((double)(long long)dist * 0x1p-16) / (double)(long long)used : 0.0;
+      if (a.xs) {
+        const unsigned long long rej = (a.it > 0 ? *a.rej_total : 0ull) + total(2);
+        *a.rej_total = rej;
+        if (a.rejected) *a.rejected = (long long)rej;
+      }
+      if (a.bk_longs) {  // the next tables start with an empty pool
+        reinterpret_cast<uint32_t*>(a.bk_longs)[0] = 0u;
+        reinterpret_cast<uint32_t*>(a.bk_longs)[1] = 0u;
+      }
     }
+    return;
   }
-  if (i >= a.N) return;
+  const int i = c0 + (int)threadIdx.x;
+  if (threadIdx.x >= kCells || i >= a.N) return;
+  const unsigned int n = (unsigned int)total(kCells * D + (int)threadIdx.x);
   float g[kMaxDim] = {0.f, 0.f, 0.f};
-  for (int c = 0; c < a.d; ++c) g[c] = lloyd_new(a, i, c);
-  for (int c = 0; c < a.d; ++c) a.grid[(size_t)i * a.d + c] = g[c];
+#pragma unroll
+  for (int c = 0; c < D; ++c) {
+    g[c] = a.grid[(size_t)i * D + c];
+    if (n == 0u) continue;
+    const double mean =
+        ((double)(long long)total((int)threadIdx.x * D + c) * 0x1p-24) / (double)n;
+    g[c] = a.gamma == 1.0 ? (float)mean : (float)((double)g[c] + a.gamma * (mean - (double)g[c]));
+    a.grid[(size_t)i * D + c] = g[c];
+  }
+  if (D > 1) a.recs[i] = record_of(g, D);
 }
 
 size_t lloyd_lds_bytes(int d, int N, int Npad, int P) {
@@ -285,40 +507,51 @@ size_t lloyd_lds_bytes(int d, int N, int Npad, int P) {
          sizeof(unsigned int) * N;
 }
 
-hipError_t launch_lloyd_prepare(const LloydArgs& a, hipStream_t s) {
-  const int n = a.d == 1 ? a.P : a.Npad;
-  hipLaunchKernelGGL(lloyd_prepare_kernel, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, a,
-                     1);
+hipError_t launch_lloyd_records(const LloydArgs& a, hipStream_t s) {
+  if (a.d == 1) return hipSuccess;
+  hipLaunchKernelGGL(lloyd_records_kernel, dim3((a.Npad + kBlock - 1) / kBlock), dim3(kBlock), 0, s,
+                     a);
   return hipGetLastError();
 }
 
-template <int D, bool SET>
-static hipError_t launch_accum(const LloydArgs& a, int blocks, size_t lds, hipStream_t s) {
+template <class KERNEL>
+static hipError_t launch_accum(KERNEL* k, const LloydArgs& a, int blocks, int threads, size_t lds,
+                               hipStream_t s) {
   hipError_t e = hipSuccess;
   if (lds > 65536)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(lloyd_accum_kernel<D, SET>),
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e == hipSuccess)
-    hipLaunchKernelGGL((lloyd_accum_kernel<D, SET>), dim3(blocks), dim3(kBlock), lds, s, a);
+  if (e == hipSuccess) hipLaunchKernelGGL(k, dim3(blocks), dim3(threads), lds, s, a);
   return e;
 }
 
 hipError_t launch_lloyd_step(const LloydArgs& a, int blocks, hipStream_t s) {
-  if (blocks < 1 || blocks > kLloydMaxBlocks) return hipErrorInvalidValue;
+  const bool wide = a.bk_B[0] > 0;
+  if (blocks < 1 || blocks > (wide ? kLloydMaxWide : kLloydMaxBlocks)) return hipErrorInvalidValue;
   const size_t lds = lloyd_lds_bytes(a.d, a.N, a.Npad, a.P);
   const bool set = a.xs != nullptr;
   hipError_t e;
-  if (a.d == 1) e = set ? launch_accum<1, true>(a, blocks, lds, s) : launch_accum<1, false>(a, blocks, lds, s);
-  else if (a.d == 2) e = set ? launch_accum<2, true>(a, blocks, lds, s) : launch_accum<2, false>(a, blocks, lds, s);
-  else e = set ? launch_accum<3, true>(a, blocks, lds, s) : launch_accum<3, false>(a, blocks, lds, s);
+  if (wide) {
+    const int tiles = a.bk_B[0] / kTileSide;
+    hipLaunchKernelGGL(lloyd_tables_kernel, dim3(tiles * tiles), dim3(kBlock),
+                       sizeof(float4) * a.N, s, a);
+    e = launch_accum(lloyd_accum_wide_kernel, a, blocks, kLloydWideThreads, lds, s);
+  } else if (a.d == 1) {
+    e = launch_accum(set ? lloyd_accum_kernel<1, true> : lloyd_accum_kernel<1, false>, a, blocks,
+                     kBlock, lds, s);
+  } else if (a.d == 2) {
+    e = launch_accum(set ? lloyd_accum_kernel<2, true> : lloyd_accum_kernel<2, false>, a, blocks,
+                     kBlock, lds, s);
+  } else {
+    e = launch_accum(set ? lloyd_accum_kernel<3, true> : lloyd_accum_kernel<3, false>, a, blocks,
+                     kBlock, lds, s);
+  }
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(lloyd_reduce_kernel, dim3((a.E + kReduceCols - 1) / kReduceCols),
-                     dim3(kBlock), 0, s, a, blocks);
-  hipLaunchKernelGGL(lloyd_update_kernel, dim3((a.N + kBlock - 1) / kBlock), dim3(kBlock), 0, s,
-                     a);
-  const int n = a.d == 1 ? a.P : a.Npad;
-  hipLaunchKernelGGL(lloyd_prepare_kernel, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, s, a,
-                     0);
+  const dim3 groups((a.N + kCells - 1) / kCells + 1);
+  if (a.d == 1) hipLaunchKernelGGL(lloyd_update_kernel<1>, groups, dim3(kBlock), 0, s, a, blocks);
+  else if (a.d == 2)
+    hipLaunchKernelGGL(lloyd_update_kernel<2>, groups, dim3(kBlock), 0, s, a, blocks);
+  else hipLaunchKernelGGL(lloyd_update_kernel<3>, groups, dim3(kBlock), 0, s, a, blocks);
   return hipGetLastError();
 }
 

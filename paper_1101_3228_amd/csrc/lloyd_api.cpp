@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <algorithm>
 #include <cstring>
 #include <string>
 
@@ -28,7 +29,7 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 struct LloydLayout {
   int Npad, P, logP;
-  size_t recs, mids, cnt, sum, acc, part, total;
+  size_t recs, rej_total, part, total;
 };
 constexpr int kExtra = 3;  // partial-table words per row beyond sums and counts
 
@@ -44,14 +45,8 @@ LloydLayout layout(int d, int N) {
   size_t off = 0;
   l.recs = off;
   off = align_up(off + (d == 1 ? 0 : sizeof(float4) * (size_t)l.Npad), 256);
-  l.mids = off;
-  off = align_up(off + (d == 1 ? sizeof(float) * (size_t)l.P : 0), 256);
-  l.cnt = off;
-  off = align_up(off + sizeof(unsigned int) * (size_t)N, 256);
-  l.sum = off;
-  off = align_up(off + sizeof(unsigned long long) * (size_t)N * d, 256);
-  l.acc = off;  // distortion, admissible, inadmissible, running inadmissible total
-  off = align_up(off + 4 * sizeof(unsigned long long), 256);
+  l.rej_total = off;
+  off = align_up(off + sizeof(unsigned long long), 256);
   l.part = off;
   off = align_up(off + sizeof(unsigned long long) * qtree::kLloydMaxBlocks *
                            ((size_t)N * d + (size_t)N + kExtra),
@@ -71,26 +66,47 @@ qtree::LloydArgs args_of(int d, int N, const LloydLayout& l, float* grid, void* 
   a.logP = l.logP;
   a.grid = grid;
   a.recs = reinterpret_cast<float4*>(ws + l.recs);
-  a.mids = reinterpret_cast<float*>(ws + l.mids);
-  a.cnt = reinterpret_cast<unsigned int*>(ws + l.cnt);
-  a.sum = reinterpret_cast<unsigned long long*>(ws + l.sum);
-  auto* acc = reinterpret_cast<unsigned long long*>(ws + l.acc);
-  a.dist = acc;
-  a.used = acc + 1;
-  a.rej = acc + 2;
-  a.rej_total = acc + 3;
+  a.rej_total = reinterpret_cast<unsigned long long*>(ws + l.rej_total);
   a.part = reinterpret_cast<unsigned long long*>(ws + l.part);
   a.E = N * d + N + kExtra;
   a.gamma = 1.0;
   return a;
 }
 
-// Two accumulation workgroups per CU (at most kLloydMaxBlocks), fewer when
-// the samples of a step are few.
-int accum_blocks(int d, uint64_t M, int cus) {
-  const uint64_t per_block = 256ull * (d == 1 ? 1 : 8);  // samples per workgroup round
-  const uint64_t want = (M + per_block - 1) / per_block;
-  const uint64_t cap = std::min<uint64_t>(2ull * (uint64_t)cus, qtree::kLloydMaxBlocks);
+// Bucket tables for a step on Philox samples, d = 2: the box holds every
+// sample (coordinate r is at most kZMax sum_c |L_rc|; one outside would take
+// the full scan).  Filling them costs about 9 us a step, the scan about 0.1 us
+// per point where the samples are few and N M / (2 10^12) s where they are
+// many; both rules are where the two measured alike.
+constexpr int kTableMinN = 100;
+constexpr double kTableMinWork = 6e7;
+void table_args(qtree::LloydArgs& a, int N) {
+  if (a.d != 2 || a.xs) return;
+  if (N < kTableMinN && (double)N * (double)a.M < kTableMinWork) return;
+  const int B = qtree::lloyd_side(N);
+  for (int r = 0; r < 2; ++r) {
+    const double half =
+        1.0001 * kZMax * (std::fabs((double)a.L[2 * r]) + std::fabs((double)a.L[2 * r + 1]));
+    if (!(half > 1e-18)) return;  // a (nearly) constant coordinate
+    a.bk_lo[r] = (float)-half;
+    a.bk_scale[r] = (float)(B / (2.0 * half));
+  }
+  a.bk_rows = reinterpret_cast<uint16_t*>(a.part + (size_t)qtree::kLloydMaxWide * a.E);
+  a.bk_longs = a.bk_rows + (size_t)B * B * qtree::kBucketRow;
+  a.bk_pool = (int)qtree::long_rows((int64_t)B * B);
+  a.bk_B[0] = a.bk_B[1] = B;
+}
+
+// Two accumulation workgroups per CU (at most kLloydMaxBlocks), or one wide
+// one, and fewer when the samples of a step are few.
+int accum_blocks(const qtree::LloydArgs& a, int cus) {
+  const bool wide = a.bk_B[0] > 0;
+  const uint64_t per_block =  // samples per workgroup round
+      wide ? (uint64_t)qtree::kLloydWideThreads * qtree::kLloydWideSamples
+           : 256ull * (a.d == 1 ? 1 : 8);
+  const uint64_t want = (a.M + per_block - 1) / per_block;
+  const uint64_t cap = wide ? std::min(cus, qtree::kLloydMaxWide)
+                            : std::min(2 * cus, qtree::kLloydMaxBlocks);
   return (int)std::max<uint64_t>(1, want < cap ? want : cap);
 }
 
@@ -171,10 +187,9 @@ qtree_status qtree_lloyd(int32_t d, int32_t N, const float* L, const float* grid
   e = hipMemcpyAsync(grid, grid0, sizeof(float) * (size_t)N * d, hipMemcpyHostToDevice, s);
   if (e != hipSuccess) return set_error(QTREE_EDEVICE, std::string("start grid copy: ") +
                                                            hipGetErrorString(e));
-  e = qtree::launch_lloyd_prepare(a, s);
-  // two workgroups per CU (at most kLloydMaxBlocks), fewer when the samples
-  // of a step are few
-  const int blocks = accum_blocks(d, M, cus);
+  table_args(a, N);
+  e = qtree::launch_lloyd_records(a, s);
+  const int blocks = accum_blocks(a, cus);
   for (int32_t it = 0; it < steps && e == hipSuccess; ++it) {
     a.it = it;
     a.it_ctr = fresh ? (uint32_t)it : 0u;
@@ -217,8 +232,8 @@ qtree_status qtree_lloyd_samples(int32_t d, int32_t N, const float* grid0, float
       hipMemcpyAsync(grid, grid0, sizeof(float) * (size_t)N * d, hipMemcpyHostToDevice, s);
   if (e != hipSuccess) return set_error(QTREE_EDEVICE, std::string("start grid copy: ") +
                                                            hipGetErrorString(e));
-  e = qtree::launch_lloyd_prepare(a, s);
-  const int blocks = accum_blocks(d, batch, cus);
+  e = qtree::launch_lloyd_records(a, s);
+  const int blocks = accum_blocks(a, cus);
   for (int32_t it = 0; it < steps && e == hipSuccess; ++it) {
     a.it = it;
     a.start = ((uint64_t)it * batch) % M;  // t batch < 2^62

@@ -354,11 +354,14 @@ struct LloydArgs {
   uint64_t M;                // samples per step
   float* grid;               // [N][d], updated in place
   float4* recs;              // d >= 2: [Npad] (g, |g|^2 / 2)
-  float* mids;               // d = 1: [P] midpoints padded with +inf
-  unsigned int* cnt;         // [N]
-  unsigned long long* sum;   // [N][d] two's complement sums of rint(x 2^24)
-  unsigned long long* dist;  // sum of rint(|x - g|^2 2^16)
   double* distortion;        // [steps] or null
+  // d = 2 on Philox samples: bucket tables of the current grid over the
+  // samples' box (fields as at LayerDev), rebuilt every step; bk_B[0] = 0: none
+  float bk_lo[2], bk_scale[2];
+  int32_t bk_B[2];
+  int32_t bk_off;            // 0
+  uint16_t *bk_rows, *bk_longs;
+  int bk_pool;
   // per-workgroup partials of the accumulation: row b holds workgroup b's
   // sums [N d], counts [N], distortion, admissible and inadmissible samples
   // (E = N d + N + 3 words)
@@ -371,19 +374,32 @@ struct LloydArgs {
   uint64_t Ms;
   uint64_t start;
   double gamma;              // new point g + gamma (mean - g); 1: the mean
-  unsigned long long* used;  // admissible samples of the step
-  unsigned long long* rej;   // inadmissible samples of the step
   unsigned long long* rej_total;  // running total over the steps
   long long* rejected;       // caller's copy of the total, or null
 };
 constexpr int kLloydMaxBlocks = 512;  // accumulation workgroups per step at most
+// With bucket tables: half as many, four times as wide, and the tables take
+// the place of the other half of their partials.
+constexpr int kLloydMaxWide = kLloydMaxBlocks / 2;
+constexpr int kLloydWideThreads = 1024, kLloydWideSamples = 2;  // samples per thread and round
+constexpr int kLloydTile = 4;
+// Buckets per side, a multiple of kLloydTile: about 32 per point over the
+// samples' whole box (a fifth of them where the points are), at most 192.
+// More make the lists short and the corner tests few, but all have to be
+// filled in every step: 8 / 16 / 32 / 64 per point take 32 / 25 / 23 / 27 us a
+// step at N = 500 and 10^5 samples, and at N = 2048 42 / 42 / 54 / 87.
+inline int lloyd_side(int N) {
+  int b = kLloydTile;
+  while ((double)b * b < 32.0 * N) b += kLloydTile;
+  return b < 192 ? b : 192;
+}
 size_t lloyd_lds_bytes(int d, int N, int Npad, int P);
 // Bucket rows of the d = 2 bucketed cell search of every layer (records
 // and LayerDev already in the workspace).
 hipError_t launch_bucket_build(const LayerDev* layers, int n_layers_total, int total_buckets,
                                const float4* pts, uint16_t* rows, uint16_t* longs,
                                hipStream_t s);
-hipError_t launch_lloyd_prepare(const LloydArgs& a, hipStream_t s);
+hipError_t launch_lloyd_records(const LloydArgs& a, hipStream_t s);
 hipError_t launch_lloyd_step(const LloydArgs& a, int blocks, hipStream_t s);
 // Moment-matching grids: exact integer moment sums of a device sample set,
 // sums = [count, s1 (d), s2 (d d)], and the grid mean + chol(cov) base.

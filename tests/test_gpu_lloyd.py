@@ -77,3 +77,40 @@ def test_lloyd_errors_leave_the_output_untouched():
     with pytest.raises(qt.QtreeError):
         qt.lloyd(2, np.zeros((4, 2)) + 100.0, np.eye(2), 1000, 1, 1, grid=out)
     assert torch.all(out == 7.0)
+
+
+def _grid_2d(kind, N):
+    rng = np.random.default_rng(N)
+    g = rng.normal(size=(N, 2))
+    if kind == "dot":  # every bucket near it has all points on its list: the step scans
+        g = 1e-3 * g
+    elif kind == "half dot":
+        g[: N // 2] = 0.25 + 1e-4 * g[: N // 2]
+    elif kind == "doubles":  # equal keys: the lowest index
+        g[1::2] = g[: N // 2 * 2 : 2][: len(g[1::2])]
+    elif kind == "far":  # points beyond the samples' box
+        g[::3] *= 40.0 / np.abs(g[::3]).max()
+    elif kind == "lattice":  # four cells meet at every corner
+        s = int(round(N ** 0.5))
+        g = np.stack(np.meshgrid(np.arange(s) - s / 2, np.arange(s) - s / 2, indexing="ij"),
+                     -1).reshape(-1, 2) * (4.0 / s)
+    return g.astype(np.float32)
+
+
+@pytest.mark.parametrize("kind,N,M,L", [
+    ("plain", 99, 30_011, (1.0, 0.0, 0.45, 0.9)),  # the largest that scans
+    ("plain", 100, 30_011, (1.0, 0.0, 0.45, 0.9)),
+    ("plain", 128, 1, (1.0, 0.0, 0.45, 0.9)),
+    ("plain", 777, 2049, (0.02, 0.0, 3.0, 7.0)),
+    ("plain", 32, 1_900_000, (1.0, 0.0, 0.45, 0.9)),  # few points, many samples
+    ("plain", 300, 30_011, (1.0, 0.0, 0.999, 0.01)),  # a thin ellipse in its box
+    ("plain", 300, 30_011, (1.0, 0.0, 0.0, 0.0)),     # a constant coordinate: no tables
+    ("dot", 200, 30_011, (1.0, 0.0, 0.45, 0.9)),
+    ("half dot", 401, 30_011, (1.0, 0.0, 0.45, 0.9)),
+    ("doubles", 255, 30_011, (1.0, 0.0, 0.45, 0.9)),
+    ("far", 256, 30_011, (1.0, 0.0, 0.45, 0.9)),
+    ("lattice", 256, 30_011, (1.0, 0.0, 0.0, 1.0)),
+])
+def test_lloyd_2d_tables_bitwise(kind, N, M, L):
+    _case(f"lloyd d=2 tables {kind} N={N} M={M}")
+    _compare(2, _grid_2d(kind, N), np.array(L).reshape(2, 2), M, 3, 0x5EED0027, True)
