@@ -84,11 +84,12 @@ const char *qtree_version(void);
  * LAYERWISE samples per layer per pass (0: 2^22).  Larger M runs in several
  * passes; a plan uses all the scratch its workspace has room for.  For d = 2
  * it includes the bucket tables of the cell search, 24 bytes per bucket and
- * about 36 buckets per grid point (1.7 MB for a layer of 2000 points), and for
- * layers of up to about 1450 points the cell scratch of PATHWISE calls, 2
- * bytes per layer and path for up to 2^17 paths a pass, at most 96 MiB (a
- * plan given a smaller workspace counts those calls with atomics).  Pure host
- * arithmetic. */
+ * about 36 buckets per grid point (1.7 MB for a layer of 2000 points), for
+ * d = 3 those of 32 bytes and about 32 per point (1 MB for 1000 points, 256 MB
+ * for a plan at most), and for layers of up to about 1450 points the cell
+ * scratch of PATHWISE calls, 2 bytes per layer and path for up to 2^17 paths a
+ * pass, at most 96 MiB.  A plan given a smaller workspace counts PATHWISE
+ * calls with atomics, and scans all points for d = 3.  Pure host arithmetic. */
 qtree_status qtree_workspace_size(int32_t d, int32_t n, const int32_t *N, uint64_t batch_samples,
                                   size_t *bytes);
 
@@ -162,13 +163,13 @@ int64_t qtree_plan_points(const qtree_plan *plan);        /* sum_k N_k */
  *                        layers in percent of each other group's (10..100,
  *                        default 100: equal groups); its histogram pass is
  *                        the one no sampling pass overlaps.
- *   QTREE_TUNE_BUCKETS : d = 2: 1 (default) finds cells through the plan's
+ *   QTREE_TUNE_BUCKETS : d = 2, 3: 1 (default) finds cells through the plan's
  *                        bucket tables (each bucket of a layer's reachable box
  *                        lists every point that can be the FP32 argmin in it,
  *                        the key's rounding included, so the cell is the full
  *                        scan's), 0 scans every point (the brute-force search
- *                        of Sec. 4); used by the LAYERWISE two-pass forward
- *                        and qtree_cells.
+ *                        of Sec. 4); used by the LAYERWISE two-pass forward,
+ *                        the PATHWISE forward and, for d = 2, qtree_cells.
  */
 typedef enum {
   QTREE_TUNE_CHUNK = 0,

@@ -112,7 +112,20 @@ int64_t path_cells(int n, const int32_t* N) {
   return c < 4096 ? 0 : c;
 }
 
-WsLayout ws_layout(int d, int n, const int32_t* N, int64_t batch_chunks, int64_t cells) {
+// Buckets of the d = 3 search over all layers: layers take tables in order
+// while the rows so far stay within kMaxCubes.
+int64_t total_cubes(int n, const int32_t* N) {
+  int64_t b = 0;
+  for (int k = 0; k <= n; ++k) {
+    if (N[k] < kCubeMinN) continue;
+    const int64_t side = cube_side(N[k]), b3 = side * side * side;
+    if (b + b3 <= kMaxCubes) b += b3;
+  }
+  return b;
+}
+
+WsLayout ws_layout(int d, int n, const int32_t* N, int64_t batch_chunks, int64_t cells,
+                   int64_t cubes) {
   WsLayout l{};
   size_t off = 0;
   l.layers = off;
@@ -141,6 +154,10 @@ WsLayout ws_layout(int d, int n, const int32_t* N, int64_t batch_chunks, int64_t
   off = align_up(off + sizeof(uint16_t) * kBucketRow * (size_t)buckets, 256);
   l.bk_long = off;
   off = align_up(off + sizeof(uint16_t) * kLongRow * (size_t)long_rows(buckets), 256);
+  l.cubes = off;
+  if (cubes > 0) off = align_up(off + sizeof(Cubes) * (size_t)(n + 1), 256);
+  l.cube_rows = off;
+  off = align_up(off + sizeof(uint16_t) * kCubeRow * (size_t)cubes, 256);
   l.path = off;
   off = align_up(off + sizeof(uint16_t) * (size_t)n * (size_t)cells, 256);
   // scratch of the two-pass counting (only when every count block has at
@@ -292,7 +309,8 @@ qtree_status qtree_workspace_size(int32_t d, int32_t n, const int32_t* N, uint64
   if (batch_samples == 0) batch_samples = qtree::kDefaultBatch;
   if (batch_samples > (1ull << 31)) return fail(QTREE_EINVAL, "batch_samples must be <= 2^31");
   *bytes = qtree::ws_layout(d, n, N, qtree::chunks_for(d, batch_samples),
-                            qtree::path_cells(n, N)).total;
+                            qtree::path_cells(n, N), d == 3 ? qtree::total_cubes(n, N) : 0)
+               .total;
   return QTREE_OK;
 }
 
@@ -423,6 +441,53 @@ static void bucket_boxes(qtree_plan& p, const qtree_model* model, const float* g
   if (off > 0) p.tune_nd_samples = 4;
 }
 
+// Boxes of the d = 3 search.  The bounds above, the sums of every row, are two
+// to four times the samples' spread along each axis, and of such a box in
+// three dimensions a few percent hold the samples.  So the box is kCubeSigma
+// standard deviations of the union of both marginals of X_k, mu_k + L_k z and
+// A_{k-1} X_{k-1} + b_{k-1} + T_{k-1} eps: a sample in 10^4 is outside, and its
+// wave scans for it (3.8 and 4.8 standard deviations: the same within 2 %).
+static void cube_boxes(qtree_plan& p, const qtree_model* model, qtree::Cubes* cubes) {
+  constexpr double kCubeSigma = 4.2;
+  int64_t off = 0;
+  for (int k = 0; k <= p.n; ++k) {
+    qtree::Cubes& C = cubes[k];
+    C = qtree::Cubes{};
+    C.off = (int32_t)off;
+    C.N = p.N[k];
+    C.pt_off = (int32_t)p.pt_off[k];
+    if (p.N[k] < qtree::kCubeMinN) continue;
+    const int64_t B = qtree::cube_side(p.N[k]);
+    if (off + B * B * B > qtree::kMaxCubes) continue;
+    for (int r = 0; r < 3; ++r) {
+      const float* Lk = model->L + (size_t)k * 9 + r * 3;
+      double var = 0.0;
+      for (int c = 0; c < 3; ++c) var += (double)Lk[c] * (double)Lk[c];
+      const double m0 = (double)model->mu[(size_t)k * 3 + r], h0 = kCubeSigma * std::sqrt(var);
+      double lo = m0 - h0, hi = m0 + h0;
+      if (k > 0) {
+        const float* A = model->A + (size_t)(k - 1) * 9 + r * 3;
+        const float* T = model->T + (size_t)(k - 1) * 9 + r * 3;
+        const float* L0 = model->L + (size_t)(k - 1) * 9;
+        double m1 = (double)model->b[(size_t)(k - 1) * 3 + r], v1 = 0.0;
+        for (int c = 0; c < 3; ++c) {
+          double al = 0.0;  // (A L)_rc
+          for (int q = 0; q < 3; ++q) al += (double)A[q] * (double)L0[q * 3 + c];
+          v1 += al * al + (double)T[c] * (double)T[c];
+          m1 += (double)A[c] * (double)model->mu[(size_t)(k - 1) * 3 + c];
+        }
+        lo = std::min(lo, m1 - kCubeSigma * std::sqrt(v1));
+        hi = std::max(hi, m1 + kCubeSigma * std::sqrt(v1));
+      }
+      const double m = 1e-3 * (hi - lo) + 1e-6 * (1.0 + std::fabs(lo) + std::fabs(hi));
+      C.lo[r] = (float)(lo - m);
+      C.scale[r] = (float)((double)B / (hi + m - (double)C.lo[r]));
+      C.B[r] = (int32_t)B;
+    }
+    off += B * B * B;
+  }
+}
+
 qtree_status qtree_plan_create(const qtree_model* model, const float* grid, const int32_t* N,
                                void* workspace, size_t workspace_bytes, qtree_plan** out) {
   if (!out) return fail(QTREE_EINVAL, "out is NULL");
@@ -477,31 +542,35 @@ qtree_status qtree_plan_create(const qtree_model* model, const float* grid, cons
   }
   // the scratch takes whatever the workspace holds beyond the layer tables
   p.max_tiles = qtree::max_tiles_of(n, N);
-  qtree::WsLayout base = qtree::ws_layout(d, n, N, 0, 0);
+  qtree::WsLayout base = qtree::ws_layout(d, n, N, 0, 0, 0);
   if (workspace_bytes < base.total)
     return fail(QTREE_ENOMEM, "workspace needs at least " + std::to_string(base.total) + " bytes");
   // the pathwise scratch, where the workspace holds it beside a chunk per layer
   const bool two = qtree::two_pass_fits(d, n, N);
+  // (the same for the tables of the d = 3 search)
+  const int64_t cubes = d == 3 ? qtree::total_cubes(n, N) : 0;
+  if (cubes > 0 && qtree::ws_layout(d, n, N, two ? 1 : 0, 0, cubes).total <= workspace_bytes)
+    p.cubes = cubes;
   const int64_t cells = qtree::path_cells(n, N);
-  if (cells > 0 && qtree::ws_layout(d, n, N, two ? 1 : 0, cells).total <= workspace_bytes) {
+  if (cells > 0 &&
+      qtree::ws_layout(d, n, N, two ? 1 : 0, cells, p.cubes).total <= workspace_bytes)
     p.path_cells = cells;
-    base = qtree::ws_layout(d, n, N, 0, cells);
-  }
+  base = qtree::ws_layout(d, n, N, 0, p.path_cells, p.cubes);
   p.batch_chunks = 0;
   if (two) {
     const size_t per = (size_t)n * (sizeof(uint16_t) * qtree::kChunk +
                                     sizeof(uint32_t) * (size_t)(p.max_tiles + 1));
     int64_t c = (int64_t)((workspace_bytes - base.total) / per);
-    while (c > 0 && qtree::ws_layout(d, n, N, c, p.path_cells).total > workspace_bytes) --c;
+    while (c > 0 && qtree::ws_layout(d, n, N, c, p.path_cells, p.cubes).total > workspace_bytes) --c;
     p.batch_chunks = c;
   }
   p.two_pass_ok = p.batch_chunks > 0;
   p.two_pass_shape = two;
-  p.lay = qtree::ws_layout(d, n, N, p.batch_chunks, p.path_cells);
+  p.lay = qtree::ws_layout(d, n, N, p.batch_chunks, p.path_cells, p.cubes);
 
   // host image of the workspace's tables (the bucket rows are built on the
   // device, the scratch behind them is written before it is read)
-  std::vector<char> img(p.lay.bk_rows, 0);
+  std::vector<char> img(p.cubes > 0 ? p.lay.cube_rows : p.lay.bk_rows, 0);
   auto* layers = reinterpret_cast<qtree::LayerDev*>(img.data() + p.lay.layers);
   // histogram parts: a layer with fewer super tiles than the largest layer
   // is split over the chunks into up to that ratio (at most 16), so that no
@@ -615,6 +684,8 @@ qtree_status qtree_plan_create(const qtree_model* model, const float* grid, cons
       pts[t] = make_float4(g[0], d > 1 ? g[1] : 0.f, d > 2 ? g[2] : 0.f, h);
     }
     if (d == 2) bucket_boxes(p, model, grid, layers);
+    if (p.cubes > 0)
+      cube_boxes(p, model, reinterpret_cast<qtree::Cubes*>(img.data() + p.lay.cubes));
   }
   hipError_t e = hipMemcpy(workspace, img.data(), img.size(), hipMemcpyHostToDevice);
   if (e != hipSuccess) return hip_fail(e, "hipMemcpy(workspace)");
@@ -626,6 +697,14 @@ qtree_status qtree_plan_create(const qtree_model* model, const float* grid, cons
         reinterpret_cast<const float4*>(p.ws + p.lay.points),
         reinterpret_cast<uint16_t*>(p.ws + p.lay.bk_rows),
         reinterpret_cast<uint16_t*>(p.ws + p.lay.bk_long), nullptr);
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+    if (e != hipSuccess) return hip_fail(e, "bucket tables");
+  }
+  if (p.cubes > 0) {
+    e = qtree::launch_cube_build(reinterpret_cast<const qtree::Cubes*>(p.ws + p.lay.cubes), n + 1,
+                                 (int)p.cubes,
+                                 reinterpret_cast<const float4*>(p.ws + p.lay.points),
+                                 reinterpret_cast<uint16_t*>(p.ws + p.lay.cube_rows), nullptr);
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     if (e != hipSuccess) return hip_fail(e, "bucket tables");
   }
@@ -670,6 +749,10 @@ static qtree::FwdArgs fwd_args(const qtree_plan* p, uint64_t m0, uint64_t M, uin
   a.total_tiles = p->unit_off[p->n];
   a.nd_samples = p->tune_nd_samples;
   a.bucketed = (p->buckets > 0 && p->tune_buckets) ? 1 : 0;
+  if (p->cubes > 0 && p->tune_buckets) {
+    a.cubes = reinterpret_cast<const qtree::Cubes*>(p->ws + p->lay.cubes);
+    a.cube_rows = reinterpret_cast<const uint4*>(p->ws + p->lay.cube_rows);
+  }
   a.bk.rows = reinterpret_cast<const uint4*>(p->ws + p->lay.bk_rows);
   a.bk.longs = reinterpret_cast<const uint4*>(p->ws + p->lay.bk_long);
   return a;

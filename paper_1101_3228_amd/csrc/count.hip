@@ -45,6 +45,7 @@ constexpr int kSamplesNd2 = 8;
 // the two): the first-group reads of all 2 S searches of a round are in
 // flight together, so S sets the registers and the overlap of LDS reads
 constexpr int kBkSamplesLo = 1, kBkSamplesHi = 2;
+constexpr int kCubeSamples = 2;  // samples per lane and round of the bucketed d = 3 search
 constexpr int kStageLoads = 4;  // grid records in flight per lane while staging (bucketed)
 constexpr int kCountBlock = 1024;
 constexpr int kGuideSub = 4;         // sub-counters per tile in the guide kernel's sort
@@ -70,6 +71,8 @@ struct KeysJob {
   uint16_t* keys;  // kChunk slots of this chunk
   uint32_t* seg;   // T + 1 segment starts of this chunk
   BucketTab bk;          // d = 2 bucket rows (bucketed search only)
+  const Cubes *C0, *C1;  // d = 3: the layers' tables and their rows
+  const uint4* cube_rows;
   int nd_sub;            // d >= 2: sub-counters per tile in the sort (kNdSub or 1)
 };
 
@@ -402,9 +405,11 @@ __device__ __forceinline__ void keys_chunk_nd(const KeysJob& j, float4* lds4) {
   const LayerDev& L0 = *j.L0;
   const LayerDev& L1 = *j.L1;
   const int N0 = L0.N, N1 = L0.N1, T = L0.tiles;
-  // both grids padded to whole scan tiles with records whose key is +inf
-  const int P0 = (N0 + kScanTile - 1) / kScanTile * kScanTile;
-  const int P1 = (N1 + kScanTile - 1) / kScanTile * kScanTile;
+  // both grids padded to whole scan tiles with records whose key is +inf (one
+  // at least where bucket rows name it)
+  constexpr int kPad = BK && D == 3 ? kScanTile : kScanTile - 1;
+  const int P0 = (N0 + kPad) / kScanTile * kScanTile;
+  const int P1 = (N1 + kPad) / kScanTile * kScanTile;
   // the scan: 16-byte records (x, .., h); the bucketed search: (x, y)
   // pairs and the pad pair at N, each layer's block a whole number of 16
   // bytes
@@ -476,6 +481,12 @@ __device__ __forceinline__ void keys_chunk_nd(const KeysJob& j, float4* lds4) {
         ii[s] = cell_index(ii[s]);
         jj[s] = cell_index(jj[s]);
       }
+    } else if constexpr (BK) {
+      uint4 wx[S][2], wy[S][2];
+      cube_rows<S>(*j.C0, j.cube_rows, xs, wx);
+      cube_rows<S>(*j.C1, j.cube_rows, ys, wy);
+      cube_cells<S>(*j.C0, gk, xs, wx, ii);
+      cube_cells<S>(*j.C1, gk1, ys, wy, jj);
     } else {
       argmin_scan_tiled<D, S, kNdTile>(gk, P0, xs, ii);
       argmin_scan_tiled<D, S, kNdTile>(gk1, P1, ys, jj);
@@ -639,6 +650,9 @@ __device__ __forceinline__ KeysJob plan_job(const FwdArgs& a, int k, int c) {
   j.keys = a.keys + ((size_t)k * a.chunks + c) * kChunk;
   j.seg = a.segs + ((size_t)k * a.chunks + c) * a.seg_stride;
   j.bk = a.bk;
+  j.C0 = a.cubes ? a.cubes + k : nullptr;
+  j.C1 = a.cubes ? a.cubes + k + 1 : nullptr;
+  j.cube_rows = a.cube_rows;
   j.nd_sub = nd_subs(a.max_tiles);
   return j;
 }
@@ -666,6 +680,9 @@ __global__ __launch_bounds__(kBlock) void fwd_keys_1d_guide(FwdArgs a) {
   guide_chunk<kBlock, GK, S>(j, g);
 }
 
+// d = 3 with tables: 12 layers of 1000 points, 3 10^5 pairs per layer, 770 us
+// by the full scan (2 x 1000 records a sample, bound by the vector units) and
+// 110 us by the rows (two gathers of 32 bytes a sample, 60 VGPRs).
 template <int D, int S, bool BK = false>
 __global__ __launch_bounds__(kBlockNd) void fwd_keys_nd(FwdArgs a) {
   extern __shared__ float4 lds4[];
@@ -950,6 +967,11 @@ hipError_t launch_fwd_keys(const FwdArgs& a, hipStream_t s) {
     const size_t lds = keys_lds_nd(a.maxN, a.max_tiles);
     if ((e = allow_lds(fwd_keys_nd<2, kSamplesNd2>, lds)) != hipSuccess) return e;
     hipLaunchKernelGGL((fwd_keys_nd<2, kSamplesNd2>), keys_grid(a), dim3(kBlockNd), lds, s, a);
+  } else if (a.cubes && keys_lds_nd(a.maxN + kScanTile, a.max_tiles) <= 160 * 1024) {
+    const size_t lds = keys_lds_nd(a.maxN + kScanTile, a.max_tiles);
+    if ((e = allow_lds(fwd_keys_nd<3, kCubeSamples, true>, lds)) != hipSuccess) return e;
+    hipLaunchKernelGGL((fwd_keys_nd<3, kCubeSamples, true>), keys_grid(a), dim3(kBlockNd), lds, s,
+                       a);
   } else {
     const size_t lds = keys_lds_nd(a.maxN, a.max_tiles);
     if ((e = allow_lds(fwd_keys_nd<3, 4>, lds)) != hipSuccess) return e;

@@ -283,7 +283,7 @@ __global__ __launch_bounds__(kBlock) void walk_2d(FwdArgs a, Visits v) {
 
 // d = 2 without tables, d = 3: the full scan over the next layer's grid,
 // staged in LDS at every step (the whole block walks the layers together).
-template <int D, bool STORE>
+template <int D, bool STORE, bool BK = false>
 __global__ __launch_bounds__(kBlock) void walk_scan(FwdArgs a, Visits v) {
   extern __shared__ float4 g[];
   const uint64_t t = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -299,6 +299,7 @@ __global__ __launch_bounds__(kBlock) void walk_scan(FwdArgs a, Visits v) {
     const LayerDev& L1 = a.layers[k + 1];
     __syncthreads();
     for (int q = threadIdx.x; q < L1.N; q += kBlock) g[q] = a.pts[L1.pt_off + q];
+    if (BK && threadIdx.x == 0) g[L1.N] = make_float4(0.f, 0.f, 0.f, __builtin_huge_valf());
     __syncthreads();
     float e[D];
     if (D == 2) {
@@ -326,7 +327,13 @@ __global__ __launch_bounds__(kBlock) void walk_scan(FwdArgs a, Visits v) {
       y[0][r] = z;
     }
     int j;
-    argmin_scan<D, 1>(g, L1.N, y, &j);
+    if constexpr (BK && D == 3) {
+      uint4 w[1][2];
+      cube_rows<1>(a.cubes[k + 1], a.cube_rows, y, w);
+      cube_cells<1>(a.cubes[k + 1], g, y, w, &j);
+    } else {
+      argmin_scan<D, 1>(g, L1.N, y, &j);
+    }
     visit<STORE>(a, v, k, t, live, i, j);
     i = j;
 #pragma unroll
@@ -412,7 +419,8 @@ static hipError_t launch_walk(const FwdArgs& a, const Visits& v, hipStream_t s) 
     return hipGetLastError();
   }
   if (a.d == 2 && a.bucketed) return go(walk_2d, sizeof(float2) * (size_t)(a.maxN + 1));
-  const size_t lds = sizeof(float4) * (size_t)a.maxN;
+  const size_t lds = sizeof(float4) * (size_t)(a.maxN + 1);
+  if (a.d == 3 && a.cubes) return go(walk_scan<3, STORE, true>, lds);
   return a.d == 2 ? go(walk_scan<2, STORE>, lds) : go(walk_scan<3, STORE>, lds);
 }
 

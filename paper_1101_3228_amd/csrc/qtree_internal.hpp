@@ -109,6 +109,32 @@ inline int bucket_side(int N) {
   return b < 512 ? b : 512;
 }
 
+// d = 3 bucketed cell search of a layer (B[0] = 0: none), on the same rule: the
+// box from lo in B[0] x B[1] x B[2] buckets, bucket (i0, i1, i2) owns row
+// off + (i0 B[1] + i1) B[2] + i2 of kCubeRow entries: its candidate count, then
+// the candidates' indices in increasing order, then the pad N (a record whose
+// key is +inf); kCubeFull where they do not fit, and the full scan decides.
+struct Cubes {
+  float lo[3], scale[3];
+  int32_t B[3];
+  int32_t off;
+  int32_t N, pt_off;
+};
+constexpr int kCubeRow = 16;               // uint16 entries (32 bytes)
+constexpr int kCubeCap = kCubeRow - 1;
+constexpr uint16_t kCubeFull = 0xFFFF;
+constexpr int kCubeMinN = 2;               // smaller layers scan
+constexpr int kCubeTile = 4;               // B is a multiple of it
+constexpr int64_t kMaxCubes = 1ll << 23;   // rows of a plan (256 MB); later layers scan
+// Buckets per axis of a layer of N points: about 32 per point, at most 64 per
+// axis.  16 / 32 / 64 per point: 294 / 289 / 288 us for a 12-layer tree of
+// 1000 points and 3 10^5 pairs per layer (the full scan: 927 us).
+inline int cube_side(int N) {
+  int b = kCubeTile;
+  while ((double)b * b * b < 32.0 * N) b += kCubeTile;
+  return b < 64 ? b : 64;
+}
+
 // Workspace layout (byte offsets from the workspace base).
 struct WsLayout {
   size_t layers;   // LayerDev[n+1]
@@ -120,6 +146,8 @@ struct WsLayout {
                    // of the R = sum_{k<n} N_k count rows (banded stratified counts)
   size_t bk_rows;  // d == 2: uint16[buckets][kBucketRow] bucket rows (count, candidates)
   size_t bk_long;  // d == 2: uint16[long_rows][kLongRow] pool of longer rows
+  size_t cubes;    // d == 3: Cubes[n + 1], where the plan has tables
+  size_t cube_rows; // d == 3: uint16[buckets][kCubeRow]
   size_t path;     // uint16[n][path cells] cells of the pathwise mode
   size_t keys;     // uint16[n][batch chunks][kChunk] pass-A keys
   size_t segs;     // uint32[n][batch chunks][max tiles + 1] segment starts
@@ -182,6 +210,9 @@ struct FwdArgs {
   // d = 2 bucketed cell search (bucketed = 0: the full scan)
   int32_t bucketed;
   BucketTab bk;
+  // d = 3 bucketed cell search (null: the full scan)
+  const Cubes* cubes;
+  const uint4* cube_rows;
 };
 
 // Forward obstacle on the sum of the factors (see qtree_payoff_forward).
@@ -399,6 +430,9 @@ size_t lloyd_lds_bytes(int d, int N, int Npad, int P);
 hipError_t launch_bucket_build(const LayerDev* layers, int n_layers_total, int total_buckets,
                                const float4* pts, uint16_t* rows, uint16_t* longs,
                                hipStream_t s);
+// Rows of the d = 3 search of every layer, `total` of them.
+hipError_t launch_cube_build(const Cubes* cubes, int n_layers_total, int total, const float4* pts,
+                             uint16_t* rows, hipStream_t s);
 hipError_t launch_lloyd_records(const LloydArgs& a, hipStream_t s);
 hipError_t launch_lloyd_step(const LloydArgs& a, int blocks, hipStream_t s);
 // Moment-matching grids: exact integer moment sums of a device sample set,

@@ -351,6 +351,124 @@ __device__ __forceinline__ void bucket_argmin(const float2* __restrict__ g, int 
   for (int s = 0; s < S; ++s) idx[s] = cell_index(idx[s]);
 }
 
+// d = 3 cells by the layer's bucket tables (rows at Cubes): the first minimum
+// over the bucket's list, the full scan's cell.  g holds the layer's records
+// and, at N, a pad whose key is +inf and wins no comparison; the entries are
+// taken in groups of 4, 4 and 7 (cells of a product grid meet at most eight at
+// a time).  Outside the box, for NaN, in a full bucket and in a layer without
+// tables the scan over the N records decides.
+__device__ __forceinline__ float record_key(const float4& r, const float* x) {
+  return fmaf(-x[2], r.z, fmaf(-x[1], r.y, fmaf(-x[0], r.x, r.w)));
+}
+__device__ __forceinline__ int cube_of(const Cubes& C, const float* x) {
+  float f[3];
+  bool in = true;
+#pragma unroll
+  for (int r = 0; r < 3; ++r) {
+    f[r] = (x[r] - C.lo[r]) * C.scale[r];
+    in = in && f[r] >= 0.0f && f[r] < (float)C.B[r];
+  }
+  return in ? C.off + ((int)f[0] * C.B[1] + (int)f[1]) * C.B[2] + (int)f[2] : -1;
+}
+template <int E0, int E1>
+__device__ __forceinline__ void cube_group(const float4* g, const uint4* w, const float* x,
+                                           float& best, int& idx) {
+#pragma unroll
+  for (int e = E0; e < E1; ++e) {
+    const int p = bucket_entry(w[e >> 3], e & 7);
+    const float key = record_key(g[p], x);
+    const bool lt = key < best;
+    best = lt ? key : best;
+    idx = lt ? p : idx;
+  }
+}
+// The rows of S points (row 0 where there is none, so that the loads are not
+// under a branch), then their cells.
+template <int S>
+__device__ __forceinline__ void cube_rows(const Cubes& C, const uint4* rows, const float (*xs)[3],
+                                          uint4 (*w)[2]) {
+  int r[S];
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    r[s] = cube_of(C, xs[s]);
+    const uint4* row = rows + 2 * (size_t)max(r[s], 0);
+    w[s][0] = row[0];
+    w[s][1] = row[1];
+  }
+  const uint32_t pads = (uint32_t)C.N * 0x10001u;
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    w[s][0].x = r[s] < 0 ? pads | 0xFFFFu : w[s][0].x;
+    w[s][0].y = r[s] < 0 ? pads : w[s][0].y;
+    w[s][0].z = r[s] < 0 ? pads : w[s][0].z;
+  }
+}
+// The full scan for the lanes of `need`, one after the other, each by the
+// whole wave (the records split over its lanes): a lane scanning alone holds
+// its workgroup up for 15 us at N = 1100, the wave for less than one.
+__device__ __forceinline__ int wave_scan(const float4* g, int N, const float* x, uint64_t need,
+                                         int idx) {
+  const int lane = (int)(threadIdx.x & 63);
+  while (need) {
+    const int from = __ffsll((unsigned long long)need) - 1;
+    need &= need - 1;
+    const float q[3] = {__shfl(x[0], from, 64), __shfl(x[1], from, 64), __shfl(x[2], from, 64)};
+    float best = __builtin_huge_valf();
+    int at = 0x7FFFFFFF;
+#pragma unroll 2
+    for (int p = lane; p < N; p += 64) {
+      const float key = record_key(g[p], q);
+      const bool lt = key < best;
+      best = lt ? key : best;
+      at = lt ? p : at;
+    }
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const float o = __shfl_xor(best, off, 64);
+      const int oat = __shfl_xor(at, off, 64);
+      const bool lt = o < best || (o == best && oat < at);
+      best = lt ? o : best;
+      at = lt ? oat : at;
+    }
+    if (at == 0x7FFFFFFF) at = 0;  // no key below +inf
+    idx = lane == from ? at : idx;
+  }
+  return idx;
+}
+constexpr int kWaveScans = 16;  // more lanes than this scan side by side
+// (All lanes of the wave come here together.)
+template <int S>
+__device__ __forceinline__ void cube_cells(const Cubes& C, const float4* g, const float (*xs)[3],
+                                           const uint4 (*w)[2], int* idx) {
+  const int N = C.N;
+  if (C.B[0] == 0) {  // the layer has no tables
+    argmin_scan<3, S>(g, N, xs, idx);
+    return;
+  }
+  float best[S];
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    best[s] = __builtin_huge_valf();
+    idx[s] = 0;
+    cube_group<1, 5>(g, w[s], xs[s], best[s], idx[s]);
+  }
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    const uint32_t c = w[s][0].x & 0xFFFFu;
+    if (c > 4 && c != kCubeFull) {
+      cube_group<5, 9>(g, w[s], xs[s], best[s], idx[s]);
+      if (c > 8) cube_group<9, 16>(g, w[s], xs[s], best[s], idx[s]);
+    }
+    const uint64_t need = __ballot(c == kCubeFull);
+    if (need == 0) continue;
+    if (__popcll(need) <= kWaveScans) {
+      idx[s] = wave_scan(g, N, xs[s], need, idx[s]);
+    } else if (c == kCubeFull) {
+      argmin_scan<3, 1>(g, N, xs + s, idx + s);
+    }
+  }
+}
+
 // Standard normals z (for X_k) and eps (for the innovation) of LAYERWISE
 // sample m of layer k.  Philox counter (block, k, contract, tag): d = 1 uses
 // block m >> 1 and the Box-Muller pair m & 1; d = 2 block m; d = 3 blocks

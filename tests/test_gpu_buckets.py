@@ -162,3 +162,61 @@ def test_lists_of_many_candidates(case):
     assert np.array_equal(plan.transitions(30_001, 9).cpu().numpy(), ref)
     ref = O.transitions(_omodel(spec), grid, N, 30_001, seed=9, mode=1, nthreads=8)
     assert np.array_equal(plan.transitions(30_001, 9, mode=qt.PATHWISE).cpu().numpy(), ref)
+
+
+def _grid_3d(case, rng):
+    if case == "product":  # eight cells meet at a corner
+        a, b, c = qt.gauss_quantizer(7), qt.gauss_quantizer(8), qt.gauss_quantizer(9)
+        return np.stack(np.meshgrid(a, b, c, indexing="ij"), -1).reshape(-1, 3)
+    if case == "sphere":  # more than fifteen cells meet in the centre: the full scan
+        g = rng.standard_normal((40, 3))
+        return g / np.linalg.norm(g, axis=1, keepdims=True)
+    if case == "piles":  # exact ties, lists up to the row's fifteen and beyond
+        c = rng.standard_normal((10, 3))
+        g = np.repeat(c, [1, 2, 3, 4, 5, 8, 14, 15, 16, 70], axis=0)
+        return g[rng.permutation(len(g))]
+    if case == "plane":
+        g = rng.standard_normal((150, 3))
+        g[:, 2] = 0.25
+        return g
+    return rng.standard_normal((int(case), 3))
+
+
+@pytest.mark.parametrize("case", ["product", "sphere", "piles", "plane", "2", "17", "1100"])
+def test_3d_tables_equal_full_scan_and_oracle(case):
+    """d = 3 counts, layerwise and pathwise, with the tables on and off."""
+    _case(f"3-D tables {case}")
+    g = _grid_3d(case, np.random.default_rng(5)).astype(np.float32)
+    spec = synth.bm_model(3, 3, T=1.0, rho=0.3)
+    grid = np.concatenate([np.zeros((1, 3), np.float32), g, 2.0 * g, g[: len(g) // 2 + 1]])
+    N = np.array([1, len(g), len(g), len(g) // 2 + 1], np.int32)
+    plan = qt.Plan(spec, grid, N)
+    M = 30_011
+    for mode in (0, qt.PATHWISE):
+        ref = O.transitions(_omodel(spec), grid, N, M, seed=9, mode=mode, nthreads=8)
+        for on in (1, 0):
+            plan.tune(buckets=on)
+            got = plan.transitions(M, 9, mode=mode).cpu().numpy()
+            assert np.array_equal(got, ref), (mode, on)
+    plan.tune(buckets=1)
+
+
+def test_3d_plan_in_a_workspace_without_room_for_tables(monkeypatch):
+    """The layers' records and one chunk per layer alone (no tables, no
+    pathwise scratch) still give the same counts."""
+    _case("3-D workspace without tables")
+    rng = np.random.default_rng(6)
+    g = rng.standard_normal((60, 3)).astype(np.float32)
+    spec = synth.bm_model(3, 2, T=1.0)
+    grid = np.concatenate([np.zeros((1, 3), np.float32), g, g])
+    N = np.array([1, 60, 60], np.int32)
+    M = 20_001
+    ref = O.transitions(_omodel(spec), grid, N, M, seed=4, nthreads=8)
+    full = qt.Plan(spec, grid, N)
+    assert np.array_equal(full.transitions(M, 4).cpu().numpy(), ref)
+    monkeypatch.setattr(qt, "workspace_size", lambda *args: 64 * 1024)
+    small = qt.Plan(spec, grid, N)
+    assert small.batch_samples > 0
+    assert np.array_equal(small.transitions(M, 4).cpu().numpy(), ref)
+    assert np.array_equal(small.transitions(M, 4, mode=qt.PATHWISE).cpu().numpy(),
+                          full.transitions(M, 4, mode=qt.PATHWISE).cpu().numpy())
