@@ -15,6 +15,7 @@ namespace {
 constexpr int kBlock = 256;
 constexpr int kPay = 16;     // payoffs per pass: the columns of a matrix-core tile
 constexpr int kRows = 16;    // rows per workgroup: the rows of a tile
+constexpr int kLayerWaves = 8;
 constexpr int kFewPay = 2;   // payoffs a pass of the few-payoff path takes
 constexpr int kFewRows = 4;  // ... and rows per workgroup
 constexpr int kFewWaves = 4;
@@ -36,9 +37,9 @@ struct TileRows {
 //
 // What bounds a layer is the latency of one launch: counts and values are
 // one round trip, and nothing is reduced across lanes.  N = 500, 12
-// payoffs: 5.2 us a layer, against 14.0 when a wave walked one row and
-// reduced its 16 sums over the lanes with about 200 shuffles; N = 256: 4.2
-// against 12.1; N = 2000: 14.7 against 39.8.
+// payoffs: 4.7 us a layer, against 14.0 when a wave walked one row and
+// reduced its 16 sums over the lanes with about 200 shuffles; N = 256: 3.8
+// against 12.1; N = 2000: 13.0 against 39.8.
 template <int W, int AHEAD, bool DENSE>
 __device__ __forceinline__ bool tile_sums(const TileRows& R, const double* __restrict__ x, int n1,
                                           double& sum, int64_t& total) {
@@ -204,10 +205,9 @@ __device__ __forceinline__ bool few_sums(const int32_t* __restrict__ rows, int n
 // One layer for every payoff: workgroup (x, y) takes rows 16 x .. + 15 and
 // payoffs 16 y .. + 15 (the count rows are re-read per group of payoffs, from
 // L2 for all but the first).
-template <int W, int AHEAD, bool DENSE>
-__global__ __launch_bounds__(64 * W) void bdp_layer_kernel(BdpArgs a, int N_k, int N_k1,
-                                                           int64_t pt_k, int64_t pt_k1,
-                                                           int64_t cnt_k) {
+template <int AHEAD, bool DENSE>
+__global__ __launch_bounds__(64 * kLayerWaves) void bdp_layer_kernel(
+    BdpArgs a, int N_k, int N_k1, int64_t pt_k, int64_t pt_k1, int64_t cnt_k) {
   const int lane = threadIdx.x & 63;
   const int q0 = blockIdx.y * kPay;
   const int nq = (a.n_pay - q0) < kPay ? (a.n_pay - q0) : kPay;
@@ -239,7 +239,7 @@ __global__ __launch_bounds__(64 * W) void bdp_layer_kernel(BdpArgs a, int N_k, i
   const int q = lane & 15;
   double s;
   int64_t p;
-  if (!tile_sums<W, AHEAD, DENSE>(R, a.V + (int64_t)(q0 + (q < nq ? q : 0)) * a.P + pt_k1, N_k1,
+  if (!tile_sums<kLayerWaves, AHEAD, DENSE>(R, a.V + (int64_t)(q0 + (q < nq ? q : 0)) * a.P + pt_k1, N_k1,
                                   s, p))
     return;
   const int row = i0 + (int)(threadIdx.x >> 4), col = (int)(threadIdx.x & 15);
@@ -292,15 +292,22 @@ hipError_t launch_bdp_layer(const BdpArgs& a, int k, int N_k, int N_k1, int64_t 
     return hipGetLastError();
   }
   const dim3 grid((unsigned)((N_k + kRows - 1) / kRows), (unsigned)((a.n_pay + kPay - 1) / kPay));
-#define QTREE_BDP(W, DENSE)                                                                    \
-  hipLaunchKernelGGL((bdp_layer_kernel<W, 4, DENSE>), grid, dim3(64 * W), 0, s, a, N_k, N_k1, \
-                     pt_k, pt_k1, cnt_k)
-  // waves enough for a row to be in flight at once, up to 1024 columns
-  if (!dense) QTREE_BDP(8, false);
-  else if (N_k1 <= 256) QTREE_BDP(4, true);
-  else if (N_k1 <= 512) QTREE_BDP(8, true);
-  else QTREE_BDP(16, true);
-#undef QTREE_BDP
+  // kLayerWaves waves cover 128 columns at a time, one chunk each; two in
+  // flight per wave where a row is longer than two such turns.  More chunks
+  // or waves bring a row in sooner, but their registers and slots are what a
+  // sampling pass on another stream leaves free: four chunks (68 registers more)
+  // take 4.2 / 5.2 / 7.2 / 13.9 us at N = 256 / 500 / 1000 / 2000 against 3.8 /
+  // 4.7 / 6.8 / 13.0, and a 50-layer forward beside it 1.84 against 1.74 ms.
+  const dim3 block(64 * kLayerWaves);
+  if (!dense)
+    hipLaunchKernelGGL((bdp_layer_kernel<2, false>), grid, block, 0, s, a, N_k, N_k1, pt_k, pt_k1,
+                       cnt_k);
+  else if (N_k1 <= 2 * 16 * kLayerWaves)
+    hipLaunchKernelGGL((bdp_layer_kernel<1, true>), grid, block, 0, s, a, N_k, N_k1, pt_k, pt_k1,
+                       cnt_k);
+  else
+    hipLaunchKernelGGL((bdp_layer_kernel<2, true>), grid, block, 0, s, a, N_k, N_k1, pt_k, pt_k1,
+                       cnt_k);
   return hipGetLastError();
 }
 
@@ -318,7 +325,6 @@ hipError_t launch_copy_last_layer(const BdpArgs& a, int64_t pt_n, int N_n, hipSt
 // is one tile for the job's up to kPay payoffs; a batch whose jobs all have
 // at most kFewPay payoffs and no layer below four points cuts a task into
 // workgroups of kFewRows rows instead.
-constexpr int kStepWaves = 8;
 static_assert(kBdpTaskRows == kRows, "a task is one tile");
 static_assert(kBdpTaskRows % kFewRows == 0, "a task is whole few-payoff workgroups");
 
@@ -335,7 +341,7 @@ __global__ void bdp_batch_copy_kernel(const BdpJob* jobs) {
 }
 
 template <bool DENSE>
-__global__ __launch_bounds__(64 * kStepWaves) void bdp_step_kernel(const BdpTask* tasks) {
+__global__ __launch_bounds__(64 * kLayerWaves) void bdp_step_kernel(const BdpTask* tasks) {
   const BdpTask& T = tasks[blockIdx.x];
   const int lane = threadIdx.x & 63;
   const int n1 = T.n1, nrows = T.nrows, nq = T.nq;
@@ -348,7 +354,7 @@ __global__ __launch_bounds__(64 * kStepWaves) void bdp_step_kernel(const BdpTask
   const double* x = as_global(T.next) + (int64_t)(r < nq ? r : 0) * P;
   double s;
   int64_t p;
-  if (!tile_sums<kStepWaves, 4, DENSE>(R, x, n1, s, p)) return;
+  if (!tile_sums<kLayerWaves, 2, DENSE>(R, x, n1, s, p)) return;
   const int row = (int)(threadIdx.x >> 4), col = (int)(threadIdx.x & 15);
   if (row < nrows && col < nq) {
     const double cont = p > 0 ? s / (double)p : 0.0;
@@ -395,10 +401,10 @@ hipError_t launch_bdp_steps(const BdpJob* jobs, int n_jobs, int max_last, int ma
                          dim3(64 * kFewWaves), 0, s,
                          tasks + step_off[j]);
     else if (min_n1 >= 4)
-      hipLaunchKernelGGL(bdp_step_kernel<true>, dim3((unsigned)cnt), dim3(64 * kStepWaves), 0, s,
+      hipLaunchKernelGGL(bdp_step_kernel<true>, dim3((unsigned)cnt), dim3(64 * kLayerWaves), 0, s,
                          tasks + step_off[j]);
     else
-      hipLaunchKernelGGL(bdp_step_kernel<false>, dim3((unsigned)cnt), dim3(64 * kStepWaves), 0, s,
+      hipLaunchKernelGGL(bdp_step_kernel<false>, dim3((unsigned)cnt), dim3(64 * kLayerWaves), 0, s,
                          tasks + step_off[j]);
   }
   return hipGetLastError();
