@@ -677,7 +677,7 @@ def run_batch(args):
         "roofline": {"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK_SLOTS / 1e12,
                      "unit": "Tlane-slot/s", "frac": achieved / PEAK_SLOTS, "traffic": None,
                      "kernel": "whole step (batch_keys_nd + batch_keys_1d + batch_count + "
-                               "bdp_batch_kernel); the per-kernel split is in the profile"},
+                               "backward steps); the per-kernel split is in the profile"},
     }
     if not args.no_cpu_baseline:
         # the oracle on the host cores over a sample of the contracts: the
@@ -835,7 +835,7 @@ def run_c5(args):
         "tree_roofline": {"bound": "fp64", "achieved": tree_tflops, "peak": 78.6,
                           "unit": "TFLOP/s", "frac": tree_tflops / 78.6,
                           "kernel": "bdp_many_kernel (every tree in one launch, all "
-                                    "layers, 64 contracts per workgroup; FLOP = 2 x the "
+                                    "layers, 16 or 64 contracts per workgroup; FLOP = 2 x the "
                                     "multiply-adds inside the rows' nonzero bands, obstacles "
                                     "not counted)"},
         "with_fallback_options_per_s": blended,
@@ -846,7 +846,7 @@ def run_c5(args):
         "train_s": fit_s, "final_loss": hist[-1],
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": 2500.0, "unit": "TFLOP/s",
                      "frac": achieved / 2500.0, "traffic": None,
-                     "kernel": f"mlp_forward<{args.act_terms},false>"},
+                     "kernel": f"mlp_forward_pairs<{args.act_terms}>"},
         # what binds this kernel in practice: SiLU on the vector ALUs
         "valu_view": {"alg_slots_per_query": MLP_SLOTS_PER_QUERY,
                       "achieved": MLP_SLOTS_PER_QUERY * value / 1e12,
@@ -1096,7 +1096,8 @@ def run_nn(args):
         ms = e0.elapsed_time(e1) / args.steps
         out[f"N{Nn}"] = {"ms": ms, "searches_per_s": Q / (ms * 1e-3),
                          "paper_convention_gflops": 6.0 * Q * Nn / (ms * 1e-3) / 1e9}
-        slots = ALG_SLOTS_2D_POINT * Q * Nn / (ms * 1e-3)
+        # a bucketed search, priced with the one candidate that every list has
+        slots = (BUCKET_LOCATE + BUCKET_CAND) * Q / (ms * 1e-3)
     print(json.dumps({
         "metric": "brute-force 2-D nearest-neighbour searches/s", "value": out["N500"]["searches_per_s"],
         "unit": "searches/s", "n_gpus": 1, "steps": args.steps, "warmup": 1,
@@ -1106,9 +1107,8 @@ def run_nn(args):
         "runs": out, "paper_context_gtx480_s": {"N100": 0.09, "N250": 0.23, "N500": 0.41},
         "roofline": {"bound": "alu", "achieved": slots / 1e12, "peak": PEAK_SLOTS / 1e12,
                      "unit": "Tlane-slot/s", "frac": slots / PEAK_SLOTS, "traffic": None,
-                     "kernel": "cells_kernel<2> at N = 500 (3 lane-slots per query and "
-                               "grid point: 2 FMA + half of a 3-input min at its issue "
-                               "cost)"},
+                     "kernel": "cells_kernel<2, true> at N = 500 (30 lane-slots per query: "
+                               "the bucket and one candidate)"},
     }), flush=True)
 
 
@@ -1139,8 +1139,9 @@ def run_lloyd(args):
     ms = e0.elapsed_time(e1)
     dd = dist.cpu().numpy()
     value = M * steps / (ms * 1e-3)
-    # search + Philox + two Box-Muller + L z (4 fma)
-    alg = ALG_SLOTS_2D_POINT * N + PHILOX_CALL + 2 * BOX_MULLER + 4 * F
+    # Philox + two Box-Muller + L z (4 fma) + a bucketed search, priced with
+    # the one candidate that every list has
+    alg = PHILOX_CALL + 2 * BOX_MULLER + 4 * F + BUCKET_LOCATE + BUCKET_CAND
     out = {
         "metric": "Lloyd samples/s (grid optimization, eq. Qerr)", "value": value,
         "unit": "samples/s", "n_gpus": 1, "steps": steps, "warmup": 1, "ms_per_step": ms / steps,
@@ -1151,9 +1152,8 @@ def run_lloyd(args):
         "distortion_first_last": [float(dd[0]), float(dd[-1])],
         "roofline": {"bound": "alu", "achieved": alg * value / 1e12, "peak": PEAK_SLOTS / 1e12,
                      "unit": "Tlane-slot/s", "frac": alg * value / PEAK_SLOTS, "traffic": None,
-                     "kernel": f"lloyd_accum_kernel<2> ({ALG_SLOTS_2D_POINT} lane-slots per "
-                               f"sample and grid point + {alg - ALG_SLOTS_2D_POINT * N:.0f} per "
-                               "sample)"},
+                     "kernel": f"whole step ({alg} lane-slots per sample: its draw and a "
+                               "bucketed search of one candidate)"},
     }
     if not args.no_cpu_baseline:
         import oracle as O

@@ -282,7 +282,7 @@ typedef struct {
  *   V_n = phi_n,  V_k(i) = max(phi_k(i), sum_j pi^k_ij V_{k+1}(j)),
  * with phi_k the obstacle of qtree_payoff computed from the contract's
  * record where it is needed (never stored), and pi from qtree_pi; one
- * launch prices every contract (64 per workgroup, their value vectors
+ * launch prices every contract (16 or 64 per workgroup, their value vectors
  * resident on chip through all layers).  specs: device
  * qtree_payoff_spec[n_q] (not validated: non-finite parameters give
  * non-finite prices); V0: device double[n_q] output, V_0 of each contract.

@@ -693,7 +693,7 @@ qtree_status qtree_plan_create(const qtree_model* model, const float* grid, cons
   if (p.buckets > 0) {
     // the bucket rows, from the records just uploaded
     e = qtree::launch_bucket_build(
-        reinterpret_cast<const qtree::LayerDev*>(p.ws + p.lay.layers), n + 1, (int)p.buckets,
+        reinterpret_cast<const qtree::LayerDev*>(p.ws + p.lay.layers), n + 1, p.maxN, p.buckets,
         reinterpret_cast<const float4*>(p.ws + p.lay.points),
         reinterpret_cast<uint16_t*>(p.ws + p.lay.bk_rows),
         reinterpret_cast<uint16_t*>(p.ws + p.lay.bk_long), nullptr);

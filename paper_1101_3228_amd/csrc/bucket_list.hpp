@@ -68,4 +68,149 @@ __device__ __forceinline__ bool write_bucket_row(uint16_t* out, uint16_t* longs,
   return true;
 }
 
+// The rows of a tile of kListTile x kListTile buckets (i0, j0) .. of a layer,
+// by one workgroup.  One thread per bucket would loop over the N points twice,
+// and over its candidates' pairs (30 ms for 31 layers of 2000 points, 23 for 366
+// of 500; now 1.5 and 1.9 ms with everything else of a plan); here the
+// workgroup first lists the points that can win anywhere in the tile (a
+// bucket's limit is at most its tile's), in increasing index, and 16 lanes per
+// bucket then share those.  Per step of the grid optimizer (128 x 128
+// buckets, 500 points) 10 us; tiles of 8 x 8 and 4 lanes take 24, the corner
+// tests of the crowded buckets being the longest chain, and tiles of 2 x 2
+// read all points too often.
+// g: the layer's N records; list: LDS, [N].  Returns false in the lane whose
+// bucket's candidates did not fit.
+constexpr int kListTile = 4, kListThreads = 256;
+constexpr int kListBuckets = kListTile * kListTile;
+constexpr int kPerBucket = kListThreads / kListBuckets;
+constexpr int kTileCand = 64;  // candidates of a bucket before the corner test
+struct ListLds {
+  uint16_t cand[kListBuckets][kTileCand];
+  double red[4][kListThreads / 64];
+  int wave_n[kListThreads / 64];
+};
+__device__ __forceinline__ bool list_tile(float4* list, ListLds& lds, const float4* g, int N,
+                                          const float* lo, const float* scale, const int32_t* B,
+                                          int i0, int j0, uint16_t* rows, uint16_t* longs,
+                                          int pool) {
+  const int t = (int)threadIdx.x, lane = t & 63, wave = t >> 6;
+  const double w0 = 1.0 / (double)scale[0], w1 = 1.0 / (double)scale[1];
+  auto box_of = [&](int i, int j, int n) {
+    BucketBox b;
+    b.a0 = (double)lo[0] + (double)i * w0 - w0 / 64.0;
+    b.b0 = (double)lo[0] + (double)(i + n) * w0 + w0 / 64.0;
+    b.a1 = (double)lo[1] + (double)j * w1 - w1 / 64.0;
+    b.b1 = (double)lo[1] + (double)(j + n) * w1 + w1 / 64.0;
+    return b;
+  };
+  BucketBox tile = box_of(i0, j0, kListTile);
+  double U = __builtin_huge_val(), hmax = 0.0, G0 = 0.0, G1 = 0.0;
+  for (int p = t; p < N; p += kListThreads) {
+    const float4 q = g[p];
+    U = fmin(U, tile.far2(q.x, q.y));
+    hmax = fmax(hmax, (double)q.w);
+    G0 = fmax(G0, fabs((double)q.x));
+    G1 = fmax(G1, fabs((double)q.y));
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    U = fmin(U, __shfl_xor(U, off, 64));
+    hmax = fmax(hmax, __shfl_xor(hmax, off, 64));
+    G0 = fmax(G0, __shfl_xor(G0, off, 64));
+    G1 = fmax(G1, __shfl_xor(G1, off, 64));
+  }
+  if (lane == 0) {
+    lds.red[0][wave] = U;
+    lds.red[1][wave] = hmax;
+    lds.red[2][wave] = G0;
+    lds.red[3][wave] = G1;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kListThreads / 64; ++w) {
+    U = fmin(U, lds.red[0][w]);
+    hmax = fmax(hmax, lds.red[1][w]);
+    G0 = fmax(G0, lds.red[2][w]);
+    G1 = fmax(G1, lds.red[3][w]);
+  }
+  tile.set_error(hmax, G0, G1);
+  const double tile_thr = tile.limit(U);
+  int n = 0;
+  for (int p0 = 0; p0 < N; p0 += kListThreads) {
+    const int p = p0 + t;
+    float4 q = g[p < N ? p : 0];
+    const bool in = p < N && tile.near2(q.x, q.y) <= tile_thr;
+    const uint64_t mask = __ballot(in);
+    if (lane == 0) lds.wave_n[wave] = __popcll(mask);
+    __syncthreads();
+    int at = n + __popcll(mask & ((1ull << lane) - 1));
+#pragma unroll
+    for (int w = 0; w < kListThreads / 64; ++w) {
+      if (w < wave) at += lds.wave_n[w];
+      n += lds.wave_n[w];
+    }
+    if (in) {
+      q.z = __int_as_float(p);
+      list[at] = q;
+    }
+    __syncthreads();
+  }
+  const int b = t / kPerBucket, sub = t % kPerBucket;
+  const int bi = i0 + b / kListTile, bj = j0 + b % kListTile;
+  BucketBox box = box_of(bi, bj, 1);
+  box.set_error(hmax, G0, G1);
+  U = __builtin_huge_val();
+  float nx = list[0].x, ny = list[0].y;  // n >= 1: the point that sets the tile's U
+  for (int p = sub; p < n; p += kPerBucket) {
+    const float4 q = list[p];
+    const double d = box.far2(q.x, q.y);
+    nx = d < U ? q.x : nx;
+    ny = d < U ? q.y : ny;
+    U = fmin(U, d);
+  }
+#pragma unroll
+  for (int off = 1; off < kPerBucket; off <<= 1) {
+    const double o = __shfl_xor(U, off, 64);
+    const float ox = __shfl_xor(nx, off, 64), oy = __shfl_xor(ny, off, 64);
+    nx = o < U ? ox : nx;
+    ny = o < U ? oy : ny;
+    U = fmin(U, o);
+  }
+  // (on equal U the lanes may hold different points; each is a valid witness)
+  const double thr = box.limit(U);
+  constexpr uint64_t kGroup = ~0ull >> (64 - kPerBucket);
+  const int shift = lane & ~(kPerBucket - 1);
+  int c = 0;
+  for (int p0 = 0; p0 < n; p0 += kPerBucket) {
+    const float4 q = list[min(p0 + sub, n - 1)];
+    const bool in = p0 + sub < n && box.near2(q.x, q.y) <= thr && !box.beaten(q.x, q.y, nx, ny);
+    const uint64_t group = __ballot(in) >> shift & kGroup;
+    const int at = c + __popcll(group & ((1ull << sub) - 1));
+    if (in && at < kTileCand) lds.cand[b][at] = (uint16_t)(p0 + sub);
+    c += __popcll(group);
+  }
+  __syncthreads();
+  const int listed = c < kTileCand ? c : kTileCand;
+  uint64_t keep = 0;
+  for (int p = sub; p < listed; p += kPerBucket) {
+    const float4 gp = list[lds.cand[b][p]];
+    bool out = false;
+    for (int q = 0; q < listed && !out; ++q) {
+      const float4 gq = list[lds.cand[b][q]];
+      out = q != p && box.beaten(gp.x, gp.y, gq.x, gq.y);
+    }
+    keep |= out ? 0ull : 1ull << p;
+  }
+#pragma unroll
+  for (int off = 1; off < kPerBucket; off <<= 1) keep |= __shfl_xor(keep, off, 64);
+  if (sub != 0 || bi >= B[0] || bj >= B[1]) return true;
+  return write_bucket_row(rows + (int64_t)(bi * B[1] + bj) * kBucketRow, longs, pool, N,
+                          c <= kTileCand, __popcll(keep), [&](int) {
+                            // called in order
+                            const int p = __ffsll((unsigned long long)keep) - 1;
+                            keep &= keep - 1;
+                            return __float_as_int(list[lds.cand[b][p]].z);
+                          });
+}
+
 }  // namespace qtree

@@ -15,6 +15,8 @@
 // kept about 3.  R is the bucket widened by 1/64 of its width on every side,
 // more than the FP32 rounding of the bucket index can move a point.  FP64
 // throughout.  Rows as described at LayerDev.
+#include <algorithm>
+
 #include "bucket_list.hpp"
 
 namespace qtree {
@@ -23,76 +25,40 @@ namespace {
 constexpr int kBlock = 256;
 }
 
-__global__ __launch_bounds__(kBlock) void bucket_build_kernel(const LayerDev* layers, int nl,
-                                                              int total, const float4* pts,
-                                                              uint16_t* rows, uint16_t* longs,
-                                                              int pool) {
-  __shared__ uint16_t cand[kBlock][kLongCap];
-  const int t = (int)(blockIdx.x * kBlock + threadIdx.x);
-  if (t >= total) return;
-  int lo = 0, hi = nl - 1;  // the layer holding bucket t: largest k with bk_off_k <= t
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (layers[mid].bk_off <= t) lo = mid; else hi = mid - 1;
-  }
-  const LayerDev& L = layers[lo];
-  const int r = t - L.bk_off;
-  const int i = r / L.bk_B[1], j = r - i * L.bk_B[1];
-  const double w0 = 1.0 / (double)L.bk_scale[0], w1 = 1.0 / (double)L.bk_scale[1];
-  BucketBox box;
-  box.a0 = (double)L.bk_lo[0] + (double)i * w0 - w0 / 64.0;
-  box.b0 = (double)L.bk_lo[0] + (double)(i + 1) * w0 + w0 / 64.0;
-  box.a1 = (double)L.bk_lo[1] + (double)j * w1 - w1 / 64.0;
-  box.b1 = (double)L.bk_lo[1] + (double)(j + 1) * w1 + w1 / 64.0;
-  const float4* g = pts + L.pt_off;
-  double U = __builtin_huge_val(), hmax = 0.0, G0 = 0.0, G1 = 0.0;
-  float4 near = g[0];  // a point whose farthest corner distance is U
-  for (int p = 0; p < L.N; ++p) {
-    const float4 q = g[p];
-    const double d = box.far2(q.x, q.y);
-    near = d < U ? q : near;
-    U = fmin(U, d);
-    hmax = fmax(hmax, (double)q.w);
-    G0 = fmax(G0, fabs((double)q.x));
-    G1 = fmax(G1, fabs((double)q.y));
-  }
-  box.set_error(hmax, G0, G1);
-  const double thr = box.limit(U);
-  uint16_t* list = cand[threadIdx.x];
-  int c = 0;
-  for (int p = 0; p < L.N; ++p) {
-    const float4 q = g[p];
-    if (box.near2(q.x, q.y) <= thr && !box.beaten(q.x, q.y, near.x, near.y)) {
-      if (c < kLongCap) list[c] = (uint16_t)p;
-      ++c;
-    }
-  }
-  const int listed = c < kLongCap ? c : kLongCap;
-  int kept = 0;  // ends >= 1: the nearest point at some corner stays
-  uint32_t keep = 0;
-  for (int p = 0; p < listed; ++p) {
-    bool out = false;
-    for (int q = 0; q < listed; ++q) {
-      const float4 gp = g[list[p]], gq = g[list[q]];
-      out = out || (q != p && box.beaten(gp.x, gp.y, gq.x, gq.y));
-    }
-    keep |= out ? 0u : 1u << p;
-  }
-  for (int p = 0; p < listed; ++p)
-    if (keep >> p & 1) list[kept++] = list[p];
-  write_bucket_row(rows + (int64_t)t * kBucketRow, longs, pool, L.N, c <= kLongCap, kept,
-                   [&](int e) { return (int)list[e]; });
+// Workgroup (x, k): tile x of layer k.
+__global__ __launch_bounds__(kListThreads) void bucket_build_kernel(const LayerDev* layers,
+                                                                    const float4* pts,
+                                                                    uint16_t* rows,
+                                                                    uint16_t* longs, int pool) {
+  extern __shared__ float4 list[];
+  __shared__ ListLds lds;
+  const LayerDev& L = layers[blockIdx.y];
+  const int t0 = (L.bk_B[0] + kListTile - 1) / kListTile;
+  const int t1 = (L.bk_B[1] + kListTile - 1) / kListTile;
+  if ((int)blockIdx.x >= t0 * t1) return;
+  list_tile(list, lds, pts + L.pt_off, L.N, L.bk_lo, L.bk_scale, L.bk_B,
+            (int)blockIdx.x / t1 * kListTile, (int)blockIdx.x % t1 * kListTile,
+            rows + (int64_t)L.bk_off * kBucketRow, longs, pool);
 }
 
-hipError_t launch_bucket_build(const LayerDev* layers, int n_layers_total, int total_buckets,
-                               const float4* pts, uint16_t* rows, uint16_t* longs,
-                               hipStream_t s) {
+hipError_t launch_bucket_build(const LayerDev* layers, int n_layers_total, int maxN,
+                               int64_t total_buckets, const float4* pts, uint16_t* rows,
+                               uint16_t* longs, hipStream_t s) {
   if (total_buckets <= 0) return hipSuccess;
-  const hipError_t e = launch_zero_i32(reinterpret_cast<int32_t*>(longs), 1, s);
+  hipError_t e = launch_zero_i32(reinterpret_cast<int32_t*>(longs), 1, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(bucket_build_kernel, dim3((unsigned)((total_buckets + kBlock - 1) / kBlock)),
-                     dim3(kBlock), 0, s, layers, n_layers_total, total_buckets, pts, rows, longs,
-                     (int)long_rows(total_buckets));
+  const size_t lds = sizeof(float4) * (size_t)maxN;
+  if (lds + sizeof(ListLds) > 65536) {
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(bucket_build_kernel),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  const unsigned tiles = (unsigned)((bucket_side(maxN) + kListTile - 1) / kListTile);
+  for (int k0 = 0; k0 < n_layers_total; k0 += 65535) {
+    const unsigned layers_now = (unsigned)std::min(65535, n_layers_total - k0);
+    hipLaunchKernelGGL(bucket_build_kernel, dim3(tiles * tiles, layers_now), dim3(kListThreads),
+                       lds, s, layers + k0, pts, rows, longs, (int)long_rows(total_buckets));
+  }
   return hipGetLastError();
 }
 

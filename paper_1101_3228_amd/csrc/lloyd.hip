@@ -149,145 +149,17 @@ __global__ void lloyd_records_kernel(LloydArgs a) {
                       : make_float4(0.f, 0.f, 0.f, __builtin_huge_valf());
 }
 
-// Bucket tables of the current grid (candidate rule: buckets.hip).  They are
-// made anew in every step, so the N-point loops of one thread per bucket
-// (about 20 us at N = 500) are split: a workgroup takes a tile of 4 x 4
-// buckets and first lists the points that can win anywhere in the tile (a
-// bucket's limit is at most its tile's), in increasing index; 16 lanes per
-// bucket then share those.  (Tiles of 8 x 8 and 4 lanes: 24 us a step instead
-// of 10, the corner tests of the crowded buckets being the longest chain;
-// tiles of 2 x 2 read all points too often, 38 instead of 25 us for the
-// whole step.)  A bucket whose candidates fit nowhere is counted
-// in the pool's second word, and the step then scans: tables pay only where
-// they answer nearly every sample.
-constexpr int kTileSide = kLloydTile;
-constexpr int kPerBucket = kBlock / (kTileSide * kTileSide);
-constexpr int kTileCand = 64;  // candidates of a bucket before the corner test
-__global__ __launch_bounds__(kBlock) void lloyd_tables_kernel(LloydArgs a) {
-  extern __shared__ float4 list[];  // [N] the tile's points: x, y, index
-  __shared__ uint16_t cand[kTileSide * kTileSide][kTileCand];
-  __shared__ double red[4][kBlock / 64];
-  __shared__ int wave_n[kBlock / 64];
-  const int t = (int)threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int tiles = a.bk_B[1] / kTileSide;
-  const int i0 = (int)(blockIdx.x / tiles) * kTileSide, j0 = (int)(blockIdx.x % tiles) * kTileSide;
-  const double w0 = 1.0 / (double)a.bk_scale[0], w1 = 1.0 / (double)a.bk_scale[1];
-  auto box_of = [&](int i, int j, int n) {
-    BucketBox b;
-    b.a0 = (double)a.bk_lo[0] + (double)i * w0 - w0 / 64.0;
-    b.b0 = (double)a.bk_lo[0] + (double)(i + n) * w0 + w0 / 64.0;
-    b.a1 = (double)a.bk_lo[1] + (double)j * w1 - w1 / 64.0;
-    b.b1 = (double)a.bk_lo[1] + (double)(j + n) * w1 + w1 / 64.0;
-    return b;
-  };
-  BucketBox tile = box_of(i0, j0, kTileSide);
-  double U = __builtin_huge_val(), hmax = 0.0, G0 = 0.0, G1 = 0.0;
-  for (int p = t; p < a.N; p += kBlock) {
-    const float4 q = a.recs[p];
-    U = fmin(U, tile.far2(q.x, q.y));
-    hmax = fmax(hmax, (double)q.w);
-    G0 = fmax(G0, fabs((double)q.x));
-    G1 = fmax(G1, fabs((double)q.y));
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    U = fmin(U, __shfl_xor(U, off, 64));
-    hmax = fmax(hmax, __shfl_xor(hmax, off, 64));
-    G0 = fmax(G0, __shfl_xor(G0, off, 64));
-    G1 = fmax(G1, __shfl_xor(G1, off, 64));
-  }
-  if (lane == 0) {
-    red[0][wave] = U;
-    red[1][wave] = hmax;
-    red[2][wave] = G0;
-    red[3][wave] = G1;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int w = 0; w < kBlock / 64; ++w) {
-    U = fmin(U, red[0][w]);
-    hmax = fmax(hmax, red[1][w]);
-    G0 = fmax(G0, red[2][w]);
-    G1 = fmax(G1, red[3][w]);
-  }
-  tile.set_error(hmax, G0, G1);
-  const double tile_thr = tile.limit(U);
-  int n = 0;
-  for (int p0 = 0; p0 < a.N; p0 += kBlock) {
-    const int p = p0 + t;
-    float4 q = a.recs[p < a.N ? p : 0];
-    const bool in = p < a.N && tile.near2(q.x, q.y) <= tile_thr;
-    const uint64_t mask = __ballot(in);
-    if (lane == 0) wave_n[wave] = __popcll(mask);
-    __syncthreads();
-    int at = n + __popcll(mask & ((1ull << lane) - 1));
-#pragma unroll
-    for (int w = 0; w < kBlock / 64; ++w) {
-      if (w < wave) at += wave_n[w];
-      n += wave_n[w];
-    }
-    if (in) {
-      q.z = __int_as_float(p);
-      list[at] = q;
-    }
-    __syncthreads();
-  }
-  const int b = t / kPerBucket, sub = t % kPerBucket;
-  const int bi = i0 + b / kTileSide, bj = j0 + b % kTileSide;
-  BucketBox box = box_of(bi, bj, 1);
-  box.set_error(hmax, G0, G1);
-  U = __builtin_huge_val();
-  float nx = list[0].x, ny = list[0].y;  // n >= 1: the point that sets the tile's U
-  for (int p = sub; p < n; p += kPerBucket) {
-    const float4 q = list[p];
-    const double d = box.far2(q.x, q.y);
-    nx = d < U ? q.x : nx;
-    ny = d < U ? q.y : ny;
-    U = fmin(U, d);
-  }
-#pragma unroll
-  for (int off = 1; off < kPerBucket; off <<= 1) {
-    const double o = __shfl_xor(U, off, 64);
-    const float ox = __shfl_xor(nx, off, 64), oy = __shfl_xor(ny, off, 64);
-    nx = o < U ? ox : nx;
-    ny = o < U ? oy : ny;
-    U = fmin(U, o);
-  }
-  // (on equal U the lanes may hold different points; each is a valid witness)
-  const double thr = box.limit(U);
-  constexpr uint64_t kGroup = ~0ull >> (64 - kPerBucket);
-  const int shift = lane & ~(kPerBucket - 1);
-  int c = 0;
-  for (int p0 = 0; p0 < n; p0 += kPerBucket) {
-    const float4 q = list[min(p0 + sub, n - 1)];
-    const bool in = p0 + sub < n && box.near2(q.x, q.y) <= thr && !box.beaten(q.x, q.y, nx, ny);
-    const uint64_t group = __ballot(in) >> shift & kGroup;
-    const int at = c + __popcll(group & ((1ull << sub) - 1));
-    if (in && at < kTileCand) cand[b][at] = (uint16_t)(p0 + sub);
-    c += __popcll(group);
-  }
-  __syncthreads();
-  const int listed = c < kTileCand ? c : kTileCand;
-  uint64_t keep = 0;
-  for (int p = sub; p < listed; p += kPerBucket) {
-    const float4 gp = list[cand[b][p]];
-    bool out = false;
-    for (int q = 0; q < listed && !out; ++q) {
-      const float4 gq = list[cand[b][q]];
-      out = q != p && box.beaten(gp.x, gp.y, gq.x, gq.y);
-    }
-    keep |= out ? 0ull : 1ull << p;
-  }
-#pragma unroll
-  for (int off = 1; off < kPerBucket; off <<= 1) keep |= __shfl_xor(keep, off, 64);
-  if (sub != 0) return;
-  const bool ok = write_bucket_row(
-      a.bk_rows + (size_t)(bi * a.bk_B[1] + bj) * kBucketRow, a.bk_longs, a.bk_pool, a.N,
-      c <= kTileCand, __popcll(keep), [&](int) {
-        const int p = __ffsll((unsigned long long)keep) - 1;  // called in order
-        keep &= keep - 1;
-        return __float_as_int(list[cand[b][p]].z);
-      });
+// Bucket tables of the current grid.  A bucket whose candidates fit nowhere is
+// counted in the pool's second word, and the step then scans: tables pay only
+// where they answer nearly every sample.
+__global__ __launch_bounds__(kListThreads) void lloyd_tables_kernel(LloydArgs a) {
+  extern __shared__ float4 list[];  // [N]
+  __shared__ ListLds lds;
+  const int tiles = (a.bk_B[1] + kListTile - 1) / kListTile;
+  const bool ok = list_tile(list, lds, a.recs, a.N, a.bk_lo, a.bk_scale, a.bk_B,
+                            (int)(blockIdx.x / tiles) * kListTile,
+                            (int)(blockIdx.x % tiles) * kListTile, a.bk_rows, a.bk_longs,
+                            a.bk_pool);
   if (!ok) atomicAdd(reinterpret_cast<uint32_t*>(a.bk_longs) + 1, 1u);
 }
 
@@ -532,8 +404,8 @@ hipError_t launch_lloyd_step(const LloydArgs& a, int blocks, hipStream_t s) {
   const bool set = a.xs != nullptr;
   hipError_t e;
   if (wide) {
-    const int tiles = a.bk_B[0] / kTileSide;
-    hipLaunchKernelGGL(lloyd_tables_kernel, dim3(tiles * tiles), dim3(kBlock),
+    const int tiles = (a.bk_B[0] + kListTile - 1) / kListTile;
+    hipLaunchKernelGGL(lloyd_tables_kernel, dim3(tiles * tiles), dim3(kListThreads),
                        sizeof(float4) * a.N, s, a);
     e = launch_accum(lloyd_accum_wide_kernel, a, blocks, kLloydWideThreads, lds, s);
   } else if (a.d == 1) {

@@ -413,23 +413,22 @@ constexpr int kLloydMaxBlocks = 512;  // accumulation workgroups per step at mos
 // the place of the other half of their partials.
 constexpr int kLloydMaxWide = kLloydMaxBlocks / 2;
 constexpr int kLloydWideThreads = 1024, kLloydWideSamples = 2;  // samples per thread and round
-constexpr int kLloydTile = 4;
-// Buckets per side, a multiple of kLloydTile: about 32 per point over the
+// Buckets per side, a multiple of 4: about 32 per point over the
 // samples' whole box (a fifth of them where the points are), at most 192.
 // More make the lists short and the corner tests few, but all have to be
 // filled in every step: 8 / 16 / 32 / 64 per point take 32 / 25 / 23 / 27 us a
 // step at N = 500 and 10^5 samples, and at N = 2048 42 / 42 / 54 / 87.
 inline int lloyd_side(int N) {
-  int b = kLloydTile;
-  while ((double)b * b < 32.0 * N) b += kLloydTile;
+  int b = 4;
+  while ((double)b * b < 32.0 * N) b += 4;
   return b < 192 ? b : 192;
 }
 size_t lloyd_lds_bytes(int d, int N, int Npad, int P);
 // Bucket rows of the d = 2 bucketed cell search of every layer (records
 // and LayerDev already in the workspace).
-hipError_t launch_bucket_build(const LayerDev* layers, int n_layers_total, int total_buckets,
-                               const float4* pts, uint16_t* rows, uint16_t* longs,
-                               hipStream_t s);
+hipError_t launch_bucket_build(const LayerDev* layers, int n_layers_total, int maxN,
+                               int64_t total_buckets, const float4* pts, uint16_t* rows,
+                               uint16_t* longs, hipStream_t s);
 // Rows of the d = 3 search of every layer, `total` of them.
 hipError_t launch_cube_build(const Cubes* cubes, int n_layers_total, int total, const float4* pts,
                              uint16_t* rows, hipStream_t s);
