@@ -71,7 +71,7 @@ __device__ __forceinline__ bool write_bucket_row(uint16_t* out, uint16_t* longs,
 // The rows of a tile of kListTile x kListTile buckets (i0, j0) .. of a layer,
 // by one workgroup.  One thread per bucket would loop over the N points twice,
 // and over its candidates' pairs (30 ms for 31 layers of 2000 points, 23 for 366
-// of 500; now 1.5 and 1.9 ms with everything else of a plan); here the
+// of 500; a whole plan of them now takes 1.9 and 2.6 ms); here the
 // workgroup first lists the points that can win anywhere in the tile (a
 // bucket's limit is at most its tile's), in increasing index, and 16 lanes per
 // bucket then share those.  Per step of the grid optimizer (128 x 128

@@ -66,7 +66,7 @@ hipError_t launch_bucket_build(const LayerDev* layers, int n_layers_total, int m
 // box has tens of thousands of buckets, a workgroup takes a tile of 4 x 4 x 4 of
 // them, first lists the points that can win anywhere in the tile (a bucket's
 // limit is at most its tile's), in increasing index, and 4 lanes per bucket
-// then share those (12 layers of 1000 points, 5.6 10^5 buckets: 0.27 ms).
+// then share those (12 layers of 990 points, 5.6 10^5 buckets: 0.27 ms).
 namespace {
 struct CubeBox {
   double a[3], b[3], E;

@@ -2,6 +2,7 @@
 // launch sequences of inference and training.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <string>
 #include <vector>
@@ -58,6 +59,13 @@ MlpLayout mlp_layout(int64_t max_batch) {
     L.usum = take(4 * tiles * M::kHid * M::kUnitSums);
     L.tsum = take(4 * tiles * 2);
     L.part = take(4 * 2 * (size_t)(bp / M::kChunk) * M::kHid * M::kHid);
+    // the size callers have known, from when z1..z3 and dz1..dz3 were stored
+    // in FP32: what was large enough stays so, what was too small too
+    size_t known = L.h1;
+    for (size_t bytes : {12 * per, 4 * per, 12 * per, 32 * (size_t)bp, 4 * (size_t)bp, 4 * tiles,
+                         (size_t)(bp / M::kChunk) * 8 * M::kHid * M::kHid})
+      known = align_up(known + bytes, 256);
+    off = std::max(off, known);
   }
   L.total = off;
   return L;

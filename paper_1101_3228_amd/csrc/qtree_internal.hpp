@@ -128,7 +128,7 @@ constexpr int kCubeTile = 4;               // B is a multiple of it
 constexpr int64_t kMaxCubes = 1ll << 23;   // rows of a plan (256 MB); later layers scan
 // Buckets per axis of a layer of N points: about 32 per point, at most 64 per
 // axis.  16 / 32 / 64 per point: 294 / 289 / 288 us for a 12-layer tree of
-// 1000 points and 3 10^5 pairs per layer (the full scan: 927 us).
+// 990 points and 3 10^5 pairs per layer (the full scan: 927 us).
 inline int cube_side(int N) {
   int b = kCubeTile;
   while ((double)b * b * b < 32.0 * N) b += kCubeTile;

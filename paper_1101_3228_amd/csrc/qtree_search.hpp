@@ -405,7 +405,7 @@ __device__ __forceinline__ void cube_rows(const Cubes& C, const uint4* rows, con
 }
 // The full scan for the lanes of `need`, one after the other, each by the
 // whole wave (the records split over its lanes): a lane scanning alone holds
-// its workgroup up for 15 us at N = 1100, the wave for less than one.
+// its workgroup up for 15 us at N = 990, the wave for less than one.
 __device__ __forceinline__ int wave_scan(const float4* g, int N, const float* x, uint64_t need,
                                          int idx) {
   const int lane = (int)(threadIdx.x & 63);
