@@ -5,10 +5,12 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cfloat>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -28,6 +30,64 @@ qtree_status fail(qtree_status s, const std::string& msg) {
 }  // namespace
 
 namespace qtree {
+
+namespace {
+std::atomic<double*> g_slots{nullptr};
+std::atomic<uint32_t> g_slots_taken{0};
+std::mutex g_slots_lock;
+}  // namespace
+
+void HostSlot::reserve() {
+  if (g_slots.load(std::memory_order_acquire)) return;
+  std::lock_guard<std::mutex> hold(g_slots_lock);
+  if (g_slots.load(std::memory_order_relaxed)) return;
+  void* p = nullptr;
+  if (hipHostMalloc(&p, sizeof(double) * kDoubles * kSlots, hipHostMallocPortable) != hipSuccess) {
+    (void)hipGetLastError();  // calls copy without it
+    return;
+  }
+  g_slots.store(static_cast<double*>(p), std::memory_order_release);
+}
+
+HostSlot::HostSlot(int64_t n) {
+  double* base = g_slots.load(std::memory_order_acquire);
+  if (!base || n > kDoubles) return;
+  uint32_t taken = g_slots_taken.load(std::memory_order_relaxed);
+  for (;;) {
+    const uint32_t free_mask = ~taken & ((1u << kSlots) - 1u);
+    if (free_mask == 0) return;
+    const int i = __builtin_ctz(free_mask);
+    if (g_slots_taken.compare_exchange_weak(taken, taken | 1u << i, std::memory_order_acquire)) {
+      i_ = i;
+      p_ = base + kDoubles * i;
+      return;
+    }
+  }
+}
+
+HostSlot::~HostSlot() {
+  if (i_ >= 0) g_slots_taken.fetch_and(~(1u << i_), std::memory_order_release);
+}
+
+hipError_t HostSlot::finish(double* out, int64_t n, hipStream_t s) {
+  const hipError_t e = hipStreamSynchronize(s);
+  if (e == hipSuccess) std::memcpy(out, p_, sizeof(double) * (size_t)n);
+  else i_ = -1;
+  return e;
+}
+
+hipError_t results_to_host(const double* V, int64_t stride, int64_t n, double* out,
+                           hipStream_t s) {
+  HostSlot slot(n);
+  if (slot.ptr()) {
+    const hipError_t e = launch_v0(V, stride, (int)n, slot.ptr(), s);
+    return e == hipSuccess ? slot.finish(out, n, s) : e;
+  }
+  const hipError_t e =
+      hipMemcpy2DAsync(out, sizeof(double), V, sizeof(double) * (size_t)stride, sizeof(double),
+                       (size_t)n, hipMemcpyDeviceToHost, s);
+  return e == hipSuccess ? hipStreamSynchronize(s) : e;
+}
 qtree_status set_error(qtree_status s, const std::string& msg) { return fail(s, msg); }
 }  // namespace qtree
 
@@ -690,6 +750,7 @@ qtree_status qtree_plan_create(const qtree_model* model, const float* grid, cons
   hipError_t e = hipMemcpy(workspace, img.data(), img.size(), hipMemcpyHostToDevice);
   if (e != hipSuccess) return hip_fail(e, "hipMemcpy(workspace)");
   p.ws = static_cast<char*>(workspace);
+  qtree::HostSlot::reserve();
   if (p.buckets > 0) {
     // the bucket rows, from the records just uploaded
     e = qtree::launch_bucket_build(
@@ -1431,11 +1492,8 @@ static qtree_status bdp_impl(const qtree_plan* plan, const int32_t* counts, cons
     if (e != hipSuccess) return hip_fail(e, "bdp launch");
   }
   if (V0_host) {
-    e = hipMemcpy2DAsync(V0_host, sizeof(double), V, sizeof(double) * (size_t)plan->points,
-                         sizeof(double), (size_t)n_pay, hipMemcpyDeviceToHost, s);
+    e = qtree::results_to_host(V, plan->points, n_pay, V0_host, s);
     if (e != hipSuccess) return hip_fail(e, "V0 copy");
-    e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return hip_fail(e, "stream synchronize");
   }
   return QTREE_OK;
 }
@@ -1714,8 +1772,7 @@ qtree_status qtree_swing(const qtree_plan* plan, const int32_t* counts, const do
   hipError_t e = qtree::launch_swing(a, plan->N.data(), s);
   if (e != hipSuccess) return hip_fail(e, "swing launch");
   if (P0_host) {
-    e = hipMemcpyAsync(P0_host, P, sizeof(double), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    e = qtree::results_to_host(P, 1, 1, P0_host, s);
     if (e != hipSuccess) return hip_fail(e, "swing P0 copy");
   }
   return QTREE_OK;

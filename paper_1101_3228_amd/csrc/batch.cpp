@@ -427,6 +427,7 @@ qtree_status qtree_batch_plan(const qtree_contract* contracts, int32_t n, qtree_
       j.n = p->n;
       j.q0 = q0;
       j.nq = std::min(16, C.n_pay - q0);
+      j.v0_at = (int32_t)std::min<int64_t>(v0_off + q0, qtree::HostSlot::kDoubles);
       b->jobs.push_back(j);
       job_contract.push_back(i);
       b->max_last = std::max(b->max_last, j.nq * p->N[p->n]);
@@ -666,6 +667,12 @@ qtree_status qtree_batch_run(qtree_batch* b, double* V0_host, void* stream) {
     }
   }
   if (V0_host) {
+    qtree::HostSlot slot(b->n_v0);
+    if (slot.ptr() && !b->jobs.empty()) {
+      e = qtree::launch_v0_jobs(b->d_jobs, (int)b->jobs.size(), slot.ptr(), s);
+      if (e == hipSuccess) e = slot.finish(V0_host, b->n_v0, s);
+      return e == hipSuccess ? QTREE_OK : hip_error(e, "V0 copy");
+    }
     int64_t at = 0;
     for (const qtree_contract& C : b->c) {
       e = hipMemcpy2DAsync(V0_host + at, sizeof(double), C.V,

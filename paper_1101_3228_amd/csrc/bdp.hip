@@ -311,6 +311,27 @@ hipError_t launch_bdp_layer(const BdpArgs& a, int k, int N_k, int N_k1, int64_t 
   return hipGetLastError();
 }
 
+// Results of layer 0 to `out` in pinned host memory: V[q stride], or of the jobs
+// of a batch.
+__global__ void v0_kernel(const double* V, int64_t stride, int n, double* out) {
+  for (int q = threadIdx.x; q < n; q += blockDim.x) out[q] = V[(int64_t)q * stride];
+}
+__global__ void v0_jobs_kernel(const BdpJob* jobs, double* out) {
+  const BdpJob& J = jobs[blockIdx.x];
+  if ((int)threadIdx.x < J.nq)
+    out[J.v0_at + (int)threadIdx.x] = as_global(J.V)[(int64_t)(J.q0 + (int)threadIdx.x) * J.P];
+}
+
+hipError_t launch_v0(const double* V, int64_t stride, int n, double* out, hipStream_t s) {
+  hipLaunchKernelGGL(v0_kernel, dim3(1), dim3(kBlock), 0, s, V, stride, n, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_v0_jobs(const BdpJob* jobs, int n_jobs, double* out, hipStream_t s) {
+  hipLaunchKernelGGL(v0_jobs_kernel, dim3(n_jobs), dim3(64), 0, s, jobs, out);
+  return hipGetLastError();
+}
+
 hipError_t launch_copy_last_layer(const BdpArgs& a, int64_t pt_n, int N_n, hipStream_t s) {
   const int64_t total = (int64_t)a.n_pay * N_n;
   const unsigned blocks = (unsigned)((total + kBlock - 1) / kBlock);

@@ -76,7 +76,8 @@ struct BdpJob {
   const double* phi;
   double* V;
   int64_t P;
-  int32_t n, q0, nq, pad_;
+  int32_t n, q0, nq;
+  int32_t v0_at;  // of payoff q0 in the batch's V_0
 };
 
 // nrows <= kBdpTaskRows rows of a layer of a job, with everything a step needs
@@ -96,6 +97,7 @@ constexpr int kBdpTaskRows = 16;
 // then step j = 0, 1, ... runs tasks [step_off[j], step_off[j + 1]) -- layer
 // n - 1 - j of every job with n > j -- one launch per step.  max_last:
 // largest N_n; max_nq: most payoffs of a job; min_n1: smallest N_k, k >= 1.
+hipError_t launch_v0_jobs(const BdpJob* jobs, int n_jobs, double* out, hipStream_t s);
 hipError_t launch_bdp_steps(const BdpJob* jobs, int n_jobs, int max_last, int max_nq, int min_n1,
                             const BdpTask* tasks, const int* step_off, int n_steps,
                             hipStream_t s);

@@ -269,6 +269,7 @@ struct BdpArgs {
 };
 hipError_t launch_bdp_layer(const BdpArgs& a, int k, int N_k, int N_k1, int64_t pt_k,
                             int64_t pt_k1, int64_t cnt_k, hipStream_t s);
+hipError_t launch_v0(const double* V, int64_t stride, int n, double* out, hipStream_t s);
 hipError_t launch_copy_last_layer(const BdpArgs& a, int64_t pt_n, int N_n, hipStream_t s);
 
 struct Contract {

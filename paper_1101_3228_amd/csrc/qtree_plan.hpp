@@ -71,6 +71,36 @@ struct qtree_plan {
 };
 
 namespace qtree {
+// A few results on their way to the host: a kernel writes them to a slot of
+// pinned memory, and a blocking call copies them out when its stream is done.
+// A copy into the caller's pageable memory costs 12 us, a strided one 7 us a
+// row more (97 us for 12 payoffs); the kernel and the wait cost 16.  One array
+// of kSlots slots, made with the first plan and kept until the process ends,
+// serves all plans, threads and devices; a call holds a slot while it waits,
+// and one that finds none free, or has more results, copies as before.
+class HostSlot {
+ public:
+  static constexpr int kSlots = 16;
+  static constexpr int64_t kDoubles = 2048;
+  static void reserve();            // at plan creation
+  explicit HostSlot(int64_t n);     // ptr() is null without a slot
+  ~HostSlot();
+  HostSlot(const HostSlot&) = delete;
+  HostSlot& operator=(const HostSlot&) = delete;
+  double* ptr() const { return p_; }
+  // Waits for the stream and copies n results out.  After an error the slot
+  // stays taken: the kernel may still write to it.
+  hipError_t finish(double* out, int64_t n, hipStream_t s);
+
+ private:
+  double* p_ = nullptr;
+  int i_ = -1;
+};
+// n results, `stride` apart, to host memory; waits for the stream.
+hipError_t results_to_host(const double* V, int64_t stride, int64_t n, double* out, hipStream_t s);
+}  // namespace qtree
+
+namespace qtree {
 // Record a failure for qtree_last_error and return its status.
 qtree_status set_error(qtree_status s, const std::string& msg);
 

@@ -9,6 +9,8 @@ in another order; a row of m terms differs by at most 2 m 2^-53 of its largest
 term, and the layers' errors add up: 2 n m 2^-53 <= 1e-11 of the largest value
 for the sizes here (n = 4, m <= 2100).
 """
+import threading
+
 import numpy as np
 import pytest
 
@@ -91,3 +93,33 @@ def test_batch_steps(pays, small):
         c = it["counts"][:it["plan"].entries].cpu().numpy()
         _close(it["V"].cpu().numpy(), O.bdp(c, it["plan"].N, it["phi"].cpu().numpy(),
                                             want_all=True)[1])
+
+
+@pytest.mark.parametrize("n_pay,threads", [(1, 1), (17, 1), (2048, 1), (2049, 1), (3, 24)])
+def test_v0_on_the_host_is_the_first_value(n_pay, threads):
+    """V_0 to the host through a slot of 2048 results, one more than it holds,
+    and more callers at a time than there are slots."""
+    print(f"[gpu-case] V0 n_pay={n_pay} threads={threads}", flush=True)
+    plan, _, counts = _tree([1, 7, 9], M=2000)
+    torch.cuda.synchronize()
+    out = [None] * threads
+
+    def call(t):
+        rng = np.random.default_rng(100 + t)
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            phi = torch.from_numpy(rng.random((n_pay, plan.points))).cuda()
+            got = []
+            for _ in range(5):
+                V0, V = plan.bdp(counts, phi, stream=stream)
+                got.append((V0, V[:, 0].cpu().numpy()))
+            out[t] = got
+
+    ts = [threading.Thread(target=call, args=(t,)) for t in range(threads)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    for got in out:
+        for V0, first in got:
+            assert V0.shape == (n_pay,) and np.array_equal(V0, first)
