@@ -150,7 +150,7 @@ int64_t qtree_plan_points(const qtree_plan *plan);        /* sum_k N_k */
  *                        LDS histogram per tile; uses the workspace scratch).
  *   QTREE_TUNE_GROUPS  : two-pass only: the layers are split into this many
  *                        groups (1..8; 0 = automatic, the default: 4 for
- *                        d = 1, 1 for d >= 2); the histogram pass of a
+ *                        d = 1 from 2 10^8 pairs on, else 1); the histogram pass of a
  *                        group runs on a stream of the plan, concurrently with
  *                        the sampling pass of the next group.  The call still
  *                        completes in order on `stream` (which waits for it).

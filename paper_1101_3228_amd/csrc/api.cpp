@@ -647,8 +647,9 @@ qtree_status qtree_plan_create(const qtree_model* model, const float* grid, cons
     st_max = std::max<int64_t>(st_max, st);
     st_all += st;
   }
+  p.st_max = st_max;
   const int64_t split_base = st_all >= kManySuperTiles ? 1 : 2;
-  int32_t total_units = 0;
+  int32_t total_units = 0, few_units = 0;
   for (int k = 0; k <= n; ++k) {
     qtree::LayerDev L{};
     L.cnt_off = k < n ? p.cnt_off[k] : 0;
@@ -672,6 +673,12 @@ qtree_status qtree_plan_create(const qtree_model* model, const float* grid, cons
     p.split.push_back(L.split);
     p.unit_off.push_back(total_units);
     total_units += (int32_t)(st_k * L.split);
+    // a call with few samples leaves the splitting in two out
+    L.few_split = std::max(1, L.split / (int32_t)split_base);
+    L.few_off = few_units;
+    p.few_split.push_back(L.few_split);
+    p.few_off.push_back(few_units);
+    few_units += (int32_t)(st_k * L.few_split);
     if (k < n) {
       std::memcpy(L.A, model->A + dd * k, sizeof(float) * dd);
       std::memcpy(L.b, model->b + (size_t)d * k, sizeof(float) * d);
@@ -857,10 +864,15 @@ static hipError_t two_pass(const qtree_plan* p, qtree::FwdArgs a, bool zero, hip
                                 : (uint64_t)sc.chunks * qtree::kChunk;
   a.keys = sc.keys;
   a.segs = sc.segs;
-  // automatic: four groups hide most of the 1-D histogram pass; for d >= 2
-  // two (with the bucketed search that pass is a fifth of the forward, and
-  // more launches add tails)
-  const int want = p->tune_groups > 0 ? p->tune_groups : (p->d == 1 ? 4 : 2);
+  // automatic: one group.  Its launches end once instead of four times and
+  // wait for no other stream: a put on 50 layers of 500 points 356 -> 303 us at
+  // 10^5 pairs a layer, 832 -> 767 at 3 10^6, the 2-D ones alike or less.  From
+  // kGroupPairs on, a 1-D plan takes four: by itself that costs 5 % (1.98 -> 2.09
+  // ms at 5 10^8 pairs, 12 payoffs), but the backward layers of another stream
+  // find room between the launches (a pipelined step 1.86 -> 1.78 ms).
+  constexpr double kGroupPairs = 2e8;
+  const bool many = p->d == 1 && (double)p->n * (double)std::min(bs, a.M) >= kGroupPairs;
+  const int want = p->tune_groups > 0 ? p->tune_groups : many ? 4 : 1;
   const int groups = std::max(1, std::min(std::min(want, sc.max_groups), p->n));
   if (groups > 1) {
     hipError_t e = ensure_aux(p, groups);
@@ -882,6 +894,13 @@ static hipError_t two_pass(const qtree_plan* p, qtree::FwdArgs a, bool zero, hip
     b.chunks = (int32_t)chunks;
     b.xcd_map = p->tune_xcd_map;
     b.first_batch = first ? 1 : 0;
+    // under 2^16 keys a super tile, clearing its block and adding into it costs
+    // more than the second workgroup saves: 60 super tiles a layer, 5000 keys
+    // each, 212 -> 180 us a call; 62 000 keys 447 -> 428, 190 000 767 -> 761, 10^6
+    // (one super tile) 436 -> 473
+    b.few = mb / (uint64_t)p->st_max < (1ull << 16) ? 1 : 0;
+    const std::vector<int32_t>& split = b.few ? p->few_split : p->split;
+    const std::vector<int32_t>& unit = b.few ? p->few_off : p->unit_off;
     hipError_t e = hipSuccess;
     if (groups > 1 && lo > a.m0) e = hipStreamWaitEvent(s, p->join, 0);  // scratch reuse
     for (int g = 0; g < groups && e == hipSuccess; ++g) {
@@ -891,13 +910,21 @@ static hipError_t two_pass(const qtree_plan* p, qtree::FwdArgs a, bool zero, hip
       c.layer0 = k0;
       c.units = (k1 - k0) * b.chunks;
       c.units_per_xcd = (c.units + 7) / 8;
-      c.tile0 = p->unit_off[k0];
-      c.total_tiles = p->unit_off[k1] - p->unit_off[k0];
+      c.tile0 = unit[k0];
+      c.total_tiles = unit[k1] - unit[k0];
       // a split layer's histogram parts add into its count block: clear it
       // first (ordered before the histogram pass by the stream and the fork)
-      bool any_split = false;
-      for (int k = k0; k < k1; ++k) any_split = any_split || p->split[k] > 1;
-      if (b.first_batch && any_split) e = qtree::launch_zero_split(c, k1 - k0, s);
+      int z0 = k1, z1 = k0;
+      for (int k = k0; k < k1; ++k)
+        if (split[k] > 1) {
+          z0 = std::min(z0, k);
+          z1 = k + 1;
+        }
+      if (b.first_batch && z0 < z1) {
+        qtree::FwdArgs z = c;
+        z.layer0 = z0;
+        e = qtree::launch_zero_split(z, z1 - z0, s);
+      }
       if (e == hipSuccess) e = qtree::launch_fwd_keys(c, s);
       if (e != hipSuccess) break;
       if (g == groups - 1 && p->trace_keys) e = hipEventRecord(p->trace_keys, s);

@@ -720,7 +720,8 @@ __global__ __launch_bounds__(kCountBlock) void count_tiles(FwdArgs a) {
   int lo = 0, hi = a.n - 1;  // largest k with unit_off_k <= b
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
-    if (a.layers[mid].unit_off <= b) lo = mid; else hi = mid - 1;
+    const LayerDev& L = a.layers[mid];
+    if ((a.few ? L.few_off : L.unit_off) <= b) lo = mid; else hi = mid - 1;
   }
   const int k = lo;
   TileJob j;
@@ -730,8 +731,9 @@ __global__ __launch_bounds__(kCountBlock) void count_tiles(FwdArgs a) {
   j.seg_stride = a.seg_stride;
   j.chunks = a.chunks;
   // unit = super tile * split + part; part p takes chunks [p C / split, (p+1) C / split)
-  const int split = a.layers[k].split > 1 ? a.layers[k].split : 1;
-  const int r = b - a.layers[k].unit_off;
+  const int parts = a.few ? a.layers[k].few_split : a.layers[k].split;
+  const int split = parts > 1 ? parts : 1;
+  const int r = b - (a.few ? a.layers[k].few_off : a.layers[k].unit_off);
   j.t = r / split;
   const int part = r - j.t * split;
   j.c_lo = (int)((int64_t)a.chunks * part / split);
@@ -987,7 +989,7 @@ hipError_t launch_fwd_keys(const FwdArgs& a, hipStream_t s) {
 constexpr int kZeroBlocks = 16;
 __global__ __launch_bounds__(256) void zero_split_kernel(FwdArgs a) {
   const LayerDev& L = a.layers[a.layer0 + (int)blockIdx.y];
-  if (L.split <= 1) return;
+  if ((a.few ? L.few_split : L.split) <= 1) return;
   const int64_t n = (int64_t)L.N * L.N1;
   int32_t* dst = a.counts + L.cnt_off;
   const int64_t stride = (int64_t)kZeroBlocks * 256;

@@ -83,6 +83,8 @@ struct alignas(16) LayerDev {
   float bk_lo[2], bk_scale[2];
   int32_t bk_B[2];
   int32_t bk_off;
+  // split and unit_off for few samples (FwdArgs::few)
+  int32_t few_split, few_off;
 };
 constexpr int kBucketRow = 8;             // uint16 entries of a bucket row (16 bytes)
 constexpr int kBucketCap = kBucketRow - 1; // candidates it holds
@@ -204,6 +206,7 @@ struct FwdArgs {
   int32_t max_tiles;
   int32_t total_tiles;    // histogram units of this launch (pass-B grid)
   int32_t first_batch;    // pass B overwrites instead of adding
+  int32_t few;            // pass B split as for few samples
   int32_t layer0;         // first layer of this launch (units and tiles)
   int32_t nd_samples;     // d >= 2: samples per lane sharing each grid read (8 or 4)
   int32_t tile0;          // first histogram unit of this launch

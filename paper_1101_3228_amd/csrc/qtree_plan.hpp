@@ -28,9 +28,11 @@ struct qtree_plan {
   int32_t tune_buckets = 1;     // d = 2, 3: cells through the bucket tables
   int64_t buckets = 0;          // d = 2: buckets over all layers (0: no tables)
   int64_t cubes = 0;            // d = 3: the same
+  int64_t st_max = 1;           // super tiles of the largest count block
   int32_t max_tiles = 0, total_tiles = 0;
   std::vector<int32_t> tile_off;  // first super tile of every layer (host copy)
   std::vector<int32_t> unit_off;  // first histogram unit of every layer (host copy)
+  std::vector<int32_t> few_split, few_off;  // split and unit_off for few samples
   std::vector<int32_t> split;     // histogram parts per super tile of every layer
   std::vector<float> marg_L;      // d = 1: the marginal factor L_k of every layer
   std::vector<double> edges;      // d = 1: host copy of the cell-edge probabilities

@@ -443,3 +443,23 @@ def test_autotune_choice_and_every_candidate_give_the_same_counts(name):
     for g, t, s in cands:
         plan.tune(groups=g, tail=t, nd_samples=s)
         assert np.array_equal(plan.transitions(M, seed, contract=3).cpu().numpy(), ref), (g, t, s)
+
+
+@pytest.mark.parametrize("sizes,M", [([1, 50, 50], 65_535), ([1, 50, 50], 65_536),
+                                     ([1, 200, 300, 100], 262_143), ([1, 200, 300, 100], 262_144),
+                                     ([1, 700, 3, 700], 50_001)])
+def test_histogram_parts_by_samples(sizes, M):
+    """Below 2^16 samples per super tile of the largest block a super tile is
+    counted by one workgroup (the first layer's by several), from there on by
+    two: the counts of both are the oracle's, into a block of old values too."""
+    print(f"[gpu-case] histogram parts {sizes} {M}", flush=True)
+    spec = synth.bm_model(1, len(sizes) - 1)
+    grid, N = synth.layer_grids(spec, sizes)
+    plan = qt.Plan(spec, grid, N)
+    ref = O.transitions(_omodel(spec), grid, N, M, seed=11, nthreads=8)
+    counts = plan.new_counts()
+    counts.fill_(7)
+    for groups in (0, 2):
+        plan.tune(groups=groups)
+        got = plan.transitions(M, 11, counts=counts).cpu().numpy()
+        assert np.array_equal(got, ref), groups
