@@ -682,7 +682,7 @@ __global__ __launch_bounds__(kBlock) void fwd_keys_1d_guide(FwdArgs a) {
 
 // d = 3 with tables: 12 layers of 990 points, 3 10^5 pairs per layer, 770 us
 // by the full scan (2 x 990 records a sample, bound by the vector units) and
-// 110 us by the rows (two gathers of 32 bytes a sample, 60 VGPRs).
+// 73 us by the rows (two gathers of 32 bytes a sample, 60 VGPRs).
 template <int D, int S, bool BK = false>
 __global__ __launch_bounds__(kBlockNd) void fwd_keys_nd(FwdArgs a) {
   extern __shared__ float4 lds4[];
