@@ -17,6 +17,7 @@ namespace {
 constexpr int kBlock = 256;
 constexpr int kStep = 4;        // d = 1: layers whose midpoints are staged together
 constexpr int kCountBlock = 1024;
+constexpr size_t kLdsBytes = 160 * 1024;  // of a CU
 
 // Where a path's cells go.
 struct Visits {
@@ -159,6 +160,8 @@ constexpr int kWidePaths = 128, kSegments = 4, kWideSteps = 2 * kSegments;
 constexpr int kWideBlock = kWidePaths * kSegments;
 static_assert(kWideSteps * kRecWords <= kWideBlock, "one word of the records per thread");
 
+// LDS of a workgroup, 64 bytes per point of the largest layer: more than a CU
+// has from 2412 points on, whatever the count blocks are.
 size_t wide_lds(int maxN) {
   return 2 * sizeof(StepRec) * kWideSteps + sizeof(float) * 2 * kWideSteps * kWidePaths +
          sizeof(float2) * kWideSteps * (size_t)((maxN + 2) & ~1);
@@ -245,8 +248,10 @@ void walk_2d_wide(FwdArgs a, Visits v) {
   }
 }
 
-// d = 2 with bucket tables, one lane per path, counted on the spot: the next
-// layer's points staged in LDS (pairs, as in the time-layer kernels).
+// d = 2 with bucket tables, one lane per path: the next layer's points staged
+// in LDS (pairs, as in the time-layer kernels).  For paths counted on the spot,
+// and for layers whose points walk_2d_wide cannot stage.
+template <bool STORE>
 __global__ __launch_bounds__(kBlock) void walk_2d(FwdArgs a, Visits v) {
   extern __shared__ float2 xy[];
   const uint64_t t = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -276,7 +281,7 @@ __global__ __launch_bounds__(kBlock) void walk_2d(FwdArgs a, Visits v) {
     bucket_rows<1>(layers[k + 1], N1, a.bk, x, w);
     __syncthreads();
     bucket_argmin<1>(xy, N1, a.bk, x, w, j);
-    visit<false>(a, v, k, t, live, i, j[0]);
+    visit<STORE>(a, v, k, t, live, i, j[0]);
     i = j[0];
   }
 }
@@ -406,7 +411,7 @@ static hipError_t launch_walk(const FwdArgs& a, const Visits& v, hipStream_t s) 
   if (a.d == 1)
     return a.maxP <= 4096 ? go(walk_1d<true, STORE>, sizeof(float) * kStep * (size_t)a.maxP)
                           : go(walk_1d<false, STORE>, 0);
-  if (a.d == 2 && a.bucketed && STORE) {
+  if (a.d == 2 && a.bucketed && STORE && wide_lds(a.maxN) <= kLdsBytes) {
     const size_t lds = wide_lds(a.maxN);
     if (lds > 65536) {
       const hipError_t e =
@@ -418,7 +423,7 @@ static hipError_t launch_walk(const FwdArgs& a, const Visits& v, hipStream_t s) 
                        dim3(kWideBlock), lds, s, a, v);
     return hipGetLastError();
   }
-  if (a.d == 2 && a.bucketed) return go(walk_2d, sizeof(float2) * (size_t)(a.maxN + 1));
+  if (a.d == 2 && a.bucketed) return go(walk_2d<STORE>, sizeof(float2) * (size_t)(a.maxN + 1));
   const size_t lds = sizeof(float4) * (size_t)(a.maxN + 1);
   if (a.d == 3 && a.cubes) return go(walk_scan<3, STORE, true>, lds);
   return a.d == 2 ? go(walk_scan<2, STORE>, lds) : go(walk_scan<3, STORE>, lds);

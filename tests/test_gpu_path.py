@@ -1,7 +1,8 @@
 """GPU checks of the pathwise counts where their kernels change form, bit for
 bit against the oracle: layers in groups of four (d = 1) and a remainder, one
 super tile and several, the bucket tables and the full scan (d = 2), d = 3,
-layers too large for the staged search, more paths than one pass of the cell
+layers too large for the staged search (or, d = 2, for several layers' points
+in LDS beside small neighbours), more paths than one pass of the cell
 scratch holds, added counts, a workspace without the scratch, other streams,
 and a captured call."""
 import numpy as np
@@ -53,6 +54,23 @@ def test_paths_nd(d, side, buckets):
     plan = qt.Plan(spec, grid, N, batch_samples=1).tune(buckets=buckets)
     got = plan.transitions(10_001, SEED, mode=qt.PATHWISE).cpu().numpy()
     assert np.array_equal(got, _ref(spec, grid, N, 10_001))
+
+
+@pytest.mark.parametrize("sizes", [[1, (1, 2411), (3, 3)], [1, (36, 67), (2, 2), (5, 4)],
+                                   [1, (50, 60)], [1, (4, 5), (64, 64), (3, 4), (64, 64)],
+                                   [1, (20, 20), (50, 80), (20, 20)]], ids=str)
+@pytest.mark.parametrize("buckets", [1, 0])
+def test_paths_2d_one_large_layer(sizes, buckets):
+    """2411 points are the most whose staged layers fit in LDS; larger ones
+    beside small neighbours still have the cell scratch."""
+    _case(f"paths 2-D {sizes} {buckets}")
+    spec = synth.bm_model(2, len(sizes) - 1, rho=0.3)
+    grid, N = synth.layer_grids(spec, sizes)
+    plan = qt.Plan(spec, grid, N, batch_samples=1).tune(buckets=buckets)
+    counts = plan.transitions(20_001, SEED, mode=qt.PATHWISE)
+    assert np.array_equal(counts.cpu().numpy(), _ref(spec, grid, N, 20_001))
+    plan.transitions_add(counts, 130, SEED, mode=qt.PATHWISE, m0=20_001)
+    assert np.array_equal(counts.cpu().numpy(), _ref(spec, grid, N, 20_131))
 
 
 def _tree():
