@@ -1092,10 +1092,12 @@ qtree_status qtree_plan_tune(qtree_plan* plan, int32_t key, int64_t value) {
 }
 
 // Pathwise counts through the plan's cell scratch, in passes of at most
-// path_cells paths.  Calls on other streams or threads keep working: the
-// scratch is handed over by an event, and a stream under capture, whose
-// replays no event could order, does not use it (*used = false: nothing was
-// launched).
+// path_cells paths.  Calls on other streams or threads keep working: every
+// call waits for the event of the one before (a stream cannot be told by its
+// handle: hipStreamPerThread is one handle for a stream of each thread, and a
+// new stream may get a destroyed one's), and a stream under capture, whose
+// replays no event could order, does not use the scratch (*used = false:
+// nothing was launched).
 static hipError_t path_passes(const qtree_plan* p, qtree::FwdArgs a, bool zero, hipStream_t s,
                               bool* used) {
   *used = false;
@@ -1109,11 +1111,8 @@ static hipError_t path_passes(const qtree_plan* p, qtree::FwdArgs a, bool zero, 
   qtree_plan::PathUse& u = *p->path_use;
   std::lock_guard<std::mutex> hold(u.lock);
   hipError_t e = hipSuccess;
-  if (!u.done) {
-    e = hipEventCreateWithFlags(&u.done, hipEventDisableTiming);
-  } else if (u.last != s) {
-    e = hipStreamWaitEvent(s, u.done, 0);
-  }
+  if (!u.done) e = hipEventCreateWithFlags(&u.done, hipEventDisableTiming);
+  else e = hipStreamWaitEvent(s, u.done, 0);
   if (e != hipSuccess) return e;
   *used = true;
   a.total_tiles = p->total_tiles;
@@ -1126,7 +1125,6 @@ static hipError_t path_passes(const qtree_plan* p, qtree::FwdArgs a, bool zero, 
   }
   // recorded also after a failed launch: what was queued before it may run
   const hipError_t r = hipEventRecord(u.done, s);
-  u.last = s;
   return e != hipSuccess ? e : r;
 }
 

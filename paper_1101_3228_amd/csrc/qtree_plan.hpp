@@ -51,12 +51,11 @@ struct qtree_plan {
   mutable hipEvent_t fork[kMaxGroups] = {};
   mutable hipEvent_t join = nullptr;
 
-  // The pathwise scratch serves one call at a time: a call on another stream
-  // than the last one's waits on the device for that call's event.
+  // The pathwise scratch serves one call at a time: each waits on the device
+  // for the event of the one before.
   struct PathUse {
     std::mutex lock;
-    hipEvent_t done = nullptr;   // recorded after each use
-    hipStream_t last = nullptr;  // stream of the last use (once `done` exists)
+    hipEvent_t done = nullptr;  // recorded after each use
     ~PathUse() {
       if (done) (void)hipEventDestroy(done);
     }

@@ -3,8 +3,8 @@ bit against the oracle: layers in groups of four (d = 1) and a remainder, one
 super tile and several, the bucket tables and the full scan (d = 2), d = 3,
 layers too large for the staged search (or, d = 2, for several layers' points
 in LDS beside small neighbours), more paths than one pass of the cell
-scratch holds, added counts, a workspace without the scratch, other streams,
-and a captured call."""
+scratch holds, added counts, a workspace without the scratch, other streams
+and threads, and a captured call."""
 import numpy as np
 import pytest
 
@@ -129,6 +129,43 @@ def test_paths_on_two_streams_share_the_plan():
         ref = O.transitions(_model(spec), grid, N, 50_000, seed=SEED, contract=i, mode=1,
                             nthreads=8)
         assert np.array_equal(out[:plan.entries].cpu().numpy(), ref), i
+
+
+def test_paths_of_threads_on_their_own_default_streams():
+    """One handle (hipStreamPerThread) names a stream of each host thread;
+    their calls share the plan's scratch."""
+    _case("paths on per-thread streams")
+    import threading
+    per_thread = 2                      # the value of the hipStreamPerThread handle
+    spec, grid, N = _tree()
+    plan = qt.Plan(spec, grid, N, batch_samples=1)
+    threads, calls, M = 4, 12, 50_000
+    outs = [[plan.new_counts() for _ in range(calls)] for _ in range(threads)]
+    torch.cuda.synchronize()
+    go, failed = threading.Barrier(threads), []
+
+    def work(t):
+        torch.cuda.set_device(0)
+        go.wait()
+        for c in range(calls):
+            status = qt.lib().qtree_transitions(plan.handle, 0, M, SEED, calls * t + c,
+                                                qt.PATHWISE, outs[t][c].data_ptr(), per_thread)
+            if status:
+                failed.append((t, c, status))
+        torch.cuda.ExternalStream(per_thread).synchronize()
+
+    pool = [threading.Thread(target=work, args=(t,)) for t in range(threads)]
+    for th in pool:
+        th.start()
+    for th in pool:
+        th.join()
+    torch.cuda.synchronize()
+    assert not failed
+    for t in range(threads):
+        for c in range(calls):
+            ref = O.transitions(_model(spec), grid, N, M, seed=SEED, contract=calls * t + c,
+                                mode=1, nthreads=8)
+            assert np.array_equal(outs[t][c][:plan.entries].cpu().numpy(), ref), (t, c)
 
 
 def test_captured_paths_replay():
