@@ -431,6 +431,15 @@ static void band_table(qtree_plan& p, const qtree_model* model, const float* mid
               sizeof(int32_t) * (size_t)R);
 }
 
+// Whether a box in FP32 is one that a point can be located in: a model with
+// coefficients near the type's limits may have corners beyond them.  Such a
+// layer has no tables (its rows stay unused), and the full scan decides.
+static bool box_fits(int d, const float* lo, const float* scale) {
+  for (int r = 0; r < d; ++r)
+    if (!std::isfinite(lo[r]) || !std::isnormal(scale[r]) || scale[r] < 0.0f) return false;
+  return true;
+}
+
 // Boxes of the d = 2 bucketed cell search.  Layer k's time-layer samples
 // are X_k = mu_k + L_k z (as the first point of a pair) and
 // A_{k-1} X_{k-1} + b_{k-1} + T_{k-1} eps (as the second), every normal
@@ -491,8 +500,8 @@ static void bucket_boxes(qtree_plan& p, const qtree_model* model, const float* g
       hi[r] += m;
       L.bk_lo[r] = (float)lo[r];
       L.bk_scale[r] = (float)((double)B / (hi[r] - (double)L.bk_lo[r]));
-      L.bk_B[r] = B;
     }
+    if (box_fits(2, L.bk_lo, L.bk_scale)) L.bk_B[0] = L.bk_B[1] = B;
     off += (int64_t)B * B;
   }
   p.buckets = off;
@@ -542,8 +551,8 @@ static void cube_boxes(qtree_plan& p, const qtree_model* model, qtree::Cubes* cu
       const double m = 1e-3 * (hi - lo) + 1e-6 * (1.0 + std::fabs(lo) + std::fabs(hi));
       C.lo[r] = (float)(lo - m);
       C.scale[r] = (float)((double)B / (hi + m - (double)C.lo[r]));
-      C.B[r] = (int32_t)B;
     }
+    if (box_fits(3, C.lo, C.scale)) C.B[0] = C.B[1] = C.B[2] = (int32_t)B;
     off += B * B * B;
   }
 }

@@ -135,6 +135,7 @@ __global__ __launch_bounds__(kBlock) void cube_build_kernel(const Cubes* cubes, 
     if (cubes[mid].off <= row0) lo = mid; else hi = mid - 1;
   }
   const Cubes& C = cubes[lo];
+  if (C.B[0] == 0) return;  // rows of a layer without a box
   const int N = C.N;
   const float4* g = pts + C.pt_off;
   const int nt1 = C.B[1] / kCubeTile, nt2 = C.B[2] / kCubeTile;

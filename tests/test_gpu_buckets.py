@@ -220,3 +220,30 @@ def test_3d_plan_in_a_workspace_without_room_for_tables(monkeypatch):
     assert np.array_equal(small.transitions(M, 4).cpu().numpy(), ref)
     assert np.array_equal(small.transitions(M, 4, mode=qt.PATHWISE).cpu().numpy(),
                           full.transitions(M, 4, mode=qt.PATHWISE).cpu().numpy())
+
+
+@pytest.mark.parametrize("d", [2, 3])
+def test_boxes_beyond_the_type_have_no_tables(d):
+    """Coefficients whose box passes FP32's range (the samples drawn here stay
+    within it): no tables, and the full scan's counts."""
+    _case(f"box beyond FP32 {d}-D")
+    rng = np.random.default_rng(11)
+    scale = np.float32(8.5e37)
+    spec = synth.bm_model(d, 2, T=2.0)
+    spec["A"][1] = 0.0
+    for k in range(2):
+        spec["T"][k] = scale * np.eye(d, dtype=np.float32)
+        spec["L"][k + 1] = scale * np.eye(d, dtype=np.float32)
+    g = (0.1 * rng.standard_normal((60, d))).astype(np.float32)
+    grid = np.concatenate([np.zeros((1, d), np.float32), g, g[::-1]])
+    N = np.array([1, len(g), len(g)], np.int32)
+    plan = qt.Plan(spec, grid, N)
+    M = 501
+    for k in (1, 2):
+        lo, sc, B = plan.buckets(k)
+        assert (B == 0).all()
+    x, y = qt.layer_samples(plan, 1, 0, M, 3)
+    assert torch.isfinite(x).all() and torch.isfinite(y).all()
+    for mode in (0, qt.PATHWISE):
+        ref = O.transitions(_omodel(spec), grid, N, M, seed=3, mode=mode, nthreads=8)
+        assert np.array_equal(plan.transitions(M, 3, mode=mode).cpu().numpy(), ref), mode
