@@ -647,6 +647,66 @@ typedef const uint64_t __attribute__((address_space(1)))* GlobalU64;
 // of a step were 8 apart, their bands' union half as wide again.
 constexpr int kManyWaves = 8;
 
+// V_0 of one contract by the workgroup's waves, a row at a time, where a weight
+// of zero adds nothing whatever the value is.  A tile's product has many of
+// them (columns of other rows' bands, the rest of a group of 16, rows of Vs past
+// the layer), and where an obstacle overflowed they are 0 x inf, NaN.  A NaN
+// stays one through every later product and maximum, so a price that is not
+// NaN met none, and only contracts of finite parameters whose price is NaN come
+// here.  (Tests of the values or of the products within the tiles: 6 % of the
+// whole call.)  v: LDS, 2 a.np_max doubles.
+template <int D>
+__device__ __forceinline__ double price_by_rows(const ManyTree& T, const Contract& C, double* v,
+                                                int np_max) {
+  const GlobalI32 lay = (GlobalI32)T.layers;
+  constexpr int kLayWords = (int)(sizeof(LayerDev) / 4);
+  constexpr int kN = (int)(offsetof(LayerDev, N) / 4), kN1 = (int)(offsetof(LayerDev, N1) / 4),
+                kPt = (int)(offsetof(LayerDev, pt_off) / 4);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  double *now = v, *next = v + np_max;
+  for (int k = T.n; k >= 0; --k) {
+    const int Nk = lay[k * kLayWords + kN];
+    const int64_t pt = lay[k * kLayWords + kPt];
+    const LayerObstacle ob = layer_obstacle<D>(C, T.n, k);
+    const int N1p = k < T.n ? (lay[k * kLayWords + kN1] + 3) & ~3 : 0;
+    const GlobalF64 P = (GlobalF64)T.pi + (k < T.n ? ((GlobalI64)T.pi_off)[k] : 0);
+    __syncthreads();  // `now` is not read any more
+#pragma unroll 1
+    for (int i = wave; i < Nk; i += kManyWaves) {
+      double sum = -__builtin_huge_val();
+      if (k < T.n) {
+        const GlobalF64 row = P + (int64_t)i * N1p;
+        sum = 0.0;
+#pragma unroll 1
+        for (int j = lane; j < N1p; j += 64) {
+          const double w = row[j];
+          if (w != 0.0) sum = fma(w, next[j], sum);
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+      }
+      float xs[3];
+      grid_point<D>(T, pt, i, xs);
+      const double f = obstacle<D>(C, ob, xs);
+      if (lane == 0) now[i] = k == T.n || f > sum ? f : sum;
+    }
+    __syncthreads();
+    double* const t = now;
+    now = next;
+    next = t;
+  }
+  return next[0];
+}
+
+__device__ __forceinline__ bool finite_parameters(const Contract& C, int d) {
+  bool ok = __builtin_isfinite(C.S0) && __builtin_isfinite(C.K) && __builtin_isfinite(C.r) &&
+            __builtin_isfinite(C.Tm);
+  for (int c = 0; c < d; ++c) ok = ok && __builtin_isfinite(C.sigma[c]);
+  for (int c = 0; c < d * d; ++c) ok = ok && (!C.has_mix || __builtin_isfinite(C.mix[c]));
+  return ok;
+}
+
 template <int D, int CTS, int TILES>
 __global__ __launch_bounds__(64 * kManyWaves) void bdp_many_kernel(ManyArgs a) {
   constexpr int kCols = 16 * CTS, kRowTiles = kManyWaves / CTS;
@@ -761,7 +821,27 @@ __global__ __launch_bounds__(64 * kManyWaves) void bdp_many_kernel(ManyArgs a) {
     }
     __syncthreads();
   }
-  if (threadIdx.x < kCols && qb + threadIdx.x < qe) a.V0[qb + threadIdx.x] = Vs[threadIdx.x];
+  bool again = false;
+  if (threadIdx.x < kCols && qb + threadIdx.x < qe) {
+    const double v0 = Vs[threadIdx.x];
+    a.V0[qb + threadIdx.x] = v0;
+    again = v0 != v0;
+  }
+  __shared__ uint64_t redo;
+  if (wave == 0) {
+    const uint64_t mask = __ballot(again);
+    if (lane == 0) redo = mask;
+  }
+  __syncthreads();
+  uint64_t mask = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(redo >> 32));
+  mask = mask << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)redo);
+  for (; mask != 0; mask &= mask - 1) {
+    const int64_t qc = qb + __ffsll((unsigned long long)mask) - 1;
+    const Contract one = a.specs[qc];
+    if (!finite_parameters(one, D)) continue;
+    const double v0 = price_by_rows<D>(T, one, Vs, a.np_max);
+    if (threadIdx.x == 0) a.V0[qc] = v0;
+  }
 }
 
 bool bdp_many_fits(int max_n) { return max_n <= 256; }

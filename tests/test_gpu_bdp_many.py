@@ -160,3 +160,45 @@ def test_workgroups_of_16_and_64_contracts_agree(d, sizes):
     many = plan.bdp_many(pi, sp).cpu().numpy()
     few = plan.bdp_many(pi, sp[-1005:]).cpu().numpy()
     assert np.array_equal(many[-1005:].view(np.uint64), few.view(np.uint64))
+
+
+@pytest.mark.parametrize("nq", [40, 1024 * 64])
+@pytest.mark.parametrize("d,sizes", [(1, [1, 5, 6, 40, 33]), (1, [1, 130, 250, 19]),
+                                     (2, [1, (3, 2), (5, 5), (2, 3)])], ids=str)
+def test_obstacles_that_overflow(d, sizes, nq):
+    """A weight of zero adds nothing where an obstacle is infinite: at points
+    that no sample reaches, at points that some rows reach, and with a contract
+    of NaN parameters among the others, in both workgroup forms, against
+    qtree_payoff + qtree_bdp."""
+    _case(f"bdp_many overflow d={d} {sizes} {nq}")
+    spec = synth.bm_model(d, len(sizes) - 1, T=1.0)
+    grid, N = synth.layer_grids(spec, sizes)
+    off = O.point_offsets(N)
+    for k in range(1, len(N)):
+        grid[off[k + 1] - 1, 0] = 60.0     # no sample reaches it
+    plan = qt.Plan(spec, grid, N)
+    counts = plan.transitions(20_000, 5)
+    pi = plan.pi(counts)
+    rng = np.random.default_rng(7)
+    kinds = 1 + 2 * rng.integers(0, 2, 40)
+    S0, K, r = rng.uniform(80.0, 125.0, 40), np.full(40, 100.0), rng.uniform(0.0, 0.1, 40)
+    T = rng.uniform(0.25, 2.0, 40)
+    # exp(20 * 60 - 200 T) overflows; with the factors times 30, points that
+    # samples reach do so as well
+    far, near = np.arange(40) % 3 > 0, np.arange(40) % 3 > 1
+    sigma = np.repeat(np.where(far, 20.0, 0.2)[:, None], d, axis=1)
+    mix = np.where(near, 30.0, 1.0)[:, None, None] * np.eye(d)
+    r[11] = np.nan
+    specs = np.tile(qt.payoff_specs(d, kinds, S0, K, r, T, sigma, mix), -(-nq // 40))[:nq]
+    got = plan.bdp_many(pi, specs).cpu().numpy()
+    want = np.full(40, np.nan)
+    for q in np.flatnonzero(np.isfinite(r)):
+        phi = plan.payoff(int(kinds[q]), S0[q], K[q], r[q], T[q], sigma[q], mix[q])
+        assert bool(torch.isinf(phi[phi > 0]).any()) == far[q]
+        want[q] = plan.bdp(counts, phi)[0][0]
+    ok = np.isfinite(r)
+    assert np.isfinite(want[ok & ~near]).all() and np.isinf(want[ok & near]).any()
+    want = np.tile(want, -(-nq // 40))[:nq]
+    ok = np.isfinite(want)
+    assert np.array_equal(got[~ok], want[~ok], equal_nan=True)
+    assert np.all(np.abs(got[ok] - want[ok]) <= 1e-12 * np.abs(want[ok]) + 1e-14)
