@@ -88,8 +88,15 @@ const char *qtree_version(void);
  * d = 3 those of 32 bytes and about 32 per point (1 MB for 1000 points, 256 MB
  * for a plan at most), and for layers of up to about 1450 points the cell
  * scratch of PATHWISE calls, 2 bytes per layer and path for up to 2^17 paths a
- * pass, at most 96 MiB.  A plan given a smaller workspace counts PATHWISE
- * calls with atomics, and scans all points for d = 3.  Pure host arithmetic. */
+ * pass, at most 96 MiB.  Pure host arithmetic.
+ * In a workspace of another size a plan takes, after the layer tables: the
+ * d = 3 tables, if they leave scratch for 2^16 LAYERWISE samples per layer a
+ * pass (or all that there would be without them; else d = 3 scans all points);
+ * then the cell scratch of PATHWISE calls, if it leaves one chunk of 4096 (else
+ * PATHWISE calls count with atomics); the rest is the counting scratch.
+ * LAYERWISE calls that would need more passes in that rest use the cell
+ * scratch's room as well, in turn with the PATHWISE calls (not under capture,
+ * where the passes stay). */
 qtree_status qtree_workspace_size(int32_t d, int32_t n, const int32_t *N, uint64_t batch_samples,
                                   size_t *bytes);
 
@@ -107,7 +114,8 @@ void qtree_plan_destroy(qtree_plan *plan);
  * two-pass calls record it on their stream right after each sampling pass
  * (before the histogram pass), so callers can time the two kernels apart. */
 qtree_status qtree_plan_trace(qtree_plan *plan, void *event_after_keys);
-/* LAYERWISE samples per layer one counting pass holds (0: one-pass atomics only). */
+/* LAYERWISE samples per layer one counting pass holds beside the cell scratch
+ * (0: one-pass atomics only). */
 int64_t qtree_plan_batch_samples(const qtree_plan *plan);
 /* The 1-D cell search of the LAYERWISE forward and the stratified counts
  * (host query, no device work): *guide_k = the largest number of midpoints

@@ -368,9 +368,12 @@ qtree_status qtree_workspace_size(int32_t d, int32_t n, const int32_t* N, uint64
   if (s != QTREE_OK) return s;
   if (batch_samples == 0) batch_samples = qtree::kDefaultBatch;
   if (batch_samples > (1ull << 31)) return fail(QTREE_EINVAL, "batch_samples must be <= 2^31");
-  *bytes = qtree::ws_layout(d, n, N, qtree::chunks_for(d, batch_samples),
-                            qtree::path_cells(n, N), d == 3 ? qtree::total_cubes(n, N) : 0)
+  const int64_t cubes = d == 3 ? qtree::total_cubes(n, N) : 0;
+  *bytes = qtree::ws_layout(d, n, N, qtree::chunks_for(d, batch_samples), qtree::path_cells(n, N),
+                            cubes)
                .total;
+  if (cubes > 0 && qtree::two_pass_fits(d, n, N))
+    *bytes = std::max(*bytes, qtree::ws_layout(d, n, N, qtree::kCubeChunks, 0, cubes).total);
   return QTREE_OK;
 }
 
@@ -611,28 +614,34 @@ qtree_status qtree_plan_create(const qtree_model* model, const float* grid, cons
   }
   // the scratch takes whatever the workspace holds beyond the layer tables
   p.max_tiles = qtree::max_tiles_of(n, N);
-  qtree::WsLayout base = qtree::ws_layout(d, n, N, 0, 0, 0);
+  const qtree::WsLayout base = qtree::ws_layout(d, n, N, 0, 0, 0);
   if (workspace_bytes < base.total)
     return fail(QTREE_ENOMEM, "workspace needs at least " + std::to_string(base.total) + " bytes");
-  // the pathwise scratch, where the workspace holds it beside a chunk per layer
   const bool two = qtree::two_pass_fits(d, n, N);
-  // (the same for the tables of the d = 3 search)
-  const int64_t cubes = d == 3 ? qtree::total_cubes(n, N) : 0;
-  if (cubes > 0 && qtree::ws_layout(d, n, N, two ? 1 : 0, 0, cubes).total <= workspace_bytes)
-    p.cubes = cubes;
-  const int64_t cells = qtree::path_cells(n, N);
-  if (cells > 0 &&
-      qtree::ws_layout(d, n, N, two ? 1 : 0, cells, p.cubes).total <= workspace_bytes)
-    p.path_cells = cells;
-  base = qtree::ws_layout(d, n, N, 0, p.path_cells, p.cubes);
-  p.batch_chunks = 0;
-  if (two) {
+  // chunks per layer beside so many path cells and d = 3 buckets, -1 where
+  // these alone do not fit
+  auto room = [&](int64_t cells, int64_t cubes) -> int64_t {
+    const size_t fixed = qtree::ws_layout(d, n, N, 0, cells, cubes).total;
+    if (fixed > workspace_bytes) return -1;
+    if (!two) return 0;
     const size_t per = (size_t)n * (sizeof(uint16_t) * qtree::kChunk +
                                     sizeof(uint32_t) * (size_t)(p.max_tiles + 1));
-    int64_t c = (int64_t)((workspace_bytes - base.total) / per);
-    while (c > 0 && qtree::ws_layout(d, n, N, c, p.path_cells, p.cubes).total > workspace_bytes) --c;
-    p.batch_chunks = c;
-  }
+    int64_t c = (int64_t)((workspace_bytes - fixed) / per);
+    while (c > 0 && qtree::ws_layout(d, n, N, c, cells, cubes).total > workspace_bytes) --c;
+    return c;
+  };
+  // What a workspace of the caller's own size holds: the tables of the d = 3
+  // search beside kCubeChunks chunks, or all that there would be without them;
+  // the path cells beside one chunk, as the two-pass counting takes their room
+  // as well where that saves it passes (all_chunks).
+  const int64_t cubes = d == 3 ? qtree::total_cubes(n, N) : 0;
+  if (cubes > 0 &&
+      room(0, cubes) >= (two ? std::max<int64_t>(1, std::min(qtree::kCubeChunks, room(0, 0))) : 0))
+    p.cubes = cubes;
+  const int64_t cells = qtree::path_cells(n, N);
+  if (cells > 0 && room(cells, p.cubes) >= (two ? 1 : 0)) p.path_cells = cells;
+  p.batch_chunks = room(p.path_cells, p.cubes);
+  p.all_chunks = room(0, p.cubes);
   p.two_pass_ok = p.batch_chunks > 0;
   p.two_pass_shape = two;
   p.lay = qtree::ws_layout(d, n, N, p.batch_chunks, p.path_cells, p.cubes);
@@ -860,6 +869,12 @@ static int group_start(const qtree_plan* p, int groups, int g) {
   return std::min(k, p->n - (groups - g));
 }
 
+// Samples per layer that `chunks` chunks hold (a d = 1 pass may start on an odd
+// sample).
+static uint64_t pass_samples(int d, int64_t chunks) {
+  return (uint64_t)chunks * qtree::kChunk - (d == 1 ? 2 : 0);
+}
+
 // Two-pass forward over sample batches that fit the scratch.  The layers are
 // split into `groups`; with more than one, the histogram pass of group g runs
 // on the plan's stream while the sampling pass of group g + 1 runs on `s`
@@ -869,8 +884,7 @@ static int group_start(const qtree_plan* p, int groups, int g) {
 static hipError_t two_pass(const qtree_plan* p, qtree::FwdArgs a, bool zero, hipStream_t s,
                            const qtree::CountScratch& sc) {
   const uint64_t end = a.m0 + a.M;
-  const uint64_t bs = p->d == 1 ? (uint64_t)sc.chunks * qtree::kChunk - 2
-                                : (uint64_t)sc.chunks * qtree::kChunk;
+  const uint64_t bs = pass_samples(p->d, sc.chunks);
   a.keys = sc.keys;
   a.segs = sc.segs;
   // automatic: one group.  Its launches end once instead of four times and
@@ -1054,7 +1068,7 @@ qtree_status qtree_plan_cell_search(const qtree_plan* plan, int32_t* guide_k,
 
 int64_t qtree_plan_batch_samples(const qtree_plan* p) {
   if (!p || !p->two_pass_ok) return 0;
-  return p->d == 1 ? p->batch_chunks * qtree::kChunk - 2 : p->batch_chunks * qtree::kChunk;
+  return (int64_t)pass_samples(p->d, p->batch_chunks);
 }
 
 qtree_status qtree_plan_tune(qtree_plan* plan, int32_t key, int64_t value) {
@@ -1100,30 +1114,54 @@ qtree_status qtree_plan_tune(qtree_plan* plan, int32_t key, int64_t value) {
   return fail(QTREE_EINVAL, "unknown tuning key");
 }
 
+// A call's turn at the room of the path cells.  Calls on other streams or
+// threads keep working: every turn waits for the event of the one before (a
+// stream cannot be told by its handle: hipStreamPerThread is one handle for a
+// stream of each thread, and a new stream may get a destroyed one's), and a
+// stream under capture, whose replays no event could order, gets none (taken()
+// is false).  Held until end().
+namespace {
+class PathTurn {
+ public:
+  PathTurn(const qtree_plan* p, hipStream_t s) : u_(*p->path_use), s_(s) {
+    if (s) {
+      hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+      error = hipStreamIsCapturing(s, &st);
+      if (error != hipSuccess || st != hipStreamCaptureStatusNone) return;
+    }
+    hold_ = std::unique_lock<std::mutex>(u_.lock);
+    if (!u_.done) error = hipEventCreateWithFlags(&u_.done, hipEventDisableTiming);
+    else error = hipStreamWaitEvent(s, u_.done, 0);
+    taken_ = error == hipSuccess;
+  }
+  bool taken() const { return taken_; }
+  // After the turn's launches, also where one failed: what was queued before it
+  // may run.
+  hipError_t end(hipError_t e) {
+    const hipError_t r = hipEventRecord(u_.done, s_);
+    hold_.unlock();
+    return e != hipSuccess ? e : r;
+  }
+  hipError_t error = hipSuccess;
+
+ private:
+  qtree_plan::PathUse& u_;
+  hipStream_t s_;
+  std::unique_lock<std::mutex> hold_;
+  bool taken_ = false;
+};
+}  // namespace
+
 // Pathwise counts through the plan's cell scratch, in passes of at most
-// path_cells paths.  Calls on other streams or threads keep working: every
-// call waits for the event of the one before (a stream cannot be told by its
-// handle: hipStreamPerThread is one handle for a stream of each thread, and a
-// new stream may get a destroyed one's), and a stream under capture, whose
-// replays no event could order, does not use the scratch (*used = false:
-// nothing was launched).
+// path_cells paths (*used = false: nothing was launched).
 static hipError_t path_passes(const qtree_plan* p, qtree::FwdArgs a, bool zero, hipStream_t s,
                               bool* used) {
   *used = false;
   if (p->path_cells == 0) return hipSuccess;
-  if (s) {
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    const hipError_t e = hipStreamIsCapturing(s, &st);
-    if (e != hipSuccess) return e;
-    if (st != hipStreamCaptureStatusNone) return hipSuccess;
-  }
-  qtree_plan::PathUse& u = *p->path_use;
-  std::lock_guard<std::mutex> hold(u.lock);
-  hipError_t e = hipSuccess;
-  if (!u.done) e = hipEventCreateWithFlags(&u.done, hipEventDisableTiming);
-  else e = hipStreamWaitEvent(s, u.done, 0);
-  if (e != hipSuccess) return e;
+  PathTurn turn(p, s);
+  if (!turn.taken()) return turn.error;
   *used = true;
+  hipError_t e = hipSuccess;
   a.total_tiles = p->total_tiles;
   uint16_t* cells = reinterpret_cast<uint16_t*>(p->ws + p->lay.path);
   const uint64_t m0 = a.m0, M = a.M;
@@ -1132,9 +1170,32 @@ static hipError_t path_passes(const qtree_plan* p, qtree::FwdArgs a, bool zero, 
     a.M = std::min<uint64_t>((uint64_t)p->path_cells, M - lo);
     e = qtree::launch_path_counts(a, cells, p->path_cells, zero && lo == 0, s);
   }
-  // recorded also after a failed launch: what was queued before it may run
-  const hipError_t r = hipEventRecord(u.done, s);
-  return e != hipSuccess ? e : r;
+  return turn.end(e);
+}
+
+// Two-pass counting in the plan's scratch.  Where more chunks than lie behind
+// the path cells save passes (each but the last reads and writes every count
+// once more), it takes its turn at the cells' room too.
+static hipError_t two_pass_in_plan(const qtree_plan* p, const qtree::FwdArgs& a, bool zero,
+                                   hipStream_t s, qtree::CountScratch sc) {
+  auto passes = [&](int64_t chunks) {
+    const uint64_t bs = pass_samples(p->d, chunks);
+    return (a.M + bs - 1) / bs;
+  };
+  if (p->all_chunks > sc.chunks && passes(p->all_chunks) < passes(sc.chunks)) {
+    PathTurn turn(p, s);
+    if (turn.error != hipSuccess) return turn.error;
+    if (turn.taken()) {
+      sc.chunks = p->all_chunks;
+      sc.keys = reinterpret_cast<uint16_t*>(p->ws + p->lay.path);
+      sc.segs = reinterpret_cast<uint32_t*>(
+          p->ws +
+          align_up(p->lay.path + sizeof(uint16_t) * (size_t)p->n * (size_t)sc.chunks * qtree::kChunk,
+                   256));
+      return turn.end(two_pass(p, a, zero, s, sc));
+    }
+  }
+  return two_pass(p, a, zero, s, sc);
 }
 
 static qtree_status transitions_impl(const qtree_plan* plan, uint64_t m0, uint64_t M,
@@ -1181,7 +1242,7 @@ static qtree_status transitions_impl(const qtree_plan* plan, uint64_t m0, uint64
   if (mode == QTREE_PATHWISE) {
     e = qtree::launch_fwd_path(a, s);
   } else if (two) {
-    e = two_pass(plan, a, zero, s, sc);
+    e = scratch ? two_pass(plan, a, zero, s, sc) : two_pass_in_plan(plan, a, zero, s, sc);
   } else {
     plan_units(a, plan);
     e = plan->d == 1 ? qtree::launch_fwd_layer_1d(a, s) : qtree::launch_fwd_layer_nd(a, s);

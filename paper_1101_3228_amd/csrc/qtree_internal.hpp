@@ -127,6 +127,10 @@ constexpr int kCubeCap = kCubeRow - 1;
 constexpr uint16_t kCubeFull = 0xFFFF;
 constexpr int kCubeMinN = 2;               // smaller layers scan
 constexpr int kCubeTile = 4;               // B is a multiple of it
+// Two-pass chunks (2^16 samples) that the tables leave in a workspace that has
+// them: a pass of 4096 samples would spend longer on its counts than the tables
+// save.
+constexpr int64_t kCubeChunks = 16;
 constexpr int64_t kMaxCubes = 1ll << 23;   // rows of a plan (256 MB); later layers scan
 // Buckets per axis of a layer of N points: about 32 per point, at most 64 per
 // axis.  16 / 32 / 64 per point: 294 / 289 / 288 us for a 12-layer tree of
@@ -167,9 +171,11 @@ constexpr int64_t kPathBytes = 96ll << 20;
 constexpr int kPathTiles = 128;
 int64_t path_cells(int n, const int32_t* N);
 
-// Layout for a scratch that holds `batch_chunks` chunks per layer (0: none)
-// and `cells` path cells per layer (path_cells or 0).
-WsLayout ws_layout(int d, int n, const int32_t* N, int64_t batch_chunks, int64_t cells);
+// Layout for a scratch that holds `batch_chunks` chunks per layer (0: none),
+// `cells` path cells per layer (path_cells or 0) and `cubes` buckets of the
+// d = 3 search (0: none).
+WsLayout ws_layout(int d, int n, const int32_t* N, int64_t batch_chunks, int64_t cells,
+                   int64_t cubes);
 bool two_pass_fits(int d, int n, const int32_t* N);
 
 // The rows of the d = 2 bucketed cell search of a plan.

@@ -41,6 +41,7 @@ struct qtree_plan {
   int32_t gt_Kmax = -1;           // d = 1: largest guide K over the layers (-1: no tables)
   int32_t gt_Bmax = 1;            // d = 1: largest guide table
   int64_t batch_chunks = 0;      // scratch chunks per layer per pass
+  int64_t all_chunks = 0;        // ... with the path cells' room (from lay.path on)
   int64_t path_cells = 0;        // pathwise scratch: cells per layer (0: none)
   bool two_pass_ok = false;       // the workspace holds two-pass scratch
   bool two_pass_shape = false;    // the count blocks and LDS allow two-pass counting
@@ -51,8 +52,8 @@ struct qtree_plan {
   mutable hipEvent_t fork[kMaxGroups] = {};
   mutable hipEvent_t join = nullptr;
 
-  // The pathwise scratch serves one call at a time: each waits on the device
-  // for the event of the one before.
+  // The path cells' room serves one call at a time: each waits on the device for
+  // the event of the one before.
   struct PathUse {
     std::mutex lock;
     hipEvent_t done = nullptr;  // recorded after each use

@@ -3,8 +3,8 @@ bit against the oracle: layers in groups of four (d = 1) and a remainder, one
 super tile and several, the bucket tables and the full scan (d = 2), d = 3,
 layers too large for the staged search (or, d = 2, for several layers' points
 in LDS beside small neighbours), more paths than one pass of the cell
-scratch holds, added counts, a workspace without the scratch, other streams
-and threads, and a captured call."""
+scratch holds, added counts, a workspace without the scratch or shared with
+layerwise calls, other streams and threads, and captured calls."""
 import numpy as np
 import pytest
 
@@ -187,3 +187,116 @@ def test_captured_paths_replay():
         torch.cuda.synchronize()
         assert np.array_equal(out[:plan.entries].cpu().numpy(), ref)
         assert np.array_equal(eager.cpu().numpy(), other)
+
+
+def _plan_in(plan, size):
+    """The same model and grids in a workspace of `size` bytes."""
+    import ctypes
+    model = qt._Model(plan.d, plan.n, *(plan._keep[k].ctypes.data
+                                        for k in ("A", "b", "T", "mu", "L", "x0")))
+    other = qt.Plan.__new__(qt.Plan)
+    other.__dict__.update({k: v for k, v in plan.__dict__.items() if k != "_h"})
+    other.workspace = torch.empty(size, dtype=torch.uint8, device="cuda")
+    h = ctypes.c_void_p()
+    qt._check(qt.lib().qtree_plan_create(ctypes.byref(model), qt._np_ptr(plan.grid),
+                                         qt._np_ptr(plan.N), other.workspace.data_ptr(), size,
+                                         ctypes.byref(h)))
+    other._h = h
+    other.batch_samples = int(qt.lib().qtree_plan_batch_samples(h))
+    return other
+
+
+def _best_ms(call, runs=7):
+    times = []
+    for _ in range(runs):
+        e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        e0.record()
+        call()
+        e1.record()
+        torch.cuda.synchronize()
+        times.append(e0.elapsed_time(e1))
+    return min(times)
+
+
+def test_layerwise_calls_use_the_room_of_the_cells():
+    """A workspace with one chunk per layer behind the path cells: a layerwise
+    call that fits the room of both takes one pass, not 25 (whose counts are
+    read and written once more each)."""
+    _case("layerwise in the cells' room")
+    spec = synth.bm_model(1, 50)
+    grid, N = synth.layer_grids(spec, [1] + [100] * 50)
+    M = 100_000
+    own, small = (qt.Plan(spec, grid, N, batch_samples=b) for b in (M, 1))
+    assert small.batch_samples < 5000
+    counts = [own.new_counts() for _ in range(2)]
+    t_own, t_small = (_best_ms(lambda p=p, c=c: p.transitions(M, SEED, counts=c))
+                      for p, c in zip((own, small), counts))
+    assert torch.equal(counts[0], counts[1])
+    assert t_small < 3.0 * t_own, (t_small, t_own)
+
+
+@pytest.mark.parametrize("d,sizes", [(1, [1, 20, 150, 130, 7, 40, 33]),
+                                     (2, [1, (9, 9), (10, 11), (5, 5)]),
+                                     (3, [1, (3, 4, 5), (5, 5, 5), (2, 3, 4)])], ids=str)
+def test_both_modes_share_a_workspace_of_any_size(d, sizes):
+    """From the smallest workspace to the full one, both modes on two streams at
+    once and in passes of both views, bit for bit."""
+    _case(f"both modes in one workspace {d}-D")
+    spec = synth.bm_model(d, len(sizes) - 1, rho=0.2 if d > 1 else 0.0)
+    grid, N = synth.layer_grids(spec, sizes)
+    full = qt.Plan(spec, grid, N, batch_samples=1)
+    M, m0 = 301_111, 1
+    refs = [O.transitions(_model(spec), grid, N, M, seed=SEED, m0=m0, mode=mode, nthreads=8)
+            for mode in (0, 1)]
+    top = full.workspace.numel()
+    fits = 0
+    for size in sorted({int(top * f) // 16 * 16 for f in
+                        (0.02, 0.05, 0.1, 0.2, 0.4, 0.6, 0.8, 0.95, 0.99, 1.0, 1.5)}):
+        try:
+            plan = _plan_in(full, size)
+        except qt.QtreeError as err:
+            assert err.status == 2 and not fits       # below the layer tables
+            continue
+        fits += 1
+        streams = [torch.cuda.Stream() for _ in range(2)]
+        outs = [[plan.new_counts() for _ in range(3)] for _ in range(2)]
+        torch.cuda.synchronize()
+        for c in range(3):
+            for mode in (0, 1):
+                plan.transitions(M, SEED, mode=mode, m0=m0, counts=outs[mode][c],
+                                 stream=streams[mode])
+        torch.cuda.synchronize()
+        for mode in (0, 1):
+            for c in range(3):
+                assert np.array_equal(outs[mode][c][:plan.entries].cpu().numpy(),
+                                      refs[mode]), (size, mode, c)
+    assert fits >= 5
+
+
+def test_captured_layerwise_call_beside_paths():
+    """A captured layerwise call keeps to its own scratch, so that its replays
+    may run beside pathwise calls of another stream."""
+    _case("captured layerwise call beside paths")
+    spec, grid, N = _tree()
+    plan = qt.Plan(spec, grid, N, batch_samples=1)
+    M = 30_000
+    layer = O.transitions(_model(spec), grid, N, M, seed=SEED, mode=0, nthreads=8)
+    path = _ref(spec, grid, N, 100_000)
+    assert plan.batch_samples < M
+    assert np.array_equal(plan.transitions(M, SEED).cpu().numpy(), layer)
+    out, s, other = plan.new_counts(), torch.cuda.Stream(), torch.cuda.Stream()
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, stream=s):
+        plan.transitions(M, SEED, counts=out, stream=s)
+    for _ in range(3):
+        out.zero_()
+        torch.cuda.synchronize()
+        eager = [plan.new_counts() for _ in range(3)]
+        for c in eager:
+            plan.transitions(100_000, SEED, mode=qt.PATHWISE, counts=c, stream=other)
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(out[:plan.entries].cpu().numpy(), layer)
+        for c in eager:
+            assert np.array_equal(c[:plan.entries].cpu().numpy(), path)
