@@ -90,7 +90,7 @@ const char *qtree_version(void);
  * scratch of PATHWISE calls, 2 bytes per layer and path for up to 2^17 paths a
  * pass, at most 96 MiB.  Pure host arithmetic.
  * In a workspace of another size a plan takes, after the layer tables: the
- * d = 3 tables, if they leave scratch for 2^16 LAYERWISE samples per layer a
+ * d = 3 tables, if they leave scratch for 2^15 LAYERWISE samples per layer a
  * pass (or all that there would be without them; else d = 3 scans all points);
  * then the cell scratch of PATHWISE calls, if it leaves one chunk of 4096 (else
  * PATHWISE calls count with atomics); the rest is the counting scratch.
