@@ -76,8 +76,18 @@ hipError_t HostSlot::finish(double* out, int64_t n, hipStream_t s) {
   return e;
 }
 
+hipError_t HostSlot::can_wait(hipStream_t s) {
+  if (!s) return hipSuccess;
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  const hipError_t e = hipStreamIsCapturing(s, &st);
+  if (e != hipSuccess) return e;
+  return st == hipStreamCaptureStatusNone ? hipSuccess : hipErrorStreamCaptureUnsupported;
+}
+
 hipError_t results_to_host(const double* V, int64_t stride, int64_t n, double* out,
                            hipStream_t s) {
+  const hipError_t wait = HostSlot::can_wait(s);
+  if (wait != hipSuccess) return wait;
   HostSlot slot(n);
   if (slot.ptr()) {
     const hipError_t e = launch_v0(V, stride, (int)n, slot.ptr(), s);

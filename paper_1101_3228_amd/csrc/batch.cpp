@@ -667,6 +667,7 @@ qtree_status qtree_batch_run(qtree_batch* b, double* V0_host, void* stream) {
     }
   }
   if (V0_host) {
+    if ((e = qtree::HostSlot::can_wait(s)) != hipSuccess) return hip_error(e, "V0 copy");
     qtree::HostSlot slot(b->n_v0);
     if (slot.ptr() && !b->jobs.empty()) {
       e = qtree::launch_v0_jobs(b->d_jobs, (int)b->jobs.size(), slot.ptr(), s);

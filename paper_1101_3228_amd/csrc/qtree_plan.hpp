@@ -90,6 +90,9 @@ class HostSlot {
   HostSlot(const HostSlot&) = delete;
   HostSlot& operator=(const HostSlot&) = delete;
   double* ptr() const { return p_; }
+  // An error for a stream under capture, which nothing can wait for (the wait
+  // would end the capture, and finish() would keep the slot).
+  static hipError_t can_wait(hipStream_t s);
   // Waits for the stream and copies n results out.  After an error the slot
   // stays taken: the kernel may still write to it.
   hipError_t finish(double* out, int64_t n, hipStream_t s);

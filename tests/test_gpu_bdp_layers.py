@@ -123,3 +123,33 @@ def test_v0_on_the_host_is_the_first_value(n_pay, threads):
     for got in out:
         for V0, first in got:
             assert V0.shape == (n_pay,) and np.array_equal(V0, first)
+
+
+def test_a_blocking_call_under_capture_is_refused_and_nothing_else():
+    """V_0 on the host cannot be waited for under capture: the call returns an
+    error, the capture goes on, and later calls (more refused ones before them
+    than there are slots) still get their results."""
+    print("[gpu-case] V0 under capture", flush=True)
+    plan, _, counts = _tree([1, 7, 9], M=2000)
+    phi = torch.from_numpy(np.random.default_rng(3).random((12, plan.points))).cuda()
+    V, V1 = torch.empty_like(phi), torch.empty_like(phi)
+    batch = qt.Batch([dict(plan=plan, M=2000, seed=1, counts=plan.new_counts(), phi=phi, V=V1)])
+    want, _ = plan.bdp(counts, phi, V=V)
+    stream, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, stream=stream):
+        for _ in range(20):
+            with pytest.raises(qt.QtreeError) as err:
+                plan.bdp(counts, phi, V=V, stream=stream)
+            assert err.value.status == 4
+            with pytest.raises(qt.QtreeError) as err:
+                batch.run(stream=stream)
+            assert err.value.status == 4
+    for _ in range(3):
+        V.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(V[:, 0].cpu().numpy(), want)
+    for _ in range(20):
+        assert np.array_equal(plan.bdp(counts, phi, V=V)[0], want)
+        assert np.array_equal(batch.run(), V1[:, 0].cpu().numpy())
