@@ -190,7 +190,7 @@ __device__ __forceinline__ bool list_tile(float4* list, ListLds& lds, const floa
     c += __popcll(group);
   }
   __syncthreads();
-  const int listed = c < kTileCand ? c : kTileCand;
+  const int listed = c <= kTileCand ? c : 0;
   uint64_t keep = 0;
   for (int p = sub; p < listed; p += kPerBucket) {
     const float4 gp = list[lds.cand[b][p]];

@@ -263,12 +263,40 @@ __global__ __launch_bounds__(kLloydWideThreads) void lloyd_accum_wide_kernel(Llo
   for (int i = threadIdx.x; i < a.N * 2; i += kThreads) sum[i] = 0ull;
   for (int i = threadIdx.x; i < a.N; i += kThreads) cnt[i] = 0u;
   __syncthreads();
-  const uint64_t per_round = (uint64_t)gridDim.x * kThreads * S;
   unsigned long long dist = 0ull, used = 0ull;
+  if (scan) {
+    // as many samples a lane as the kernel without tables; a wave's are
+    // consecutive, and the first turns go to different workgroups
+    constexpr int kPerWave = 64 * kSamplesNd;
+    const int lane = (int)(threadIdx.x & 63);
+    for (uint64_t t = blockIdx.x + (uint64_t)gridDim.x * (threadIdx.x >> 6); t * kPerWave < a.M;
+         t += (uint64_t)gridDim.x * (kThreads / 64)) {
+      float xs[kSamplesNd][2];
+      int idx[kSamplesNd];
+#pragma unroll
+      for (int s = 0; s < kSamplesNd; ++s) {
+        const uint64_t m = t * kPerWave + (uint64_t)(64 * s + lane);
+        lloyd_sample<2>(a, m < a.M ? m : 0, xs[s]);
+      }
+      argmin_scan_tiled<2, kSamplesNd, 4>(lds4, a.Npad, xs, idx);
+#pragma unroll
+      for (int s = 0; s < kSamplesNd; ++s) {
+        if (t * kPerWave + (uint64_t)(64 * s + lane) >= a.M) continue;
+        const float4 r = lds4[idx[s]];
+        const float g[2] = {r.x, r.y};
+        dist += add_sample<2>(sum, cnt, idx[s], xs[s], g);
+        used += 1ull;
+      }
+    }
+    store_partials<kThreads>(a, sum, cnt, dist, used, 0ull);
+    return;
+  }
+  const uint64_t per_round = (uint64_t)gridDim.x * kThreads * S;
   for (uint64_t base = (uint64_t)blockIdx.x * kThreads * S; base < a.M; base += per_round) {
     float xs[S][2];
     bool live[S];
     int idx[S];
+    uint4 w[S];
 #pragma unroll
     for (int s = 0; s < S; ++s) {
       const uint64_t m = base + (uint64_t)s * kThreads + threadIdx.x;
@@ -276,26 +304,13 @@ __global__ __launch_bounds__(kLloydWideThreads) void lloyd_accum_wide_kernel(Llo
       lloyd_sample<2>(a, live[s] ? m : 0, xs[s]);
       used += live[s] ? 1ull : 0ull;
     }
-    if (scan) {
-      argmin_scan_tiled<2, S, 4>(lds4, a.Npad, xs, idx);
-    } else {
-      uint4 w[S];
-      bucket_rows<S>(a, a.N, tab, xs, w);
-      bucket_argmin<S>(pairs, a.N, tab, xs, w, idx);
-    }
+    bucket_rows<S>(a, a.N, tab, xs, w);
+    bucket_argmin<S>(pairs, a.N, tab, xs, w, idx);
 #pragma unroll
     for (int s = 0; s < S; ++s) {
       if (!live[s]) continue;
-      float g[2];
-      if (scan) {
-        const float4 r = lds4[idx[s]];
-        g[0] = r.x;
-        g[1] = r.y;
-      } else {
-        const float2 r = pairs[idx[s]];
-        g[0] = r.x;
-        g[1] = r.y;
-      }
+      const float2 r = pairs[idx[s]];
+      const float g[2] = {r.x, r.y};
       dist += add_sample<2>(sum, cnt, idx[s], xs[s], g);
     }
   }

@@ -7,6 +7,7 @@
 #include <algorithm>
 #include <cstring>
 #include <string>
+#include <vector>
 
 #include "qtree.h"
 #include "qtree_internal.hpp"
@@ -77,10 +78,28 @@ qtree::LloydArgs args_of(int d, int N, const LloydLayout& l, float* grid, void* 
 // sample (coordinate r is at most kZMax sum_c |L_rc|; one outside would take
 // the full scan).  Filling them costs about 9 us a step, the scan about 0.1 us
 // per point where the samples are few and N M / (2 10^12) s where they are
-// many; both rules are where the two measured alike.
+// many; both rules are where the two measured alike.  A start grid with many
+// points in one bucket (a crowded one) has lists too long for the tables, in the
+// first steps at least, and those scan after building them; where N is small,
+// the build's pair tests alone cost more than the scan.  5 steps with tables and
+// without: 24 points in a bucket (N = 500, 10^6 samples) 341 and 387 us, 47 (N =
+// 2000) 1545 and 1111, all in one (N = 500) 658 and 385, 20 (N = 60) 344 and 168.
 constexpr int kTableMinN = 100;
 constexpr double kTableMinWork = 6e7;
-void table_args(qtree::LloydArgs& a, int N) {
+bool crowded(const qtree::LloydArgs& a, const float* grid0, int N, int B) {
+  const int most = std::min(qtree::kLongCap, std::max(16, N / 16));
+  std::vector<uint8_t> in((size_t)B * B, 0);
+  for (int i = 0; i < N; ++i) {
+    int c[2];
+    for (int r = 0; r < 2; ++r) {
+      const float f = (grid0[2 * i + r] - a.bk_lo[r]) * a.bk_scale[r];
+      c[r] = f >= 0.0f && f < (float)B ? (int)f : -1;
+    }
+    if (c[0] >= 0 && c[1] >= 0 && ++in[(size_t)c[0] * B + c[1]] > most) return true;
+  }
+  return false;
+}
+void table_args(qtree::LloydArgs& a, const float* grid0, int N) {
   if (a.d != 2 || a.xs) return;
   if (N < kTableMinN && (double)N * (double)a.M < kTableMinWork) return;
   const int B = qtree::lloyd_side(N);
@@ -91,6 +110,7 @@ void table_args(qtree::LloydArgs& a, int N) {
     a.bk_lo[r] = (float)-half;
     a.bk_scale[r] = (float)(B / (2.0 * half));
   }
+  if (crowded(a, grid0, N, B)) return;
   a.bk_rows = reinterpret_cast<uint16_t*>(a.part + (size_t)qtree::kLloydMaxWide * a.E);
   a.bk_longs = a.bk_rows + (size_t)B * B * qtree::kBucketRow;
   a.bk_pool = (int)qtree::long_rows((int64_t)B * B);
@@ -187,7 +207,7 @@ qtree_status qtree_lloyd(int32_t d, int32_t N, const float* L, const float* grid
   e = hipMemcpyAsync(grid, grid0, sizeof(float) * (size_t)N * d, hipMemcpyHostToDevice, s);
   if (e != hipSuccess) return set_error(QTREE_EDEVICE, std::string("start grid copy: ") +
                                                            hipGetErrorString(e));
-  table_args(a, N);
+  table_args(a, grid0, N);
   e = qtree::launch_lloyd_records(a, s);
   const int blocks = accum_blocks(a, cus);
   for (int32_t it = 0; it < steps && e == hipSuccess; ++it) {

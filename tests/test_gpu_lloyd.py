@@ -114,3 +114,34 @@ def _grid_2d(kind, N):
 def test_lloyd_2d_tables_bitwise(kind, N, M, L):
     _case(f"lloyd d=2 tables {kind} N={N} M={M}")
     _compare(2, _grid_2d(kind, N), np.array(L).reshape(2, 2), M, 3, 0x5EED0027, True)
+
+
+@pytest.mark.parametrize("N,M", [(128, 1), (128, 511), (200, 513), (200, 30_011),
+                                 (64, 2_200_001)])
+def test_lloyd_2d_steps_that_scan_after_all(N, M):
+    """A circle: no bucket is crowded, but all cells meet in the middle, so the
+    device finds the tables wanting and the steps scan (a wave's 512 samples at
+    a time: fewer, whole ones and a remainder)."""
+    _case(f"lloyd d=2 circle N={N} M={M}")
+    t = 2.0 * np.pi * np.arange(N) / N
+    g0 = np.stack([np.cos(t), np.sin(t)], -1).astype(np.float32)
+    _compare(2, g0, np.eye(2), M, 3, 0x5EED0028, True)
+
+
+def test_lloyd_2d_start_grids_in_one_place():
+    """No tables are built for a start grid that they could not answer: 100
+    points in one bucket take what 99 take, whose steps always scan."""
+    _case("lloyd d=2 crowded start")
+    times = []
+    for N in (99, 100):
+        g0 = (0.3 + 1e-6 * np.random.default_rng(N).normal(size=(N, 2))).astype(np.float32)
+        best = np.inf
+        for _ in range(8):
+            e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            e0.record()
+            qt.lloyd(2, g0, np.eye(2), 100_000, 5, 0x5EED0029)
+            e1.record()
+            torch.cuda.synchronize()
+            best = min(best, e0.elapsed_time(e1))
+        times.append(best)
+    assert times[1] < 1.6 * times[0], times
