@@ -18,6 +18,7 @@
 #include <algorithm>
 
 #include "bucket_list.hpp"
+#include "qtree_search.hpp"
 
 namespace qtree {
 
@@ -216,7 +217,7 @@ __global__ __launch_bounds__(kBlock) void cube_build_kernel(const Cubes* cubes, 
     c += __popcll(group);
   }
   __syncthreads();
-  const int listed = c < kCubeCand ? c : kCubeCand;
+  const int listed = c <= kCubeCand ? c : 0;
   uint64_t keep = 0;
   for (int p = sub; p < listed; p += kPerCube) {
     const float4 gp = g[cand[b][p]];
@@ -242,12 +243,37 @@ __global__ __launch_bounds__(kBlock) void cube_build_kernel(const Cubes* cubes, 
   }
 }
 
-hipError_t launch_cube_build(const Cubes* cubes, int n_layers_total, int total, const float4* pts,
-                             uint16_t* rows, hipStream_t s) {
+// Workgroup k: the samples of layer k's pairs whose bucket has no list, or that
+// are outside the box.
+__global__ __launch_bounds__(kBlock) void cube_probe_kernel(const LayerDev* layers, Cubes* cubes,
+                                                            const uint16_t* rows) {
+  const int k = (int)blockIdx.x;
+  unsigned int miss[2] = {0u, 0u};
+  for (int m = (int)threadIdx.x; m < kCubeProbes; m += kBlock) {
+    float z[3], e[3], x[2][3];
+    layer_normals<3>(0u, 0u, 0u, k, (uint64_t)m, z, e);
+    layer_pair<3>(layers[k], z, e, x[0], x[1]);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int r = cube_of(cubes[k + q], x[q]);
+      const bool no = r < 0 || rows[(size_t)r * kCubeRow] == kCubeFull;
+      miss[q] += (unsigned int)__popcll(__ballot(no));
+    }
+  }
+  if ((threadIdx.x & 63) < 2)
+    atomicAdd(&cubes[k + (int)(threadIdx.x & 63)].misses, miss[threadIdx.x & 63]);
+}
+
+hipError_t launch_cube_build(const LayerDev* layers, Cubes* cubes, int n_layers_total, int total,
+                             const float4* pts, uint16_t* rows, hipStream_t s) {
   if (total <= 0) return hipSuccess;
   if (total % kCubesPerTile) return hipErrorInvalidValue;
   hipLaunchKernelGGL(cube_build_kernel, dim3((unsigned)(total / kCubesPerTile)), dim3(kBlock), 0, s,
                      cubes, n_layers_total, pts, rows);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(cube_probe_kernel, dim3((unsigned)(n_layers_total - 1)), dim3(kBlock), 0, s,
+                     layers, cubes, rows);
   return hipGetLastError();
 }
 

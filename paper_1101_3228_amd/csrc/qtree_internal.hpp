@@ -121,6 +121,7 @@ struct Cubes {
   int32_t B[3];
   int32_t off;
   int32_t N, pt_off;
+  uint32_t misses;  // of the samples asked for at the build
 };
 constexpr int kCubeRow = 16;               // uint16 entries (32 bytes)
 constexpr int kCubeCap = kCubeRow - 1;
@@ -441,9 +442,12 @@ size_t lloyd_lds_bytes(int d, int N, int Npad, int P);
 hipError_t launch_bucket_build(const LayerDev* layers, int n_layers_total, int maxN,
                                int64_t total_buckets, const float4* pts, uint16_t* rows,
                                uint16_t* longs, hipStream_t s);
-// Rows of the d = 3 search of every layer, `total` of them.
-hipError_t launch_cube_build(const Cubes* cubes, int n_layers_total, int total, const float4* pts,
-                             uint16_t* rows, hipStream_t s);
+// Rows of the d = 3 search of every layer, `total` of them; and how many of
+// kCubeProbes pairs (X_k, X_{k+1}) per layer k find no list, counted in `misses`
+// of both layers.
+constexpr int kCubeProbes = 1024;
+hipError_t launch_cube_build(const LayerDev* layers, Cubes* cubes, int n_layers_total, int total,
+                             const float4* pts, uint16_t* rows, hipStream_t s);
 hipError_t launch_lloyd_records(const LloydArgs& a, hipStream_t s);
 hipError_t launch_lloyd_step(const LloydArgs& a, int blocks, hipStream_t s);
 // Moment-matching grids: exact integer moment sums of a device sample set,

@@ -28,6 +28,7 @@ struct qtree_plan {
   int32_t tune_buckets = 1;     // d = 2, 3: cells through the bucket tables
   int64_t buckets = 0;          // d = 2: buckets over all layers (0: no tables)
   int64_t cubes = 0;            // d = 3: the same
+  double cube_misses = 0.0;     // ... and the share of the search they leave to scans
   int64_t st_max = 1;           // super tiles of the largest count block
   int32_t max_tiles = 0, total_tiles = 0;
   std::vector<int32_t> tile_off;  // first super tile of every layer (host copy)

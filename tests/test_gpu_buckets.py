@@ -247,3 +247,37 @@ def test_boxes_beyond_the_type_have_no_tables(d):
     for mode in (0, qt.PATHWISE):
         ref = O.transitions(_omodel(spec), grid, N, M, seed=3, mode=mode, nthreads=8)
         assert np.array_equal(plan.transitions(M, 3, mode=mode).cpu().numpy(), ref), mode
+
+
+def _forward_ms(plan, M, counts):
+    best = np.inf
+    for _ in range(8):
+        e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        e0.record()
+        plan.transitions(M, 9, counts=counts)
+        e1.record()
+        torch.cuda.synchronize()
+        best = min(best, e0.elapsed_time(e1))
+    return best
+
+
+@pytest.mark.parametrize("rho,M", [(0.0, 300_001), (0.95, 30_011), (0.95, 1_000_001),
+                                   (0.99, 300_001)])
+def test_3d_grids_that_lists_do_not_answer_are_scanned(rho, M):
+    """Thin clouds crowd the buckets: with the tables on, a layerwise call takes
+    no longer than the full scan, and the counts are the same."""
+    _case(f"3-D thin clouds {rho} {M}")
+    spec = synth.bm_model(3, 4, rho=rho)
+    grid, N = synth.layer_grids(spec, [1] + [1000] * 4)
+    plan = qt.Plan(spec, grid, N, batch_samples=M)
+    times, counts = [], [plan.new_counts() for _ in range(2)]
+    for on in (1, 0):
+        plan.tune(buckets=on)
+        times.append(_forward_ms(plan, M, counts[on]))
+    assert torch.equal(counts[0], counts[1])
+    if M < 100_000:
+        ref = O.transitions(_omodel(spec), grid, N, M, seed=9, nthreads=8)
+        assert np.array_equal(counts[0][:plan.entries].cpu().numpy(), ref)
+    assert times[0] < 1.25 * times[1], times
+    if rho == 0.0:
+        assert times[0] < 0.7 * times[1], times
