@@ -1179,12 +1179,23 @@ class PathTurn {
 };
 }  // namespace
 
+// Whether a pathwise call goes through the cell scratch.
+//   - Few paths added to a large tree: the counting pass reads and writes every
+//     count (about 4.4 ps each), where 52 ps of atomics a step would do.  365
+//     layers of 500 points, 1 / 1000 / 10^4 paths added: 516 / 762 / 796 us on the
+//     spot, 923 / 919 / 902 through the cells, 10^5 1595 / 1079.  (Not for d = 2,
+//     whose walk on the spot is the slower one.)
+static bool through_cells(const qtree_plan* p, const qtree::FwdArgs& a, bool zero) {
+  if (p->path_cells == 0) return false;
+  const double steps = (double)p->n * (double)a.M;
+  return zero || p->d == 2 || 12.0 * steps >= (double)p->entries;
+}
+
 // Pathwise counts through the plan's cell scratch, in passes of at most
 // path_cells paths (*used = false: nothing was launched).
 static hipError_t path_passes(const qtree_plan* p, qtree::FwdArgs a, bool zero, hipStream_t s,
                               bool* used) {
   *used = false;
-  if (p->path_cells == 0) return hipSuccess;
   PathTurn turn(p, s);
   if (!turn.taken()) return turn.error;
   *used = true;
@@ -1270,7 +1281,7 @@ static qtree_status transitions_impl(const qtree_plan* plan, uint64_t m0, uint64
   hipError_t e = hipSuccess;
   qtree::FwdArgs a = fwd_args(plan, m0, M, seed, contract_id, counts);
   if (mode == QTREE_LAYERWISE && !cubes_answer(plan, M)) a.cubes = nullptr;
-  if (mode == QTREE_PATHWISE && M > 0 && !scratch) {
+  if (mode == QTREE_PATHWISE && M > 0 && !scratch && through_cells(plan, a, zero)) {
     bool used = false;
     e = path_passes(plan, a, zero, s, &used);
     if (e != hipSuccess) return hip_fail(e, "pathwise launch");

@@ -300,3 +300,39 @@ def test_captured_layerwise_call_beside_paths():
         assert np.array_equal(out[:plan.entries].cpu().numpy(), layer)
         for c in eager:
             assert np.array_equal(c[:plan.entries].cpu().numpy(), path)
+
+
+def _without_cells(plan):
+    """The same model in a workspace of its tables (within 2 %), which holds no
+    path cells: every call counts on the spot."""
+    size = 4096
+    while True:
+        try:
+            return _plan_in(plan, size)
+        except qt.QtreeError as err:
+            assert err.status == 2
+            size = int(1.02 * size) // 16 * 16
+
+
+def test_few_paths_added_to_a_large_tree():
+    """Adding a few paths does not read and write every count (their time is that
+    of counting on the spot), and counts the same on either side of the line
+    12 M n < entries."""
+    _case("few paths added")
+    spec = synth.bm_model(1, 6)
+    grid, N = synth.layer_grids(spec, [1] + [90] * 6)
+    plan = qt.Plan(spec, grid, N, batch_samples=1)
+    line = plan.entries // (12 * 6)
+    counts = plan.transitions(5000, SEED, mode=qt.PATHWISE)
+    m0 = 5000
+    for M in (1, line, line + 1, 20_000):
+        plan.transitions_add(counts, M, SEED, mode=qt.PATHWISE, m0=m0)
+        m0 += M
+    assert np.array_equal(counts.cpu().numpy(), _ref(spec, grid, N, m0))
+    spec = synth.bm_model(1, 100)
+    grid, N = synth.layer_grids(spec, [1] + [1000] * 100)
+    plan = qt.Plan(spec, grid, N, batch_samples=1)
+    counts = plan.transitions(1000, SEED, mode=qt.PATHWISE)
+    own, spot = (_best_ms(lambda p=p: p.transitions_add(counts, 100, SEED, mode=qt.PATHWISE))
+                 for p in (plan, _without_cells(plan)))
+    assert own < 1.5 * spot, (own, spot)
