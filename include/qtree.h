@@ -176,9 +176,10 @@ int64_t qtree_plan_points(const qtree_plan *plan);        /* sum_k N_k */
  *                        lists every point that can be the FP32 argmin in it,
  *                        the key's rounding included, so the cell is the full
  *                        scan's), 0 scans every point (the brute-force search
- *                        of Sec. 4); used by the LAYERWISE two-pass forward
- *                        (d = 3: where the lists answer nearly every sample),
- *                        the PATHWISE forward and, for d = 2, qtree_cells.
+ *                        of Sec. 4); used by the LAYERWISE two-pass forward,
+ *                        the PATHWISE forward (d = 3: both where the lists
+ *                        answer nearly every sample) and, for d = 2,
+ *                        qtree_cells.
  */
 typedef enum {
   QTREE_TUNE_CHUNK = 0,

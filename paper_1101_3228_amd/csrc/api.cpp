@@ -1185,10 +1185,17 @@ class PathTurn {
 //     layers of 500 points, 1 / 1000 / 10^4 paths added: 516 / 762 / 796 us on the
 //     spot, 923 / 919 / 902 through the cells, 10^5 1595 / 1079.  (Not for d = 2,
 //     whose walk on the spot is the slower one.)
+//   - Walks that scan their layers (d = 2 without tables, d = 3 without them or
+//     where they do not answer): the scan hides the atomics, and a pass of 2^17
+//     paths only half fills the chip.  30 layers, d = 3, 3 10^5 paths: 216 points
+//     758 / 675, 343 845 / 969, 512 931 / 1395, 1000 1638 / 2754; 10^5 paths, 512
+//     points 509 / 489, 1000 911 / 967.
 static bool through_cells(const qtree_plan* p, const qtree::FwdArgs& a, bool zero) {
   if (p->path_cells == 0) return false;
   const double steps = (double)p->n * (double)a.M;
-  return zero || p->d == 2 || 12.0 * steps >= (double)p->entries;
+  if (!zero && p->d != 2 && 12.0 * steps < (double)p->entries) return false;
+  const bool scans = p->d == 2 ? !a.bucketed : p->d == 3 && !a.cubes;
+  return !scans || p->points < (a.M > (uint64_t)p->path_cells ? 300 : 900) * (int64_t)p->n;
 }
 
 // Pathwise counts through the plan's cell scratch, in passes of at most
@@ -1236,18 +1243,21 @@ static hipError_t two_pass_in_plan(const qtree_plan* p, const qtree::FwdArgs& a,
   return two_pass(p, a, zero, s, sc);
 }
 
-// Whether a layerwise call of M samples goes through the plan's d = 3 tables.  A
-// sample without a list is scanned for by its wave alone, where the full scan
+// Whether a call of M samples goes through the plan's d = 3 tables.  A sample
+// without a list is scanned for by its wave alone, where the layerwise scan
 // shares each record among 256 samples, and in a small call the waves with such
-// samples are the last to end.  By tables / scan: misses 0.034 (N = 300), 6000
-// pairs 104 / 90 us; 0.045 (300), 2 10^5 109 / 98, 6 10^6 345 / 427; 0.06 (1000),
-// 2 10^5, 6 10^5, 10^6 and 6 10^6 225 / 213, 222 / 236, 223 / 377, 566 / 1075;
-// 0.11 (512), 6 10^5 and 6 10^6 168 / 145 and 516 / 610; 0.33 (1000) 479 / 236 and
-// 1840 / 1040.  Product grids of Brownian layers miss 0.0003 up to a correlation
-// of 0.9, 0.3 at 0.95 and nearly all at 0.99; a normal sample as a grid 0.06.
-static bool cubes_answer(const qtree_plan* p, uint64_t M) {
+// samples are the last to end.  By tables / scan, layerwise: misses 0.034 (N = 300),
+// 6000 pairs 104 / 90 us; 0.045 (300), 2 10^5 109 / 98, 6 10^6 345 / 427; 0.06
+// (1000), 2 10^5, 6 10^5, 10^6 and 6 10^6 225 / 213, 222 / 236, 223 / 377, 566 /
+// 1075; 0.11 (512), 6 10^5 and 6 10^6 168 / 145 and 516 / 610; 0.33 (1000) 479 /
+// 236 and 1840 / 1040.  Pathwise, 10 layers of 1000 points, 10^5 and 3 10^5 paths:
+// 0.06 164 / 322 and 477 / 591, 0.14 267 / 332 and 750 / 618, 0.33 350 / 332 and
+// 988 / 608.  Product grids of Brownian layers miss 0.0003 up to a correlation of
+// 0.9, 0.3 at 0.95 and nearly all at 0.99; a normal sample as a grid 0.06.
+static bool cubes_answer(const qtree_plan* p, qtree_mode mode, uint64_t M) {
   const double pairs = (double)p->n * (double)M;
-  return p->cube_misses <= (pairs < 2e5 ? 0.03 : pairs < 1e6 ? 0.06 : 0.12);
+  return p->cube_misses <=
+         (mode == QTREE_PATHWISE ? 0.15 : pairs < 2e5 ? 0.03 : pairs < 1e6 ? 0.06 : 0.12);
 }
 
 static qtree_status transitions_impl(const qtree_plan* plan, uint64_t m0, uint64_t M,
@@ -1280,7 +1290,7 @@ static qtree_status transitions_impl(const qtree_plan* plan, uint64_t m0, uint64
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e = hipSuccess;
   qtree::FwdArgs a = fwd_args(plan, m0, M, seed, contract_id, counts);
-  if (mode == QTREE_LAYERWISE && !cubes_answer(plan, M)) a.cubes = nullptr;
+  if (!cubes_answer(plan, mode, M)) a.cubes = nullptr;
   if (mode == QTREE_PATHWISE && M > 0 && !scratch && through_cells(plan, a, zero)) {
     bool used = false;
     e = path_passes(plan, a, zero, s, &used);

@@ -336,3 +336,23 @@ def test_few_paths_added_to_a_large_tree():
     own, spot = (_best_ms(lambda p=p: p.transitions_add(counts, 100, SEED, mode=qt.PATHWISE))
                  for p in (plan, _without_cells(plan)))
     assert own < 1.5 * spot, (own, spot)
+
+
+@pytest.mark.parametrize("d,N1", [(2, 1024), (3, 1000)])
+def test_scanned_walks_of_many_paths(d, N1):
+    """Without tables the walk scans its layers: more paths than a pass of the
+    cells take what counting on the spot takes, and count the same."""
+    _case(f"scanned walks {d}-D {N1}")
+    spec = synth.bm_model(d, 10, rho=0.3)
+    grid, N = synth.layer_grids(spec, [1] + [N1] * 10)
+    plan = qt.Plan(spec, grid, N, batch_samples=1)
+    M = 300_001
+    want = plan.transitions(M, SEED, mode=qt.PATHWISE).clone()
+    plan.tune(buckets=0)
+    other = _without_cells(plan).tune(buckets=0)
+    counts = plan.new_counts()
+    own, spot = (_best_ms(lambda p=p: p.transitions(M, SEED, mode=qt.PATHWISE, counts=counts))
+                 for p in (plan, other))
+    plan.transitions(M, SEED, mode=qt.PATHWISE, counts=counts)
+    assert torch.equal(counts[:plan.entries], want)
+    assert own < 1.25 * spot, (own, spot)
