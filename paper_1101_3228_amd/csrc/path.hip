@@ -16,6 +16,7 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kStep = 4;        // d = 1: layers whose midpoints are staged together
+constexpr int kStageP = 1024;   // ... where the largest is no larger (padded)
 constexpr int kCountBlock = 1024;
 constexpr size_t kLdsBytes = 160 * 1024;  // of a CU
 
@@ -44,8 +45,10 @@ __device__ __forceinline__ void visit(const FwdArgs& a, const Visits& v, int k, 
 // d = 1: kStep layers at a time (one Philox block gives kStep normals): the
 // states first, a chain of fused multiply-adds, then the searches of all
 // kStep cells side by side over midpoints staged in LDS while the normals
-// are drawn.  STAGE = false (layers above 4096 points): the searches read
-// the midpoints from memory.
+// are drawn.  STAGE = false (layers above kStageP points): the searches read
+// the midpoints from memory, as a workgroup's 256 paths would not use what it
+// stages (32 KB for 2048 points; 20 layers of 1448 points, 2 10^4 paths 114 us
+// staged, 103 not; 50 of 500 points 116 and 142).
 template <bool STAGE, bool STORE>
 __global__ __launch_bounds__(kBlock) void walk_1d(FwdArgs a, Visits v) {
   extern __shared__ float lds[];  // [kStep][maxP]
@@ -76,9 +79,7 @@ __global__ __launch_bounds__(kBlock) void walk_1d(FwdArgs a, Visits v) {
       y[s] = x;
     }
     if (STAGE) __syncthreads();
-    // the deepest search of the kStep layers serves all: a midpoint past a
-    // layer's own padded array is not read (its steps are skipped)
-    int c[kStep], lg[kStep], top = 0;
+    int lg[kStep], top = 0;
     const float* m[kStep];
 #pragma unroll
     for (int s = 0; s < kStep; ++s) {
@@ -86,8 +87,22 @@ __global__ __launch_bounds__(kBlock) void walk_1d(FwdArgs a, Visits v) {
       m[s] = STAGE ? lds + s * a.maxP : a.mids + L1.aux_off;
       lg[s] = s < steps ? L1.logP : 0;
       top = max(top, lg[s]);
-      c[s] = 0;
     }
+    if (!STORE) {
+      // one after the other: the atomics of a step run beside the next search
+      // (5 layers of 3000 points, 10^5 paths 71 us, side by side 79)
+#pragma unroll
+      for (int s = 0; s < kStep; ++s)
+        if (s < steps) {
+          const int c = cell_1d(m[s], lg[s], y[s]);
+          visit<STORE>(a, v, k + s, t, live, i, c);
+          i = c;
+        }
+      continue;
+    }
+    // the deepest search of the kStep layers serves all: a midpoint past a
+    // layer's own padded array is not read (its steps are skipped)
+    int c[kStep] = {};
     for (int h = top - 1; h >= 0; --h) {
 #pragma unroll
       for (int s = 0; s < kStep; ++s)
@@ -409,7 +424,7 @@ static hipError_t launch_walk(const FwdArgs& a, const Visits& v, hipStream_t s) 
     return hipGetLastError();
   };
   if (a.d == 1)
-    return a.maxP <= 4096 ? go(walk_1d<true, STORE>, sizeof(float) * kStep * (size_t)a.maxP)
+    return a.maxP <= kStageP ? go(walk_1d<true, STORE>, sizeof(float) * kStep * (size_t)a.maxP)
                           : go(walk_1d<false, STORE>, 0);
   if (a.d == 2 && a.bucketed && STORE && wide_lds(a.maxN) <= kLdsBytes) {
     const size_t lds = wide_lds(a.maxN);

@@ -44,6 +44,20 @@ def test_paths_1d(sizes, M):
     assert np.array_equal(got, _ref(spec, grid, N, M, m0=3))
 
 
+@pytest.mark.parametrize("sizes", [[1, 1024, 7], [1, 1025, 3, 1024, 5, 2048], [1, 2, 513, 12]],
+                         ids=str)
+def test_paths_1d_staged_and_not(sizes):
+    """Midpoints through LDS up to 1024 points a layer, from memory beyond;
+    through the cells and on the spot."""
+    _case(f"paths 1-D staged or not {sizes}")
+    spec = synth.bm_model(1, len(sizes) - 1)
+    grid, N = synth.layer_grids(spec, sizes)
+    plan = qt.Plan(spec, grid, N, batch_samples=1)
+    ref = _ref(spec, grid, N, 30_001)
+    for p in (plan, _without_cells(plan)):
+        assert np.array_equal(p.transitions(30_001, SEED, mode=qt.PATHWISE).cpu().numpy(), ref)
+
+
 @pytest.mark.parametrize("d,side", [(2, (1, 1)), (2, (5, 6)), (2, (33, 34)), (2, (16, 16)),
                                     (3, (4, 5, 6))], ids=str)
 @pytest.mark.parametrize("buckets", [1, 0])
