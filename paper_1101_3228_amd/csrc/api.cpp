@@ -1190,12 +1190,22 @@ class PathTurn {
 //     paths only half fills the chip.  30 layers, d = 3, 3 10^5 paths: 216 points
 //     758 / 675, 343 845 / 969, 512 931 / 1395, 1000 1638 / 2754; 10^5 paths, 512
 //     points 509 / 489, 1000 911 / 967.
+//   - Many super tiles a layer, each of which reads every path's cells: 50 layers,
+//     d = 1, one pass of 2^17 paths, 30 / 45 / 62 / 88 tiles (700 to 1200 points)
+//     348 / 337 / 355 / 450 us on the spot, 234 / 283 / 339 / 485 through the cells
+//     (5 10^4 paths 182 / 188 / 197 / 306 and 173 / 202 / 223 / 316); 3 10^5 paths
+//     721 / 704 / 725 / 865 and 614 / 741 / 874 / 1415.  30 layers, d = 2, 38 / 64 /
+//     92 tiles 241 / 222 / 240 and 168 / 223 / 335; 500 / 458 / 483 and 401 / 539 /
+//     810.
 static bool through_cells(const qtree_plan* p, const qtree::FwdArgs& a, bool zero) {
   if (p->path_cells == 0) return false;
   const double steps = (double)p->n * (double)a.M;
   if (!zero && p->d != 2 && 12.0 * steps < (double)p->entries) return false;
+  const bool several = a.M > (uint64_t)p->path_cells;  // passes
   const bool scans = p->d == 2 ? !a.bucketed : p->d == 3 && !a.cubes;
-  return !scans || p->points < (a.M > (uint64_t)p->path_cells ? 300 : 900) * (int64_t)p->n;
+  if (scans) return p->points < (several ? 300 : 900) * (int64_t)p->n;
+  const int most = p->d == 1 ? (several ? 32 : 48) : several ? 48 : 64;
+  return p->d == 3 || p->total_tiles <= most * p->n;
 }
 
 // Pathwise counts through the plan's cell scratch, in passes of at most

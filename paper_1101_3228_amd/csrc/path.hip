@@ -4,8 +4,10 @@
 // count block in LDS, or are counted on the spot with one device-scope atomic
 // per step (no scratch, or count blocks of too many tiles).
 //
-// A device-scope atomic costs about 52 ps of the whole chip; reading a cell
-// pair once per super tile of its block, 0.15 ps and the walk's two bytes.
+// A device-scope atomic costs about 50 ps of the whole chip; reading a cell
+// pair once per super tile of its block, 0.7 ps, the walk's two bytes, and a
+// read and a write of every count in each pass (through_cells in api.cpp
+// weighs them).
 #include "qtree_internal.hpp"
 #include "qtree_rng.hpp"
 #include "qtree_search.hpp"

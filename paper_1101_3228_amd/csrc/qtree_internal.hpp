@@ -167,8 +167,7 @@ struct WsLayout {
 // paths a pass (a path's walk is a serial chain: 2^17 fill the chip) in at
 // most 96 MiB (n = 365 still takes 2^17); no scratch where that is under 4096
 // paths, or where a count block has more than kPathTiles super tiles (about
-// 1450 points a layer), each of which reads every cell pair: the direct
-// atomics then cost about as much.
+// 1450 points a layer), each of which reads every cell pair.
 constexpr int64_t kPathCells = 1 << 17;
 constexpr int64_t kPathBytes = 96ll << 20;
 constexpr int kPathTiles = 128;

@@ -370,3 +370,19 @@ def test_scanned_walks_of_many_paths(d, N1):
     plan.transitions(M, SEED, mode=qt.PATHWISE, counts=counts)
     assert torch.equal(counts[:plan.entries], want)
     assert own < 1.25 * spot, (own, spot)
+
+
+@pytest.mark.parametrize("d,n,N1,M", [(1, 20, 1400, 300_001), (1, 20, 1200, 120_001),
+                                      (2, 10, 1369, 300_001)])
+def test_paths_through_large_count_blocks(d, n, N1, M):
+    """Where a count block has so many super tiles that reading the cells once in
+    each costs more than the atomics, the paths are counted on the spot."""
+    _case(f"large count blocks {d}-D {N1} {M}")
+    spec = synth.bm_model(d, n, rho=0.3 if d > 1 else 0.0)
+    grid, N = synth.layer_grids(spec, [1] + [N1] * n)
+    plan = qt.Plan(spec, grid, N, batch_samples=1)
+    counts = [plan.new_counts() for _ in range(2)]
+    own, spot = (_best_ms(lambda p=p, c=c: p.transitions(M, SEED, mode=qt.PATHWISE, counts=c))
+                 for p, c in zip((plan, _without_cells(plan)), counts))
+    assert torch.equal(counts[0], counts[1])
+    assert own < 1.2 * spot, (own, spot)
