@@ -640,6 +640,10 @@ typedef const uint64_t __attribute__((address_space(1)))* GlobalU64;
 // the K order of bdp_tile.hpp (lane group g takes columns 4 g .. + 3 of the
 // 16, 32 bytes of its row).
 //
+// R: a lane has rows g, g + 4, ... of a tile; layers of at most 4 R points have R
+// of them, and no others' obstacles are computed (50 layers of 4 points, one
+// contract 77 -> 60 us, 20000 138 -> 75).
+//
 // The products (64 clocks of a matrix core for 1024 multiply-adds, the rate
 // of the vector units) run beside the obstacles' exponentials of other waves.
 // With lane = contract, vector multiply-adds and the weights as scalar
@@ -707,7 +711,7 @@ __device__ __forceinline__ bool finite_parameters(const Contract& C, int d) {
   return ok;
 }
 
-template <int D, int CTS, int TILES>
+template <int D, int CTS, int TILES, int R = 4>
 __global__ __launch_bounds__(64 * kManyWaves) void bdp_many_kernel(ManyArgs a) {
   constexpr int kCols = 16 * CTS, kRowTiles = kManyWaves / CTS;
   extern __shared__ double Vs[];  // [np_max][kCols]
@@ -802,7 +806,7 @@ __global__ __launch_bounds__(64 * kManyWaves) void bdp_many_kernel(ManyArgs a) {
                                                      Vs[(jc + u) * kCols + col], acc, 0, 0, 0);
       }
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
+      for (int r = 0; r < R; ++r) {
         const int ir = min(i0 + g + 4 * r, Nk - 1);
         float xs[3];
         grid_point<D>(T, pt, ir, xs);
@@ -816,7 +820,7 @@ __global__ __launch_bounds__(64 * kManyWaves) void bdp_many_kernel(ManyArgs a) {
       const int i0 = 16 * (rt0 + kRowTiles * t);
       if (i0 >= Nk) break;
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
+      for (int r = 0; r < R; ++r)
         if (i0 + g + 4 * r < Nk) Vs[(i0 + g + 4 * r) * kCols + col] = res[t][r];
     }
     __syncthreads();
@@ -854,7 +858,11 @@ bool bdp_many_fits(int max_n) { return max_n <= 256; }
 // 100 layers of 100 points, 16 / 64 contracts a workgroup: 1000 contracts 324 /
 // 904 us, 15000 470 / 894, 30000 767 / 970, 100000 2338 / 2162 (the lane =
 // contract kernel: 6470 us).
-int bdp_many_cols(int64_t blocks64) { return blocks64 < 1024 ? 16 : 64; }
+// Layers of one tile keep one wave of a workgroup of 16 busy: from 192 of 64 on
+// those are better (50 layers of 12 points, 20000 contracts 144 / 107 us).
+int bdp_many_cols(int64_t blocks64, int max_n) {
+  return blocks64 < (max_n <= 16 ? 192 : 1024) ? 16 : 64;
+}
 
 template <int D>
 static hipError_t launch_bdp_many_d(const ManyArgs& a, hipStream_t s) {
@@ -870,6 +878,10 @@ static hipError_t launch_bdp_many_d(const ManyArgs& a, hipStream_t s) {
     return hipGetLastError();
   };
   if (!bdp_many_fits(a.max_n)) return hipErrorInvalidValue;
+  if (a.max_n <= 4)
+    return a.cols == 16 ? go(bdp_many_kernel<D, 1, 1, 1>) : go(bdp_many_kernel<D, 4, 1, 1>);
+  if (a.max_n <= 8)
+    return a.cols == 16 ? go(bdp_many_kernel<D, 1, 1, 2>) : go(bdp_many_kernel<D, 4, 1, 2>);
   const bool small = a.max_n <= 128;
   if (a.cols == 16) return small ? go(bdp_many_kernel<D, 1, 1>) : go(bdp_many_kernel<D, 1, 2>);
   return small ? go(bdp_many_kernel<D, 4, 4>) : go(bdp_many_kernel<D, 4, 8>);

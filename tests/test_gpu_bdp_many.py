@@ -202,3 +202,47 @@ def test_obstacles_that_overflow(d, sizes, nq):
     ok = np.isfinite(want)
     assert np.array_equal(got[~ok], want[~ok], equal_nan=True)
     assert np.all(np.abs(got[ok] - want[ok]) <= 1e-12 * np.abs(want[ok]) + 1e-14)
+
+
+@pytest.mark.parametrize("d,sizes", [(1, [1, 1, 4, 2, 3]), (1, [1, 8, 5, 1, 7]), (1, [1, 16, 9, 2]),
+                                     (2, [1, (2, 2), (1, 3)]), (3, [1, (2, 2, 2), (1, 2, 3)])],
+                         ids=str)
+def test_small_layers(d, sizes):
+    """Layers of at most 4, 8 and 16 points have workgroups of their own; both
+    forms (64 contracts from 192 workgroups of 64 on) against the oracle, and
+    each other bit for bit."""
+    _case(f"bdp_many small layers {d} {sizes}")
+    spec = synth.bm_model(d, len(sizes) - 1, T=1.0)
+    grid, N = synth.layer_grids(spec, sizes)
+    plan = qt.Plan(spec, grid, N)
+    counts = plan.transitions(30_000, 3)
+    _check(plan, spec, grid, N, counts, 37, 8)
+    pi = plan.pi(counts)
+    kinds, S0, K, r, T, sigma, mix = _contracts(np.random.default_rng(2), 192 * 64 + 5, d)
+    sp = qt.payoff_specs(d, kinds, S0, K, r, T, sigma, mix)
+    many = plan.bdp_many(pi, sp).cpu().numpy()
+    few = plan.bdp_many(pi, sp[-1005:]).cpu().numpy()
+    assert np.array_equal(many[-1005:].view(np.uint64), few.view(np.uint64))
+
+
+def test_small_layers_take_less_than_large_ones():
+    """The rows of a tile that a small layer does not have cost nothing."""
+    _case("bdp_many small layers' time")
+    times = []
+    for size in (4, 16):
+        spec = synth.bm_model(1, 60, T=1.0)
+        grid, N = synth.layer_grids(spec, [1] + [size] * 60)
+        plan = qt.Plan(spec, grid, N)
+        pi = plan.pi(plan.transitions(10_000, 3))
+        specs = torch.from_numpy(qt.payoff_specs(1, np.zeros(64, np.int32), 100.0, 100.0, 0.05,
+                                                 1.0, [[0.2]]).view(np.uint8).reshape(-1)).cuda()
+        best = np.inf
+        for _ in range(8):
+            e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            e0.record()
+            plan.bdp_many(pi, specs)
+            e1.record()
+            torch.cuda.synchronize()
+            best = min(best, e0.elapsed_time(e1))
+        times.append(best)
+    assert times[0] < 0.9 * times[1], times
