@@ -281,3 +281,31 @@ def test_3d_grids_that_lists_do_not_answer_are_scanned(rho, M):
     assert times[0] < 1.25 * times[1], times
     if rho == 0.0:
         assert times[0] < 0.7 * times[1], times
+
+
+@pytest.mark.parametrize("sizes", [[23, 24, 8, 40], [4, 23, 2, 12], [24, 25, 3, 24]], ids=str)
+@pytest.mark.parametrize("mode", [0, 1])
+def test_3d_layers_on_either_side_of_the_tables(sizes, mode):
+    """Layers of fewer than 24 points have no tables; beside others that have
+    them, and alone."""
+    _case(f"3-D small layers {sizes} {mode}")
+    rng = np.random.default_rng(13)
+    spec = synth.bm_model(3, len(sizes), T=1.0, rho=0.2)
+    grid = np.concatenate([np.zeros((1, 3))] + [rng.standard_normal((s, 3)) for s in sizes])
+    grid = grid.astype(np.float32)
+    N = np.array([1] + sizes, np.int32)
+    plan = qt.Plan(spec, grid, N)
+    ref = O.transitions(_omodel(spec), grid, N, 30_011, seed=4, mode=mode, nthreads=8)
+    assert np.array_equal(plan.transitions(30_011, 4, mode=mode).cpu().numpy(), ref)
+
+
+def test_3d_small_layers_take_no_longer_than_the_scan():
+    _case("3-D small layers' time")
+    spec = synth.bm_model(3, 50, T=1.0, rho=0.2)
+    grid, N = synth.layer_grids(spec, [1] + [(2, 2, 2)] * 50)
+    plan = qt.Plan(spec, grid, N, batch_samples=1_000_000)
+    counts, times = plan.new_counts(), []
+    for on in (1, 0):
+        plan.tune(buckets=on)
+        times.append(_forward_ms(plan, 1_000_000, counts))
+    assert times[0] < 1.08 * times[1], times
