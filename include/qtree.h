@@ -85,10 +85,10 @@ const char *qtree_version(void);
  * passes; a plan uses all the scratch its workspace has room for.  For d = 2
  * it includes the bucket tables of the cell search, 24 bytes per bucket and
  * about 36 buckets per grid point (1.7 MB for a layer of 2000 points), for
- * d = 3 those of 32 bytes and about 32 per point (1 MB for 1000 points, 256 MB
- * for a plan at most), and for layers of up to about 1450 points the cell
- * scratch of PATHWISE calls, 2 bytes per layer and path for up to 2^17 paths a
- * pass, at most 96 MiB.  Pure host arithmetic.
+ * d = 3 those of 32 bytes and about 32 per point (1 MB for 1000 points; 16 per
+ * point, or none, where a plan's would be more than 256 MB), and for layers of
+ * up to about 1450 points the cell scratch of PATHWISE calls, 2 bytes per layer
+ * and path for up to 2^17 paths a pass, at most 96 MiB.  Pure host arithmetic.
  * In a workspace of another size a plan takes, after the layer tables: the
  * d = 3 tables, if they leave scratch for 2^15 LAYERWISE samples per layer a
  * pass (or all that there would be without them; else d = 3 scans all points);

@@ -182,16 +182,25 @@ int64_t path_cells(int n, const int32_t* N) {
   return c < 4096 ? 0 : c;
 }
 
-// Buckets of the d = 3 search over all layers: layers take tables in order
-// while the rows so far stay within kMaxCubes.
-int64_t total_cubes(int n, const int32_t* N) {
+// Buckets of the d = 3 search over all layers, `per` a point.
+static int64_t cube_rows_of(int n, const int32_t* N, int per) {
   int64_t b = 0;
   for (int k = 0; k <= n; ++k) {
-    if (N[k] < kCubeMinN) continue;
-    const int64_t side = cube_side(N[k]), b3 = side * side * side;
-    if (b + b3 <= kMaxCubes) b += b3;
+    const int64_t side = cube_side(N[k], per);
+    if (N[k] >= kCubeMinN) b += side * side * side;
   }
   return b;
+}
+
+int cubes_per_point(int n, const int32_t* N) {
+  for (int per : {32, 16})
+    if (cube_rows_of(n, N, per) <= kMaxCubes) return per;
+  return 0;
+}
+
+int64_t total_cubes(int n, const int32_t* N) {
+  const int per = cubes_per_point(n, N);
+  return per > 0 ? cube_rows_of(n, N, per) : 0;
 }
 
 WsLayout ws_layout(int d, int n, const int32_t* N, int64_t batch_chunks, int64_t cells,
@@ -531,6 +540,7 @@ static void bucket_boxes(qtree_plan& p, const qtree_model* model, const float* g
 // wave scans for it (3.8 and 4.8 standard deviations: the same within 2 %).
 static void cube_boxes(qtree_plan& p, const qtree_model* model, qtree::Cubes* cubes) {
   constexpr double kCubeSigma = 4.2;
+  const int per = qtree::cubes_per_point(p.n, p.N.data());
   int64_t off = 0;
   for (int k = 0; k <= p.n; ++k) {
     qtree::Cubes& C = cubes[k];
@@ -539,8 +549,7 @@ static void cube_boxes(qtree_plan& p, const qtree_model* model, qtree::Cubes* cu
     C.N = p.N[k];
     C.pt_off = (int32_t)p.pt_off[k];
     if (p.N[k] < qtree::kCubeMinN) continue;
-    const int64_t B = qtree::cube_side(p.N[k]);
-    if (off + B * B * B > qtree::kMaxCubes) continue;
+    const int64_t B = qtree::cube_side(p.N[k], per);
     for (int r = 0; r < 3; ++r) {
       const float* Lk = model->L + (size_t)k * 9 + r * 3;
       double var = 0.0;

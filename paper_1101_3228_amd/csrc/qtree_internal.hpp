@@ -137,15 +137,20 @@ constexpr int kCubeTile = 4;               // B is a multiple of it
 // 1157 / 616 / 316 us, the full scan in one pass 805; 10^6 samples 3765 / 1915 /
 // 1004 against 2387; 4 layers of 4096 points 1408 / 848 / 468 against 1460.
 constexpr int64_t kCubeChunks = 8;
-constexpr int64_t kMaxCubes = 1ll << 23;   // rows of a plan (256 MB); later layers scan
-// Buckets per axis of a layer of N points: about 32 per point, at most 64 per
+constexpr int64_t kMaxCubes = 1ll << 23;   // rows of a plan (256 MB)
+// Buckets per axis of a layer of N points: about `per` per point, at most 64 per
 // axis.  16 / 32 / 64 per point: 294 / 289 / 288 us for a 12-layer tree of
-// 990 points and 3 10^5 pairs per layer (the full scan: 927 us).
-inline int cube_side(int N) {
+// 990 points and 3 10^5 pairs per layer (the full scan: 927 us).  A plan takes
+// 32, or 16 where those would be too many rows, and beyond that no tables: the
+// layers of a plan that had tables for some only scanned alone at the end of a
+// launch (290 layers of 1000 points, 3 10^4 samples 2584 us, the scan 1998).
+inline int cube_side(int N, int per) {
   int b = kCubeTile;
-  while ((double)b * b * b < 32.0 * N) b += kCubeTile;
+  while ((double)b * b * b < (double)per * N) b += kCubeTile;
   return b < 64 ? b : 64;
 }
+// 32, 16 or 0.
+int cubes_per_point(int n, const int32_t* N);
 
 // Workspace layout (byte offsets from the workspace base).
 struct WsLayout {

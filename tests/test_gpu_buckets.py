@@ -309,3 +309,25 @@ def test_3d_small_layers_take_no_longer_than_the_scan():
         plan.tune(buckets=on)
         times.append(_forward_ms(plan, 1_000_000, counts))
     assert times[0] < 1.08 * times[1], times
+
+
+@pytest.mark.parametrize("large", [64, 100])
+def test_3d_plans_of_many_buckets(large):
+    """64 layers of 4096 points take 16 buckets a point instead of 32, 100 of
+    them none (all layers alike)."""
+    _case(f"3-D many buckets {large}")
+    rng = np.random.default_rng(14)
+    n = 2 * large
+    spec = synth.bm_model(3, n, T=1.0, rho=0.2)
+    g = rng.standard_normal((4096, 3))
+    parts, N = [np.zeros((1, 3))], [1]
+    for k in range(1, n + 1):
+        parts.append(g * np.sqrt(k / n) if k % 2 else np.zeros((1, 3)))
+        N.append(len(parts[-1]))
+    grid, N = np.concatenate(parts).astype(np.float32), np.array(N, np.int32)
+    plan = qt.Plan(spec, grid, N, batch_samples=1)
+    rows = qt.workspace_size(3, n, N, 1) / 32
+    assert (rows > 5_000_000) == (large == 64)
+    for mode in (0, 1):
+        ref = O.transitions(_omodel(spec), grid, N, 300, seed=4, mode=mode, nthreads=8)
+        assert np.array_equal(plan.transitions(300, 4, mode=mode).cpu().numpy(), ref), mode
