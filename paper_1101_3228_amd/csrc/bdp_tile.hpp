@@ -72,11 +72,42 @@ __device__ __forceinline__ void drop_tails(int n, int j, int stride, T (&x)[A][4
   for (int a = 0; a < A; ++a) drop_front(x[a], Cols4(j + stride * a, n).drop);
 }
 
+// Elements 0 .. 3 - d of x behind d zeros, d >= 0 (a lane's own).
+template <class T>
+__device__ __forceinline__ void drop_back(T (&x)[4], int d) {
+  const bool one = (d & 1) != 0, two = (d & 2) != 0;
+#pragma unroll
+  for (int u = 3; u > 0; --u) x[u] = one ? x[u - 1] : x[u];
+  x[0] = one ? (T)0 : x[0];
+#pragma unroll
+  for (int u = 3; u >= 0; --u) x[u] = d >= 4 ? (T)0 : (two ? (u > 1 ? x[u - 2] : (T)0) : x[u]);
+}
+
 // Counts of A chunks from a row that holds columns [lo, hi), hi > lo, at
-// row[lo .. hi) (a band, or a row too short for Cols4), zero outside.
+// row[lo .. hi) (a band, or a row too short for Cols4), zero outside.  Rows of
+// four columns and more (`wide`, the same for the wave) are loaded four at a
+// time, as by Cols4 but at both ends.
 template <int A>
 __device__ __forceinline__ void load_band(const int32_t* __restrict__ row, int lo, int hi, int j,
-                                          int stride, int32_t (&c)[A][4]) {
+                                          int stride, bool wide, int32_t (&c)[A][4]) {
+  if (wide) {
+    int shift[A];
+#pragma unroll
+    for (int a = 0; a < A; ++a) {
+      const int t = j + stride * a, at = min(max(t, lo), hi - 4);
+      shift[a] = t - at;
+      const Int4U q = *reinterpret_cast<const Int4U*>(row + at);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) c[a][u] = q.v[u];
+    }
+#pragma unroll
+    for (int a = 0; a < A; ++a)
+      if (__any(shift[a] != 0)) {
+        drop_front(c[a], max(shift[a], 0));
+        drop_back(c[a], max(-shift[a], 0));
+      }
+    return;
+  }
 #pragma unroll
   for (int a = 0; a < A; ++a)
 #pragma unroll

@@ -153,3 +153,32 @@ def test_a_blocking_call_under_capture_is_refused_and_nothing_else():
     for _ in range(20):
         assert np.array_equal(plan.bdp(counts, phi, V=V)[0], want)
         assert np.array_equal(batch.run(), V1[:, 0].cpu().numpy())
+
+
+@pytest.mark.parametrize("pays", [1, 2, 3, 17])
+@pytest.mark.parametrize("noise", [1.0, 0.05, 0.002])
+@pytest.mark.parametrize("sizes", SIZES, ids=str)
+def test_banded_layers(sizes, noise, pays):
+    """Bands from all columns down to one or two (rows of fewer than four
+    entries, four at a time, several turns of a wave; bands that begin and end
+    anywhere), with an infinite terminal value that only some bands hold."""
+    print(f"[gpu-case] banded layers {sizes} {noise} {pays}", flush=True)
+    spec = synth.bm_model(1, len(sizes) - 1)
+    spec["T"] *= np.float32(noise)
+    grid, N = synth.layer_grids(spec, sizes)
+    plan = qt.Plan(spec, grid, N)
+    counts = plan.transitions_stratified(300, 11)
+    band, overflow = plan.transitions_stratified_banded(300, 11)
+    assert int(overflow.item()) == 0
+    phi = np.random.default_rng(pays).uniform(0.0, 2.0, (pays, plan.points))
+    phi[0, :-int(N[-1])] = -np.inf                      # European
+    if N[-1] > 2:
+        phi[-1, -2] = np.inf
+    ph = torch.from_numpy(phi).cuda()
+    V0, V = plan.bdp_banded(band, ph)
+    _, dense = plan.bdp(counts, ph)
+    _close(V.cpu().numpy(), dense.cpu().numpy())
+    assert np.array_equal(V0, V[:, 0].cpu().numpy())
+    phi[-1, -2] = 1.0
+    _, V = plan.bdp_banded(band, torch.from_numpy(phi).cuda())
+    _close(V.cpu().numpy(), O.bdp(counts.cpu().numpy(), N, phi, want_all=True)[1])
