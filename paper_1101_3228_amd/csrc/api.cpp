@@ -1802,7 +1802,7 @@ qtree_status qtree_bdp_many(const qtree_plan* plan, const void* pi, size_t pi_by
   a.d = plan->d;
   a.max_n = plan->maxN;
   a.np_max = (plan->maxN + 3) & ~3;
-  a.cols = qtree::bdp_many_cols((n_q + 63) / 64, plan->maxN);
+  a.cols = qtree::bdp_many_cols((n_q + 63) / 64, plan->points, plan->n + 1);
   hipError_t e = qtree::launch_bdp_many(a, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? QTREE_OK : hip_fail(e, "bdp_many launch");
 }
@@ -1819,7 +1819,7 @@ qtree_status qtree_bdp_many_trees(int32_t n_trees, const qtree_plan* const* plan
     return fail(QTREE_EINVAL, "plans, pi, pi_bytes and q_begin must be non-NULL");
   if (q_begin[0] < 0) return fail(QTREE_EINVAL, "q_begin[0] must be >= 0");
   int d = 0, max_n = 0;
-  int64_t blocks = 0;
+  int64_t blocks = 0, points = 0, layers = 0;
   std::vector<int> order((size_t)n_trees);
   for (int t = 0; t < n_trees; ++t) {
     const qtree_plan* p = plans[t];
@@ -1832,6 +1832,8 @@ qtree_status qtree_bdp_many_trees(int32_t n_trees, const qtree_plan* const* plan
     if (q_begin[t + 1] < q_begin[t]) return fail(QTREE_EINVAL, "q_begin must be nondecreasing");
     max_n = std::max(max_n, p->maxN);
     blocks += (q_begin[t + 1] - q_begin[t] + 63) / 64;
+    points += p->points;
+    layers += p->n + 1;
     order[(size_t)t] = t;
   }
   if (q_begin[n_trees] > q_begin[0] && (!specs || !V0))
@@ -1845,7 +1847,7 @@ qtree_status qtree_bdp_many_trees(int32_t n_trees, const qtree_plan* const* plan
     return fail(QTREE_ENOMEM, "workspace must hold " + std::to_string(n_trees) + " tree records");
   if (reinterpret_cast<uintptr_t>(workspace) % 16) return fail(QTREE_EINVAL, "workspace must be 16-byte aligned");
   if (blocks == 0) return QTREE_OK;
-  const int64_t cols = qtree::bdp_many_cols(blocks, max_n);
+  const int64_t cols = qtree::bdp_many_cols(blocks, points, layers);
   // trees with the most layers (the longest workgroups) first
   std::stable_sort(order.begin(), order.end(),
                    [&](int x, int y) { return plans[x]->n > plans[y]->n; });

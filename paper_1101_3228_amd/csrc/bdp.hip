@@ -929,18 +929,19 @@ __global__ __launch_bounds__(64 * kManyWaves) void bdp_many_kernel(ManyArgs a) {
 
 bool bdp_many_fits(int max_n) { return max_n <= 256; }
 
-
-
 // A layer of a workgroup is a chain (products, obstacles, two barriers): 16
 // contracts and a tile of rows per wave make it short and the workgroups many,
 // 64 and four tiles load each weight once for four products.  Trees of 10 to
 // 100 layers of 100 points, 16 / 64 contracts a workgroup: 1000 contracts 324 /
 // 904 us, 15000 470 / 894, 30000 767 / 970, 100000 2338 / 2162 (the lane =
 // contract kernel: 6470 us).
-// Layers of one tile keep one wave of a workgroup of 16 busy: from 192 of 64 on
-// those are better (50 layers of 12 points, 20000 contracts 144 / 107 us).
-int bdp_many_cols(int64_t blocks64, int max_n) {
-  return blocks64 < (max_n <= 16 ? 192 : 1024) ? 16 : 64;
+// Up to 48 points a layer (on average) a layer's work is small beside its chain,
+// and the workgroups are better half as many: from 192 of 64 on those win.  60
+// layers, 12000 / 16000 / 20000 contracts, 16 against 64: 12 points 97/102,
+// 168/102, 169/123 us; 43 points 189/198, 249/201, 287/311; sizes of 1 to 44
+// 113/118, 187/118, 190/164; 62 points 220/287, 292/289, 335/453.
+int bdp_many_cols(int64_t blocks64, int64_t points, int64_t layers) {
+  return blocks64 < (points <= 48 * layers ? 192 : 1024) ? 16 : 64;
 }
 
 template <int D>

@@ -225,6 +225,26 @@ def test_small_layers(d, sizes):
     assert np.array_equal(many[-1005:].view(np.uint64), few.view(np.uint64))
 
 
+@pytest.mark.parametrize("nq", [191 * 64, 191 * 64 + 1])
+@pytest.mark.parametrize("sizes", [[1] + [48, 2, 17] * 8 + [44], [1, 96], [1, 48, 95], [1, 50, 96]])
+def test_layers_of_about_48_points(sizes, nq):
+    """From 192 workgroups of 64 contracts on, layers of up to 48 points on
+    average take 64 a workgroup and larger ones 16: the same prices, bit for
+    bit, as the last contracts alone, and the oracle's."""
+    _case(f"bdp_many layers of about 48 points {len(sizes)} {nq}")
+    spec = synth.bm_model(1, len(sizes) - 1, T=1.0)
+    grid, N = synth.layer_grids(spec, sizes)
+    plan = qt.Plan(spec, grid, N)
+    counts = plan.transitions(30_000, 3)
+    _check(plan, spec, grid, N, counts, 9, 8)
+    pi = plan.pi(counts)
+    kinds, S0, K, r, T, sigma, mix = _contracts(np.random.default_rng(4), nq, 1)
+    sp = qt.payoff_specs(1, kinds, S0, K, r, T, sigma, mix)
+    many = plan.bdp_many(pi, sp).cpu().numpy()
+    few = plan.bdp_many(pi, sp[-1003:]).cpu().numpy()
+    assert np.array_equal(many[-1003:].view(np.uint64), few.view(np.uint64))
+
+
 def test_small_layers_take_less_than_large_ones():
     """The rows of a tile that a small layer does not have cost nothing."""
     _case("bdp_many small layers' time")
