@@ -390,7 +390,8 @@ qtree_status qtree_swing(const qtree_plan *plan, const int32_t *counts, const do
  *
  * Autotuner.  A run's launch configuration (never its results) is a code:
  * bit 0 set = 4 instead of 8 samples per lane share each grid read in the
- * d >= 2 sampling launch; bit 1 = the 1-D sampling launch runs on a second
+ * d >= 2 sampling launch (with bucket tables: a lane takes one sample a round
+ * instead of two); bit 1 = the 1-D sampling launch runs on a second
  * stream beside the d >= 2 one instead of after it; bits 8-15 = at most that
  * many workgroups per CU for the d >= 2 launch (0: its occupancy limit).
  * With a tuner, the first run of a batch whose shape signature the tuner
@@ -401,7 +402,8 @@ qtree_status qtree_swing(const qtree_plan *plan, const int32_t *counts, const do
  * that run blocks the host until the timings are in.  The tuner caches
  * (signature, code, milliseconds) in a text file (path given, else
  * $QTREE_TUNE_CACHE, else memory only), so later batches of the same shape
- * skip the timing.  Without a tuner the default code 0 is used.
+ * skip the timing.  Without a tuner the code is 1 where the contracts of
+ * d >= 2 all have d = 2 and bucket tables, else 0.
  * ---------------------------------------------------------------------- */
 typedef struct {
   const qtree_plan *plan;

@@ -633,7 +633,6 @@ qtree_status qtree_plan_create(const qtree_model* model, const float* grid, cons
   }
   p.points = p.pt_off[n + 1];
   p.entries = p.cnt_off[n];
-  p.mids_total = p.aux_off[n + 1];
   if (!all_finite(grid, (size_t)p.points * d)) return fail(QTREE_EINVAL, "grid must be finite");
   if (d == 1) {
     for (int k = 0; k <= n; ++k) {
@@ -863,7 +862,6 @@ static qtree::FwdArgs fwd_args(const qtree_plan* p, uint64_t m0, uint64_t M, uin
   a.d = p->d;
   a.maxP = p->maxP;
   a.maxN = p->maxN;
-  a.mids_total = p->mids_total;
   a.keys = reinterpret_cast<uint16_t*>(p->ws + p->lay.keys);
   a.segs = reinterpret_cast<uint32_t*>(p->ws + p->lay.segs);
   a.max_tiles = p->max_tiles;

@@ -169,10 +169,11 @@ static_assert(offsetof(LayerDev, bk_scale) == offsetof(LayerDev, bk_lo) + 8 &&
 // One wave per 64 paths and all of their work (1e5 paths: 1.5 waves per SIMD)
 // took 1.4 us a step at 240 points, 312 instructions at 11 clocks each: a
 // serial chain on an idle chip.  64 VGPRs let 1024 of these workgroups be
-// resident (1e5 paths are 782; at 80 VGPRs 14 of them ran after the others,
-// 611 us for 365 steps against 408), and the layers' records come through LDS
-// a turn ahead (333 us; as scalar loads, every step of the chain waited for
-// its own).
+// resident while the LDS holds four of them per CU, up to 490 points a layer
+// (1e5 paths are 782; at 80 VGPRs 14 of them ran after the others, 611 us for
+// 365 steps of 240 points against 408), and the layers' records come through
+// LDS a turn ahead (333 us; as scalar loads, every step of the chain waited
+// for its own).  At 500 points three fit and 14 of the 782 run after the rest.
 constexpr int kWidePaths = 128, kSegments = 4, kWideSteps = 2 * kSegments;
 constexpr int kWideBlock = kWidePaths * kSegments;
 static_assert(kWideSteps * kRecWords <= kWideBlock, "one word of the records per thread");

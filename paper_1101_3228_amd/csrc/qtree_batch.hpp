@@ -95,11 +95,13 @@ constexpr int kBdpTaskRows = 16;
 
 // Backward steps of a batch: V_n = phi_n for every job (grid over jobs),
 // then step j = 0, 1, ... runs tasks [step_off[j], step_off[j + 1]) -- layer
-// n - 1 - j of every job with n > j -- one launch per step.  max_last:
-// largest N_n; max_nq: most payoffs of a job; min_n1: smallest N_k, k >= 1.
-hipError_t launch_v0_jobs(const BdpJob* jobs, int n_jobs, double* out, hipStream_t s);
+// n - 1 - j of every job with n > j -- one launch per step.  max_last: largest
+// payoffs x N_n of a job; max_nq: most payoffs of a job; min_n1: smallest N_k,
+// k >= 1.
 hipError_t launch_bdp_steps(const BdpJob* jobs, int n_jobs, int max_last, int max_nq, int min_n1,
                             const BdpTask* tasks, const int* step_off, int n_steps,
                             hipStream_t s);
+// The V_0 of every job and payoff, together.
+hipError_t launch_v0_jobs(const BdpJob* jobs, int n_jobs, double* out, hipStream_t s);
 
 }  // namespace qtree

@@ -214,7 +214,6 @@ struct FwdArgs {
   uint64_t chunk_len;     // samples per chunk (even)
   int32_t maxP;           // largest padded midpoint count (1-D LDS sizing)
   int32_t maxN;           // largest layer size (d >= 2 LDS sizing)
-  int64_t mids_total;     // 1-D: padded midpoints over all layers
   // two-pass counting
   uint16_t* keys;
   uint32_t* segs;

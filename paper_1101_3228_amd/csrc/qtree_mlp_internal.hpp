@@ -19,7 +19,6 @@ constexpr int kOffB4 = kOffW4 + kHid;
 constexpr int kParams = kOffB4 + 1;  // 133 633
 constexpr int kBlock = 256;          // 4 waves
 constexpr int kWaveRows = 32;        // samples per wave (one MFMA column block)
-constexpr int kBlockRows = kBlock / 64 * kWaveRows;
 constexpr int kChunk = 256;          // samples per weight-gradient partial; training rows pad to it
 
 // Network as the kernels read it.  Matrix weights are BF16 (raw bits);

@@ -15,7 +15,7 @@ struct qtree_plan {
   std::vector<int32_t> N;
   std::vector<int64_t> pt_off, cnt_off, aux_off;
   std::vector<int32_t> P;
-  int64_t points = 0, entries = 0, mids_total = 0;
+  int64_t points = 0, entries = 0;
   int32_t maxN = 0, maxP = 0;
   char* ws = nullptr;
   qtree::WsLayout lay{};

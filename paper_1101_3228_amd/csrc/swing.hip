@@ -88,7 +88,7 @@ __global__ __launch_bounds__(64 * kWaves, 4) void swing_layer_kernel(SwingArgs a
 #pragma unroll
   for (int e = 0; e < kRows / kWaves; ++e) vi[e] = a.v[pt + min(i0 + wave + kWaves * e, N - 1)];
   // the lane's levels of a point: byte offsets in its row of P_{k+1}
-  // (below 2^32: at most 4096 points of 2047 levels)
+  // (below 2^32: at most 16384 points of 2047 levels, 8 bytes each)
   const char* next = reinterpret_cast<const char*>(a.P + pt1 * levels);
   bool used[TILES];
   uint32_t lev[TILES];
