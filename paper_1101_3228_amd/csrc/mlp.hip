@@ -267,11 +267,12 @@ __global__ __launch_bounds__(kTileBlock) void mlp_forward(Weights W, FwdIO io) {
 // two tiles at a time, two barriers a turn.  The outputs of a turn are finished
 // by one wave, another each time, after the next turn's first barrier.
 //
-// 1e6 queries: 345 us with one activation term, 13.6 k clocks a turn of 64
-// samples; the exponentials and reciprocals of SiLU (6.1 k), the matrix cores
+// 1e6 queries: 366 us a call with one activation term, 13.6 k clocks a turn of
+// 64 samples; the exponentials and reciprocals of SiLU (6.1 k), the matrix cores
 // (4.2 k) and the LDS reads of the operands (4.1 k) follow one another.  One
 // tile's products interleaved with the other's SiLU by the scheduler's
-// groups, at a barrier per product: 360 us.
+// groups, at a barrier per product, is slower: 360 against 345 us where the two
+// were compared, launches back to back.
 constexpr int S = 2;
 template <int TERMS>
 __global__ __launch_bounds__(kTileBlock) void mlp_forward_pairs(Weights W, FwdIO io,
