@@ -690,13 +690,23 @@ qtree_status qtree_plan_create(const qtree_model* model, const float* grid, cons
   // workgroups (1-D workload, n = 50, N = 500, M = 1e7: 1.835 ms per step
   // against 1.899 unsplit and 1.838 with four parts); with many, splitting
   // only costs the clearing of the split blocks (the parts add into them).
-  int64_t st_max = 1, st_all = 0;
+  int64_t st_max = 1, st_all = 0, largest = 1;
   for (int k = 0; k < n; ++k) {
-    const int64_t st = ((int64_t)N[k] * N[k + 1] + qtree::kSuper - 1) / qtree::kSuper;
+    const int64_t block = (int64_t)N[k] * N[k + 1];
+    const int64_t st = (block + qtree::kSuper - 1) / qtree::kSuper;
     st_max = std::max<int64_t>(st_max, st);
     st_all += st;
+    largest = std::max(largest, block);
   }
   p.st_max = st_max;
+  // under 2^16 keys a super tile, clearing its block and adding into it costs
+  // more than the second workgroup saves: 60 super tiles a layer, 5000 keys
+  // each, 212 -> 180 us a call; 62 000 keys 447 -> 428, 190 000 767 -> 761, 10^6
+  // (one super tile) 436 -> 473.  A handful of counts is another matter, as a
+  // workgroup's additions to the same one follow one another: one layer of 3
+  // points, 30 000 / 65 000 keys 44 / 61 us in one part, 42 / 49 in two, of 12
+  // points 39 / 42 and 42 / 42.
+  p.few_keys = (uint64_t)std::min<int64_t>(largest, 16) << 12;
   const int64_t split_base = st_all >= kManySuperTiles ? 1 : 2;
   int32_t total_units = 0, few_units = 0;
   for (int k = 0; k <= n; ++k) {
@@ -951,11 +961,7 @@ static hipError_t two_pass(const qtree_plan* p, qtree::FwdArgs a, bool zero, hip
     b.chunks = (int32_t)chunks;
     b.xcd_map = p->tune_xcd_map;
     b.first_batch = first ? 1 : 0;
-    // under 2^16 keys a super tile, clearing its block and adding into it costs
-    // more than the second workgroup saves: 60 super tiles a layer, 5000 keys
-    // each, 212 -> 180 us a call; 62 000 keys 447 -> 428, 190 000 767 -> 761, 10^6
-    // (one super tile) 436 -> 473
-    b.few = mb / (uint64_t)p->st_max < (1ull << 16) ? 1 : 0;
+    b.few = mb / (uint64_t)p->st_max < p->few_keys ? 1 : 0;
     const std::vector<int32_t>& split = b.few ? p->few_split : p->split;
     const std::vector<int32_t>& unit = b.few ? p->few_off : p->unit_off;
     hipError_t e = hipSuccess;

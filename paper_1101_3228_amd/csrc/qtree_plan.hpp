@@ -30,6 +30,7 @@ struct qtree_plan {
   int64_t cubes = 0;            // d = 3: the same
   double cube_misses = 0.0;     // ... and the share of the search they leave to scans
   int64_t st_max = 1;           // super tiles of the largest count block
+  uint64_t few_keys = 0;        // keys of a super tile below which it is not split in two
   int32_t max_tiles = 0, total_tiles = 0;
   std::vector<int32_t> tile_off;  // first super tile of every layer (host copy)
   std::vector<int32_t> unit_off;  // first histogram unit of every layer (host copy)

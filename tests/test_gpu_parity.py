@@ -463,3 +463,23 @@ def test_histogram_parts_by_samples(sizes, M):
         plan.tune(groups=groups)
         got = plan.transitions(M, 11, counts=counts).cpu().numpy()
         assert np.array_equal(got, ref), groups
+
+
+@pytest.mark.parametrize("sizes", [[1, 1], [1, 3], [1, 3, 5], [1, 1, 16]])
+def test_histogram_parts_of_a_handful_of_counts(sizes):
+    """Blocks of at most 16 counts are counted by two workgroups from 4096 keys
+    a count of the largest on: the oracle's counts on both sides of the line,
+    over old values and added to them."""
+    print(f"[gpu-case] histogram parts of a handful of counts {sizes}", flush=True)
+    spec = synth.bm_model(1, len(sizes) - 1)
+    grid, N = synth.layer_grids(spec, sizes)
+    plan = qt.Plan(spec, grid, N)
+    line = 4096 * min(16, max(int(a) * int(b) for a, b in zip(N, N[1:])))
+    for M in (line - 1, line, line + 4097):
+        ref = O.transitions(_omodel(spec), grid, N, M, seed=11, nthreads=8)
+        counts = plan.new_counts()
+        counts.fill_(7)
+        got = plan.transitions(M, 11, counts=counts).cpu().numpy()
+        assert np.array_equal(got[:ref.size], ref), M
+        plan.transitions_add(counts, M, 11)
+        assert np.array_equal(counts.cpu().numpy()[:ref.size], 2 * ref), M
