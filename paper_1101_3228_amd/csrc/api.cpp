@@ -1267,20 +1267,31 @@ static hipError_t two_pass_in_plan(const qtree_plan* p, const qtree::FwdArgs& a,
 }
 
 // Whether a call of M samples goes through the plan's d = 3 tables.  A sample
-// without a list is scanned for by its wave alone, where the layerwise scan
-// shares each record among 256 samples, and in a small call the waves with such
-// samples are the last to end.  By tables / scan, layerwise: misses 0.034 (N = 300),
-// 6000 pairs 104 / 90 us; 0.045 (300), 2 10^5 109 / 98, 6 10^6 345 / 427; 0.06
-// (1000), 2 10^5, 6 10^5, 10^6 and 6 10^6 225 / 213, 222 / 236, 223 / 377, 566 /
-// 1075; 0.11 (512), 6 10^5 and 6 10^6 168 / 145 and 516 / 610; 0.33 (1000) 479 /
-// 236 and 1840 / 1040.  Pathwise, 10 layers of 1000 points, 10^5 and 3 10^5 paths:
-// 0.06 164 / 322 and 477 / 591, 0.14 267 / 332 and 750 / 618, 0.33 350 / 332 and
-// 988 / 608.  Product grids of Brownian layers miss 0.0003 up to a correlation of
-// 0.9, 0.3 at 0.95 and nearly all at 0.99; a normal sample as a grid 0.06.
+// without a list is scanned for by its wave alone, which takes about as long
+// whatever the layer's size, where a scan by all lanes grows with it; and in a
+// small call the waves with such samples are the last to end.  By tables / scan,
+// layerwise: misses 0.034 (N = 300), 6000 pairs 104 / 90 us; 0.045 (300), 2 10^5
+// 109 / 98, 6 10^6 345 / 427; 0.06 (1000), 2 10^5, 6 10^5, 10^6 and 6 10^6 225 /
+// 213, 222 / 236, 223 / 377, 566 / 1075; 0.11 (512), 6 10^5 and 6 10^6 168 / 145
+// and 516 / 610; 0.33 (1000) 479 / 236 and 1840 / 1040; 100 layers, 2 10^7 pairs:
+// 0.05 (120, 144, 192, 300) 775 / 640, 787 / 715, 759 / 863, 822 / 1209, 0.07 (216)
+// 1016 / 898, 0.12 (192) 1324 / 865.  Pathwise, 10 layers of 1000 points, 10^5 and
+// 3 10^5 paths: 0.06 164 / 322 and 477 / 591, 0.14 267 / 332 and 750 / 618, 0.33
+// 350 / 332 and 988 / 608; 100 layers, 3 10^4 paths: 0.05 (120, 144, 192, 300) 600 /
+// 405, 604 / 463, 588 / 576, 638 / 908, 0.07 (216) 732 / 644, 0.12 (192) 919 / 576.
+// Product grids of Brownian layers miss 0.0003 up to a correlation of 0.9, 0.3 at
+// 0.95 and nearly all at 0.99, and 0.05 and more where a side has 20 points and
+// another 2; a normal sample as a grid 0.001 (50 points) to 0.06 (1000).
 static bool cubes_answer(const qtree_plan* p, qtree_mode mode, uint64_t M) {
-  const double pairs = (double)p->n * (double)M;
-  return p->cube_misses <=
-         (mode == QTREE_PATHWISE ? 0.15 : pairs < 2e5 ? 0.03 : pairs < 1e6 ? 0.06 : 0.12);
+  const double pairs = (double)p->n * (double)M, N = (double)p->points / p->n;
+  double most;
+  if (mode == QTREE_PATHWISE) {
+    most = std::clamp((N - 70.0) / 2300.0, 0.004, 0.15);
+  } else {
+    most = std::clamp((N - 28.0) / 2750.0, 0.004, 0.12);
+    most *= pairs < 2e5 ? 0.25 : pairs < 1e6 ? 0.5 : 1.0;
+  }
+  return p->cube_misses <= most;
 }
 
 static qtree_status transitions_impl(const qtree_plan* plan, uint64_t m0, uint64_t M,
