@@ -1817,7 +1817,7 @@ qtree_status qtree_bdp_many(const qtree_plan* plan, const void* pi, size_t pi_by
   a.d = plan->d;
   a.max_n = plan->maxN;
   a.np_max = (plan->maxN + 3) & ~3;
-  a.cols = qtree::bdp_many_cols((n_q + 63) / 64, plan->points, plan->n + 1);
+  a.cols = qtree::bdp_many_cols(plan->d, (n_q + 63) / 64, plan->points, plan->n + 1);
   hipError_t e = qtree::launch_bdp_many(a, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? QTREE_OK : hip_fail(e, "bdp_many launch");
 }
@@ -1862,7 +1862,7 @@ qtree_status qtree_bdp_many_trees(int32_t n_trees, const qtree_plan* const* plan
     return fail(QTREE_ENOMEM, "workspace must hold " + std::to_string(n_trees) + " tree records");
   if (reinterpret_cast<uintptr_t>(workspace) % 16) return fail(QTREE_EINVAL, "workspace must be 16-byte aligned");
   if (blocks == 0) return QTREE_OK;
-  const int64_t cols = qtree::bdp_many_cols(blocks, points, layers);
+  const int64_t cols = qtree::bdp_many_cols(d, blocks, points, layers);
   // trees with the most layers (the longest workgroups) first
   std::stable_sort(order.begin(), order.end(),
                    [&](int x, int y) { return plans[x]->n > plans[y]->n; });

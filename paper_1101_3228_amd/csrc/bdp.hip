@@ -790,13 +790,14 @@ __device__ __forceinline__ bool finite_parameters(const Contract& C, int d) {
   return ok;
 }
 
-template <int D, int CTS, int TILES, int R = 4>
+template <int D, int CTS, int TILES, int R = 4, int SPLIT = 1>
 __global__ __launch_bounds__(64 * kManyWaves) void bdp_many_kernel(ManyArgs a) {
-  constexpr int kCols = 16 * CTS, kRowTiles = kManyWaves / CTS;
+  constexpr int kCols = 16 * CTS, kRowWaves = kManyWaves / CTS, kRowTiles = kRowWaves / SPLIT;
   extern __shared__ double Vs[];  // [np_max][kCols]
   const int lane = threadIdx.x & 63, g = lane >> 4, m = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int ct = wave % CTS, rt0 = wave / CTS;
+  const int ct = wave % CTS, rw = wave / CTS;
+  const int rt0 = rw % kRowTiles, r0 = R * (rw / kRowTiles);
   // the workgroup's tree: the one tree, or the last table entry with
   // blk0 <= blockIdx.x
   ManyTree T;
@@ -842,7 +843,7 @@ __global__ __launch_bounds__(64 * kManyWaves) void bdp_many_kernel(ManyArgs a) {
     const int Nn = lay[T.n * kLayWords + kN];
     const int64_t pt = lay[T.n * kLayWords + kPt];
     const LayerObstacle ob = layer_obstacle<D>(C, T.n, T.n);
-    for (int i = 4 * rt0 + g; i < Nn; i += 4 * kRowTiles) {
+    for (int i = 4 * rw + g; i < Nn; i += 4 * kRowWaves) {
       float xs[3];
       grid_point<D>(T, pt, i, xs);
       Vs[i * kCols + col] = obstacle<D>(C, ob, xs);
@@ -859,7 +860,7 @@ __global__ __launch_bounds__(64 * kManyWaves) void bdp_many_kernel(ManyArgs a) {
 #pragma unroll
     for (int t = 0; t < TILES; ++t) {
       const int i0 = 16 * (rt0 + kRowTiles * t);
-      if (i0 >= Nk) break;
+      if (i0 + 4 * r0 >= Nk) break;
       // the tile's band: whole groups of 4 columns, empty rows (lo = hi) apart
       const int i = min(i0 + m, Nk - 1);  // rows past the end repeat the last one
       int lo = B[2 * i], hi = B[2 * i + 1];
@@ -886,21 +887,24 @@ __global__ __launch_bounds__(64 * kManyWaves) void bdp_many_kernel(ManyArgs a) {
       }
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        const int ir = min(i0 + g + 4 * r, Nk - 1);
+        double cont = acc[r];
+#pragma unroll
+        for (int w = 1; w < SPLIT; ++w) cont = r0 == R * w ? acc[R * w + r] : cont;
+        const int ir = min(i0 + g + 4 * (r0 + r), Nk - 1);
         float xs[3];
         grid_point<D>(T, pt, ir, xs);
         const double f = obstacle<D>(C, ob, xs);
-        res[t][r] = f > acc[r] ? f : acc[r];
+        res[t][r] = f > cont ? f : cont;
       }
     }
     __syncthreads();
 #pragma unroll
     for (int t = 0; t < TILES; ++t) {
       const int i0 = 16 * (rt0 + kRowTiles * t);
-      if (i0 >= Nk) break;
+      if (i0 + 4 * r0 >= Nk) break;
 #pragma unroll
       for (int r = 0; r < R; ++r)
-        if (i0 + g + 4 * r < Nk) Vs[(i0 + g + 4 * r) * kCols + col] = res[t][r];
+        if (i0 + g + 4 * (r0 + r) < Nk) Vs[(i0 + g + 4 * (r0 + r)) * kCols + col] = res[t][r];
     }
     __syncthreads();
   }
@@ -936,12 +940,17 @@ bool bdp_many_fits(int max_n) { return max_n <= 256; }
 // 904 us, 15000 470 / 894, 30000 767 / 970, 100000 2338 / 2162 (the lane =
 // contract kernel: 6470 us).
 // Up to 48 points a layer (on average) a layer's work is small beside its chain,
-// and the workgroups are better half as many: from 192 of 64 on those win.  60
+// and the workgroups are better few: from 192 of 64 on (d = 1) those win.  60
 // layers, 12000 / 16000 / 20000 contracts, 16 against 64: 12 points 97/102,
 // 168/102, 169/123 us; 43 points 189/198, 249/201, 287/311; sizes of 1 to 44
-// 113/118, 187/118, 190/164; 62 points 220/287, 292/289, 335/453.
-int bdp_many_cols(int64_t blocks64, int64_t points, int64_t layers) {
-  return blocks64 < (points <= 48 * layers ? 192 : 1024) ? 16 : 64;
+// 113/118, 187/118, 190/164; 62 points 220/287, 292/289, 335/453.  That is where
+// the workgroups of 16 are more than three per CU, as many as are resident; for
+// d > 1, two.  20 layers, 6000 / 12000 contracts, 16 against 64, d = 2: 8 points
+// 44/45, 70/46, 16 points 47/58, 63/59, up to 32 points 57/67, 73/68; d = 3 47/49,
+// 79/49, 52/65, 84/66 and 62/77, 91/79.
+int bdp_many_cols(int d, int64_t blocks64, int64_t points, int64_t layers) {
+  const int64_t small = d == 1 ? 192 : 128;
+  return blocks64 < (points <= 48 * layers ? small : 1024) ? 16 : 64;
 }
 
 template <int D>
@@ -962,6 +971,10 @@ static hipError_t launch_bdp_many_d(const ManyArgs& a, hipStream_t s) {
     return a.cols == 16 ? go(bdp_many_kernel<D, 1, 1, 1>) : go(bdp_many_kernel<D, 4, 1, 1>);
   if (a.max_n <= 8)
     return a.cols == 16 ? go(bdp_many_kernel<D, 1, 1, 2>) : go(bdp_many_kernel<D, 4, 1, 2>);
+  if constexpr (D > 1) {
+    if (a.max_n <= 32 && a.cols == 16) return go(bdp_many_kernel<D, 1, 1, 1, 4>);
+    if (a.max_n <= 16) return go(bdp_many_kernel<D, 4, 1, 2, 2>);
+  }
   const bool small = a.max_n <= 128;
   if (a.cols == 16) return small ? go(bdp_many_kernel<D, 1, 1>) : go(bdp_many_kernel<D, 1, 2>);
   return small ? go(bdp_many_kernel<D, 4, 4>) : go(bdp_many_kernel<D, 4, 8>);

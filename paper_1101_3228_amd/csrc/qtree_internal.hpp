@@ -357,7 +357,7 @@ struct ManyArgs {
 bool bdp_many_fits(int max_n);  // layers of up to 256 points
 // Contracts per workgroup when 64 of them would make `blocks64` workgroups, for
 // layers of points / layers points on average.
-int bdp_many_cols(int64_t blocks64, int64_t points, int64_t layers);
+int bdp_many_cols(int d, int64_t blocks64, int64_t points, int64_t layers);
 hipError_t launch_bdp_many(const ManyArgs& a, hipStream_t s);
 
 // Stratified time-layer counts (d = 1): Ms samples per cell of layer k.

@@ -266,3 +266,50 @@ def test_small_layers_take_less_than_large_ones():
             best = min(best, e0.elapsed_time(e1))
         times.append(best)
     assert times[0] < 0.9 * times[1], times
+
+
+@pytest.mark.parametrize("d,sizes", [(2, [1, (3, 3), (2, 5), (3, 4), 1]), (2, [1, (4, 4), 13, 5, 16]),
+                                     (2, [1, 17, (4, 8), (3, 3), 31, 2]), (2, [1, 33, (4, 4)]),
+                                     (3, [1, (2, 2, 4), (3, 1, 3), 5, 12]),
+                                     (3, [1, (2, 4, 4), 19, (2, 2, 2), 1])], ids=str)
+def test_tiles_shared_by_waves(d, sizes):
+    """For d > 1, layers of up to 16 points (16 contracts a workgroup: 32) share
+    a tile between waves: rows of one wave only, remainders, and the next
+    larger form, against the oracle and each other bit for bit; 64 contracts
+    from 128 workgroups of 64 on."""
+    _case(f"bdp_many shared tiles {d} {sizes}")
+    spec = synth.bm_model(d, len(sizes) - 1, T=1.0)
+    grid, N = synth.layer_grids(spec, sizes)
+    plan = qt.Plan(spec, grid, N)
+    counts = plan.transitions(30_000, 3)
+    _check(plan, spec, grid, N, counts, 37, 8)
+    pi = plan.pi(counts)
+    kinds, S0, K, r, T, sigma, mix = _contracts(np.random.default_rng(2), 127 * 64 + 5, d)
+    sp = qt.payoff_specs(d, kinds, S0, K, r, T, sigma, mix)
+    many = plan.bdp_many(pi, sp).cpu().numpy()
+    few = plan.bdp_many(pi, sp[-1005:]).cpu().numpy()
+    assert np.array_equal(many[-1005:].view(np.uint64), few.view(np.uint64))
+
+
+def test_two_assets_on_small_layers_by_time():
+    """Eight times the contracts fill the chip; before that they cost little."""
+    _case("bdp_many small layers d=2 by time")
+    spec = synth.bm_model(2, 40, T=1.0)
+    grid, N = synth.layer_grids(spec, [1] + [(2, 4)] * 40)
+    plan = qt.Plan(spec, grid, N)
+    pi = plan.pi(plan.transitions(10_000, 3))
+    times = []
+    for nq in (1500, 12_000):
+        sp = qt.payoff_specs(2, np.full(nq, qt.MAX_CALL, np.int32), 100.0, 100.0, 0.05, 1.0,
+                             [[0.2, 0.3]])
+        specs = torch.from_numpy(sp.view(np.uint8).reshape(-1)).cuda()
+        best = np.inf
+        for _ in range(8):
+            e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            e0.record()
+            plan.bdp_many(pi, specs)
+            e1.record()
+            torch.cuda.synchronize()
+            best = min(best, e0.elapsed_time(e1))
+        times.append(best)
+    assert times[1] < 1.3 * times[0], times
