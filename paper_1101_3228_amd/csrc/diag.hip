@@ -51,8 +51,11 @@ __global__ void cells_1d_kernel(FwdArgs a, int k, const float* x, int64_t count,
 // per lane share every record read (argmin_scan_tiled, tiles of kScanTile).
 constexpr int kCellsS = 8;
 // With bucket tables (d = 2, BK): each point's bucket list, as the
-// forward's bucketed search.
-template <int D, bool BK = false>
+// forward's bucketed search.  The S searches of a lane follow one another
+// where they leave the straight code (long lists, scans), so calls of up to
+// kCellsFew points, which fill the chip with one point per lane, take one.
+constexpr int64_t kCellsFew = 1 << 17;
+template <int D, bool BK = false, int S = kCellsS>
 __global__ __launch_bounds__(kBlock) void cells_kernel(FwdArgs a, int k, const float* x,
                                                        int64_t count, int32_t* cell) {
   extern __shared__ float4 recs[];
@@ -70,25 +73,25 @@ __global__ __launch_bounds__(kBlock) void cells_kernel(FwdArgs a, int k, const f
     for (int r = threadIdx.x; r < Npad; r += kBlock) recs[r] = r < N ? a.pts[L.pt_off + r] : pad;
   }
   __syncthreads();
-  const int64_t base = (int64_t)blockIdx.x * kBlock * kCellsS + threadIdx.x;
-  float q[kCellsS][D];
-  int idx[kCellsS];
+  const int64_t base = (int64_t)blockIdx.x * kBlock * S + threadIdx.x;
+  float q[S][D];
+  int idx[S];
 #pragma unroll
-  for (int s = 0; s < kCellsS; ++s) {
+  for (int s = 0; s < S; ++s) {
     const int64_t i = base + (int64_t)s * kBlock;
     const int64_t ii = i < count ? i : count - 1;  // the tail repeats the last point
 #pragma unroll
     for (int c = 0; c < D; ++c) q[s][c] = x[ii * D + c];
   }
   if constexpr (BK && D == 2) {
-    uint4 w[kCellsS];
-    bucket_rows<kCellsS>(L, N, a.bk, q, w);
-    bucket_argmin<kCellsS>(xy, N, a.bk, q, w, idx);
+    uint4 w[S];
+    bucket_rows<S>(L, N, a.bk, q, w);
+    bucket_argmin<S, true>(xy, N, a.bk, q, w, idx);
   } else {
-    argmin_scan_tiled<D, kCellsS, kScanTile>(recs, Npad, q, idx);
+    argmin_scan_tiled<D, S, kScanTile>(recs, Npad, q, idx);
   }
 #pragma unroll
-  for (int s = 0; s < kCellsS; ++s) {
+  for (int s = 0; s < S; ++s) {
     const int64_t i = base + (int64_t)s * kBlock;
     if (i < count) cell[i] = idx[s];
   }
@@ -158,24 +161,20 @@ hipError_t launch_cells(const FwdArgs& a, int k, const float* x, int64_t count, 
     hipLaunchKernelGGL(cells_1d_kernel, dim3(blocks), dim3(kBlock), 0, s, a, k, x, count, cell);
     return hipGetLastError();
   }
-  const unsigned blocks = (unsigned)((count + kBlock * kCellsS - 1) / (kBlock * kCellsS));
   const size_t lds = sizeof(float4) * (size_t)((a.maxN + kScanTile - 1) / kScanTile * kScanTile);
-  const bool bk = a.d == 2 && a.bucketed;
-  const void* fn = bk ? reinterpret_cast<const void*>(cells_kernel<2, true>)
-                 : a.d == 2 ? reinterpret_cast<const void*>(cells_kernel<2>)
-                            : reinterpret_cast<const void*>(cells_kernel<3>);
-  hipError_t e = lds <= 65536 ? hipSuccess
-                              : hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                    (int)lds);
-  if (e != hipSuccess) return e;
-  if (bk)
-    hipLaunchKernelGGL((cells_kernel<2, true>), dim3(blocks), dim3(kBlock), lds, s, a, k, x, count,
-                       cell);
-  else if (a.d == 2)
-    hipLaunchKernelGGL((cells_kernel<2>), dim3(blocks), dim3(kBlock), lds, s, a, k, x, count, cell);
-  else
-    hipLaunchKernelGGL((cells_kernel<3>), dim3(blocks), dim3(kBlock), lds, s, a, k, x, count, cell);
-  return hipGetLastError();
+  auto go = [&](auto* kernel, int per_lane) {
+    const unsigned blocks = (unsigned)((count + kBlock * per_lane - 1) / (kBlock * per_lane));
+    if (lds > 65536) {
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kBlock), lds, s, a, k, x, count, cell);
+    return hipGetLastError();
+  };
+  if (a.d == 2 && a.bucketed)
+    return count <= kCellsFew ? go(cells_kernel<2, true, 1>, 1) : go(cells_kernel<2, true>, kCellsS);
+  return a.d == 2 ? go(cells_kernel<2>, kCellsS) : go(cells_kernel<3>, kCellsS);
 }
 
 }  // namespace qtree

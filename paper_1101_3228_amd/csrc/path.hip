@@ -260,7 +260,7 @@ void walk_2d_wide(FwdArgs a, Visits v) {
     for (int s = 0; s < 2; ++s) {
       if (s >= steps) break;
       int j[1];
-      bucket_argmin<1>(mine + s * buf, R[2 * seg + s].N, a.bk, xs[s], w[s], j);
+      bucket_argmin<1, true>(mine + s * buf, R[2 * seg + s].N, a.bk, xs[s], w[s], j);
       if (live) v.cells[(int64_t)(ks + s) * v.stride + (int64_t)t] = (uint16_t)j[0];
     }
   }
@@ -298,7 +298,7 @@ __global__ __launch_bounds__(kBlock) void walk_2d(FwdArgs a, Visits v) {
     uint4 w[1];
     bucket_rows<1>(layers[k + 1], N1, a.bk, x, w);
     __syncthreads();
-    bucket_argmin<1>(xy, N1, a.bk, x, w, j);
+    bucket_argmin<1, true>(xy, N1, a.bk, x, w, j);
     visit<STORE>(a, v, k, t, live, i, j[0]);
     i = j[0];
   }

@@ -201,6 +201,44 @@ __device__ __forceinline__ void argmin_scan_tiled(const float4* __restrict__ g, 
   }
 }
 
+// The full scan for the lanes of `need`, one after the other, each by the
+// whole wave (the points split over its lanes): a lane scanning alone holds its
+// workgroup up for 15 us at N = 990, the wave for less than one.  key(p, x) is
+// the key of point p at x; the result is idx for the other lanes.  (All lanes
+// of the wave come here together.)
+template <int D, class KEY>
+__device__ __forceinline__ int wave_scan(KEY key, int N, const float* x, uint64_t need, int idx) {
+  const int lane = (int)(threadIdx.x & 63);
+  while (need) {
+    const int from = __ffsll((unsigned long long)need) - 1;
+    need &= need - 1;
+    float q[D];
+#pragma unroll
+    for (int c = 0; c < D; ++c) q[c] = __shfl(x[c], from, 64);
+    float best = __builtin_huge_valf();
+    int at = 0x7FFFFFFF;
+#pragma unroll(D == 3 ? 2 : 1)
+    for (int p = lane; p < N; p += 64) {
+      const float v = key(p, q);
+      const bool lt = v < best;
+      best = lt ? v : best;
+      at = lt ? p : at;
+    }
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const float o = __shfl_xor(best, off, 64);
+      const int oat = __shfl_xor(at, off, 64);
+      const bool lt = o < best || (o == best && oat < at);
+      best = lt ? o : best;
+      at = lt ? oat : at;
+    }
+    if (at == 0x7FFFFFFF) at = 0;  // no key below +inf
+    idx = lane == from ? at : idx;
+  }
+  return idx;
+}
+constexpr int kWaveScans = 16;  // more lanes than this scan side by side
+
 // d = 2 cells by the layer's bucket tables, in two steps so that the row
 // loads of many points are in flight together.  A bucket's row (16 bytes)
 // holds its candidate count c in entry 0 and, from entry 1 on, every point
@@ -308,14 +346,29 @@ __device__ __forceinline__ void bucket_first(const float2* __restrict__ g, const
 }
 
 // bucket_rest: the rows of more candidates from their start, and the full
-// scan; at then holds the cells.
-template <int S>
+// scan; at then holds the cells.  A lane that scans alone waits for the LDS,
+// eight points at a time (two samples a lane: four): 2500 points on a line, 1000
+// and 10^5 paths of 12 steps 870 and 920 us, 1060 and 1096 with four.  WAVE: up
+// to kWaveScans lanes without a list are scanned for by their wave (all of it
+// comes here together).  That is for a caller's points, which may be outside the
+// box; the time layers' samples hardly are, and the question alone would cost
+// them 0.4 % of a call.
+template <int S, bool WAVE = false>
 __device__ __forceinline__ void bucket_rest(const float2* __restrict__ g, int N,
                                             const BucketTab& t, const float (*xs)[2],
                                             const uint4* w, int* at) {
 #pragma unroll
   for (int s = 0; s < S; ++s) {
     const uint32_t c = w[s].x & 0xFFFFu;
+    uint64_t alone = 0;
+    if (WAVE) {
+      alone = __ballot(c == (uint32_t)kBucketFull);
+      if (__popcll(alone) > kWaveScans) alone = 0;
+      if (alone != 0)
+        at[s] = 8 * wave_scan<2>(
+                        [&](int p, const float* q) { return half_norm_key(g[p], q[0], q[1]); }, N,
+                        xs[s], alone, cell_index(at[s]));
+    }
     if (c <= (uint32_t)kFirst) continue;
     float best = __builtin_huge_valf();
     int found = 0;
@@ -328,7 +381,8 @@ __device__ __forceinline__ void bucket_rest(const float2* __restrict__ g, int N,
       for (int q = 8; q <= cl; q += 8)
         bucket_group(g, row[q >> 3], 0, xs[s][0], xs[s][1], best, found);
     } else {
-#pragma unroll 4
+      if (alone != 0) continue;
+#pragma unroll(S == 2 ? 4 : 8)
       for (int p = 0; p < 8 * N; p += 8) {
         const float key = bucket_key(g, p, xs[s][0], xs[s][1]);
         const bool lt = key < best;
@@ -341,12 +395,12 @@ __device__ __forceinline__ void bucket_rest(const float2* __restrict__ g, int N,
 }
 
 // bucket_argmin: the cells of the S points whose rows bucket_rows fetched.
-template <int S>
+template <int S, bool WAVE = false>
 __device__ __forceinline__ void bucket_argmin(const float2* __restrict__ g, int N,
                                               const BucketTab& t, const float (*xs)[2],
                                               const uint4* w, int* idx) {
   bucket_first<S>(g, xs, w, idx);
-  bucket_rest<S>(g, N, t, xs, w, idx);
+  bucket_rest<S, WAVE>(g, N, t, xs, w, idx);
 #pragma unroll
   for (int s = 0; s < S; ++s) idx[s] = cell_index(idx[s]);
 }
@@ -403,39 +457,6 @@ __device__ __forceinline__ void cube_rows(const Cubes& C, const uint4* rows, con
     w[s][0].z = r[s] < 0 ? pads : w[s][0].z;
   }
 }
-// The full scan for the lanes of `need`, one after the other, each by the
-// whole wave (the records split over its lanes): a lane scanning alone holds
-// its workgroup up for 15 us at N = 990, the wave for less than one.
-__device__ __forceinline__ int wave_scan(const float4* g, int N, const float* x, uint64_t need,
-                                         int idx) {
-  const int lane = (int)(threadIdx.x & 63);
-  while (need) {
-    const int from = __ffsll((unsigned long long)need) - 1;
-    need &= need - 1;
-    const float q[3] = {__shfl(x[0], from, 64), __shfl(x[1], from, 64), __shfl(x[2], from, 64)};
-    float best = __builtin_huge_valf();
-    int at = 0x7FFFFFFF;
-#pragma unroll 2
-    for (int p = lane; p < N; p += 64) {
-      const float key = record_key(g[p], q);
-      const bool lt = key < best;
-      best = lt ? key : best;
-      at = lt ? p : at;
-    }
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const float o = __shfl_xor(best, off, 64);
-      const int oat = __shfl_xor(at, off, 64);
-      const bool lt = o < best || (o == best && oat < at);
-      best = lt ? o : best;
-      at = lt ? oat : at;
-    }
-    if (at == 0x7FFFFFFF) at = 0;  // no key below +inf
-    idx = lane == from ? at : idx;
-  }
-  return idx;
-}
-constexpr int kWaveScans = 16;  // more lanes than this scan side by side
 // (All lanes of the wave come here together.)
 template <int S>
 __device__ __forceinline__ void cube_cells(const Cubes& C, const float4* g, const float (*xs)[3],
@@ -462,7 +483,8 @@ __device__ __forceinline__ void cube_cells(const Cubes& C, const float4* g, cons
     const uint64_t need = __ballot(c == kCubeFull);
     if (need == 0) continue;
     if (__popcll(need) <= kWaveScans) {
-      idx[s] = wave_scan(g, N, xs[s], need, idx[s]);
+      idx[s] = wave_scan<3>([&](int p, const float* q) { return record_key(g[p], q); }, N, xs[s],
+                            need, idx[s]);
     } else if (c == kCubeFull) {
       argmin_scan<3, 1>(g, N, xs + s, idx + s);
     }

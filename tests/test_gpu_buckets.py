@@ -361,3 +361,73 @@ def test_3d_small_grids_of_uneven_sides(shape, mode):
         assert times[0] < 1.3 * times[1], (M, times)
     ref = O.transitions(_omodel(spec), grid, N, 2_003, seed=3, mode=mode, nthreads=8)
     assert np.array_equal(plan.transitions(2_003, 3, mode=mode).cpu().numpy(), ref)
+
+
+def _cells_ms(plan, x):
+    best = np.inf
+    for _ in range(8):
+        e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        e0.record()
+        qt.cells(plan, 1, x)
+        e1.record()
+        torch.cuda.synchronize()
+        best = min(best, e0.elapsed_time(e1))
+    return best
+
+
+@pytest.mark.parametrize("m", [100, 1 << 17, (1 << 17) + 1, 300_001])
+@pytest.mark.parametrize("out", [1, 16, 17, 64])
+def test_points_without_a_list_among_others(out, m):
+    """`out` of every 64 points outside the box (scanned for by the wave up to
+    16 of them, by each lane beyond), with repeated grid points, in calls of one
+    point a lane and of eight, and as layers of the forward."""
+    _case(f"bucketed cells {out} of 64 outside, {m} points")
+    rng = np.random.default_rng(8)
+    g = rng.standard_normal((301, 2))
+    g[200:240] = g[100:140]
+    spec = synth.bm_model(2, 2, T=1.0)
+    g = g.astype(np.float32)
+    grid = np.concatenate([np.zeros((1, 2), np.float32), g, g])
+    plan = qt.Plan(spec, grid, np.array([1, 301, 301], np.int32))
+    x = rng.standard_normal((m, 2)) * 0.7
+    far = np.arange(m) % 64 >= 64 - out
+    x[far] = 40.0 * x[far] / np.linalg.norm(x[far], axis=1, keepdims=True)
+    x = x.astype(np.float32)
+    got = qt.cells(plan, 1, torch.from_numpy(x).cuda()).cpu().numpy()
+    assert np.array_equal(got, O.cells_bulk(g, 2, x))
+
+
+@pytest.mark.parametrize("shape", ["circle", "line", "five rows"])
+def test_2d_grids_with_scans(shape):
+    """Grids whose lists hold too many points in a part of the box or in all of
+    it: both modes, the tables on and off, against the oracle."""
+    _case(f"2-D grids with scans: {shape}")
+    if shape == "circle":
+        t = np.arange(400) * 2 * np.pi / 400
+        g = 1.5 * np.stack([np.cos(t), np.sin(t)], 1)
+    elif shape == "line":
+        g = np.stack([np.zeros(999), np.sort(np.random.default_rng(2).standard_normal(999))], 1)
+    else:
+        a, b = synth.quantile_grid_1d(5), synth.quantile_grid_1d(400)
+        g = np.stack([m.ravel() for m in np.meshgrid(a, b, indexing="ij")], 1)
+    g = g.astype(np.float32)
+    spec = synth.bm_model(2, 3, T=1.0, rho=0.3)
+    grid = np.concatenate([np.zeros((1, 2), np.float32), g, g, g])
+    N = np.array([1] + [len(g)] * 3, np.int32)
+    plan = qt.Plan(spec, grid, N)
+    for mode in (qt.LAYERWISE, qt.PATHWISE):
+        ref = O.transitions(_omodel(spec), grid, N, 20_011, seed=9, mode=mode, nthreads=8)
+        for on in (1, 0):
+            plan.tune(buckets=on)
+            assert np.array_equal(plan.transitions(20_011, 9, mode=mode).cpu().numpy(), ref)
+
+
+def test_a_point_without_a_list_does_not_hold_up_its_wave():
+    _case("bucketed cells, time with one point of 64 outside")
+    spec = synth.bm_model(2, 2, T=1.0)
+    grid, N = synth.layer_grids(spec, [1] + [(50, 50)] * 2)
+    plan = qt.Plan(spec, grid, N)
+    x = 0.5 * np.random.default_rng(1).standard_normal((100_000, 2)).astype(np.float32)
+    inside = _cells_ms(plan, torch.from_numpy(x).cuda())
+    x[::64] = 40.0
+    assert _cells_ms(plan, torch.from_numpy(x).cuda()) < 3.0 * inside + 0.02
