@@ -397,6 +397,20 @@ def test_points_without_a_list_among_others(out, m):
     assert np.array_equal(got, O.cells_bulk(g, 2, x))
 
 
+@pytest.mark.parametrize("N,m", [(1024, (1 << 19) + 1), (1025, 1 << 19), (1025, (1 << 19) + 1)])
+def test_cells_with_one_and_eight_points_a_lane(N, m):
+    _case(f"bucketed cells N={N} m={m}")
+    rng = np.random.default_rng(4)
+    g = rng.standard_normal((N, 2)).astype(np.float32)
+    spec = synth.bm_model(2, 2, T=1.0)
+    grid = np.concatenate([np.zeros((1, 2), np.float32), g, g])
+    plan = qt.Plan(spec, grid, np.array([1, N, N], np.int32))
+    x = rng.standard_normal((m, 2)).astype(np.float32)
+    x[::5000] *= 30.0
+    got = qt.cells(plan, 1, torch.from_numpy(x).cuda()).cpu().numpy()
+    assert np.array_equal(got, O.cells_bulk(g, 2, x))
+
+
 @pytest.mark.parametrize("shape", ["circle", "line", "five rows"])
 def test_2d_grids_with_scans(shape):
     """Grids whose lists hold too many points in a part of the box or in all of
