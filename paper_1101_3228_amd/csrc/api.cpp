@@ -1193,11 +1193,21 @@ class PathTurn {
 }  // namespace
 
 // Whether a pathwise call goes through the cell scratch.
-//   - Few paths added to a large tree: the counting pass reads and writes every
-//     count (about 4.4 ps each), where 52 ps of atomics a step would do.  365
-//     layers of 500 points, 1 / 1000 / 10^4 paths added: 516 / 762 / 796 us on the
-//     spot, 923 / 919 / 902 through the cells, 10^5 1595 / 1079.  (Not for d = 2,
-//     whose walk on the spot is the slower one.)
+//   - Few paths added to a large tree (d = 1): the counting pass reads and writes
+//     every count (about 4.4 ps each), where the atomics, 42 ps a step, hide behind
+//     the walk's chain until they are more; a walk that stores its cells is 0.4 us
+//     a layer shorter.  On the spot / through the cells, us, 10^3, 3 10^4, 6 10^4 and
+//     10^5 paths: 365 layers of 100 points 444/339, 519/422, 847/429, 1371/438; 50 of
+//     300 91/82, 136/90, 218/101, 328/122; 100 of 400 166/194, 197/203, 303/216,
+//     468/234; 365 of 500 567/913, 648/939, 961/998, 1513/1072; 200 of 600 362/711,
+//     405/725, 560/771, 878/833; 20 of 700 50/77, 62/86, 87/96, 131/110; 50 of 1000
+//     103/179, 117/212, 166/248, 251/298.  (The walks of d > 1 on the spot take
+//     longer: 50 layers of 900 points, d = 2, 122/125, 154/150, 182/181, 264/273, 30 of
+//     400, d = 3, 343/90, 360/111, 377/121, 427/134.)
+//   - Few steps added in few layers: the second launch and the turn at the cells
+//     cost about 4 us, where 50 000 atomics spread out, or 27 for every count of a
+//     layer, take 2 to 3.  One layer of 13 points, 100 paths 21 us on the spot, 23
+//     through the cells; 10 of 100 points, 1000 paths 32, 35.
 //   - Walks that scan their layers (d = 2 without tables, d = 3 without them or
 //     where they do not answer): the scan hides the atomics, and a pass of 2^17
 //     paths only half fills the chip.  30 layers, d = 3, 3 10^5 paths: 216 points
@@ -1213,7 +1223,10 @@ class PathTurn {
 static bool through_cells(const qtree_plan* p, const qtree::FwdArgs& a, bool zero) {
   if (p->path_cells == 0) return false;
   const double steps = (double)p->n * (double)a.M;
-  if (!zero && p->d != 2 && 12.0 * steps < (double)p->entries) return false;
+  const double entries = (double)p->entries;
+  if (!zero && p->d == 1 && entries > 9e4 * (p->n - 10) && 5.5 * steps < entries) return false;
+  const double few = std::clamp(27.0 * entries / p->n, 512.0, 5e4);
+  if (!zero && steps <= few && p->n <= (p->d == 1 ? 16 : 1)) return false;
   const bool several = a.M > (uint64_t)p->path_cells;  // passes
   const bool scans = p->d == 2 ? !a.bucketed : p->d == 3 && !a.cubes;
   if (scans) return p->points < (several ? 300 : 900) * (int64_t)p->n;

@@ -386,3 +386,20 @@ def test_paths_through_large_count_blocks(d, n, N1, M):
                  for p, c in zip((plan, _without_cells(plan)), counts))
     assert torch.equal(counts[0], counts[1])
     assert own < 1.2 * spot, (own, spot)
+
+
+@pytest.mark.parametrize("d,sizes", [(1, [1, 9]), (1, [1, 4, 5, 3, 7]), (2, [1, 12]), (2, [1, 12, 6]),
+                                     (3, [1, 30, 12])], ids=str)
+@pytest.mark.parametrize("steps", [1, 512, 513, 2000])
+def test_few_steps_added(d, sizes, steps):
+    """Few steps added in few layers (d > 1: in one) are counted on the spot,
+    more through the cells; both onto counts that are there."""
+    _case(f"paths added {d} {sizes} {steps}")
+    n = len(sizes) - 1
+    spec = synth.bm_model(d, n)
+    grid, N = synth.layer_grids(spec, sizes)
+    plan = qt.Plan(spec, grid, N, batch_samples=1)
+    M = -(-steps // n)
+    counts = plan.transitions(1000, SEED, mode=qt.PATHWISE)
+    plan.transitions_add(counts, M, SEED, mode=qt.PATHWISE, m0=1000)
+    assert np.array_equal(counts[:plan.entries].cpu().numpy(), _ref(spec, grid, N, 1000 + M))
