@@ -455,8 +455,9 @@ void qtree_batch_destroy(qtree_batch *batch);
  * qtree_cells: Voronoi cell in layer k (0 <= k <= n) of `count` device points
  *   x (float[count][d]); cell: device int32[count].  d >= 2: the forward's
  *   search -- with bucket tables (d = 2, QTREE_TUNE_BUCKETS on) each point's
- *   bucket list, else the tiled scan over the layer's records staged in LDS,
- *   eight points per lane (the brute-force search of Sec. 4); d = 1: the
+ *   bucket list (one point per lane, eight in large calls), else the tiled scan
+ *   over the layer's records staged in LDS, eight points per lane (the
+ *   brute-force search of Sec. 4); d = 1: the
  *   binary search over the layer's sorted midpoints.
  * All asynchronous on `stream`. */
 qtree_status qtree_box_muller(const uint32_t *ra, const uint32_t *rb, int64_t count, float *z0,

@@ -52,13 +52,14 @@ __global__ void cells_1d_kernel(FwdArgs a, int k, const float* x, int64_t count,
 constexpr int kCellsS = 8;
 // With bucket tables (d = 2, BK): each point's bucket list, as the
 // forward's bucketed search.  The S searches of a lane follow one another
-// where they leave the straight code (long lists, scans), so S is 1 unless a
-// call has so many points in so large layers that staging the layer for every
-// 256 points costs more.  Normal points as a grid, 1 / 8 points a lane: N = 30,
-// 1.5 10^5 and 3 10^6 points 21 / 29 and 36 / 42 us, N = 900 21 / 29 and 41 / 43, N =
-// 2500 21 / 30 and 66 / 49, 6 10^5 28 / 30, 10^6 33 / 31.
+// where they leave the straight code (long lists, scans), so S is 1 in calls
+// that do not fill the chip for long; in the others, staging the layer for
+// every 256 points costs more.  Normal points as a grid, 1 / 8 points a lane: N =
+// 30, 1.5 10^5 and 3 10^6 points 21 / 29 and 36 / 42 us, N = 900 21 / 29 and 41 / 43,
+// N = 2500 21 / 30 and 66 / 49, 6 10^5 28 / 30, 10^6 33 / 31; 3.65 10^7 points of a
+// product grid, N = 100 190 / 123, 500 235 / 143.
 constexpr int kCellsFewN = 1024;
-constexpr int64_t kCellsFew = 1 << 19;
+constexpr int64_t kCellsFew = 1 << 21, kCellsFewLarge = 1 << 19;
 template <int D, bool BK = false, int S = kCellsS>
 __global__ __launch_bounds__(kBlock) void cells_kernel(FwdArgs a, int k, const float* x,
                                                        int64_t count, int32_t* cell) {
@@ -177,8 +178,9 @@ hipError_t launch_cells(const FwdArgs& a, int k, const float* x, int64_t count, 
     return hipGetLastError();
   };
   if (a.d == 2 && a.bucketed)
-    return a.maxN <= kCellsFewN || count <= kCellsFew ? go(cells_kernel<2, true, 1>, 1)
-                                                      : go(cells_kernel<2, true>, kCellsS);
+    return count <= (a.maxN <= kCellsFewN ? kCellsFew : kCellsFewLarge)
+               ? go(cells_kernel<2, true, 1>, 1)
+               : go(cells_kernel<2, true>, kCellsS);
   return a.d == 2 ? go(cells_kernel<2>, kCellsS) : go(cells_kernel<3>, kCellsS);
 }
 

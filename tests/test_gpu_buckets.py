@@ -397,7 +397,8 @@ def test_points_without_a_list_among_others(out, m):
     assert np.array_equal(got, O.cells_bulk(g, 2, x))
 
 
-@pytest.mark.parametrize("N,m", [(1024, (1 << 19) + 1), (1025, 1 << 19), (1025, (1 << 19) + 1)])
+@pytest.mark.parametrize("N,m", [(1024, (1 << 19) + 1), (1025, 1 << 19), (1025, (1 << 19) + 1),
+                                 (60, 1 << 21), (60, (1 << 21) + 1)])
 def test_cells_with_one_and_eight_points_a_lane(N, m):
     _case(f"bucketed cells N={N} m={m}")
     rng = np.random.default_rng(4)
