@@ -797,7 +797,7 @@ __global__ __launch_bounds__(64 * kManyWaves) void bdp_many_kernel(ManyArgs a) {
   const int lane = threadIdx.x & 63, g = lane >> 4, m = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int ct = wave % CTS, rw = wave / CTS;
-  const int rt0 = rw % kRowTiles, r0 = R * (rw / kRowTiles);
+  const int rt0 = SPLIT > 1 ? rw % kRowTiles : rw, r0 = SPLIT > 1 ? R * (rw / kRowTiles) : 0;
   // the workgroup's tree: the one tree, or the last table entry with
   // blk0 <= blockIdx.x
   ManyTree T;
@@ -914,7 +914,8 @@ __global__ __launch_bounds__(64 * kManyWaves) void bdp_many_kernel(ManyArgs a) {
     a.V0[qb + threadIdx.x] = v0;
     again = v0 != v0;
   }
-  __shared__ uint64_t redo;
+  // (kCols <= 64: wave 0 has read its values, the row after them is free)
+  uint64_t& redo = reinterpret_cast<uint64_t*>(Vs)[kCols];
   if (wave == 0) {
     const uint64_t mask = __ballot(again);
     if (lane == 0) redo = mask;
