@@ -351,8 +351,10 @@ __device__ __forceinline__ void bucket_first(const float2* __restrict__ g, const
 // and 10^5 paths of 12 steps 870 and 920 us, 1060 and 1096 with four.  WAVE: up
 // to kWaveScans lanes without a list are scanned for by their wave (all of it
 // comes here together).  That is for a caller's points, which may be outside the
-// box; the time layers' samples hardly are, and the question alone would cost
-// them 0.4 % of a call.
+// box (10^5 of them, a grid of 900 points on a circle 629 -> 34 us), and for paths,
+// whose waves are few (1000 on five rows of 500 points 1072 -> 189; 365 layers
+// whose lists answer 444 and 443); the time layers' samples hardly are outside,
+// and the question alone would cost them 0.4 % of a call.
 template <int S, bool WAVE = false>
 __device__ __forceinline__ void bucket_rest(const float2* __restrict__ g, int N,
                                             const BucketTab& t, const float (*xs)[2],
